@@ -1,13 +1,17 @@
-"""ctypes binding of libnnv.so: the same entry points as include/nnv.h, argument
-marshalling only.  torch supplies device memory and the stream handle."""
+"""Binding of libnnv.so: the same entry points as include/nnv.h, argument marshalling only.  The
+calls a program makes per pass go through the compiled module _nnvpy (csrc/pymodule.cpp), the
+queries and the calls that wait for the GPU through ctypes.  torch supplies device memory and the
+stream handle."""
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from ctypes import c_char_p, c_double, c_int, c_int32, c_size_t, c_void_p, POINTER, Structure, byref
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libnnv.so")
+MODULE_PATH = os.path.join(HERE, "_nnvpy.so")
 
 DIRECT, IM2COL_GEMM, WINO_F2, WINO_F4, DEPTHWISE, WINO_F6 = range(6)
 KINDS = {"direct": DIRECT, "im2col_gemm": IM2COL_GEMM, "wino_f2": WINO_F2, "wino_f4": WINO_F4,
@@ -47,16 +51,17 @@ class CacheIo(Structure):
 
 
 _lib = None
+_native = None      # the module _nnvpy, once the library is loaded
 
 
 def load():
-    """Load libnnv.so (building it first only if it does not exist).  torch is imported
+    """Load libnnv.so and the module beside it (building them first only if they do not exist).  torch is imported
     before the library so that both share one HIP runtime."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (loads the HIP runtime the library binds to)
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(MODULE_PATH)):
         from .build import build
         build()
     lib = ctypes.CDLL(LIB_PATH, use_errno=True)
@@ -97,8 +102,25 @@ def load():
     lib.nnv_cache_write.argtypes = [c_char_p, POINTER(ConvDesc), c_int, c_void_p, c_void_p]
     lib.nnv_cache_read.restype = c_int
     lib.nnv_cache_read.argtypes = [c_char_p, POINTER(ConvDesc), c_int, c_void_p, c_int, c_void_p, POINTER(CacheIo)]
+    spec = importlib.util.spec_from_file_location("_nnvpy", MODULE_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.setup(ConvDesc, _fail, lambda: torch.cuda.current_stream().cuda_stream, torch.cuda.current_device if not hasattr(torch._C, "_cuda_getDevice")
+                 else torch._C._cuda_getDevice, getattr(torch._C, "_cuda_getCurrentRawStream", None))
+    _native = native
     _lib = lib
     return lib
+
+
+def _calls():
+    """The compiled module, loaded on first use."""
+    if _native is None:
+        load()
+    return _native
+
+
+def _fail(status: int, where: str):
+    raise NnvError(status, where)
 
 
 def make_desc(layer, dtype: int = F32) -> ConvDesc:
@@ -155,31 +177,19 @@ def nnv_workspace_bytes(desc: ConvDesc, kind: int) -> int:
 
 
 def nnv_transform_weights(desc: ConvDesc, kind: int, w_raw, w_tx, stream=None) -> None:
-    _check(load().nnv_transform_weights(byref(desc), kind, _ptr(w_raw), _ptr(w_tx), _stream(stream)),
-           "nnv_transform_weights")
+    (_native or _calls()).transform_weights(desc, kind, w_raw, w_tx, stream)
 
 
 def nnv_transform_weights_grouped(descs, kinds, w_raw, w_tx, stream=None) -> None:
-    n = len(descs)
-    d = (ConvDesc * n)(*descs)
-    k = (c_int * n)(*kinds)
-    src = (c_void_p * n)(*[t if isinstance(t, int) else t.data_ptr() for t in w_raw])
-    dst = (c_void_p * n)(*[t if isinstance(t, int) else t.data_ptr() for t in w_tx])
-    _check(load().nnv_transform_weights_grouped(n, d, k, src, dst, _stream(stream)), "nnv_transform_weights_grouped")
+    (_native or _calls()).transform_weights_grouped(descs, kinds, w_raw, w_tx, stream)
 
 
 def nnv_conv_forward(desc: ConvDesc, kind: int, x, w_tx, bias, y, workspace, workspace_bytes=None, stream=None) -> None:
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().nnv_conv_forward(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _ptr(workspace),
-                                   workspace_bytes, _stream(stream)), "nnv_conv_forward")
+    (_native or _calls()).conv_forward(desc, kind, x, w_tx, bias, y, workspace, workspace_bytes, stream)
 
 
 def nnv_conv_forward_relu(desc: ConvDesc, kind: int, x, w_tx, bias, y, workspace, workspace_bytes=None, stream=None) -> None:
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().nnv_conv_forward_relu(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _ptr(workspace),
-                                        workspace_bytes, _stream(stream)), "nnv_conv_forward_relu")
+    (_native or _calls()).conv_forward_relu(desc, kind, x, w_tx, bias, y, workspace, workspace_bytes, stream)
 
 
 FORWARD_RELU = 1
@@ -192,21 +202,14 @@ def nnv_conv_forward_grouped_workspace_bytes(descs, kinds) -> int:
 
 def nnv_conv_forward_grouped(descs, kinds, x, w_tx, bias, y, workspace, workspace_bytes=None, flags=0, stream=None) -> None:
     """bias: None, or a list with a tensor or None per layer."""
-    n = len(descs)
-    arr = lambda ts: (c_void_p * n)(*[None if t is None else (t if isinstance(t, int) else t.data_ptr()) for t in ts])
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().nnv_conv_forward_grouped(n, (ConvDesc * n)(*descs), (c_int * n)(*kinds), arr(x), arr(w_tx),
-                                           None if bias is None else arr(bias), arr(y), _ptr(workspace), workspace_bytes,
-                                           flags, _stream(stream)), "nnv_conv_forward_grouped")
+    (_native or _calls()).conv_forward_grouped(descs, kinds, x, w_tx, bias, y, workspace, workspace_bytes, flags, stream)
 
 
 STATIC_SCRATCH_BYTES = 64 << 20
 
 
 def nnv_conv_forward_static(desc: ConvDesc, kind: int, x, w_tx, bias, y, stream=None) -> None:
-    _check(load().nnv_conv_forward_static(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _stream(stream)),
-           "nnv_conv_forward_static")
+    (_native or _calls()).conv_forward_static(desc, kind, x, w_tx, bias, y, stream)
 
 
 def nnv_time_layer(desc: ConvDesc, kind: int, w_raw, w_tx, x, y, workspace, flush=None, warmup=2, reps=10,
@@ -233,10 +236,4 @@ def nnv_cache_read(path: str, desc: ConvDesc, kind: int, w_tx, verify: bool = Fa
 
 def nnv_cold_stack(descs, kinds, w_raw, w_tx, x, y, workspace, stage_layers=1, stream_exec=None, stream_tx=None) -> None:
     """stream_tx=None runs both operations on stream_exec (the unpipelined order)."""
-    n = len(descs)
-    arr = lambda ts: (c_void_p * n)(*[t if isinstance(t, int) else t.data_ptr() for t in ts])
-    se = _stream(stream_exec)
-    stx = se if stream_tx is None else _stream(stream_tx)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().nnv_cold_stack(n, (ConvDesc * n)(*descs), (c_int * n)(*kinds), arr(w_raw), arr(w_tx), arr(x), arr(y),
-                                 _ptr(workspace), ws_bytes, stage_layers, se, stx), "nnv_cold_stack")
+    (_native or _calls()).cold_stack(descs, kinds, w_raw, w_tx, x, y, workspace, stage_layers, stream_exec, stream_tx)

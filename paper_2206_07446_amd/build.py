@@ -1,14 +1,17 @@
-"""Compile the HIP library libnnv.so for gfx950 with hipcc (in-tree, next to this file)."""
+"""Compile the HIP library libnnv.so for gfx950 with hipcc, and the Python module _nnvpy.so that
+calls it with the host compiler (both in-tree, next to this file)."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libnnv.so")
+MODULE = os.path.join(HERE, "_nnvpy.so")
 SOURCES = ("api.cpp", "cache.cpp", "transform.hip", "direct.hip", "gemm.hip", "winograd.hip")
 # packed-fp32 VALU instructions are switched off for every device translation unit
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -24,7 +27,7 @@ def _hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source (always, even if the library exists) and link libnnv.so."""
+    """Compile every source (always, even if the library exists), link libnnv.so and the module beside it."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     hipcc = _hipcc()
@@ -47,6 +50,13 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         print(res.stdout, res.stderr)
         raise RuntimeError("link failed")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pymodule.cpp"), "-o", MODULE, "-L", HERE, "-lnnv", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        print(" ".join(cmd))
+        print(res.stdout, res.stderr)
+        raise RuntimeError("g++ failed on pymodule.cpp")
     return LIB
 
 
