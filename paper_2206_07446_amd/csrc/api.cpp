@@ -79,7 +79,7 @@ bool kind_rules(const Geo &g, int kind) {
             if (g.groups == 1) return true;
             // groups: one panel block and one transformation job per group; the float16
             // channel-last copy needs each group's channels on a fragment boundary
-            if (g.groups > kMaxJobs) return false;
+            if (g.groups > kMaxGemmGroups) return false;
             return g.dtype == NNV_F32 || (g.r == 1 && g.s == 1) || g.cg % 32 == 0;
         }
         case NNV_WINO_F2:
@@ -138,13 +138,12 @@ int transform_many(int n, const nnv_conv_desc *descs, const nnv_kind *kinds, con
         if (misaligned(w_raw[i]) || misaligned(w_tx[i])) return NNV_E_ALIGN;
     }
     JobTable tbl;
-    tbl.njobs = 0;
-    int blocks = 0;
+    int njobs = 0, blocks = 0;
     size_t lds = 0;
     auto flush = [&]() -> hipError_t {
-        if (tbl.njobs == 0) return hipSuccess;
-        hipError_t e = launch_transform_jobs(tbl, blocks, lds, st);
-        tbl.njobs = 0; blocks = 0; lds = 0;
+        if (njobs == 0) return hipSuccess;
+        hipError_t e = launch_transform_jobs(tbl, njobs, blocks, lds, st);
+        njobs = 0; blocks = 0; lds = 0;
         return e;
     };
     for (int i = 0; i < n; ++i) {
@@ -164,13 +163,14 @@ int transform_many(int n, const nnv_conv_desc *descs, const nnv_kind *kinds, con
         const size_t src_step = (size_t)one.k * one.cg * one.r * one.s;
         const size_t dst_step = grouped ? tx_bytes(one, NNV_IM2COL_GEMM) : 0;
         for (int gi = 0; gi < (grouped ? geos[i].groups : 1); ++gi) {
-            TransformJob &job = tbl.job[tbl.njobs];
-            if (fill_transform_job(one, kinds[i], w_raw[i] + gi * src_step, static_cast<char *>(w_tx[i]) + gi * dst_step, &job))
+            TransformJob &job = tbl.job[njobs];
+            int nblocks;
+            if (fill_transform_job(one, kinds[i], w_raw[i] + gi * src_step, static_cast<char *>(w_tx[i]) + gi * dst_step, &job, &nblocks))
                 return NNV_E_UNSUPPORTED;
-            job.block0 = blocks;
-            blocks += job.nblocks;
+            tbl.first_block[njobs] = blocks;
+            blocks += nblocks;
             lds = std::max(lds, transform_job_lds_bytes(job));
-            if (++tbl.njobs == kMaxJobs) {
+            if (++njobs == kMaxJobs) {
                 hipError_t e = flush();
                 if (e != hipSuccess) return hip_fail(e);
             }

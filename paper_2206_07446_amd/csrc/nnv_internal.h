@@ -37,30 +37,32 @@ enum JobType { JOB_WINO = 0, JOB_GEMM = 1, JOB_DW = 2 };
 struct TransformJob {
     const float *src;
     void *dst;
-    int type;        // JobType
-    int wset;        // WinoSet (JOB_WINO)
-    int half;        // output float16
-    int K, C, RS;    // rows, channels per row, taps
-    int cchunk;      // channels handled by one block
-    int nchunks;     // blocks per 16-row group
-    int block0;      // first block of this job in the launch
-    int nblocks;
+    uint16_t K, C, RS;      // rows, channels per row, taps
+    uint16_t cchunk;        // channels handled by one block
+    uint16_t nchunks;       // blocks per 16-row group
+    uint8_t type;           // JobType
+    uint8_t wset;           // WinoSet (JOB_WINO)
+    uint8_t half;           // output float16
+    uint8_t unused[3];
 };
-constexpr int kMaxJobs = 64;   // 64 jobs of 56 bytes + 64 block offsets: the table still fits the 4 KB of kernel arguments
+// 112 jobs of 32 bytes + 112 block offsets fit the 4 KB of kernel arguments: the candidates of every
+// stack here but two go out in one launch (a second one for the last few jobs ran 15 us by itself).
+constexpr int kMaxJobs = 112;
 struct JobTable {
     TransformJob job[kMaxJobs];
-    int first_block[kMaxJobs];   // job[j].block0 again, INT_MAX beyond the last job: a block finds its job by
-                                 // counting the entries it has reached (no chain of dependent loads)
-    int njobs;
+    int first_block[kMaxJobs];   // first block of each job in the launch, INT_MAX beyond the last job: a block
+                                 // finds its job by counting the entries it has reached (no chain of dependent loads)
 };
 static_assert(sizeof(JobTable) <= 4096, "the job table is passed by value as the kernel argument");
+constexpr int kMaxGemmGroups = 64;   // groups of an IM2COL_GEMM layer: a transformation job each
 
 // Records the text of a failed HIP call for nnv_last_hip_error and returns NNV_E_HIP.
 int record_hip_error(hipError_t e);
 
-int fill_transform_job(const Geo &g, int kind, const float *src, void *dst, TransformJob *job);
+int fill_transform_job(const Geo &g, int kind, const float *src, void *dst, TransformJob *job, int *nblocks);
 size_t transform_job_lds_bytes(const TransformJob &job);
-hipError_t launch_transform_jobs(const JobTable &tbl, int total_blocks, size_t lds, hipStream_t st);
+// jobs [0, njobs) of tbl with their first_block entries set; the entries beyond are filled in here
+hipError_t launch_transform_jobs(JobTable &tbl, int njobs, int total_blocks, size_t lds, hipStream_t st);
 hipError_t launch_copy_f32(const float *src, float *dst, size_t n, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *dst, size_t n, uint32_t v, hipStream_t st);
 

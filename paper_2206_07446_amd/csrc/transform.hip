@@ -66,11 +66,17 @@ __device__ static inline uint32_t pack_half2(float a, float b) {
     return *reinterpret_cast<uint32_t *>(&h);
 }
 
-// Channels per block of a Winograd job: 32 in float32 (21 KB of LDS per block, seven blocks per CU;
-// measured 4 % faster than 64), 64 in float16 (a wavefront packs 8 channels per lane pair).
-__host__ __device__ constexpr int wino_chunk(bool half) { return half ? 64 : 32; }
+// Eight floats, `step` apart, as eight halves.
+__device__ static inline uint4v pack_half8(const float *p, int step) {
+    return uint4v{pack_half2(p[0], p[step]), pack_half2(p[2 * step], p[3 * step]), pack_half2(p[4 * step], p[5 * step]),
+                  pack_half2(p[6 * step], p[7 * step])};
+}
 
-// Winograd weight transformation of one block: 16 output channels x up to wino_chunk channels.
+// Channels per block of a Winograd job: 18.7 KB of LDS per block, eight blocks per CU (float32: measured
+// 4 % faster than 64; float16: the sixteen F(4x4) jobs of a ResNet-50-shaped stack 26.0 -> 23.3 us).
+constexpr int kWinoChunk = 32;
+
+// Winograd weight transformation of one block: 16 output channels x up to kWinoChunk channels.
 template <int SET, bool HALF>
 __device__ static inline void wino_block(const TransformJob &job, int local_block, float *lds) {
     using W = WinoMat<SET>;
@@ -78,7 +84,7 @@ __device__ static inline void wino_block(const TransformJob &job, int local_bloc
     const int kb = local_block / job.nchunks, chunk = local_block % job.nchunks;
     const int K16 = (job.K + 15) / 16;
     const int cpad = HALF ? ((job.C + 31) / 32) * 32 : ((job.C + 3) / 4) * 4;
-    constexpr int CH = wino_chunk(HALF);
+    constexpr int CH = kWinoChunk;
     const int c0 = chunk * CH;
     const int cfill = min(CH, cpad - c0);
     const int cvalid = max(0, min(CH, job.C - c0));
@@ -122,50 +128,73 @@ __device__ static inline void wino_block(const TransformJob &job, int local_bloc
             }
         }
     } else {
+        // two filters per thread: thread t owns bytes 4 t .. of the fragment of 16 x 32 halves
         __half *dst = static_cast<__half *>(job.dst);
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        const int oct = wave * 2 + (lane >> 5), hq = lane & 1, k_in = (lane >> 1) & 15;
-        if (oct * 8 < cfill) {
-            // four filters per thread (channels cl .. cl + 3 of its 8-channel lane pair), U row by row
-            float g[4][9];
-            const int cl = oct * 8 + hq * 4;
+        const int k_in = (threadIdx.x >> 2) & 15, cl = (threadIdx.x >> 6) * 8 + (threadIdx.x & 3) * 2;
+        float g[2][9];
 #pragma unroll
-            for (int f = 0; f < 4; ++f)
+        for (int f = 0; f < 2; ++f)
 #pragma unroll
-                for (int i = 0; i < 9; ++i) g[f][i] = lds[k_in * ROW + (cl + f) * 9 + i];
-            const int cabs = c0 + oct * 8;
-            const int c32n = cpad / 32;
-            __half *o = dst + ((size_t)kb * c32n + cabs / 32) * 512 + ((cabs % 32) / 8) * 128 + k_in * 8 + hq * 4;
-            const size_t xi_stride = (size_t)K16 * c32n * 512;
+            for (int i = 0; i < 9; ++i) g[f][i] = lds[k_in * ROW + (cl + f) * 9 + i];
+        const int c32n = cpad / 32;
+        uint32_t *o = reinterpret_cast<uint32_t *>(dst + ((size_t)kb * c32n + chunk) * 512) + threadIdx.x;
+        const size_t xi_stride = (size_t)K16 * c32n * 256;
 #pragma unroll
-            for (int a = 0; a < W::A; ++a) {
-                float t[4][3];
+        for (int a = 0; a < W::A; ++a) {
+            float t[2][3];
 #pragma unroll
-                for (int f = 0; f < 4; ++f)
+            for (int f = 0; f < 2; ++f)
 #pragma unroll
-                    for (int s2 = 0; s2 < 3; ++s2) {
-                        float acc = 0.f;
+                for (int s2 = 0; s2 < 3; ++s2) {
+                    float acc = 0.f;
 #pragma unroll
-                        for (int r = 0; r < 3; ++r)
-                            if (W::G[a][r] != 0.f) acc += W::G[a][r] * g[f][r * 3 + s2];
-                        t[f][s2] = acc;
-                    }
-#pragma unroll
-                for (int b = 0; b < W::A; ++b) {
-                    float u[4];
-#pragma unroll
-                    for (int f = 0; f < 4; ++f) {
-                        float acc = 0.f;
-#pragma unroll
-                        for (int s2 = 0; s2 < 3; ++s2)
-                            if (W::G[b][s2] != 0.f) acc += t[f][s2] * W::G[b][s2];
-                        u[f] = acc;
-                    }
-                    nt_store(reinterpret_cast<uint2v *>(o), uint2v{pack_half2(u[0], u[1]), pack_half2(u[2], u[3])});
-                    o += xi_stride;
+                    for (int r = 0; r < 3; ++r)
+                        if (W::G[a][r] != 0.f) acc += W::G[a][r] * g[f][r * 3 + s2];
+                    t[f][s2] = acc;
                 }
+#pragma unroll
+            for (int b = 0; b < W::A; ++b) {
+                float u[2];
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    float acc = 0.f;
+#pragma unroll
+                    for (int s2 = 0; s2 < 3; ++s2)
+                        if (W::G[b][s2] != 0.f) acc += t[f][s2] * W::G[b][s2];
+                    u[f] = acc;
+                }
+                nt_store(o, pack_half2(u[0], u[1]));
+                o += xi_stride;
             }
         }
+    }
+}
+
+// float16 pack of a 1x1 filter (C a multiple of 4, for the 16-byte loads): a lane's eight channels are 32 contiguous bytes of its row and its 16 bytes
+// of the fragment, so nothing has to be staged: a row of a fragment is one cache line of the raw
+// tensor.  All loads of a wavefront's fragments are in flight before the first store.
+__device__ static inline void pack_pointwise_half(const TransformJob &job, const int kb, const int c0, const int cfill, const int cpad) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = kb * 16 + (lane & 15), cl = (lane >> 4) * 8;
+    const float *row = job.src + (size_t)min(k, job.K - 1) * job.C;
+    __half *dst = static_cast<__half *>(job.dst) + (size_t)kb * cpad * 16 + (size_t)c0 * 16;
+    const int nfrag = cfill / 32;
+    constexpr int UN = 4;
+    for (int f0 = wave; f0 < nfrag; f0 += 4 * UN) {
+        float4 v[UN][2];
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = c0 + (f0 + 4 * u) * 32 + cl + 4 * h;
+                v[u][h] = *reinterpret_cast<const float4 *>(row + min(c, job.C - 4));
+                if (k >= job.K || c >= job.C) v[u][h] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (f0 + 4 * u < nfrag)
+                nt_store(reinterpret_cast<uint4v *>(dst + (size_t)(f0 + 4 * u) * 512 + lane * 8),
+                         uint4v{pack_half2(v[u][0].x, v[u][0].y), pack_half2(v[u][0].z, v[u][0].w), pack_half2(v[u][1].x, v[u][1].y), pack_half2(v[u][1].z, v[u][1].w)});
     }
 }
 
@@ -178,6 +207,11 @@ __device__ static inline void gemm_block(const TransformJob &job, int local_bloc
     const int c0 = chunk * job.cchunk;
     const int cfill = min(job.cchunk, cpad - c0);
     const int cvalid = max(0, min(job.cchunk, job.C - c0));
+    if constexpr (HALF)
+        if (RS == 1 && (job.C & 3) == 0) {
+            pack_pointwise_half(job, kb, c0, cfill, cpad);
+            return;
+        }
     const int ROW = lds_row_stride(min(job.cchunk, cpad) * RS);
     stage_rows(job.src, lds, ROW, kb * 16, job.K, (size_t)job.C * RS, (size_t)c0 * RS, cvalid * RS, cfill * RS);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -193,21 +227,25 @@ __device__ static inline void gemm_block(const TransformJob &job, int local_bloc
             rs += 4;
             while (rs >= RS) { rs -= RS; ++cb; }
         }
-    } else {
+    } else if (job.cchunk >= 32) {
         __half *dst = static_cast<__half *>(job.dst) + ((size_t)kb * (cpad / 32) + c0 / 32) * RS * 512;
         const int nfrag = (cfill / 32) * RS;
         int cb = 0, rs = wave;
         while (rs >= RS) { rs -= RS; ++cb; }
         for (int f = wave; f < nfrag; f += 4) {
             const float *lp = lds + k_in * ROW + (cb * 32 + grp * 8) * RS + rs;
-            uint4 v;
-            v.x = pack_half2(lp[0], lp[RS]);
-            v.y = pack_half2(lp[2 * RS], lp[3 * RS]);
-            v.z = pack_half2(lp[4 * RS], lp[5 * RS]);
-            v.w = pack_half2(lp[6 * RS], lp[7 * RS]);
-            nt_store(reinterpret_cast<uint4v *>(dst + (size_t)f * 512 + lane * 8), uint4v{v.x, v.y, v.z, v.w});
+            nt_store(reinterpret_cast<uint4v *>(dst + (size_t)f * 512 + lane * 8), pack_half8(lp, RS));
             rs += 4;
             while (rs >= RS) { rs -= RS; ++cb; }
+        }
+    } else {
+        // large filters: a chunk is 8 or 16 channels of a fragment, an octet of channels at one tap is
+        // 256 contiguous bytes of it, written by 16 lanes
+        __half *dst = static_cast<__half *>(job.dst) + ((size_t)kb * (cpad / 32) + c0 / 32) * RS * 512 + (c0 % 32) * 16;
+        const int nitem = (job.cchunk / 8) * RS;
+        for (int f = wave * 4 + grp; f < nitem; f += 16) {
+            const int oct = f / RS, rs = f - oct * RS;
+            nt_store(reinterpret_cast<uint4v *>(dst + (size_t)rs * 512 + oct * 128 + k_in * 8), pack_half8(lds + k_in * ROW + oct * 8 * RS + rs, RS));
         }
     }
 }
@@ -238,8 +276,8 @@ __global__ __launch_bounds__(256) void transform_kernel(const JobTable tbl_arg) 
     extern __shared__ __align__(16) float lds[];
     const JobTablePtr tbl = (JobTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     const int b = blockIdx.x;
-    int first_unused;
-    const int j = table_find<kMaxJobs>(&tbl->first_block[0], b, first_unused);
+    int first;
+    const int j = table_find<kMaxJobs>(&tbl->first_block[0], b, first);
     TransformJob job;
     {
         static_assert(sizeof(TransformJob) % 4 == 0, "copied word by word");
@@ -248,7 +286,7 @@ __global__ __launch_bounds__(256) void transform_kernel(const JobTable tbl_arg) 
 #pragma unroll
         for (int k = 0; k < (int)(sizeof(TransformJob) / 4); ++k) dst[k] = src[k];
     }
-    const int lb = b - job.block0;
+    const int lb = b - first;
     if (job.type == JOB_WINO) {
         if (job.wset == WS_F2) {
             if (job.half) wino_block<0, true>(job, lb, lds); else wino_block<0, false>(job, lb, lds);
@@ -268,42 +306,35 @@ __global__ __launch_bounds__(256) void transform_kernel(const JobTable tbl_arg) 
 
 // ---------------------------------------------------------------- host side
 
-int fill_transform_job(const Geo &g, int kind, const float *src, void *dst, TransformJob *job) {
-    job->src = src;
-    job->dst = dst;
-    job->half = g.dtype == NNV_F16;
-    job->K = g.k;
-    job->C = g.cg;
-    job->RS = g.r * g.s;
-    job->wset = 0;
-    job->block0 = 0;
-    const int k16 = ceil_div(g.k, 16);
+int fill_transform_job(const Geo &g, int kind, const float *src, void *dst, TransformJob *job, int *nblocks) {
+    const bool half = g.dtype == NNV_F16;
+    const int RS = g.r * g.s, k16 = ceil_div(g.k, 16);
+    const int cpad = half ? ceil_div(g.cg, 32) * 32 : ceil_div(g.cg, 4) * 4;
+    *job = TransformJob{src, dst, (uint16_t)g.k, (uint16_t)g.cg, (uint16_t)RS, 32, 1, JOB_DW, 0, half, {0, 0, 0}};
     if (is_wino(kind)) {
         job->type = JOB_WINO;
-        job->wset = wino_set(kind, g.dtype);
-        const int cpad = job->half ? ceil_div(g.cg, 32) * 32 : ceil_div(g.cg, 4) * 4;
-        job->cchunk = wino_chunk(job->half);
-        job->nchunks = ceil_div(cpad, job->cchunk);
-        job->nblocks = k16 * job->nchunks;
+        job->wset = (uint8_t)wino_set(kind, g.dtype);
+        job->cchunk = (uint16_t)kWinoChunk;
+        job->nchunks = (uint16_t)ceil_div(cpad, job->cchunk);
+        *nblocks = k16 * job->nchunks;
     } else if (kind == NNV_IM2COL_GEMM) {
         job->type = JOB_GEMM;
-        const int cpad = job->half ? ceil_div(g.cg, 32) * 32 : ceil_div(g.cg, 4) * 4;
-        // about 18 KB of LDS per block (as many resident blocks as the Winograd jobs of the
-        // same launch allow): about 288 floats per row, in whole fragments' worth of channels
-        // (float32: 4, so that even an 11x11 filter stages only 31 KB; float16: 32, twice the row)
-        const int unit = job->half ? 32 : 4;
-        int cc = ((job->half ? 576 : 288) / job->RS) / unit * unit;
-        if (cc < unit) cc = unit;
-        if (cc > 32 && !job->half) cc = cc / 32 * 32;
-        job->cchunk = cc;
-        job->nchunks = ceil_div(cpad, cc);
-        job->nblocks = k16 * job->nchunks;
+        // about 18 KB of LDS per block, as the Winograd jobs of the same launch take (every block of a
+        // launch gets what its largest job wants): about 288 floats per row, in whole fragments' worth
+        // of channels (float32: 4, so that even an 11x11 filter stages only 31 KB; float16: 32).
+        // float16 with a filter of more than 20 taps: 16 or 8 channels.  With 32 the 7x7 stem of a
+        // ResNet-50-shaped stack took 103 KB, one block fitted a CU, and its 69 jobs ran 104 us; with 37 KB
+        // (64 channels of a 3x3 filter) 59 us, now 56 us = 4.1 TB/s.  1x1 filters stage nothing (float16).
+        const int unit = half ? 32 : 4;
+        int cc = ((half && RS == 1 ? 512 : 288) / RS) / unit * unit;
+        if (cc < unit) cc = !half || unit * RS <= 640 ? unit : RS <= 40 ? 16 : 8;
+        if (cc > 32 && !half) cc = cc / 32 * 32;
+        job->cchunk = (uint16_t)cc;
+        job->nchunks = (uint16_t)ceil_div(cpad, cc);
+        *nblocks = k16 * job->nchunks;
     } else if (kind == NNV_DEPTHWISE) {
-        job->type = JOB_DW;
-        job->cchunk = 32;
-        job->nchunks = 1;
-        job->nblocks = ceil_div(ceil_div(g.c, 32) * g.r * g.s * 32, 256);
-        job->C = g.c;
+        job->C = (uint16_t)g.c;
+        *nblocks = ceil_div(ceil_div(g.c, 32) * RS * 32, 256);
     } else {
         return -1;
     }
@@ -311,7 +342,7 @@ int fill_transform_job(const Geo &g, int kind, const float *src, void *dst, Tran
 }
 
 size_t transform_job_lds_bytes(const TransformJob &job) {
-    if (job.type == JOB_WINO) return (size_t)kRows * lds_row_stride(wino_chunk(job.half) * 9) * sizeof(float);
+    if (job.type == JOB_WINO) return (size_t)kRows * lds_row_stride(kWinoChunk * 9) * sizeof(float);
     if (job.type == JOB_GEMM) {
         const int cpad = job.half ? ceil_div(job.C, 32) * 32 : ceil_div(job.C, 4) * 4;
         const int cc = job.cchunk < cpad ? job.cchunk : cpad;
@@ -320,12 +351,11 @@ size_t transform_job_lds_bytes(const TransformJob &job) {
     return 0;
 }
 
-hipError_t launch_transform_jobs(const JobTable &table, int total_blocks, size_t lds, hipStream_t st) {
+hipError_t launch_transform_jobs(JobTable &tbl, int njobs, int total_blocks, size_t lds, hipStream_t st) {
     if (total_blocks <= 0) return hipSuccess;
-    JobTable tbl = table;
-    for (int j = 0; j < kMaxJobs; ++j) tbl.first_block[j] = j < tbl.njobs ? tbl.job[j].block0 : INT_MAX;
+    for (int j = njobs; j < kMaxJobs; ++j) tbl.first_block[j] = INT_MAX;
     bool f6 = false;
-    for (int j = 0; j < tbl.njobs; ++j) f6 = f6 || (tbl.job[j].type == JOB_WINO && tbl.job[j].wset == WS_F6);
+    for (int j = 0; j < njobs; ++j) f6 = f6 || (tbl.job[j].type == JOB_WINO && tbl.job[j].wset == WS_F6);
     if (lds > 64 * 1024) {
         const void *fn = f6 ? reinterpret_cast<const void *>(transform_kernel<true>)
                             : reinterpret_cast<const void *>(transform_kernel<false>);

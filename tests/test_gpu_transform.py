@@ -182,3 +182,35 @@ def test_full_size_resnet18_transforms(env):
                 got, *_ = gpu_transform(nnv, torch, layer, kind, False, w)
                 exp64, bound = oracle_transformed(w, kind, False)
                 check_wino_u(got, exp64, bound, False)
+
+
+# float16 packs: chunks of 8, 16 and 32 channels (more than one per fragment, a ragged last one), 1x1 with and
+# without 16-byte rows and with more channels than one block takes
+HALF_PACKS = [L(50, 20, r=5, pad=2), L(70, 17, r=7, hw=16, pad=3), L(100, 33), L(37, 24, r=1, pad=0), L(516, 17, r=1, pad=0),
+              L(4, 5, r=1, pad=0)]
+
+
+@pytest.mark.parametrize("layer", HALF_PACKS, ids=lambda l: l.name)
+def test_half_gemm_pack_chunks(env, layer):
+    nnv, torch = env
+    got, *_ = gpu_transform(nnv, torch, layer, nnv.IM2COL_GEMM, True, layer_tensors(layer, 8)[0])
+    exp, _ = oracle_transformed(layer_tensors(layer, 8)[0], nnv.IM2COL_GEMM, True, 1)
+    assert np.array_equal(got.view(np.uint16), exp.view(np.uint16))
+
+
+@pytest.mark.parametrize("half", [False, True])
+def test_more_jobs_than_a_launch_holds(env, half):
+    """112 jobs go into one launch, their blocks found through two table entries per lane; the rest into a second one."""
+    nnv, torch = env
+    dev = torch.device("cuda:0")
+    layers = [L(4 + i % 7, 3 + i % 37, r=1 if i % 3 else 3, pad=0) for i in range(130)]
+    ws = [layer_tensors(l, 900 + i)[0] for i, l in enumerate(layers)]
+    descs = [nnv.make_desc(l, nnv.F16 if half else nnv.F32) for l in layers]
+    kinds = [nnv.IM2COL_GEMM] * len(layers)
+    wd = [torch.from_numpy(w).to(dev) for w in ws]
+    wt = [torch.full((nnv.nnv_transformed_bytes(d, nnv.IM2COL_GEMM),), 0x5A, dtype=torch.uint8, device=dev) for d in descs]
+    nnv.nnv_transform_weights_grouped(descs, kinds, wd, wt)
+    torch.cuda.synchronize()
+    for l, w, t in zip(layers, ws, wt):
+        exp, _ = oracle_transformed(w, nnv.IM2COL_GEMM, half, 1)
+        assert np.array_equal(t.cpu().numpy(), np.ascontiguousarray(exp).view(np.uint8).reshape(-1)), l
