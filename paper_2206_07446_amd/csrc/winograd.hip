@@ -1,6 +1,6 @@
 // Winograd F(2x2,3x3) / F(4x4,3x3) / F(6x6,3x3) convolution from transformed weights (the fastest
 // executing, most expensive to prepare kernel family of Table 2).  Three kernels:
-//   1. input transform   V[xi][tile block][c][16 tiles] = (B^T d B)[xi]   (vector ALU)
+//   1. input transform   V[xi][tile block][c][tiles] = (B^T d B)[xi]      (vector ALU)
 //   2. batched tile GEMM M[xi] = U[xi] (K x C) * V[xi] (C x T), alpha^2 independent
 //      products on the matrix cores; U and V are stored as ready-made 16-row operand
 //      fragments, so both are read with one coalesced load per fragment and no LDS;
@@ -11,6 +11,7 @@
 // precision; the transforms and the accumulation are float32.
 // float32 F(2x2) / F(4x4) layers with many tiles and few channels run instead as ONE kernel
 // (wino_fused_kernel below) that keeps V and M in registers and needs no workspace.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 #include "nnv_internal.h"
@@ -30,10 +31,10 @@ struct WinoParams {
     const float *bias;
     void *y;
     int N, C, H, W, K, ph, pw, P, Q;
-    int th, tw, T, T16;     // tiles per image (rows, cols), total tiles, 16-blocks of tiles
+    int th, tw, T;          // tiles per image (rows, cols), total tiles
+    int tn, nblk, Tpad;     // tiles come in nblk blocks of 16 tn (tn: 1 or 2); Tpad = 16 tn nblk
     int K16, cpad, csteps;  // cpad: channels padded to 4 (float32) / 32 (float16); csteps = cpad / that
     int ks_shift;           // wavefronts sharing one output tile (splitting the channels) = 1 << ks_shift
-    int ntb;                // tile-block groups per frequency: ceil(T16 / TN)
     uint32_t u_bytes, v_bytes;   // sizes of U and V (range-checked loads)
     uint32_t x_bytes;            // size of x
     int relu;                    // outputs clamped at zero before the store
@@ -56,24 +57,27 @@ struct WinoParams {
         out[i_][j_] = acc_;                                                             \
     }
 
-// ---- 1. input transform.  Block = 16 tiles x 16 channels (float32: x blockDim/16 channels, so
-// that small layers can be spread over more, smaller workgroups).
+// ---- 1. input transform.  Workgroup = a block of 16 tn tiles x as many channels as its threads cover.
 // (tb, by): tile block and channel group of the workgroup; bdim: its threads
+// V, float32: [xi][block][c][16 tn tiles], so that lane n of the tile GEMM reads its tn tiles tn n ..
+// with one load.  float16: [xi][block][t][operand fragments of 16 tiles x 32 channels], tile tn n + t of
+// the block being row n of its t-th fragment (the GEMM then stores neighbouring tiles together).
 template <int SET, bool HALF>
 __device__ __forceinline__ void wino_input_block(const WinoParams &w, const int tb, const int by, const int bdim) {
     using Wm = WinoMat<SET>;
     constexpr int A = Wm::A, M = Wm::M;
     typedef typename std::conditional<HALF, __half, float>::type T;
-    int t_in, c;
-    if (HALF) {   // lanes: 8 channels fastest, then tiles -> 128 B contiguous half stores
-        t_in = (threadIdx.x >> 3) & 15;
-        c = by * 16 + (threadIdx.x >> 7) * 8 + (threadIdx.x & 7);
-    } else {      // lanes: 16 tiles fastest, then channels -> 256 B contiguous stores
-        t_in = threadIdx.x & 15;
-        c = (by * bdim + threadIdx.x) >> 4;
+    int tl, c;      // tile within the block, channel
+    if (HALF) {   // lanes: 8 channels fastest, then tiles -> 128 B contiguous half stores; 16 tiles x 16 channels per workgroup
+        tl = ((threadIdx.x >> 3) & 15) * w.tn + by % w.tn;
+        c = (by / w.tn) * 16 + (threadIdx.x >> 7) * 8 + (threadIdx.x & 7);
+    } else {      // lanes: the tiles of the block fastest, then channels -> 256 B contiguous stores
+        const int sh = w.tn == 2 ? 5 : 4;
+        tl = threadIdx.x & ((1 << sh) - 1);
+        c = (by * bdim + threadIdx.x) >> sh;
     }
     if (c >= w.cpad) return;
-    const int t = tb * 16 + t_in;
+    const int t = tb * 16 * w.tn + tl;
     // The alpha x alpha patch, all loads in flight at once: elements in the zero padding, of
     // tiles past the end and of padding channels get an out-of-range offset and read as zero.
     float d[A][A];
@@ -102,15 +106,15 @@ __device__ __forceinline__ void wino_input_block(const WinoParams &w, const int 
     NNV_MATMUL_LEFT(Wm::BT, A, A, A, d, tmp)
     NNV_MATMUL_RIGHT_T(Wm::BT, A, A, A, tmp, V)
     if (HALF) {
-        __half *o = static_cast<__half *>(w.V) + ((size_t)tb * w.csteps + c / 32) * 512 + ((c % 32) / 8) * 128 + t_in * 8 + (c & 7);
-        const size_t xs = (size_t)w.T16 * w.csteps * 512;
+        __half *o = static_cast<__half *>(w.V) + ((size_t)(tb * w.tn + tl % w.tn) * w.csteps + c / 32) * 512 + ((c % 32) / 8) * 128 + (tl / w.tn) * 8 + (c & 7);
+        const size_t xs = (size_t)w.Tpad * w.cpad;
 #pragma unroll
         for (int u = 0; u < A; ++u)
 #pragma unroll
             for (int v = 0; v < A; ++v) o[(u * A + v) * xs] = __float2half_rn(V[u][v]);
     } else {
-        float *o = static_cast<float *>(w.V) + ((size_t)tb * w.cpad + c) * 16 + t_in;
-        const size_t xs = (size_t)w.T16 * w.cpad * 16;
+        float *o = static_cast<float *>(w.V) + ((size_t)tb * w.cpad + c) * (16 * w.tn) + tl;
+        const size_t xs = (size_t)w.Tpad * w.cpad;
 #pragma unroll
         for (int u = 0; u < A; ++u)
 #pragma unroll
@@ -123,132 +127,194 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const WinoParams w) {
     wino_input_block<SET, HALF>(w, blockIdx.x, blockIdx.y, blockDim.x);
 }
 
-// ---- 2. batched tile GEMM.  grid = (tile-block groups, k-block groups, alpha^2).
-template <bool HALF> struct WFrag {
-    typedef float type;
-    __device__ static inline float zero() { return 0.f; }
+// ---- 2. batched tile GEMM: per frequency xi, M[xi] (K x T) = U[xi] (K x C) V[xi] (C x T) on the matrix cores.
+//
+// float32: what bounds a 16x16x4 GEMM fed by one load per operand fragment is the CU's vector memory path (a
+// 256-byte wave load takes it 5-9 cycles, four SIMDs want one fragment each per 32-cycle MFMA), so here a
+// load carries the fragments of several blocks: which row of a block is which output channel is free, as
+// long as the store agrees.  With TM panels (16 output channels x 4 channels, [c][k] in memory) per tile, lane
+// (i, slot) takes TM consecutive floats, rows TM (i % (16/TM)) .. of panel i / (16/TM), channel slot: element
+// m is its operand of the m-th row block.  One 16-byte load replaces four, and V is stored so that the TN tile
+// blocks of a lane are neighbours too: 2 loads per 8 MFMAs instead of 6 (64 x 32 tile).
+// What bounds a launch now is U, V and M through the fabric: the tile GEMMs of a VGG-16-shaped F(4x4) stack move
+// 480 MB (U is 235) in 105 us, the rate of a plain copy; its pass took 207 us before, 177 now.  64 x 64 tiles
+// (TN = 4) move less through L1 and took the same time there, 10 % more on a ResNet-18-shaped stack.
+// float16: fragments are 16 bytes per lane to begin with.
+typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
+template <int N> struct FloatVec { typedef float type __attribute__((ext_vector_type(N))); };
+template <> struct FloatVec<1> { typedef float type; };
+template <int N> __device__ static inline typename FloatVec<N>::type buf_load_floats(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    if constexpr (N == 1) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    else if constexpr (N == 2) return __builtin_bit_cast(typename FloatVec<2>::type, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+    else return __builtin_bit_cast(typename FloatVec<4>::type, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+template <int N> __device__ static inline void buf_store_floats(const typename FloatVec<N>::type &v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    if constexpr (N == 1) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint32x2, v), r, voff, soff, 0);
+}
+template <int N> __device__ static inline float float_of(const typename FloatVec<N>::type &v, int i) {
+    if constexpr (N == 1) return v;
+    else return v[i];
+}
+
+// One step (4 or 32 channels) of a tile's operands.
+template <bool HALF, int TM, int TN> struct WinoStep;
+template <int TM, int TN> struct WinoStep<false, TM, TN> {
+    typename FloatVec<TM>::type a;
+    typename FloatVec<TN>::type b;
 };
-template <> struct WFrag<true> {
-    typedef half8 type;
-    __device__ static inline half8 zero() { return half8{0, 0, 0, 0, 0, 0, 0, 0}; }
+template <int TM, int TN> struct WinoStep<true, TM, TN> {
+    half8 a[TM], b[TN];
 };
 
 // The k-loop is kept to loads and MFMAs: a lone wavefront on a SIMD issues one instruction
 // every four cycles, so every select or address computation in the loop costs as much as a
 // quarter of a float32 MFMA.  Offsets are a per-lane constant (or an out-of-range constant
-// for fragments outside the problem) plus a scalar that advances by one fragment per step.
-// One wavefront's tile of one frequency: TM x TN blocks of 16 x 16, summed over the ks-th of KS
-// ranges of the channel steps; `red` is the workgroup's LDS (used if KS > 1), nt the wavefront's
-// tile slot in it.
+// for panels outside the problem) plus a scalar that advances by one fragment per step.
+// One wavefront's work on one frequency: `run` tiles, TM panels x the TN = w.tn 16-tile blocks of the tile blocks
+// tb, tb + 1, ..., summed over the ks-th of KS ranges of the channel steps (KS > 1: run = 1); `red` is the
+// workgroup's LDS (used if KS > 1), nt the wavefront's tile slot in it.  The first loads of a tile are
+// in flight while the one before it is finished and stored: with 64 channels a tile is 2 us of matrix
+// instructions, as much as it takes to look the layer up and get the first operands, and a launch of
+// such tiles ran at a third of the rate of its long ones.  kb0 >= K16: nothing is loaded, nothing stored.
 template <bool HALF, int TM, int TN, int D>
-__device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi, const int kb0, const int tb0,
+__device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi, const int kb0, const int tb, const int run,
                                                const int ks, const int KS, const int ks_shift, const int nt,
                                                const int lane, float *red) {
-    typedef typename WFrag<HALF>::type frag_t;
     const __amdgpu_buffer_rsrc_t ures = make_rsrc(w.U, w.u_bytes);
     const __amdgpu_buffer_rsrc_t vres = make_rsrc(w.V, w.v_bytes);
-    constexpr uint32_t FB = sizeof(frag_t), FRAG = 64 * FB;
-    uint32_t a_voff[TM], b_voff[TN];
-    uint32_t a_base[TM], b_base[TN];     // fragment index of step 0 (scalars)
+    const int col = lane & 15, slot = lane >> 4;
+    constexpr int QM = 16 / TM;          // float32: lanes per panel
+    constexpr uint32_t FRAG = HALF ? 1024 : 256;
+    const bool any = kb0 < w.K16;
+    uint32_t a_voff[HALF ? TM : 1], b_voff;
+    const uint32_t panel = (uint32_t)w.csteps * FRAG;        // bytes of a panel of U
+    if constexpr (HALF) {
 #pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        const bool ok = kb0 + m < w.K16;
-        a_voff[m] = ok ? lane * FB : kOobOffset;
-        a_base[m] = ok ? ((uint32_t)xi * w.K16 + kb0 + m) * w.csteps : 0u;
+        for (int m = 0; m < TM; ++m) a_voff[m] = kb0 + m < w.K16 ? (uint32_t)m * panel + lane * 16u : kOobOffset;
+        b_voff = lane * 16u;
+    } else {
+        a_voff[0] = kb0 + col / QM < w.K16 ? (uint32_t)(col / QM) * panel + (uint32_t)slot * 64u + (uint32_t)(col % QM) * (4u * TM) : kOobOffset;
+        b_voff = (uint32_t)slot * (64u * TN) + (uint32_t)col * (4u * TN);
     }
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-        const bool ok = kb0 < w.K16 && tb0 + t < w.T16;
-        b_voff[t] = ok ? lane * FB : kOobOffset;
-        b_base[t] = ok ? ((uint32_t)xi * w.T16 + tb0 + t) * w.csteps : 0u;
-    }
+    if (!any) b_voff = kOobOffset;
+    const uint32_t a_base = any ? ((uint32_t)xi * w.K16 + kb0) * panel : 0u;
+    const uint32_t b_base = any ? ((uint32_t)xi * w.nblk + tb) * (uint32_t)TN * panel : 0u;
     const int per_wave = (w.csteps + KS - 1) >> ks_shift;
     const int s_begin = min(w.csteps, ks * per_wave);
     const int s_end = min(w.csteps, s_begin + per_wave);
 
-    frag_t a[2][D][TM], b[2][D][TN];
-    // chunk of D steps starting at step s0; steps past the end re-read the last valid step (unused)
-    auto load_chunk = [&](int buf, int s0) {
+    WinoStep<HALF, TM, TN> st[2][D];
+    // chunk of D steps of tile r starting at step s0; steps past the end read as zero (their products are
+    // added like any others: one path through the loop keeps one set of accumulator registers)
+    auto load_chunk = [&](int buf, int r, int s0) __attribute__((always_inline)) {
+        const uint32_t b_tile = b_base + (uint32_t)r * (TN * panel);
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            const int st = max(min(s0 + d, s_end - 1), 0);
+            const bool in = s0 + d < s_end;          // uniform
+            const uint32_t s = in ? (uint32_t)(s0 + d) : 0u;
+            const uint32_t bo = in ? b_voff : kOobOffset;
+            if constexpr (HALF) {
 #pragma unroll
-            for (int m = 0; m < TM; ++m) a[buf][d][m] = buf_load<frag_t>(ures, a_voff[m], (a_base[m] + st) * FRAG);
+                for (int m = 0; m < TM; ++m) st[buf][d].a[m] = buf_load<half8>(ures, in ? a_voff[m] : kOobOffset, a_base + s * FRAG);
 #pragma unroll
-            for (int t = 0; t < TN; ++t) b[buf][d][t] = buf_load<frag_t>(vres, b_voff[t], (b_base[t] + st) * FRAG);
+                for (int t = 0; t < TN; ++t) st[buf][d].b[t] = buf_load<half8>(vres, bo, b_tile + (uint32_t)t * panel + s * FRAG);
+            } else {
+                st[buf][d].a = buf_load_floats<TM>(ures, in ? a_voff[0] : kOobOffset, a_base + s * FRAG);
+                st[buf][d].b = buf_load_floats<TN>(vres, bo, b_tile + s * (FRAG * TN));
+            }
         }
     };
     floatx4 acc[TM][TN];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
+        for (int m = 0; m < TM; ++m)
 #pragma unroll
-        for (int t = 0; t < TN; ++t) acc[m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto mfma_step = [&](int buf, int d) {
+            for (int t = 0; t < TN; ++t) acc[m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto mfma_step = [&](int buf, int d) __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < TM; ++m)
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
                 if constexpr (HALF)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[buf][d][m], b[buf][d][t], acc[m][t], 0, 0, 0);
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(st[buf][d].a[m], st[buf][d].b[t], acc[m][t], 0, 0, 0);
                 else
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[buf][d][m], b[buf][d][t], acc[m][t], 0, 0, 0);
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(st[buf][d].a, m), float_of<TN>(st[buf][d].b, t), acc[m][t], 0, 0, 0);
             }
     };
-    auto compute = [&](int buf, int s0) {
-        if (s0 + D <= s_end) {
+    // M[xi][k][Tpad tiles]: register (m, t, j) of lane (col, slot) is block row i = 4 slot + j of row block m, tile
+    // TN col + t.  float32: row TM (i % QM) + m of panel i / QM, a lane's part and a part that depends on
+    // (m, j) alone.
+    const uint32_t m_row = (uint32_t)w.Tpad * 4u;
+    const __amdgpu_buffer_rsrc_t mres = make_rsrc(w.M, (uint32_t)w.alpha2 * (uint32_t)w.K16 * 16u * m_row);
+    const int lane_panel = HALF ? 0 : slot * 4 / QM, lane_row = HALF ? slot * 4 : TM * (slot * 4 % QM);
+    const uint32_t m_voff = kb0 + lane_panel < w.K16 ? (uint32_t)(lane_panel * 16 + lane_row) * m_row + (uint32_t)col * (4u * TN) : kOobOffset;
+    const uint32_t m_base = any ? ((uint32_t)xi * w.K16 + kb0) * 16u * m_row + (uint32_t)tb * (64u * TN) : 0u;
+    auto store_row = [&](const int m, const int j, const typename FloatVec<TN>::type &v, const uint32_t off) __attribute__((always_inline)) {
+        if (!HALF || kb0 + m < w.K16) buf_store_floats<TN>(v, mres, m_voff, off);
+    };
+    auto finish = [&](int r) __attribute__((always_inline)) {
+        uint32_t off = m_base + (uint32_t)r * (64u * TN);
 #pragma unroll
-            for (int d = 0; d < D; ++d) mfma_step(buf, d);
-        } else {
+        for (int q = 0; q < TM * 4; ++q) {          // rows in the order of their uniform part
+            const int m = HALF ? q / 4 : q % TM, j = HALF ? q % 4 : q / TM;
+            typename FloatVec<TN>::type v;
 #pragma unroll
-            for (int d = 0; d < D; ++d)
-                if (s0 + d < s_end) mfma_step(buf, d);
+            for (int t = 0; t < TN; ++t) {
+                if constexpr (TN == 1) v = acc[m][t][j];
+                else v[t] = acc[m][t][j];
+            }
+            store_row(m, j, v, off);
+            off += HALF && j == 3 ? 13u * m_row : m_row;
         }
+        clear();
     };
     // (scheduling barriers: the loads of the next chunk stay in front of this chunk's MFMAs)
-    if (s_begin < s_end) {
-        load_chunk(0, s_begin);
-        __builtin_amdgcn_sched_barrier(0);
-        for (int s0 = s_begin; s0 < s_end; s0 += 2 * D) {
-            load_chunk(1, s0 + D);
+    int r = 0, s = s_begin;
+    clear();
+    load_chunk(0, 0, s);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    for (bool more = true; more;) {
+#pragma unroll
+        for (int buf = 0; buf < 2; ++buf) {
+            if (buf == 1 && !more) break;
+            const bool last = s + D >= s_end;
+            const int rn = last ? r + 1 : r, sn = last ? s_begin : s + D;
+            load_chunk(buf ^ 1, min(rn, run - 1), sn);
             __builtin_amdgcn_sched_barrier(0);
-            compute(0, s0);
+#pragma unroll
+            for (int d = 0; d < D; ++d) mfma_step(buf, d);
             __builtin_amdgcn_sched_barrier(0);
-            load_chunk(0, s0 + 2 * D);
-            __builtin_amdgcn_sched_barrier(0);
-            if (s0 + D < s_end) compute(1, s0 + D);
-            __builtin_amdgcn_sched_barrier(0);
+            if (last && KS == 1) finish(r);
+            more = rn < run;
+            r = rn;
+            s = sn;
         }
     }
-    constexpr int NREG = TM * TN * 4;
     if (KS > 1) {
+        constexpr int NREG = TM * TN * 4;
+        float *mine = red + (nt * KS + ks) * NREG * 64 + lane;
 #pragma unroll
         for (int m = 0; m < TM; ++m)
 #pragma unroll
             for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    red[((nt * KS + ks) * NREG + (m * TN + t) * 4 + j) * 64 + lane] = acc[m][t][j];
+                for (int j = 0; j < 4; ++j) mine[((m * 4 + j) * TN + t) * 64] = acc[m][t][j];
         __syncthreads();
-    }
-    // M[xi][kb][tb][16 k][16 t]: lane holds rows 4*(lane/16)+j, column lane%16
-    const int col = lane & 15, slot = lane >> 4;
+        for (int q = ks; q < TM * 4; q += KS) {
+            const int m = HALF ? q / 4 : q % TM, j = HALF ? q % 4 : q / TM;
+            const float *p = red + (nt * KS * NREG + (m * 4 + j) * TN) * 64 + lane;
+            typename FloatVec<TN>::type v;
 #pragma unroll
-    for (int m = 0; m < TM; ++m) {
-#pragma unroll
-        for (int t = 0; t < TN; ++t) {
-            const bool inb = kb0 + m < w.K16 && tb0 + t < w.T16;
-            float *o = w.M + (((size_t)xi * w.K16 + kb0 + m) * w.T16 + tb0 + t) * 256 + slot * 64 + col;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int reg = (m * TN + t) * 4 + j;
-                if ((reg & (KS - 1)) != ks) continue;
-                float v = acc[m][t][j];
-                if (KS > 1) {
-                    v = 0.f;
-                    for (int z = 0; z < KS; ++z) v += red[((nt * KS + z) * NREG + reg) * 64 + lane];
-                }
-                if (inb) o[j * 16] = v;
+            for (int t = 0; t < TN; ++t) {
+                float e = 0.f;
+                for (int z = 0; z < KS; ++z) e += p[(z * NREG + t) * 64];
+                if constexpr (TN == 1) v = e;
+                else v[t] = e;
             }
+            store_row(m, j, v, m_base + (uint32_t)(HALF ? m * 16 + j : q) * m_row);
         }
     }
 }
@@ -266,9 +332,9 @@ __global__ __launch_bounds__(1024) void wino_gemm_kernel(const WinoParams w) {
     const int lwg = xcd_logical_tile(w.gemm_wgs_per_xi * w.alpha2);
     if (lwg < 0) return;
     const int xi = lwg / w.gemm_wgs_per_xi;
-    const int tile = (lwg - xi * w.gemm_wgs_per_xi) * tiles_per_wg + nt;   // flattened (k-block group, tile-block group)
-    const int kbt = tile / w.ntb, tbt = tile - kbt * w.ntb;
-    wino_gemm_tile<HALF, TM, TN, D>(w, xi, kbt * TM, tbt * TN, ks, KS, w.ks_shift, nt, lane, red);   // kb0 >= K16 for surplus wavefronts
+    const int tile = (lwg - xi * w.gemm_wgs_per_xi) * tiles_per_wg + nt;   // flattened (panel group, tile block)
+    const int kbt = tile / w.nblk, tb = tile - kbt * w.nblk;
+    wino_gemm_tile<HALF, TM, TN, D>(w, xi, kbt * TM, tb, 1, ks, KS, w.ks_shift, nt, lane, red);   // kb0 >= K16 for surplus wavefronts
 }
 
 // Bias, optional clamp at zero and store of the M x M outputs of tile t, channel k, clipped to P x Q.
@@ -331,17 +397,17 @@ __device__ __forceinline__ void wino_store_tile(const WinoParams &w, float (&Y)[
     }
 }
 
-// ---- 3. output transform.  Block = 16 tiles x blockDim/16 output channels.
+// ---- 3. output transform.  A thread owns one tile of one output channel; a frequency of M is a contiguous
+// [k][Tpad] array, so the threads take its elements in order and every load of a wavefront is one piece.
 template <int SET, bool HALF>
-__device__ __forceinline__ void wino_output_block(const WinoParams &w, const int tb, const int by, const int bdim) {
+__device__ __forceinline__ void wino_output_block(const WinoParams &w, const int blk, const int bdim) {
     using Wm = WinoMat<SET>;
     constexpr int A = Wm::A, M = Wm::M;
-    const int t_in = threadIdx.x & 15;
-    const int k = (by * bdim + threadIdx.x) >> 4, kb = k >> 4, k_in = k & 15;
-    const int t = tb * 16 + t_in;
+    const int e = blk * bdim + threadIdx.x;
+    const int k = e / w.Tpad, t = e - k * w.Tpad;
     if (t >= w.T || k >= w.K) return;
-    const float *mp = w.M + ((size_t)kb * w.T16 + tb) * 256 + k_in * 16 + t_in;
-    const size_t xs = (size_t)w.K16 * w.T16 * 256;
+    const float *mp = w.M + e;
+    const size_t xs = (size_t)w.K16 * 16 * w.Tpad;
     float m[A][A];
 #pragma unroll
     for (int u = 0; u < A; ++u)
@@ -355,7 +421,7 @@ __device__ __forceinline__ void wino_output_block(const WinoParams &w, const int
 
 template <int SET, bool HALF>
 __global__ __launch_bounds__(256) void wino_output_kernel(const WinoParams w) {
-    wino_output_block<SET, HALF>(w, blockIdx.x, blockIdx.y, blockDim.x);
+    wino_output_block<SET, HALF>(w, blockIdx.x, blockDim.x);
 }
 
 // ---- many layers of one Winograd variant and storage type in three launches (input transforms,
@@ -363,15 +429,16 @@ __global__ __launch_bounds__(256) void wino_output_kernel(const WinoParams w) {
 // work-item launch: a batch-1 layer fills neither the chip nor the time its launch takes.
 // A workgroup finds its layer by counting the entries of a prefix array it has reached.
 constexpr int kWinoItemWaves = 4;
+constexpr int kWinoGroup = 8;      // consecutive tile-GEMM workgroups handed to one XCD
 struct WinoTable {
     WinoParams layer[kMaxWinoLayers];
     int in0[kMaxWinoLayers];      // first workgroup of each layer: input transform,
     int gemm0[kMaxWinoLayers];    //   tile GEMM (workgroups of work items: frequency x tile),
     int out0[kMaxWinoLayers];     //   output transform; INT_MAX beyond the last layer
-    int in_by[kMaxWinoLayers], out_by[kMaxWinoLayers];     // channel groups per tile block (the "y" extent of the single launches)
-    int tm[kMaxWinoLayers], tn[kMaxWinoLayers];            // tile of the GEMM items
+    int in_by[kMaxWinoLayers];    // channel groups per tile block (the "y" extent of the single launch)
+    int tm[kMaxWinoLayers];       // panels per tile of the GEMM items
+    int run[kMaxWinoLayers];      // tile blocks per item
     int n_in, n_gemm, n_out;
-    int gemm_waves;               // wavefronts per tile-GEMM workgroup: 1 or kWinoItemWaves
 };
 static_assert(sizeof(WinoTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) WinoTable *WinoTablePtr;
@@ -406,41 +473,45 @@ __global__ __launch_bounds__(256) void wino_output_many_kernel(const WinoTable t
     NNV_FIND_LAYER(out0, b, li, first)
     WinoParams w;
     load_wino_layer(w, tbl, li);
-    const int local = b - first, by_n = tbl->out_by[li];
-    wino_output_block<SET, HALF>(w, local / by_n, local % by_n, 256);
+    wino_output_block<SET, HALF>(w, b - first, 256);
 }
 
-// Tile GEMM work items (frequency x tile).  A launch of many items runs one item per one-wavefront
-// workgroup.  A launch of few items uses workgroups of kWinoItemWaves wavefronts, and a layer with
-// many channel steps gives each item to 2 or 4 of them that split the steps (summed through LDS in
-// a fixed order): a lone wavefront streams its U panel at the pace of the few loads it keeps in
-// flight, and the 128-step items of a 512-channel layer took 35 us each, as long as the rest of
-// the launch; the wavefronts of a workgroup otherwise take consecutive items.  Items of a layer
-// are ordered frequency slowest; groups of 8 consecutive workgroups go to one XCD.
+// Tile GEMM work items (frequency x tile) in workgroups of kWinoItemWaves wavefronts, which take
+// consecutive items (the same panels of U, neighbouring tile blocks: three of four reads of U hit the CU's
+// L1).  The items of a layer with many channel steps are given to 2 or 4 of them that split the steps
+// (summed through LDS in a fixed order).  Items of a layer are ordered frequency slowest; groups of 8
+// consecutive workgroups go to one XCD.
 template <bool HALF>
-__global__ __launch_bounds__(64 * kWinoItemWaves) void wino_gemm_many_kernel(const WinoTable tbl_arg) {
-    extern __shared__ __align__(16) float red[];      // kWinoItemWaves x 16 accumulator registers x 64 lanes
+__global__ __launch_bounds__(64 * kWinoItemWaves, 4) void wino_gemm_many_kernel(const WinoTable tbl_arg) {
+    extern __shared__ __align__(16) float red[];      // kWinoItemWaves x 32 accumulator registers x 64 lanes
     const WinoTablePtr tbl = (WinoTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
-    constexpr int G = 8;
+    constexpr int G = kWinoGroup;
     const int i = blockIdx.x, xcd = i & 7, j = i >> 3;
     const int wg = ((j / G) * 8 + xcd) * G + j % G;
     if (wg >= tbl->n_gemm) return;
+    __builtin_amdgcn_s_setprio(3);       // the look-up competes for issue slots with the k-loops of the resident wavefronts
     NNV_FIND_LAYER(gemm0, wg, li, first)
     WinoParams w;
     load_wino_layer(w, tbl, li);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int KS = 1 << w.ks_shift, ks = wave & (KS - 1), nt = wave >> w.ks_shift;
-    const int local = (wg - first) * ((int)(blockDim.x >> 6) >> w.ks_shift) + nt;
-    const int tm = tbl->tm[li], tn = tbl->tn[li];
-    const int per_xi = w.gemm_wgs_per_xi;                 // tiles per frequency
+    const int local = (wg - first) * (kWinoItemWaves >> w.ks_shift) + nt;
+    const int tm = tbl->tm[li], run = tbl->run[li];
+    const int per_row = (w.nblk + run - 1) / run;         // items per frequency and panel group: runs of tile blocks
+    const int per_xi = w.gemm_wgs_per_xi;                 // items per frequency
     const bool surplus = local >= per_xi * w.alpha2;      // the last workgroup of a layer may hold fewer items
     const int xi = surplus ? 0 : local / per_xi, tile = local - xi * per_xi;
-    const int kbt = surplus ? w.K16 : tile / w.ntb, tbt = surplus ? 0 : tile - kbt * w.ntb;   // kb0 >= K16: nothing loaded, nothing stored
-    constexpr int D = HALF ? 2 : 4;     // float32: a ring of 4 steps keeps the kernel at 71 registers (7 wavefronts per SIMD); 8 steps and 4 wavefronts were measured: 8-11 % slower on small stacks
-    if (tm == 2 && tn == 2) wino_gemm_tile<HALF, 2, 2, D>(w, xi, kbt * 2, tbt * 2, ks, KS, w.ks_shift, nt, lane, red);
-    else if (tm == 2) wino_gemm_tile<HALF, 2, 1, D>(w, xi, kbt * 2, tbt, ks, KS, w.ks_shift, nt, lane, red);
-    else wino_gemm_tile<HALF, 1, 1, D>(w, xi, kbt, tbt, ks, KS, w.ks_shift, nt, lane, red);
+    const int kbt = surplus ? w.K16 : tile / per_row, tb = surplus ? 0 : (tile - kbt * per_row) * run;   // kb0 >= K16: nothing loaded, nothing stored
+#define NNV_WINO_ITEM(TM, TN, D) wino_gemm_tile<HALF, TM, TN, D>(w, xi, kbt * TM, tb, min(run, w.nblk - tb), ks, KS, w.ks_shift, nt, lane, red)
+    if constexpr (HALF) {
+        if (w.tn == 2) { if (tm == 2) NNV_WINO_ITEM(2, 2, 2); else NNV_WINO_ITEM(1, 2, 2); }
+        else { if (tm == 2) NNV_WINO_ITEM(2, 1, 2); else NNV_WINO_ITEM(1, 1, 2); }
+    } else {
+        if (w.tn == 2) { if (tm == 4) NNV_WINO_ITEM(4, 2, 4); else if (tm == 2) NNV_WINO_ITEM(2, 2, 4); else NNV_WINO_ITEM(1, 2, 4); }
+        else { if (tm == 4) NNV_WINO_ITEM(4, 1, 4); else if (tm == 2) NNV_WINO_ITEM(2, 1, 4); else NNV_WINO_ITEM(1, 1, 4); }
+    }
+#undef NNV_WINO_ITEM
 }
 
 // ---- fused variant (float32, F(2x2) and F(4x4)): all three steps in one kernel, no workspace.
@@ -462,7 +533,8 @@ __global__ __launch_bounds__(256) void wino_fused_kernel(const WinoParams w) {
     // wavefronts of a workgroup share the patches (same tiles, four blocks of output channels)
     const int lwg = xcd_logical_tile(w.gemm_wgs_per_xi);
     if (lwg < 0) return;
-    const int kbg = lwg / w.T16, tb = lwg - kbg * w.T16;
+    const int T16 = (w.T + 15) >> 4;
+    const int kbg = lwg / T16, tb = lwg - kbg * T16;
     const int kb = kbg * 4 + wave;
     if (kb >= w.K16) return;
     const int col = lane & 15, slot = lane >> 4;
@@ -575,7 +647,7 @@ __global__ __launch_bounds__(256) void wino_fused_kernel(const WinoParams w) {
 // ---------------------------------------------------------------- host side
 
 struct WinoPlan {
-    int m, alpha, th, tw, T, T16, K16, cpad, csteps;
+    int m, alpha, th, tw, T, T16, tn, nblk, Tpad, K16, cpad, csteps;
     size_t v_bytes, m_bytes;
 };
 
@@ -588,14 +660,24 @@ static WinoPlan plan_wino(const Geo &g, int kind) {
     p.tw = ceil_div(g.q, p.m);
     p.T = g.n * p.th * p.tw;
     p.T16 = ceil_div(p.T, 16);
+    p.tn = p.T > 16 ? 2 : 1;
+    p.nblk = ceil_div(p.T, 16 * p.tn);
+    p.Tpad = 16 * p.tn * p.nblk;
     p.K16 = ceil_div(g.k, 16);
     const int cb = half ? 32 : 4;
     p.csteps = ceil_div(g.c, cb);
     p.cpad = p.csteps * cb;
     const size_t aa = (size_t)p.alpha * p.alpha;
-    p.v_bytes = align_up(aa * p.T16 * 16 * p.cpad * (half ? 2 : 4), 256);
-    p.m_bytes = align_up(aa * p.K16 * p.T16 * 256 * sizeof(float), 256);
+    p.v_bytes = align_up(aa * p.Tpad * p.cpad * (half ? 2 : 4), 256);
+    p.m_bytes = align_up(aa * p.K16 * 16 * p.Tpad * sizeof(float), 256);
     return p;
+}
+
+// Panels per tile of a tile GEMM: four (float32) unless that leaves more than a seventh of the rows empty.
+static int wino_tm(const WinoPlan &p, bool half, int most = 4) {
+    if (half || most < 4) return std::min(most, p.K16 >= 2 ? 2 : 1);
+    if (p.K16 >= 3 && ceil_div(p.K16, 4) * 4 * 100 <= ceil_div(p.K16, 2) * 2 * 115) return 4;
+    return p.K16 >= 2 ? 2 : 1;
 }
 
 // The fused kernel repeats the input transform (and the strided patch loads, which dominate its
@@ -631,65 +713,54 @@ size_t wino_workspace_bytes(const Geo &g, int kind) {
 
 template <int SET>
 static hipError_t launch_wino_fused(const WinoPlan &p, WinoParams &w, hipStream_t st) {
-    w.u_bytes = (uint32_t)((size_t)p.alpha * p.alpha * p.K16 * p.csteps * 256);
     w.gemm_wgs_per_xi = p.T16 * ceil_div(p.K16, 4);
     hipLaunchKernelGGL((wino_fused_kernel<SET>), dim3(xcd_grid(w.gemm_wgs_per_xi)), dim3(256), 0, st, w);
     return hipGetLastError();
 }
 
+template <bool HALF>
+static void launch_wino_gemm(int tm, int tn, const WinoParams &w, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
+#define NNV_WINO_GEMM(TM, TN, D) hipLaunchKernelGGL((wino_gemm_kernel<HALF, TM, TN, D>), grid, block, lds, st, w)
+    constexpr int D = HALF ? 2 : 4;
+    if (tn == 2) {
+        if (tm == 4) { if constexpr (!HALF) NNV_WINO_GEMM(4, 2, D); }
+        else if (tm == 2) NNV_WINO_GEMM(2, 2, D);
+        else NNV_WINO_GEMM(1, 2, D);
+    } else {
+        if (tm == 4) { if constexpr (!HALF) NNV_WINO_GEMM(4, 1, D); }
+        else if (tm == 2) NNV_WINO_GEMM(2, 1, D);
+        else NNV_WINO_GEMM(1, 1, D);
+    }
+#undef NNV_WINO_GEMM
+}
+
 template <int SET, bool HALF>
 static hipError_t launch_wino_t(const Geo &g, const WinoPlan &p, WinoParams &w, hipStream_t st) {
     {
-        // one wavefront per workgroup (16 tiles x 4 channels) while that keeps the launch small:
-        // a batch-1 layer then occupies four times as many CUs
+        // one wavefront per workgroup while that keeps the launch small: a batch-1 layer then occupies four times as many CUs
         const int bt = (!HALF && (long)p.T16 * ceil_div(p.cpad, 16) < 4096) ? 64 : 256;
-        dim3 grid(p.T16, HALF ? ceil_div(p.cpad, 16) : ceil_div(p.cpad * 16, bt), 1);
+        dim3 grid(p.nblk, HALF ? p.tn * ceil_div(p.cpad, 16) : ceil_div(p.cpad * 16 * p.tn, bt), 1);
         hipLaunchKernelGGL((wino_input_kernel<SET, HALF>), grid, dim3(bt), 0, st, w);
     }
     {
-        // wavefront tile, channel split and workgroup shape: cover >= 1024 wavefronts if possible
-        const long aa = (long)p.alpha * p.alpha;
         // latency-bound at batch 1 (measured on ResNet-18-shaped layers): the largest wavefront
         // tile that still leaves >= 768 wavefronts; then split the channel steps over the
         // wavefronts of a workgroup towards ~4 per SIMD, keeping >= 16 steps each
-        int tm = 1, tn = 1;
-        if (p.T16 >= 2 && aa * ceil_div(p.K16, 2) * ceil_div(p.T16, 2) >= 768) { tm = 2; tn = 2; }
-        else if (aa * ceil_div(p.K16, 2) * p.T16 >= 768) { tm = 2; }
+        const long aa = (long)p.alpha * p.alpha;
+        int tm = wino_tm(p, HALF);
+        while (tm > 1 && aa * ceil_div(p.K16, tm) * p.nblk < 768) tm = tm == 4 ? wino_tm(p, HALF, 2) : 1;
         int shift = 0;
-        const long tiles = (long)ceil_div(p.K16, tm) * ceil_div(p.T16, tn);
+        const long tiles = (long)ceil_div(p.K16, tm) * p.nblk;
         while (shift < 4 && ((aa * tiles) << shift) < 4096 && (p.csteps >> (shift + 1)) >= (HALF ? 4 : 16)) ++shift;
-        const int d = HALF ? 2 : 8;
         w.ks_shift = shift;
-        w.ntb = ceil_div(p.T16, tn);
-        w.u_bytes = (uint32_t)((size_t)aa * p.K16 * p.csteps * 64 * (HALF ? 16 : 4));
-        w.v_bytes = (uint32_t)((size_t)aa * p.T16 * p.csteps * 64 * (HALF ? 16 : 4));
-        const int KS = 1 << shift;
-        const int waves = KS;
-        const int tiles_per_wg = waves / KS;
-        const long ntiles = (long)ceil_div(p.K16, tm) * w.ntb;
-        w.gemm_wgs_per_xi = ceil_div((int)ntiles, tiles_per_wg);
-        w.alpha2 = (int)aa;
-        dim3 grid(xcd_grid(w.gemm_wgs_per_xi * (int)aa), 1, 1);
-        dim3 block(64 * waves);
-        const size_t lds = KS > 1 ? (size_t)waves * tm * tn * 4 * 64 * sizeof(float) : 0;
-        if constexpr (HALF) {
-            if (tm == 2 && tn == 2) hipLaunchKernelGGL((wino_gemm_kernel<HALF, 2, 2, 2>), grid, block, lds, st, w);
-            else if (tm == 2 && tn == 1) hipLaunchKernelGGL((wino_gemm_kernel<HALF, 2, 1, 2>), grid, block, lds, st, w);
-            else hipLaunchKernelGGL((wino_gemm_kernel<HALF, 1, 1, 2>), grid, block, lds, st, w);
-        } else if (d == 4) {
-            if (tm == 2 && tn == 2) hipLaunchKernelGGL((wino_gemm_kernel<false, 2, 2, 4>), grid, block, lds, st, w);
-            else if (tm == 2 && tn == 1) hipLaunchKernelGGL((wino_gemm_kernel<false, 2, 1, 4>), grid, block, lds, st, w);
-            else hipLaunchKernelGGL((wino_gemm_kernel<false, 1, 1, 4>), grid, block, lds, st, w);
-        } else {
-            if (tm == 2 && tn == 2) hipLaunchKernelGGL((wino_gemm_kernel<false, 2, 2, 8>), grid, block, lds, st, w);
-            else if (tm == 2 && tn == 1) hipLaunchKernelGGL((wino_gemm_kernel<false, 2, 1, 8>), grid, block, lds, st, w);
-            else hipLaunchKernelGGL((wino_gemm_kernel<false, 1, 1, 8>), grid, block, lds, st, w);
-        }
+        w.gemm_wgs_per_xi = (int)tiles;
+        const int waves = 1 << shift;
+        const size_t lds = waves > 1 ? (size_t)waves * tm * p.tn * 4 * 64 * sizeof(float) : 0;
+        launch_wino_gemm<HALF>(tm, p.tn, w, dim3(xcd_grid(w.gemm_wgs_per_xi * (int)aa)), dim3(64 * waves), lds, st);
     }
     {
         const int bt = (long)p.T16 * p.K16 < 4096 ? 64 : 256;
-        dim3 grid(p.T16, p.K16 * (256 / bt), 1);
-        hipLaunchKernelGGL((wino_output_kernel<SET, HALF>), grid, dim3(bt), 0, st, w);
+        hipLaunchKernelGGL((wino_output_kernel<SET, HALF>), dim3((unsigned)(((long)g.k * p.Tpad + bt - 1) / bt)), dim3(bt), 0, st, w);
     }
     return hipGetLastError();
 }
@@ -704,10 +775,11 @@ static WinoParams wino_params(const Geo &g, const WinoPlan &p, const void *x, co
     w.N = g.n; w.C = g.c; w.H = g.h; w.W = g.w; w.K = g.k; w.ph = g.ph; w.pw = g.pw; w.P = g.p; w.Q = g.q;
     w.x_bytes = (uint32_t)((size_t)g.n * g.c * g.h * g.w * (half ? 2 : 4));
     w.relu = g.relu;
-    w.th = p.th; w.tw = p.tw; w.T = p.T; w.T16 = p.T16; w.K16 = p.K16; w.cpad = p.cpad; w.csteps = p.csteps;
+    w.th = p.th; w.tw = p.tw; w.T = p.T; w.tn = p.tn; w.nblk = p.nblk; w.Tpad = p.Tpad;
+    w.K16 = p.K16; w.cpad = p.cpad; w.csteps = p.csteps;
     const size_t aa = (size_t)p.alpha * p.alpha;
     w.u_bytes = (uint32_t)(aa * p.K16 * p.csteps * 64 * (half ? 16 : 4));
-    w.v_bytes = (uint32_t)(aa * p.T16 * p.csteps * 64 * (half ? 16 : 4));
+    w.v_bytes = (uint32_t)(aa * p.Tpad * p.cpad * (half ? 2 : 4));
     w.alpha2 = (int)aa;
     return w;
 }
@@ -720,9 +792,8 @@ bool wino_many_supported(const Geo &g, int kind) {
 template <int SET, bool HALF>
 static void launch_wino_many_t(const WinoTable &tbl, hipStream_t st) {
     hipLaunchKernelGGL((wino_input_many_kernel<SET, HALF>), dim3(tbl.n_in), dim3(256), 0, st, tbl);
-    const int per_xcd = ceil_div(ceil_div(tbl.n_gemm, 8), 8) * 8;
-    hipLaunchKernelGGL((wino_gemm_many_kernel<HALF>), dim3(per_xcd * 8), dim3(64 * tbl.gemm_waves),
-                       (size_t)tbl.gemm_waves * 16 * 64 * sizeof(float), st, tbl);
+    hipLaunchKernelGGL((wino_gemm_many_kernel<HALF>), dim3(ceil_div(tbl.n_gemm, 8 * kWinoGroup) * 8 * kWinoGroup), dim3(64 * kWinoItemWaves),
+                       (size_t)kWinoItemWaves * 32 * 64 * sizeof(float), st, tbl);
     hipLaunchKernelGGL((wino_output_many_kernel<SET, HALF>), dim3(tbl.n_out), dim3(256), 0, st, tbl);
 }
 
@@ -735,35 +806,52 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
     const bool half = geos[0].dtype == NNV_F16;
     WinoTable tbl{};
     long n_in = 0, n_gemm = 0, n_out = 0;
-    // a launch of few items (less than two rounds of the chip's wavefront slots) ends with its longest
-    // items: there the items of layers with many channel steps are split over 2 or 4 wavefronts
-    long items = 0;
+    // An item's wavefront should not outlast its share of the launch: matrix instructions of an item against
+    // those of the launch per SIMD; the channel steps of longer items are split over 2 or 4 wavefronts, and the
+    // layers with the longest wavefronts go first.  Items much shorter than a wavefront slot's share (four
+    // per SIMD) take several tile blocks one after the other.
+    WinoPlan plans[kMaxWinoLayers];
+    int order[kMaxWinoLayers];
+    long mfmas[kMaxWinoLayers], total = 0;
     for (int i = 0; i < n; ++i) {
-        const WinoPlan p = plan_wino(geos[i], kind);
-        const int tm = p.K16 >= 2 ? 2 : 1, tn = (tm == 2 && p.T16 >= 2) ? 2 : 1;
-        items += (long)p.alpha * p.alpha * ceil_div(p.K16, tm) * ceil_div(p.T16, tn);
+        if ((geos[i].dtype == NNV_F16) != half || !wino_many_supported(geos[i], kind)) return hipErrorInvalidValue;
+        plans[i] = plan_wino(geos[i], kind);
+        const WinoPlan &p = plans[i];
+        const int tm = wino_tm(p, half);
+        // a step's panels come from HBM once per frequency, whatever the number of tile blocks that share them: at
+        // four wavefronts per SIMD 256 bytes of them take as long as three matrix instructions (half: a quarter of that per KB)
+        mfmas[i] = (long)p.csteps * std::max(tm * p.tn, (half ? 6 : 13) * tm / 4 / p.nblk);
+        total += (long)p.csteps * tm * p.tn * p.alpha * p.alpha * ceil_div(p.K16, tm) * p.nblk;
+        order[i] = i;
     }
-    const bool split = items < 8192;
-    tbl.gemm_waves = split ? kWinoItemWaves : 1;
+    const long most = std::max<long>(half ? 32 : 128, total / 1024 / 6), least = total / 4096 / 4;
+    int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) {
-        const Geo &g = geos[i];
-        if ((g.dtype == NNV_F16) != half || !wino_many_supported(g, kind)) return hipErrorInvalidValue;
-        const WinoPlan p = plan_wino(g, kind);
-        WinoParams &w = tbl.layer[i];
-        w = wino_params(g, p, x[i], U[i], bias ? bias[i] : nullptr, y[i], ws[i]);
-        // tile of a GEMM item: as large as the layer allows (the launch holds thousands of items)
-        const int tm = p.K16 >= 2 ? 2 : 1, tn = (tm == 2 && p.T16 >= 2) ? 2 : 1;
-        // then at most about 32 channel steps per wavefront
-        w.ks_shift = !split ? 0 : p.csteps > 64 ? 2 : p.csteps > 32 ? 1 : 0;
-        w.ntb = ceil_div(p.T16, tn);
-        w.gemm_wgs_per_xi = ceil_div(p.K16, tm) * w.ntb;
-        tbl.tm[i] = tm; tbl.tn[i] = tn;
-        tbl.in_by[i] = half ? p.cpad / 16 : ceil_div(p.cpad * 16, 256);
-        tbl.out_by[i] = p.K16;
-        tbl.in0[i] = (int)n_in; tbl.gemm0[i] = (int)n_gemm; tbl.out0[i] = (int)n_out;
-        n_in += (long)p.T16 * tbl.in_by[i];
-        n_gemm += ceil_div(w.alpha2 * w.gemm_wgs_per_xi, tbl.gemm_waves >> w.ks_shift);
-        n_out += (long)p.T16 * tbl.out_by[i];
+        shifts[i] = 0;
+        while (shifts[i] < 2 && (mfmas[i] >> shifts[i]) > most && (plans[i].csteps >> (shifts[i] + 1)) >= (half ? 2 : 8)) ++shifts[i];
+        runs[i] = 1;
+        if (shifts[i] == 0 && mfmas[i] < least) {
+            const int r = (int)std::min<long>(least / mfmas[i], plans[i].nblk);
+            runs[i] = ceil_div(plans[i].nblk, ceil_div(plans[i].nblk, r));      // equal runs
+            mfmas[i] *= runs[i];
+        }
+    }
+    std::stable_sort(order, order + n, [&](int a, int b) { return (mfmas[a] >> shifts[a]) > (mfmas[b] >> shifts[b]); });
+    for (int o = 0; o < n; ++o) {
+        const int i = order[o];
+        const WinoPlan &p = plans[i];
+        WinoParams &w = tbl.layer[o];
+        w = wino_params(geos[i], p, x[i], U[i], bias ? bias[i] : nullptr, y[i], ws[i]);
+        const int tm = wino_tm(p, half);
+        w.ks_shift = shifts[i];
+        w.gemm_wgs_per_xi = ceil_div(p.K16, tm) * ceil_div(p.nblk, runs[i]);
+        tbl.tm[o] = tm;
+        tbl.run[o] = runs[i];
+        tbl.in_by[o] = half ? p.tn * (p.cpad / 16) : ceil_div(p.cpad * 16 * p.tn, 256);
+        tbl.in0[o] = (int)n_in; tbl.gemm0[o] = (int)n_gemm; tbl.out0[o] = (int)n_out;
+        n_in += (long)p.nblk * tbl.in_by[o];
+        n_gemm += ceil_div(w.alpha2 * w.gemm_wgs_per_xi, kWinoItemWaves >> w.ks_shift);
+        n_out += ((long)geos[i].k * p.Tpad + 255) / 256;
         if (n_in >= (1L << 30) || n_gemm >= (1L << 30) || n_out >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.in0[i] = tbl.gemm0[i] = tbl.out0[i] = INT_MAX;
@@ -780,14 +868,7 @@ hipError_t launch_wino(const Geo &g, int kind, const void *x, const void *U, con
                        hipStream_t st) {
     const WinoPlan p = plan_wino(g, kind);
     if (p.T16 > 65535 * 16 || p.K16 > 65535) return hipErrorInvalidValue;
-    WinoParams w{};
-    w.x = x; w.U = U; w.bias = bias; w.y = y;
-    w.V = ws;
-    w.M = reinterpret_cast<float *>(static_cast<char *>(ws) + p.v_bytes);
-    w.N = g.n; w.C = g.c; w.H = g.h; w.W = g.w; w.K = g.k; w.ph = g.ph; w.pw = g.pw; w.P = g.p; w.Q = g.q;
-    w.x_bytes = (uint32_t)((size_t)g.n * g.c * g.h * g.w * (g.dtype == NNV_F16 ? 2 : 4));
-    w.relu = g.relu;
-    w.th = p.th; w.tw = p.tw; w.T = p.T; w.T16 = p.T16; w.K16 = p.K16; w.cpad = p.cpad; w.csteps = p.csteps;
+    WinoParams w = wino_params(g, p, x, U, bias, y, ws);
     const int set = wino_set(kind, g.dtype);
     if (wino_fused(g, kind, p)) {
         if (set == WS_F2) return launch_wino_fused<0>(p, w, st);
