@@ -279,8 +279,13 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
     for (int half = 0; half < 2; ++half) {
         auto same_type = [&](int i) { return (geos[i].dtype == NNV_F16) == (half == 1); };
         // (the regions of an item launch depend on the item length, which depends on the whole batch: laid out below)
-        collect(GroupedPlan::GEMM_ITEMS, NNV_IM2COL_GEMM, kMaxGemmLayers, 4,
-                [&](int i) { return kinds[i] == NNV_IM2COL_GEMM && same_type(i); }, [&](int) { return (size_t)0; });
+        // (more layers than one launch carries are dealt out evenly: a last launch of a few layers leaves most of the chip idle)
+        auto gemm_item = [&](int i) { return kinds[i] == NNV_IM2COL_GEMM && same_type(i) && im2col_items_supported(geos[i]); };
+        int gemm_layers = 0;
+        for (int i = 0; i < n; ++i) gemm_layers += gemm_item(i) ? 1 : 0;
+        const int gemm_launches = std::max(1, ceil_div(gemm_layers, kMaxGemmLayers));
+        collect(GroupedPlan::GEMM_ITEMS, NNV_IM2COL_GEMM, std::max(1, ceil_div(gemm_layers, gemm_launches)), 4,
+                gemm_item, [&](int) { return (size_t)0; });
         collect(GroupedPlan::DIRECT_MANY, NNV_DIRECT, kMaxDirectLayers, 3,
                 [&](int i) { return kinds[i] == NNV_DIRECT && same_type(i) && direct_many_supported(geos[i]); },
                 [&](int) { return (size_t)0; });

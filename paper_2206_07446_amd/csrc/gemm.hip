@@ -57,6 +57,20 @@ struct GemmParams {
                            // 0: they walk m first (an XCD keeps a pixel range of x)
 };
 
+// The parameters that follow from a layer's sizes, its storage type and its chunking mode.
+__host__ __device__ inline void gemm_derived(GemmParams &g, const bool half, const int mode) {
+    const bool gather = half && mode == 1;      // float16 1x1: B fragments gathered from NCHW
+    g.cpad = (g.C + 31) / 32 * 32;
+    g.cblocks = half ? (g.Cg + 31) / 32 : (g.Cg + 3) / 4;
+    g.c_rem = gather ? g.Cg % 32 : half ? 0 : g.Cg % 4;
+    g.plane_bytes = (uint32_t)g.H * (uint32_t)g.W * 2u;
+    g.half_out = half;
+    const uint32_t pix = (uint32_t)g.N * (uint32_t)g.H * (uint32_t)g.W;
+    g.x_bytes = half ? pix * (uint32_t)(gather ? g.C : g.cpad) * 2u : pix * (uint32_t)g.C * 4u;
+    g.w_bytes = (uint32_t)g.K16 * (uint32_t)g.cblocks * (uint32_t)(g.R * g.S) * (half ? 1024u : 256u);
+    g.cb_stride = gather ? 32u * g.plane_bytes : half ? 64u : (uint32_t)g.H * (uint32_t)g.W * 16u;
+}
+
 template <bool HALF> struct FragT { typedef float type; };
 template <> struct FragT<true> { typedef half8 type; };
 
@@ -600,16 +614,32 @@ struct GemmItemLayer {
     float *part;        // partial tiles of a split layer (workspace): [tile][split][reg][lane]
     int ntn;            // tiles along the pixels
     int nsplit;         // ranges of the reduction (1: the item stores y itself)
-    int mode, tm;       // chunking mode (ModeT); 16-row panels per tile (1 or 2)
+    int mode, tm;       // chunking mode (ModeT); 16-row panels per tile (1, 2 or 4)
 };
+// A layer as the kernel argument carries it: 64 bytes, so that the layers of one call mostly fit one
+// launch (56 of them; 20 with GemmItemLayer itself, which a wavefront derives from this in scalar registers).
+// Three launches of a third of the layers each end with a nearly empty chip three times: the
+// ResNet-50-shaped stack in float16 spent 40 + 29 + 24 us in them, the last with 368 workgroups.
+struct GemmItemRec {
+    const void *x, *wp;
+    const float *bias;
+    void *y;
+    uint32_t part256;                    // offset of the partial tiles from the table's base, in 256 bytes
+    int H, W;
+    uint16_t N, C, K, nsplit, sh, sw, ph, pw;
+    uint8_t R, S, groups;
+    uint8_t mode : 3, tm : 3, relu : 1;
+};
+static_assert(sizeof(GemmItemRec) == 64, "sixteen scalar registers");
 struct GemmItemTable {
-    GemmItemLayer layer[kMaxGemmLayers];
+    GemmItemRec layer[kMaxGemmLayers];
     // first item / first reduction workgroup of each layer, INT_MAX beyond the last layer: a
     // workgroup finds its layer by counting the entries it has reached (table_find)
     int item0[kMaxGemmLayers], red0[kMaxGemmLayers];
-    int nlayers, nitems;
+    char *part_base;
+    int nitems;
     int group;          // consecutive items handed to one XCD
-    int nred;           // workgroups of the reduction launch
+    int half;           // float16 storage
 };
 static_assert(sizeof(GemmItemTable) <= 4096, "the table is passed by value as the kernel argument");
 
@@ -660,12 +690,36 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
 // scratch memory first, in every wavefront.
 typedef const __attribute__((address_space(4))) GemmItemTable *GemmItemTablePtr;
 
-__device__ __forceinline__ void load_item_layer(GemmItemLayer &dst, const GemmItemTablePtr tbl, const int li) {
-    static_assert(sizeof(GemmItemLayer) % 4 == 0, "copied word by word");
+// All of it is uniform: scalar arithmetic on one 64-byte scalar load.
+__device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItemTablePtr tbl, const int li, const bool half) {
+    GemmItemRec r;
     const __attribute__((address_space(4))) uint32_t *src = (const __attribute__((address_space(4))) uint32_t *)&tbl->layer[li];
-    uint32_t *d = reinterpret_cast<uint32_t *>(&dst);
+    uint32_t d[sizeof(GemmItemRec) / 4];
 #pragma unroll
-    for (int i = 0; i < (int)(sizeof(GemmItemLayer) / 4); ++i) d[i] = src[i];
+    for (int i = 0; i < (int)(sizeof(GemmItemRec) / 4); ++i) d[i] = src[i];
+    __builtin_memcpy(&r, d, sizeof r);
+    GemmParams &g = L.g;
+    g.x = r.x; g.wp = r.wp; g.bias = r.bias; g.y = r.y;
+    g.N = r.N; g.C = r.C; g.H = r.H; g.W = r.W; g.K = r.K; g.R = r.R; g.S = r.S;
+    g.sh = r.sh; g.sw = r.sw; g.ph = r.ph; g.pw = r.pw;
+    // (a division by a run-time value costs tens of instructions; strides are 1 or 2, groups 1, nearly always)
+    auto out_size = [](int span, int stride) { return (stride == 1 ? span : stride == 2 ? span >> 1 : span / stride) + 1; };
+    g.P = out_size(g.H + 2 * g.ph - g.R, g.sh);
+    g.Q = out_size(g.W + 2 * g.pw - g.S, g.sw);
+    g.npix = g.N * g.P * g.Q;
+    g.Kg = r.groups == 1 ? g.K : g.K / r.groups;
+    g.Cg = r.groups == 1 ? g.C : g.C / r.groups;
+    g.kg16 = (g.Kg + 15) >> 4;
+    g.K16 = r.groups * g.kg16;
+    g.ks_shift = 0;
+    g.grid_nx = g.grid_ny = g.m_major = 0;
+    L.mode = r.mode;
+    gemm_derived(g, half, r.mode);
+    g.relu = r.relu;
+    L.part = reinterpret_cast<float *>(tbl->part_base + (size_t)r.part256 * 256);
+    L.ntn = (g.npix + 31) >> 5;
+    L.nsplit = r.nsplit;
+    L.tm = r.tm;
 }
 
 constexpr int kItemWaves = 4;      // items per workgroup (one wavefront each)
@@ -691,7 +745,7 @@ __global__ __launch_bounds__(64 * kItemWaves, 3) void gemm_items_kernel(const Ge
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->item0[0], item, first);
     GemmItemLayer L;
-    load_item_layer(L, tbl, li);                     // one batch of scalar loads
+    load_item_layer(L, tbl, li, HALF);
     const int local = item - first;
     const int lane = threadIdx.x & 63;
     if (L.tm == 4) {
@@ -729,7 +783,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmItemTable tb
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->red0[0], b, first);      // the last layer that starts at or before b
     GemmItemLayer L;
-    load_item_layer(L, tbl, li);
+    load_item_layer(L, tbl, li, tbl->half != 0);
     const int nreg = L.tm * 8;                                   // accumulator registers per lane: TM x 2 blocks x 4
     const int per_tile = nreg * 64;
     const int e = ((b - first) * 256 + threadIdx.x) * 4;          // over [tile][reg][lane]
@@ -922,17 +976,8 @@ static GemmParams gemm_params(const Geo &g, int mode, const void *x, const void 
     gp.kg16 = ceil_div(g.kg, 16);
     gp.K16 = g.groups * gp.kg16;
     gp.Kg = g.kg; gp.Cg = g.cg;
-    gp.cpad = ceil_div(g.c, 32) * 32;
-    gp.cblocks = half ? ceil_div(g.cg, 32) : ceil_div(g.cg, 4);
-    const bool gather = half && mode == 1;      // float16 1x1: B fragments gathered from NCHW
-    gp.c_rem = gather ? g.cg % 32 : half ? 0 : g.cg % 4;
-    gp.plane_bytes = (uint32_t)(g.h * g.w * 2);
-    gp.half_out = half;
     gp.relu = g.relu;
-    gp.x_bytes = gather ? (uint32_t)((size_t)g.n * g.c * g.h * g.w * 2)
-                 : half ? (uint32_t)((size_t)g.n * g.h * g.w * gp.cpad * 2) : (uint32_t)((size_t)g.n * g.c * g.h * g.w * 4);
-    gp.w_bytes = (uint32_t)((size_t)gp.K16 * gp.cblocks * g.r * g.s * 64 * (half ? 16 : 4));
-    gp.cb_stride = gather ? 32u * gp.plane_bytes : half ? 64u : (uint32_t)(4 * g.h * g.w * 4);
+    gemm_derived(gp, half, mode);
     return gp;
 }
 
@@ -1018,18 +1063,19 @@ static ItemPlan plan_items(const Geo &g, const int item_steps) {
 }
 
 // Item length of a launch of these layers.
-// float16 items of a call that fills the chip fewer than three times over are a quarter as long:
+// float16 items of a call that fills the chip fewer than three times over are a third as long:
 // such a launch ends with its longest items (a 512-channel 3x3 layer is one item of 144 steps per tile
-// otherwise), and a float16 step moves eight times the channels of a float32 one.  Measured on
-// the ResNet-18-, ResNet-50- and VGG-16-shaped stacks: 75 -> 61, 129 -> 123 and (the long items
-// kept) 184 us against 201 us with the short ones.
+// otherwise), and a float16 step moves eight times the channels of a float32 one.  Measured (us, one
+// call, items of 36 / 48 / 144 steps): ResNet-18-shaped stack 48.2 / 48.3 / 62.7, AlexNet 26.6 / 27.2 / 36.5,
+// GoogLeNet 60.2 / 55.8 / 56.0, SqueezeNet 43.7 / 43.5 / 43.8; above the line (10840 items of 144 steps or
+// more) ResNet-50 78.7 / 77.7 / 77.0 and VGG-16 179 / 178 / 162.
 // float32: a launch whose items all fit the chip at once (kItemsResident, less a sixteenth: a launch
 // that fills every slot was measured slower than one that leaves a few free) takes the shortest
 // item length, in steps of 12 down to kItemStepsMin, with which they still do: the launch lasts as
-// long as an item, and the free slots would stay idle.  Measured (us, one call): SqueezeNet-shaped
-// stack 84 -> 64, GoogLeNet 131 -> 101, AlexNet 80 -> 51, MobileNetV2 66 -> 55, ResNet-50 170 -> 159;
-// the ResNet-18-shaped stack (2882 items of 144 steps) keeps its items.
-constexpr int kItemStepsShortHalf = 36, kItemStepsMin = 48;
+// long as an item, and the free slots would stay idle.  Measured (us, one call, 48 / 72 / 144 steps):
+// AlexNet-shaped stack 35.8 / 42.8 / 63.3, SqueezeNet 42.2 / 37.6 / 38.3; launches above the line keep the long
+// items: ResNet-18 (2882 items) 65.7 / 62.9 / 52.1, ResNet-50 131 / 111 / 98, MobileNetV1 48 / 46 / 44.
+constexpr int kItemStepsShortHalf = 48, kItemStepsMin = 48;
 constexpr int kItemsResident = 256 * 3 * kItemWaves;
 
 int im2col_items_target(int n, const Geo *geos) {
@@ -1051,6 +1097,13 @@ int im2col_items_target(int n, const Geo *geos) {
             best = t;
         }
     return best;
+}
+
+// The launch's 64-byte layer records hold filter sizes and groups in 8 bits, strides, pads and the
+// number of ranges in 16 (channels and images are below 2^16 everywhere).  Only a stride or a pad of 2^16
+// and more does not fit: such a layer is launched by itself.
+bool im2col_items_supported(const Geo &g) {
+    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, kItemStepsMin / 2).nsplit < 65536;
 }
 
 size_t im2col_items_workspace_bytes(const Geo &g, int target) {
@@ -1082,12 +1135,19 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
     GemmItemTable tbl{};
     ChannelsLastTable cl{};
     int items = 0, red = 0, ncl = 0, clblocks = 0;
+    char *base = static_cast<char *>(ws[0]);
+    for (int i = 1; i < n; ++i) base = std::min(base, static_cast<char *>(ws[i]));
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
         const Geo &g = geos[i];
         const ItemPlan &ip = plans[i];
-        GemmItemLayer &L = tbl.layer[o];
-        L.g = gemm_params(g, ip.mode, x[i], w[i], bias ? bias[i] : nullptr, y[i]);
+        GemmItemRec &L = tbl.layer[o];
+        L.x = x[i]; L.wp = w[i]; L.bias = bias ? bias[i] : nullptr; L.y = y[i];
+        L.H = g.h; L.W = g.w;
+        L.N = (uint16_t)g.n; L.C = (uint16_t)g.c; L.K = (uint16_t)g.k;
+        L.sh = (uint16_t)g.sh; L.sw = (uint16_t)g.sw; L.ph = (uint16_t)g.ph; L.pw = (uint16_t)g.pw;
+        L.R = (uint8_t)g.r; L.S = (uint8_t)g.s; L.groups = (uint8_t)g.groups;
+        L.relu = g.relu ? 1 : 0;
         char *region = static_cast<char *>(ws[i]);
         if (ip.xt_bytes) {
             // all channel-last copies of the call are made by one launch in front of the item launch
@@ -1096,27 +1156,26 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
             cl.xt[ncl] = static_cast<__half *>(xt);
             cl.C[ncl] = g.c;
             cl.HW[ncl] = g.h * g.w;
-            cl.cpad[ncl] = L.g.cpad;
+            cl.cpad[ncl] = ceil_div(g.c, 32) * 32;
             cl.block0[ncl] = clblocks;
-            clblocks += ceil_div(g.h * g.w, 256) * (L.g.cpad / 32) * g.n;
+            clblocks += ceil_div(g.h * g.w, 256) * ceil_div(g.c, 32) * g.n;
             ++ncl;
-            L.g.x = xt;
+            L.x = xt;
         }
-        L.part = ip.nsplit > 1 ? reinterpret_cast<float *>(region) : nullptr;
+        L.part256 = (uint32_t)((region - base) / 256);
         tbl.item0[o] = items;
         tbl.red0[o] = red;
-        L.ntn = ip.ntn;
-        L.nsplit = ip.nsplit;
+        L.nsplit = (uint16_t)ip.nsplit;
         L.mode = ip.mode;
         L.tm = ip.tm;
         items += ip.nmt * ip.ntn * ip.nsplit;
         if (ip.nsplit > 1) red += ceil_div(ip.nmt * ip.ntn * (ip.tm * 8), 16);     // 1024 values per workgroup
     }
     for (int i = n; i < kMaxGemmLayers; ++i) tbl.item0[i] = tbl.red0[i] = INT_MAX;
-    tbl.nlayers = n;
     tbl.nitems = items;
     tbl.group = 2;       // workgroups (of kItemWaves items) handed to one XCD in a row
-    tbl.nred = red;
+    tbl.half = half;
+    tbl.part_base = base;
     if (ncl > 0) {
         for (int i = ncl; i < kMaxGemmLayers; ++i) cl.block0[i] = INT_MAX;
         cl.nblocks = clblocks;

@@ -169,6 +169,16 @@ def test_full_stacks_gemm_kind(env, name, half):
     print(name, half, f"worst rel err {worst:.2e}")
 
 
+@pytest.mark.parametrize("half", [False, True], ids=["f32", "f16"])
+@pytest.mark.parametrize("count", [56, 57], ids=["one_launch_full", "dealt_to_two"])
+def test_gemm_launch_capacity(env, half, count):
+    """As many layers as one launch carries, and one more: records of every filter size, stride, pad, group and batch."""
+    nnv, torch = env
+    odd = [Ly("s3_pad4", 12, 17, 23, 20, 5, 3, 4), Ly("r1_pad1", 24, 6, 9, 40, 1, 2, 1), Ly("wide_map", 5, 2, 700, 9, 2, 2, 0)]
+    pool = [l for l in SMALL + odd if 1 in applicable_kinds(l, half)]
+    run_grouped(nnv, torch, [Case(nnv, torch, pool[i % len(pool)], 1, half, 2100 + i, bias=(i % 2 == 1)) for i in range(count)])
+
+
 WINO_SMALL = [
     Ly("cfg1", 16, 32, 32, 16, 3, 1, 1),
     Ly("ragged", 37, 13, 19, 20, 3, 1, 1),
