@@ -179,6 +179,29 @@ def test_gemm_launch_capacity(env, half, count):
     run_grouped(nnv, torch, [Case(nnv, torch, pool[i % len(pool)], 1, half, 2100 + i, bias=(i % 2 == 1)) for i in range(count)])
 
 
+# float16 1x1 layers that read pixels in pairs, and their neighbours that may not (odd planes, strides, pads)
+PAIRS = [
+    Ly("pair_one", 32, 1, 2, 16, 1, 1, 0),                 # a single pair, one channel block, one panel
+    Ly("pair_c1", 1, 6, 5, 17, 1, 1, 0),                   # one channel of 32
+    Ly("pair_k65", 64, 14, 14, 65, 1, 1, 0),               # five panels: two per tile, last row of tiles ragged
+    Ly("pair_k64", 96, 14, 14, 64, 1, 1, 0),               # four panels per tile, three channel blocks
+    Ly("pair_k200", 72, 9, 6, 200, 1, 1, 0),               # thirteen panels: four per tile, ragged; partial block
+    Ly("pair_n3", 40, 5, 6, 48, 1, 1, 0, n=3),             # pairs next to the border between images
+    Ly("pair_deep", 1100, 4, 4, 130, 1, 1, 0),             # ranges of the reduction, last block partial
+    Ly("pair_g2", 80, 10, 7, 256, 1, 1, 0, groups=2),
+    Ly("odd_plane", 64, 7, 7, 64, 1, 1, 0, n=2),
+    Ly("strided", 64, 8, 8, 64, 1, 2, 0),
+    Ly("padded", 64, 8, 8, 64, 1, 1, 1),
+]
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["plain", "relu"])
+def test_float16_pixel_pairs(env, relu):
+    nnv, torch = env
+    cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, True, 2300 + i, bias=(i % 2 == 0)) for i, l in enumerate(PAIRS)]
+    run_grouped(nnv, torch, cases, relu=relu)
+
+
 WINO_SMALL = [
     Ly("cfg1", 16, 32, 32, 16, 3, 1, 1),
     Ly("ragged", 37, 13, 19, 20, 3, 1, 1),
