@@ -161,7 +161,7 @@ int nnv_conv_forward_relu(const nnv_conv_desc *desc, nnv_kind kind, const void *
  * the GPU nor outlasts its own launch: IM2COL_GEMM layers of one storage type share one
  * launch of single-wavefront work items (output tile x range of the reduction) and one
  * reduction launch (float16 layers with filters larger than 1x1: one more, which makes the
- * channels-last copies of all their inputs); Winograd layers of one kind and storage type share three launches (all
+ * copies of all their inputs in octets of channels); Winograd layers of one kind and storage type share three launches (all
  * input transforms, all tile GEMMs, all output transforms), except those nnv_conv_forward
  * runs as one fused kernel; DEPTHWISE layers of one storage type share one launch; DIRECT
  * layers with groups = 1 and a square 1x1, 3x3, 5x5 or 7x7 filter share up to three (one of

@@ -78,7 +78,7 @@ bool kind_rules(const Geo &g, int kind) {
             if (g.r > 32 || g.s > 32 || g.r * g.s > (g.dtype == NNV_F16 ? 64 : 128)) return false;
             if (g.groups == 1) return true;
             // groups: one panel block and one transformation job per group; the float16
-            // channel-last copy needs each group's channels on a fragment boundary
+            // copy in octets of channels needs each group's channels on a fragment boundary
             if (g.groups > kMaxGemmGroups) return false;
             return g.dtype == NNV_F32 || (g.r == 1 && g.s == 1) || g.cg % 32 == 0;
         }
