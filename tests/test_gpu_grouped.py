@@ -202,6 +202,33 @@ def test_float16_pixel_pairs(env, relu):
     run_grouped(nnv, torch, cases, relu=relu)
 
 
+# float16 layers of at most 8 input channels: four taps per step, the last step ragged or not; 9 channels are a layer like any other
+TAPS = [
+    Ly("tap_c1", 1, 9, 9, 16, 3, 1, 1),
+    Ly("tap_stem", 3, 33, 31, 64, 7, 2, 3),                # 49 taps, four panels per tile
+    Ly("tap_c4_2x2", 4, 8, 9, 24, 2, 1, 0),                # 4 taps: one step
+    Ly("tap_c5_5x5", 5, 11, 10, 80, 5, 1, 2, n=3),         # 25 taps, five panels, batch
+    Ly("tap_c8_8x8", 8, 20, 18, 17, 8, 3, 4),              # 64 taps
+    Ly("tap_c8_k200", 8, 12, 12, 200, 3, 2, 1),            # thirteen panels: four per tile, ragged
+    Ly("tap_tiny", 2, 3, 3, 1, 3, 1, 0),                   # one output
+    Ly("c9", 9, 12, 12, 32, 3, 1, 1),
+]
+
+
+def test_float16_few_channels_in_one_call(env):
+    nnv, torch = env
+    cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, True, 2400 + i, bias=(i % 2 == 0)) for i, l in enumerate(TAPS)]
+    run_grouped(nnv, torch, cases)
+    run_grouped(nnv, torch, cases, relu=True)
+
+
+@pytest.mark.parametrize("layer", TAPS + [Ly("tap_many_tiles", 3, 224, 224, 64, 3, 1, 1, n=3)], ids=lambda l: l.name)
+def test_float16_few_channels_alone(env, layer):
+    """One layer per call: every tile shape of the single launch (the last layer has thousands of tiles)."""
+    nnv, torch = env
+    run_grouped(nnv, torch, [Case(nnv, torch, layer, nnv.IM2COL_GEMM, True, 2500, bias=True)])
+
+
 WINO_SMALL = [
     Ly("cfg1", 16, 32, 32, 16, 3, 1, 1),
     Ly("ragged", 37, 13, 19, 20, 3, 1, 1),
