@@ -27,6 +27,19 @@ template <> __device__ inline half8_t buf_load<half8_t>(__amdgpu_buffer_rsrc_t r
     return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
+// N = 1, 2 or 4 consecutive floats in one load.
+template <int N> struct FloatVec { typedef float type __attribute__((ext_vector_type(N))); };
+template <> struct FloatVec<1> { typedef float type; };
+template <int N> __device__ static inline typename FloatVec<N>::type buf_load_floats(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    if constexpr (N == 1) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+    else if constexpr (N == 2) return __builtin_bit_cast(typename FloatVec<2>::type, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+    else return __builtin_bit_cast(typename FloatVec<4>::type, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+template <int N> __device__ static inline float float_of(const typename FloatVec<N>::type &v, int i) {
+    if constexpr (N == 1) return v;
+    else return v[i];
+}
+
 // One activation element (float32 or float16 storage) as float.
 template <typename T> __device__ static inline float buf_load_x(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff);
 template <> __device__ inline float buf_load_x<float>(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {

@@ -141,22 +141,10 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const WinoParams w) {
 // (TN = 4) move less through L1 and took the same time there, 10 % more on a ResNet-18-shaped stack.
 // float16: fragments are 16 bytes per lane to begin with.
 typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
-template <int N> struct FloatVec { typedef float type __attribute__((ext_vector_type(N))); };
-template <> struct FloatVec<1> { typedef float type; };
-template <int N> __device__ static inline typename FloatVec<N>::type buf_load_floats(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    if constexpr (N == 1) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-    else if constexpr (N == 2) return __builtin_bit_cast(typename FloatVec<2>::type, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-    else return __builtin_bit_cast(typename FloatVec<4>::type, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-}
 template <int N> __device__ static inline void buf_store_floats(const typename FloatVec<N>::type &v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     if constexpr (N == 1) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0);
     else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint32x2, v), r, voff, soff, 0);
 }
-template <int N> __device__ static inline float float_of(const typename FloatVec<N>::type &v, int i) {
-    if constexpr (N == 1) return v;
-    else return v[i];
-}
-
 // One step (4 or 32 channels) of a tile's operands.
 template <bool HALF, int TM, int TN> struct WinoStep;
 template <int TM, int TN> struct WinoStep<false, TM, TN> {
