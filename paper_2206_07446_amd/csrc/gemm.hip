@@ -741,7 +741,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
 // (the 32 x 32 tile is launched as one wavefront per workgroup only, and needs more than the 128
 // registers a 16-wavefront workgroup leaves each lane)
 template <bool HALF, int TM, int TN, int MODE, int NBUF>
-__global__ __launch_bounds__(TM * TN == 4 ? 64 : 1024) void im2col_gemm_kernel(const GemmParams g) {
+__global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void im2col_gemm_kernel(const GemmParams g) {
     extern __shared__ __align__(16) float red[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar
@@ -757,7 +757,9 @@ __global__ __launch_bounds__(TM * TN == 4 ? 64 : 1024) void im2col_gemm_kernel(c
     const int nb0 = (bx * tiles_per_wg + nt) * TN;
     floatx4 acc[TM][TN];
     PixState<TN> px;
-    if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
+    constexpr bool MIXED = TM == 4;                       // float32 3x3 only
+    if constexpr (MIXED) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
+    else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(g, mb0, nb0, ks, KS, lane, acc, px);
 
     // ---- sum the KS partial tiles through LDS: red[((nt * KS + ks) * NREG + reg) * 64 + lane]
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(TM * TN == 4 ? 64 : 1024) void im2col_gemm_kernel(c
     // epilogue: lane holds rows 4*slot + j, column col of each block; wavefront ks finishes the
     // accumulator registers reg = ks, ks + KS, ...
     RowState<TM> rs;
-    gemm_rows<TM>(g, mb0, slot, rs);
+    gemm_rows<TM, MIXED>(g, mb0, slot, rs);
     const __amdgpu_buffer_rsrc_t yres = gemm_y_rsrc(g);
     const bool relu = g.relu, half_out = g.half_out;
     uint32_t pixoff[TN];
@@ -1145,6 +1147,23 @@ static GemmPlan plan_im2col(const Geo &g) {
             ++shift;
         return shift;
     };
+    // Large float32 3x3 layers: 64 x 32 tiles, 9 loads per 24 MFMAs.  One such tile of 256 channels is 61 us of matrix
+    // instructions, so a workgroup of two or four wavefronts shares it: as many as give every SIMD one
+    // (1400), and more as long as each keeps 108 steps.  Below that number the smaller tiles are the better ones,
+    // unless the reduction is long.  Measured, us (channels, maps, tiles): 256, 8x56x56, 3136: 283 -> 252;
+    // 256, 1x56x56, 392: 49 -> 44; 512, 8x14x14, 392: 100 -> 81; 512, 16x7x7, 200: 59 -> 48; 200 to 400, 8x20x20, 700: 62 -> 51; 64, 1x224x224, 1568:
+    // 46.5 -> 44.5; 64, 1x112x112, 392: 17.2 -> 17.0; 64, 1x56x56, 98: 7.7 against 12.2 (kept).  1x1 layers lose 20 %.
+    if (!half && g.groups == 1 && pl.mode == 3 && (kg16 % 4 == 0 || kg16 >= 12)) {
+        const long t = tiles(4, 2);
+        const int steps = cblocks * 9;
+        int shift = 0;
+        while (shift < 2 && ((t << shift) < 1400 || (steps >> (shift + 1)) >= 108)) ++shift;
+        if ((t << shift) >= 1400 || (t >= 180 && steps >= 576)) {
+            pl.tm = 4; pl.tn = 2; pl.nbuf = 2;
+            pl.ks_shift = shift;
+            return pl;
+        }
+    }
     // (the float16 1x1 gather keeps eight loads per fragment in flight: no room for the 32x32 tile)
     if (tiles(2, 2) >= 4096 && !(half && pl.mode == 1)) { pl.tm = 2; pl.tn = 2; pl.ks_shift = 0; }
     else if (tiles(2, 1) >= 160) { pl.tm = 2; pl.tn = 1; pl.ks_shift = split_for(tiles(2, 1), 2048); }
@@ -1182,7 +1201,9 @@ static void launch_gemm_mode(int mode, const GemmParams &gp, dim3 grid, dim3 blo
 
 template <bool HALF>
 static void launch_gemm_variant(const GemmPlan &pl, const GemmParams &gp, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
-    if (pl.tm == 2 && pl.tn == 2) launch_gemm_mode<HALF, 2, 2, 2>(pl.mode, gp, grid, block, lds, st);
+    if (pl.tm == 4) {
+        if constexpr (!HALF) hipLaunchKernelGGL((im2col_gemm_kernel<false, 4, 2, 3, 2>), grid, block, lds, st, gp);
+    } else if (pl.tm == 2 && pl.tn == 2) launch_gemm_mode<HALF, 2, 2, 2>(pl.mode, gp, grid, block, lds, st);
     else if (pl.tm == 2 && pl.tn == 1) {
         if (!HALF && pl.nbuf >= 3) launch_gemm_mode<HALF, 2, 1, 3>(pl.mode, gp, grid, block, lds, st);
         else launch_gemm_mode<HALF, 2, 1, 2>(pl.mode, gp, grid, block, lds, st);

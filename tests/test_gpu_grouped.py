@@ -229,6 +229,19 @@ def test_float16_few_channels_alone(env, layer):
     run_grouped(nnv, torch, [Case(nnv, torch, layer, nnv.IM2COL_GEMM, True, 2500, bias=True)])
 
 
+# float32 3x3 layers large enough for the 64 x 32 tile of the single launch, shared by one, two or four wavefronts
+@pytest.mark.parametrize("layer", [
+    Ly("wide_one", 5, 190, 236, 64, 3, 1, 1),              # 1402 tiles, 18 steps: one wavefront, partial channel block
+    Ly("wide_two", 64, 103, 131, 200, 3, 2, 1, n=3),       # thirteen panels, strided, image borders inside a tile
+    Ly("wide_four", 36, 107, 105, 64, 3, 1, 1),            # 352 tiles, four wavefronts with 3, 3, 3 and 0 blocks
+    Ly("wide_long", 260, 29, 29, 450, 3, 1, 1),            # 216 tiles of 585 steps
+    Ly("wide_ragged_k", 24, 61, 193, 250, 3, 1, 0, n=2),   # sixteen panels, the last with 10 rows, no padding
+], ids=lambda l: l.name)
+def test_large_float32_3x3_alone(env, layer):
+    nnv, torch = env
+    run_grouped(nnv, torch, [Case(nnv, torch, layer, nnv.IM2COL_GEMM, False, 2600, bias=True)], big=True, relu=True)
+
+
 WINO_SMALL = [
     Ly("cfg1", 16, 32, 32, 16, 3, 1, 1),
     Ly("ragged", 37, 13, 19, 20, 3, 1, 1),
