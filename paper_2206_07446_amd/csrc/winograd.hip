@@ -427,7 +427,6 @@ struct WinoTable {
     int tm[kMaxWinoLayers];       // panels per tile of the GEMM items
     int run[kMaxWinoLayers];      // tile blocks per item
     int n_in, n_gemm, n_out;
-    int narrow;                   // float32: no item of more than two panels
 };
 static_assert(sizeof(WinoTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) WinoTable *WinoTablePtr;
@@ -470,8 +469,8 @@ __global__ __launch_bounds__(256) void wino_output_many_kernel(const WinoTable t
 // L1).  The items of a layer with many channel steps are given to 2 or 4 of them that split the steps
 // (summed through LDS in a fixed order).  Items of a layer are ordered frequency slowest; groups of 8
 // consecutive workgroups go to one XCD.
-template <bool HALF, int TM_MOST>
-__global__ __launch_bounds__(64 * kWinoItemWaves, HALF ? 5 : TM_MOST == 4 ? 4 : 8) void wino_gemm_many_kernel(const WinoTable tbl_arg) {
+template <bool HALF>
+__global__ __launch_bounds__(64 * kWinoItemWaves, 5) void wino_gemm_many_kernel(const WinoTable tbl_arg) {
     extern __shared__ __align__(16) float red[];      // kWinoItemWaves x 32 accumulator registers x 64 lanes
     const WinoTablePtr tbl = (WinoTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr int G = kWinoGroup;
@@ -497,10 +496,8 @@ __global__ __launch_bounds__(64 * kWinoItemWaves, HALF ? 5 : TM_MOST == 4 ? 4 : 
         if (w.tn == 2) { if (tm == 2) NNV_WINO_ITEM(2, 2, 2); else NNV_WINO_ITEM(1, 2, 2); }
         else { if (tm == 2) NNV_WINO_ITEM(2, 1, 2); else NNV_WINO_ITEM(1, 1, 2); }
     } else {
-        if constexpr (TM_MOST == 4)
-            if (tm == 4) { if (w.tn == 2) NNV_WINO_ITEM(4, 2, 4); else NNV_WINO_ITEM(4, 1, 4); return; }
-        if (w.tn == 2) { if (tm == 2) NNV_WINO_ITEM(2, 2, 4); else NNV_WINO_ITEM(1, 2, 4); }
-        else { if (tm == 2) NNV_WINO_ITEM(2, 1, 4); else NNV_WINO_ITEM(1, 1, 4); }
+        if (w.tn == 2) { if (tm == 4) NNV_WINO_ITEM(4, 2, 4); else if (tm == 2) NNV_WINO_ITEM(2, 2, 4); else NNV_WINO_ITEM(1, 2, 4); }
+        else { if (tm == 4) NNV_WINO_ITEM(4, 1, 4); else if (tm == 2) NNV_WINO_ITEM(2, 1, 4); else NNV_WINO_ITEM(1, 1, 4); }
     }
 #undef NNV_WINO_ITEM
 }
@@ -783,10 +780,8 @@ bool wino_many_supported(const Geo &g, int kind) {
 template <int SET, bool HALF>
 static void launch_wino_many_t(const WinoTable &tbl, hipStream_t st) {
     hipLaunchKernelGGL((wino_input_many_kernel<SET, HALF>), dim3(tbl.n_in), dim3(256), 0, st, tbl);
-    const dim3 grid(ceil_div(tbl.n_gemm, 8 * kWinoGroup) * 8 * kWinoGroup), block(64 * kWinoItemWaves);
-    const size_t lds = (size_t)kWinoItemWaves * 64 * sizeof(float);       // per accumulator register
-    if (HALF || tbl.narrow) hipLaunchKernelGGL((wino_gemm_many_kernel<HALF, 2>), grid, block, lds * 16, st, tbl);
-    else if constexpr (!HALF) hipLaunchKernelGGL((wino_gemm_many_kernel<HALF, 4>), grid, block, lds * 32, st, tbl);
+    hipLaunchKernelGGL((wino_gemm_many_kernel<HALF>), dim3(ceil_div(tbl.n_gemm, 8 * kWinoGroup) * 8 * kWinoGroup), dim3(64 * kWinoItemWaves),
+                       (size_t)kWinoItemWaves * 32 * 64 * sizeof(float), st, tbl);
     hipLaunchKernelGGL((wino_output_many_kernel<SET, HALF>), dim3(tbl.n_out), dim3(256), 0, st, tbl);
 }
 
@@ -801,7 +796,7 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
     long n_in = 0, n_gemm = 0, n_out = 0;
     // An item's wavefront should not outlast its share of the launch: matrix instructions of an item against
     // those of the launch per SIMD; the channel steps of longer items are split over 2 or 4 wavefronts, and the
-    // layers with the longest wavefronts go first.  float16 F(2x2) items much shorter than a wavefront slot's
+    // layers with the longest wavefronts go first (but see below).  float16 F(2x2) items much shorter than a wavefront slot's
     // share (four per SIMD) take several tile blocks one after the other (VGG-16-shaped stack 163 -> 157 us; the same on
     // F(4x4) 106 -> 108, float32 F(4x4) 175 -> 177, F(6x6) 196 -> 208).
     WinoPlan plans[kMaxWinoLayers];
@@ -814,24 +809,22 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
         total += (long)p.csteps * p.tn * p.alpha * p.alpha * p.K16 * p.nblk;
         order[i] = i;
     }
-    // Matrix instructions of the launch per SIMD.  float32 launches of fewer than 2000 (the stacks lie at 130..1400
-    // and from 4200) are bound by how much of U is in flight and by their last items, not by the matrix cores:
-    // there a tile has two panels, whose kernel keeps eight wavefronts on a SIMD instead of five, and items
-    // are split over 2 or 4 wavefronts only beyond 128 instructions, or 512 where the launch has items enough for its
-    // slots by itself (300..1250).  Measured, us a call, four panels / two: F(4x4) GoogLeNet-shaped stack
-    // 34 / 27, ResNet-18 52 / 48, ResNet-50 57 / 54; F(6x6) GoogLeNet 42 / 38; F(2x2) ResNet-18 43 / 40; and
-    // VGG-16 above the line 177 / 198, 207 / 235, 261 / 276.  Split at 128 / 512: ResNet-18 F(4x4) 50 / 48, but AlexNet
-    // F(2x2) (232) 20 / 22 and ResNet-50 F(6x6) (1376) 90 / 93.
+    // Matrix instructions of the launch per SIMD.  Where it lies between 300 and 1250 (float32) the launch has items
+    // enough for its slots by itself, and a split costs more than the last items do: they are split beyond 512
+    // instructions only, elsewhere beyond 128 (float16: 96).  Measured with U in HBM, us a call, 128 / 512:
+    // F(2x2) ResNet-18-shaped stack 47.5 / 45.5, ResNet-50 52 / 50, F(4x4) GoogLeNet 37 / 32; AlexNet F(2x2) (232) 20 / 22.
+    // float32 F(4x4) and F(6x6) launches of fewer than 2000 keep the order of the layers: they are bound by U, and
+    // deep layers first put all of it in front of the arithmetic (ResNet-18 F(4x4) at batch 2 62 -> 60, F(6x6)
+    // 85 -> 82.5, ResNet-50 F(4x4) 69 -> 67; VGG-16, above the line, 198 sorted, 216 not).
     const long per_simd = total / 1024;
-    const int tm_most = half || per_simd < 2000 ? 2 : 4;
     for (int i = 0; i < n; ++i) {
         const WinoPlan &p = plans[i];
-        const int tm = wino_tm(p, half, tm_most);
+        const int tm = wino_tm(p, half);
         // a step's panels come from HBM once per frequency, whatever the number of tile blocks that share them: at
         // four wavefronts per SIMD 256 bytes of them take as long as three matrix instructions (half: a quarter of that per KB)
         mfmas[i] = (long)p.csteps * std::max(tm * p.tn, (half ? 6 : 13) * tm / 4 / p.nblk);
     }
-    const long shortest = half ? 48 : per_simd >= 300 && per_simd < 1250 ? 512 : 128;
+    const long shortest = half ? 96 : per_simd >= 300 && per_simd < 1250 ? 512 : 128;
     const long most = std::max(shortest, per_simd / 6), least = per_simd / 4 / 4;
     int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) {
@@ -844,13 +837,14 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
             mfmas[i] *= runs[i];
         }
     }
-    std::stable_sort(order, order + n, [&](int a, int b) { return (mfmas[a] >> shifts[a]) > (mfmas[b] >> shifts[b]); });
+    if (half || kind == NNV_WINO_F2 || per_simd >= 2000)
+        std::stable_sort(order, order + n, [&](int a, int b) { return (mfmas[a] >> shifts[a]) > (mfmas[b] >> shifts[b]); });
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
         const WinoPlan &p = plans[i];
         WinoParams &w = tbl.layer[o];
         w = wino_params(geos[i], p, x[i], U[i], bias ? bias[i] : nullptr, y[i], ws[i]);
-        const int tm = wino_tm(p, half, tm_most);
+        const int tm = wino_tm(p, half);
         w.ks_shift = shifts[i];
         w.gemm_wgs_per_xi = ceil_div(p.K16, tm) * ceil_div(p.nblk, runs[i]);
         tbl.tm[o] = tm;
@@ -863,7 +857,6 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
         if (n_in >= (1L << 30) || n_gemm >= (1L << 30) || n_out >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.in0[i] = tbl.gemm0[i] = tbl.out0[i] = INT_MAX;
-    tbl.narrow = tm_most < 4;
     tbl.n_in = (int)n_in; tbl.n_gemm = (int)n_gemm; tbl.n_out = (int)n_out;
     const int set = wino_set(kind, geos[0].dtype);
     if (set == WS_F2) { if (half) launch_wino_many_t<0, true>(tbl, st); else launch_wino_many_t<0, false>(tbl, st); }
