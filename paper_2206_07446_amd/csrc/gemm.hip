@@ -62,6 +62,9 @@ struct GemmParams {
 constexpr int kModePairs = 2;
 // ... and of float16 layers of at most 8 input channels with a filter larger than 1x1 (gemm_accumulate_taps).
 constexpr int kModeTaps = 4, kTapsMaxChannels = 8;
+// ... and of the work items of float16 1x1 layers of many channels whose pixels cannot be read in pairs
+// (gemm_accumulate_octets); fewer channel blocks or output panels than this are gathered from NCHW.
+constexpr int kModeOctets = 6, kOctetsMinBlocks = 16, kOctetsMinPanels = 32;
 
 // The parameters that follow from a layer's sizes, its storage type and its chunking mode.
 __host__ __device__ inline void gemm_derived(GemmParams &g, const bool half, const int mode) {
@@ -492,6 +495,84 @@ __device__ __forceinline__ void gemm_accumulate_1x1(const GemmParams &g, const i
     }
 }
 
+// float16 1x1 filters that cannot read pixels in pairs (odd planes, strides, padding), with 512 input and 512
+// output channels or more:
+// from the copy in octets of channels, as the larger filters.  Gathered from NCHW, two channel blocks take 36 loads
+// and run one ahead, about 1 us each time: an item of 2048 channels was 30 us, half of its whole launch.  Here a
+// block takes 6 loads and kRing - 1 blocks are in flight.  Measured, us a call: ResNet-50-shaped stack 64 -> 58, batch 2
+// at 150 x 187 75 -> 63.  With fewer channels on either side the copy costs what the loads save: from 256 input channels
+// and any number of outputs on, EfficientNet-B0 took 46 instead of 40.5, MobileNetV2 30.7 instead of 28.7; and one 1152 ->
+// 320 layer alone does not pay for a copy launch (EfficientNet-B0 45 instead of 40).
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_accumulate_octets(const GemmParams &g, const int mb0, const int nb0, const int ks,
+                                                       const int nsplit, const int lane, floatx4 (&acc)[TM][TN],
+                                                       PixState<TN> &px) {
+    constexpr int kRing = 4;
+    const int slot = lane >> 4;
+    int ih0[TN], iw0[TN], xb32[TN];
+    gemm_pixels<TN>(g, mb0, nb0, lane, px, ih0, iw0, xb32);          // (xb32: the float32 origin, not used)
+    uint32_t voff[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+        const bool ok = px.valid[t] && (unsigned)ih0[t] < (unsigned)g.H && (unsigned)iw0[t] < (unsigned)g.W;
+        voff[t] = ok ? (uint32_t)((((px.img[t] * (g.cpad >> 3) + slot) * g.H + ih0[t]) * g.W + iw0[t]) * 16) : kOobOffset;
+    }
+    const int cblocks = g.cblocks;
+    const int per = (cblocks + nsplit - 1) / nsplit;
+    const int u_begin = min(cblocks, ks * per), u_end = min(cblocks, u_begin + per);
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(g.x, g.x_bytes);
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(g.wp, g.w_bytes);
+    const __amdgpu_buffer_rsrc_t zres = make_rsrc(g.x, 0u);        // blocks past the range read zeros
+    uint32_t a_voff[TM], a_base[TM];
+#pragma unroll
+    for (int m = 0; m < TM; ++m) {
+        const bool ok = mb0 + m < g.K16;
+        a_voff[m] = ok ? (uint32_t)lane * 16u : kOobOffset;
+        a_base[m] = ok ? (uint32_t)(mb0 + m) * (uint32_t)cblocks : 0u;
+    }
+    half8 a[kRing][TM], b[kRing][TN];
+    auto load_unit = [&](const int buf, const int u) __attribute__((always_inline)) {
+        const bool ok = u < u_end;                                  // uniform
+        const uint32_t cb = ok ? (uint32_t)u : 0u;
+        const __amdgpu_buffer_rsrc_t wsel = ok ? wres : zres, xsel = ok ? xres : zres;
+#pragma unroll
+        for (int m = 0; m < TM; ++m) a[buf][m] = buf_load<half8>(wsel, a_voff[m], (a_base[m] + cb) * 1024u);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) b[buf][t] = buf_load<half8>(xsel, voff[t], cb * g.cb_stride);
+    };
+    auto compute = [&](const int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+                acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[buf][m], b[buf][t], acc[m][t], 0, 0, 0);
+    };
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int t = 0; t < TN; ++t) acc[m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (u_begin >= u_end) return;
+#pragma unroll
+    for (int i = 0; i < kRing - 1; ++i) load_unit(i, u_begin + i);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    int u = u_begin;
+    while (u + kRing - 1 < u_end) {
+#pragma unroll
+        for (int i = 0; i < kRing; ++i) {
+            load_unit((i + kRing - 1) % kRing, u + i + kRing - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        u += kRing;
+    }
+    if (u < u_end) {
+#pragma unroll
+        for (int i = 0; i < kRing - 1; ++i) compute(i);      // blocks past the range are zeros
+    }
+}
+
 // float16 layers of at most 8 input channels (a network's first layer): a k-step of 32 channels at one tap
 // would be three quarters zeros or more, and the 49 taps of a 7x7 filter 49 such steps.  The position
 // of an element along k is free as long as both fragments agree, so here a step is 8 channels at four
@@ -855,6 +936,7 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
     floatx4 acc[TM][TN];
     PixState<TN> px;
     if constexpr (!HALF && MODE == 3) gemm_accumulate_3x3<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
+    else if constexpr (MODE == kModeOctets) gemm_accumulate_octets<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (MODE == kModePairs) gemm_accumulate_pairs<TM>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (!HALF && MODE == 1) gemm_accumulate_1x1<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
@@ -971,6 +1053,7 @@ __global__ __launch_bounds__(64 * kItemWaves, 3) void gemm_items_kernel(const Ge
             else gemm_item<false, 4, 1, NBUF>(L, local, lane);
         } else {
             if (L.mode == kModePairs) gemm_item<true, 4, kModePairs>(L, local, lane);
+            else if (L.mode == kModeOctets) gemm_item<true, 4, kModeOctets>(L, local, lane);
             else gemm_item<true, 4, kModeTaps>(L, local, lane);
         }
     } else if (L.tm == 2) {
@@ -1290,6 +1373,10 @@ static ItemPlan plan_items(const Geo &g, const int item_steps) {
     if (half && pl.mode == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && (g.h * g.w) % 2 == 0) {
         ip.mode = kModePairs;
         if (g.groups == 1 && (kg16 % 4 == 0 || kg16 >= 12)) ip.tm = 4;
+    } else if (half && pl.mode == 1 && g.groups == 1 && ceil_div(g.c, 32) >= kOctetsMinBlocks && kg16 >= kOctetsMinPanels) {
+        ip.mode = kModeOctets;
+        ip.tm = 4;
+        ip.xt_bytes = align_up((size_t)g.n * g.h * g.w * copy_channels(g, ip.mode) * sizeof(__half), 256);
     }
     if (pl.mode == kModeTaps && (kg16 % 4 == 0 || kg16 >= 12)) ip.tm = 4;
     ip.nmt = ceil_div(K16, ip.tm);

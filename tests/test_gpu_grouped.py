@@ -192,6 +192,13 @@ PAIRS = [
     Ly("odd_plane", 64, 7, 7, 64, 1, 1, 0, n=2),
     Ly("strided", 64, 8, 8, 64, 1, 2, 0),
     Ly("padded", 64, 8, 8, 64, 1, 1, 1),
+    # 512 input and 512 output channels or more: from the copy in octets
+    Ly("oct_512", 512, 7, 7, 512, 1, 1, 0),                # sixteen blocks, eight tiles of four panels
+    Ly("oct_490", 490, 5, 5, 500, 1, 1, 0, n=3),           # the last block and the last panel partial, batch
+    Ly("oct_strided", 600, 9, 9, 540, 1, 2, 0),            # thirty-four panels: the last tile half empty; nineteen blocks
+    Ly("oct_padded", 545, 4, 6, 512, 1, 1, 1),             # padding, one channel in the last block
+    Ly("oct_deep", 2048, 3, 3, 512, 1, 1, 0),              # 64 blocks, split, fewer pixels than a block
+    Ly("oct_few", 480, 7, 7, 512, 1, 1, 0),                # fifteen blocks: gathered
 ]
 
 
