@@ -32,7 +32,7 @@ struct WinoParams {
     void *y;
     int N, C, H, W, K, ph, pw, P, Q;
     int th, tw, T;          // tiles per image (rows, cols), total tiles
-    int tn, nblk, Tpad;     // tiles come in nblk blocks of 16 tn (tn: 1 or 2); Tpad = 16 tn nblk
+    int tn, nblk, Tpad;     // tiles come in nblk blocks of 16 tn (tn: 1 or 2), of which the last may hold 16 only; Tpad: T padded to 16
     int K16, cpad, csteps;  // cpad: channels padded to 4 (float32) / 32 (float16); csteps = cpad / that
     int ks_shift;           // wavefronts sharing one output tile (splitting the channels) = 1 << ks_shift
     uint32_t u_bytes, v_bytes;   // sizes of U and V (range-checked loads)
@@ -62,6 +62,9 @@ struct WinoParams {
 // V, float32: [xi][block][c][16 tn tiles], so that lane n of the tile GEMM reads its tn tiles tn n ..
 // with one load.  float16: [xi][block][t][operand fragments of 16 tiles x 32 channels], tile tn n + t of
 // the block being row n of its t-th fragment (the GEMM then stores neighbouring tiles together).
+// tn = 2 with an odd number of 16-tile blocks: the last block has 16 tiles in the first 8 of these lanes, [c][16 tiles],
+// or one row of fragments with tile 2 n + t in row n + 8 t, so that V and M are no larger than the tiles need.
+__device__ __forceinline__ bool wino_short_block(const WinoParams &w, const int tb) { return (tb + 1) * 16 * w.tn > w.Tpad; }
 template <int SET, bool HALF>
 __device__ __forceinline__ void wino_input_block(const WinoParams &w, const int tb, const int by, const int bdim) {
     using Wm = WinoMat<SET>;
@@ -76,8 +79,9 @@ __device__ __forceinline__ void wino_input_block(const WinoParams &w, const int 
         tl = threadIdx.x & ((1 << sh) - 1);
         c = (by * bdim + threadIdx.x) >> sh;
     }
-    if (c >= w.cpad) return;
     const int t = tb * 16 * w.tn + tl;
+    if (c >= w.cpad || t >= w.Tpad) return;
+    const bool narrow = wino_short_block(w, tb);
     // The alpha x alpha patch, all loads in flight at once: elements in the zero padding, of
     // tiles past the end and of padding channels get an out-of-range offset and read as zero.
     float d[A][A];
@@ -106,14 +110,15 @@ __device__ __forceinline__ void wino_input_block(const WinoParams &w, const int 
     NNV_MATMUL_LEFT(Wm::BT, A, A, A, d, tmp)
     NNV_MATMUL_RIGHT_T(Wm::BT, A, A, A, tmp, V)
     if (HALF) {
-        __half *o = static_cast<__half *>(w.V) + ((size_t)(tb * w.tn + tl % w.tn) * w.csteps + c / 32) * 512 + ((c % 32) / 8) * 128 + (tl / w.tn) * 8 + (c & 7);
+        const int frag = narrow ? 0 : tl % w.tn, row = narrow ? (tl >> 1) + 8 * (tl & 1) : tl / w.tn;
+        __half *o = static_cast<__half *>(w.V) + ((size_t)(tb * w.tn + frag) * w.csteps + c / 32) * 512 + ((c % 32) / 8) * 128 + row * 8 + (c & 7);
         const size_t xs = (size_t)w.Tpad * w.cpad;
 #pragma unroll
         for (int u = 0; u < A; ++u)
 #pragma unroll
             for (int v = 0; v < A; ++v) o[(u * A + v) * xs] = __float2half_rn(V[u][v]);
     } else {
-        float *o = static_cast<float *>(w.V) + ((size_t)tb * w.cpad + c) * (16 * w.tn) + tl;
+        float *o = static_cast<float *>(w.V) + (size_t)tb * w.cpad * (16 * w.tn) + c * (narrow ? 16 : 16 * w.tn) + tl;
         const size_t xs = (size_t)w.Tpad * w.cpad;
 #pragma unroll
         for (int u = 0; u < A; ++u)
@@ -176,6 +181,9 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
     constexpr uint32_t FRAG = HALF ? 1024 : 256;
     const bool any = kb0 < w.K16;
     uint32_t a_voff[HALF ? TM : 1], b_voff;
+    // the last block may be short (then KS = 1 runs end with it): its tiles are those of the lanes col < 8
+    auto is_short = [&](int r) __attribute__((always_inline)) { return TN == 2 && (tb + r + 1) * (16 * TN) > w.Tpad; };
+    const uint32_t b_step = !HALF && is_short(0) ? FRAG : FRAG * TN;      // float32: bytes of V per step
     const uint32_t panel = (uint32_t)w.csteps * FRAG;        // bytes of a panel of U
     if constexpr (HALF) {
 #pragma unroll
@@ -183,11 +191,12 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
         b_voff = lane * 16u;
     } else {
         a_voff[0] = kb0 + col / QM < w.K16 ? (uint32_t)(col / QM) * panel + (uint32_t)slot * 64u + (uint32_t)(col % QM) * (4u * TM) : kOobOffset;
-        b_voff = (uint32_t)slot * (64u * TN) + (uint32_t)col * (4u * TN);
+        b_voff = (uint32_t)slot * (b_step / 4u) + (uint32_t)col * (4u * TN);
+        if (is_short(0) && col >= 8) b_voff = kOobOffset;
     }
     if (!any) b_voff = kOobOffset;
     const uint32_t a_base = any ? ((uint32_t)xi * w.K16 + kb0) * panel : 0u;
-    const uint32_t b_base = any ? ((uint32_t)xi * w.nblk + tb) * (uint32_t)TN * panel : 0u;
+    const uint32_t b_base = any ? ((uint32_t)xi * (w.Tpad >> 4) + (uint32_t)tb * TN) * panel : 0u;
     const int per_wave = (w.csteps + KS - 1) >> ks_shift;
     const int s_begin = min(w.csteps, ks * per_wave);
     const int s_end = min(w.csteps, s_begin + per_wave);
@@ -197,6 +206,7 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
     // added like any others: one path through the loop keeps one set of accumulator registers)
     auto load_chunk = [&](int buf, int r, int s0) __attribute__((always_inline)) {
         const uint32_t b_tile = b_base + (uint32_t)r * (TN * panel);
+        const bool narrow = HALF && is_short(r);     // uniform; float16: fragment 1 of a short block is the rows 8.. of fragment 0
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const bool in = s0 + d < s_end;          // uniform
@@ -206,10 +216,13 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
 #pragma unroll
                 for (int m = 0; m < TM; ++m) st[buf][d].a[m] = buf_load<half8>(ures, in ? a_voff[m] : kOobOffset, a_base + s * FRAG);
 #pragma unroll
-                for (int t = 0; t < TN; ++t) st[buf][d].b[t] = buf_load<half8>(vres, bo, b_tile + (uint32_t)t * panel + s * FRAG);
+                for (int t = 0; t < TN; ++t) {
+                    const uint32_t bt = t > 0 && narrow ? (col < 8 ? bo + t * 128u : kOobOffset) : bo;
+                    st[buf][d].b[t] = buf_load<half8>(vres, bt, b_tile + (narrow ? 0u : (uint32_t)t * panel) + s * FRAG);
+                }
             } else {
                 st[buf][d].a = buf_load_floats<TM>(ures, in ? a_voff[0] : kOobOffset, a_base + s * FRAG);
-                st[buf][d].b = buf_load_floats<TN>(vres, bo, b_tile + s * (FRAG * TN));
+                st[buf][d].b = buf_load_floats<TN>(vres, bo, b_tile + s * b_step);
             }
         }
     };
@@ -237,10 +250,10 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
     const uint32_t m_row = (uint32_t)w.Tpad * 4u;
     const __amdgpu_buffer_rsrc_t mres = make_rsrc(w.M, (uint32_t)w.alpha2 * (uint32_t)w.K16 * 16u * m_row);
     const int lane_panel = HALF ? 0 : slot * 4 / QM, lane_row = HALF ? slot * 4 : TM * (slot * 4 % QM);
-    const uint32_t m_voff = kb0 + lane_panel < w.K16 ? (uint32_t)(lane_panel * 16 + lane_row) * m_row + (uint32_t)col * (4u * TN) : kOobOffset;
+    const uint32_t m_voff = kb0 + lane_panel < w.K16 && !(!HALF && is_short(0) && col >= 8) ? (uint32_t)(lane_panel * 16 + lane_row) * m_row + (uint32_t)col * (4u * TN) : kOobOffset;
     const uint32_t m_base = any ? ((uint32_t)xi * w.K16 + kb0) * 16u * m_row + (uint32_t)tb * (64u * TN) : 0u;
-    auto store_row = [&](const int m, const int j, const typename FloatVec<TN>::type &v, const uint32_t off) __attribute__((always_inline)) {
-        if (!HALF || kb0 + m < w.K16) buf_store_floats<TN>(v, mres, m_voff, off);
+    auto store_row = [&](const int r, const int m, const typename FloatVec<TN>::type &v, const uint32_t off) __attribute__((always_inline)) {
+        if (!HALF || kb0 + m < w.K16) buf_store_floats<TN>(v, mres, HALF && is_short(r) && col >= 8 ? kOobOffset : m_voff, off);
     };
     auto finish = [&](int r) __attribute__((always_inline)) {
         uint32_t off = m_base + (uint32_t)r * (64u * TN);
@@ -253,7 +266,7 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
                 if constexpr (TN == 1) v = acc[m][t][j];
                 else v[t] = acc[m][t][j];
             }
-            store_row(m, j, v, off);
+            store_row(r, m, v, off);
             off += HALF && j == 3 ? 13u * m_row : m_row;
         }
         clear();
@@ -302,7 +315,7 @@ __device__ __forceinline__ void wino_gemm_tile(const WinoParams &w, const int xi
                 if constexpr (TN == 1) v = e;
                 else v[t] = e;
             }
-            store_row(m, j, v, m_base + (uint32_t)(HALF ? m * 16 + j : q) * m_row);
+            store_row(0, m, v, m_base + (uint32_t)(HALF ? m * 16 + j : q) * m_row);
         }
     }
 }
@@ -650,7 +663,7 @@ static WinoPlan plan_wino(const Geo &g, int kind) {
     p.T16 = ceil_div(p.T, 16);
     p.tn = p.T > 16 ? 2 : 1;
     p.nblk = ceil_div(p.T, 16 * p.tn);
-    p.Tpad = 16 * p.tn * p.nblk;
+    p.Tpad = 16 * p.T16;
     p.K16 = ceil_div(g.k, 16);
     const int cb = half ? 32 : 4;
     p.csteps = ceil_div(g.c, cb);

@@ -149,3 +149,33 @@ def test_filter_size_limits_of_the_gemm_kind():
     assert not nnv.nnv_kind_supported(D(c=3, h=224, w=224, k=64, r=11, s=11, stride_h=4, stride_w=4, pad_h=2, pad_w=2, dtype=1), 1)
     assert nnv.nnv_kind_supported(D(r=8, s=8, pad_h=4, pad_w=4, dtype=1), 1)
     assert not nnv.nnv_kind_supported(D(c=4, h=40, w=40, r=12, s=12), 1)
+
+
+@pytest.mark.parametrize("half", [False, True], ids=["f32", "f16"])
+@pytest.mark.parametrize("kind", [nnv.WINO_F2, nnv.WINO_F4, nnv.WINO_F6], ids=["f2", "f4", "f6"])
+def test_winograd_workspace_holds_sixteen_tile_blocks(kind, half):
+    """V and M hold the tiles rounded up to blocks of 16 and nothing more, whatever the kernels' own tile is."""
+    m = {nnv.WINO_F2: 2, nnv.WINO_F4: 4, nnv.WINO_F6: 6}[kind]
+    up = lambda v, a: -(-v // a) * a
+    shapes = [(c, k, h, w, 1) for c in (17, 64, 256) for k in (20, 160) for h, w in ((7, 7), (14, 14), (28, 28), (31, 45))]
+    shapes += [(1088, 1088, 56, 56, 1), (96, 144, 14, 14, 3), (40, 136, 56, 56, 2)]
+    odd = 0
+    for c, k, h, w, n in shapes:
+        d = D(n=n, c=c, k=k, h=h, w=w, dtype=int(half))
+        if not nnv.nnv_kind_supported(d, kind):
+            assert half and kind == nnv.WINO_F6
+            continue
+        got = nnv.nnv_workspace_bytes(d, kind)
+        tiles = n * -(-h // m) * -(-w // m)
+        t16, freqs = -(-tiles // 16), (m + 2) ** 2
+        odd += t16 % 2
+        v = freqs * t16 * 16 * up(c, 32 if half else 4) * (2 if half else 4)
+        expect = up(v, 256) + up(freqs * up(k, 16) * t16 * 16 * 4, 256)
+        assert got == expect or (got == 0 and not half and kind != nnv.WINO_F6 and t16 >= 32), (c, k, h, w, n)
+    assert odd or (half and kind == nnv.WINO_F6)
+
+
+def test_winograd_workspace_at_the_static_limit():
+    """1088 -> 1088 channels at 56x56, float32 F(4x4): 13 blocks of tiles, 62.2 of the 64 MiB of static scratch."""
+    d = D(c=1088, k=1088, h=56, w=56)
+    assert nnv.nnv_workspace_bytes(d, nnv.WINO_F4) == 65175552 <= nnv.STATIC_SCRATCH_BYTES

@@ -289,6 +289,42 @@ def test_winograd_layers_in_one_call(env, kind, half):
             assert np.abs(a - b).max() <= 0.1 * conv_tolerance(kind, False) * np.abs(b).max(), c.layer.name
 
 
+# Layers by their Winograd tiles (th x tw of m x m outputs): an odd number of 16-tile blocks, so that the last 32-tile block of
+# the tile GEMM is a short one, with one, some or all of its 16 tiles in use
+SHORT_BLOCK = [
+    ("t33_k16", 20, 16, 11, 3, 1),                         # one tile in the short block, one panel
+    ("t36_k40", 37, 40, 6, 6, 1),                          # three panels, partial channel block
+    ("t48_k64", 64, 64, 8, 6, 1),                          # a full short block
+    ("t69_deep", 516, 200, 23, 3, 1),                      # split over wavefronts, panels ragged
+    ("t147_n3", 24, 72, 7, 7, 3),                          # images and the short block not aligned
+    ("t32_even", 32, 48, 8, 4, 1),
+]
+
+
+@pytest.mark.parametrize("kind", [2, 3, 5], ids=["f2", "f4", "f6"])
+@pytest.mark.parametrize("half", [False, True], ids=["f32", "f16"])
+def test_winograd_short_tile_block(env, kind, half):
+    nnv, torch = env
+    if half and kind == 5:
+        pytest.skip("F(6x6) exists in float32 only")
+    m = {2: 2, 3: 4, 5: 6}[kind]
+    layers = [Ly(name, c, th * m - (i % 2), tw * m, k, 3, 1, 1, n=n) for i, (name, c, k, th, tw, n) in enumerate(SHORT_BLOCK)]
+    cases = [Case(nnv, torch, l, kind, half, 2700 + i, bias=(i % 2 == 0)) for i, l in enumerate(layers)]
+    run_grouped(nnv, torch, cases)
+    run_grouped(nnv, torch, cases, relu=True)
+    for c in cases:
+        run_grouped(nnv, torch, [c])
+
+
+def test_winograd_float16_runs_of_tile_blocks(env):
+    """Short float16 F(2x2) items: several tile blocks one after the other per wavefront, the last run of a layer shorter
+    than the others and, where the blocks of 16 tiles are odd in number, ending with a short block."""
+    nnv, torch = env
+    layers = [Ly("run_odd", 64, 222, 222, 64, 3, 1, 1), Ly("run_even", 64, 224, 220, 64, 3, 1, 1), Ly("run_k24", 40, 206, 230, 24, 3, 1, 1),
+              Ly("run_n2", 64, 150, 166, 64, 3, 1, 1, n=2)]
+    run_grouped(nnv, torch, [Case(nnv, torch, l, nnv.WINO_F2, True, 2800 + i, bias=(i == 1)) for i, l in enumerate(layers)])
+
+
 @pytest.mark.parametrize("name,kind,half", [("resnet18", 2, False), ("resnet18", 3, False), ("resnet18", 5, False),
                                             ("vgg16", 3, False), ("resnet50", 3, True), ("resnet50", 2, True)])
 def test_full_stacks_winograd(env, name, kind, half):
