@@ -1,17 +1,20 @@
 """Binding of libnnv.so: the same entry points as include/nnv.h, argument marshalling only.  The
-calls a program makes per pass go through the compiled module _nnvpy (csrc/pymodule.cpp), the
-queries and the calls that wait for the GPU through ctypes.  torch supplies device memory and the
-stream handle."""
+calls a program makes per pass go through the compiled module _nnvpy (csrc/pymodule.cpp) or, where that
+cannot be built, through ctypes (_CtypesCalls); the queries and the calls that wait for the GPU
+always through ctypes.  torch supplies device memory and the stream handle."""
 from __future__ import annotations
 
 import ctypes
 import importlib.util
 import os
+import warnings
 from ctypes import c_char_p, c_double, c_int, c_int32, c_size_t, c_void_p, POINTER, Structure, byref
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-LIB_PATH = os.path.join(HERE, "libnnv.so")
-MODULE_PATH = os.path.join(HERE, "_nnvpy.so")
+from . import build as _build
+
+HERE = _build.HERE
+LIB_PATH = _build.LIB
+MODULE_PATH = _build.MODULE
 
 DIRECT, IM2COL_GEMM, WINO_F2, WINO_F4, DEPTHWISE, WINO_F6 = range(6)
 KINDS = {"direct": DIRECT, "im2col_gemm": IM2COL_GEMM, "wino_f2": WINO_F2, "wino_f4": WINO_F4,
@@ -51,19 +54,18 @@ class CacheIo(Structure):
 
 
 _lib = None
-_native = None      # the module _nnvpy, once the library is loaded
+_native = None      # the module _nnvpy (or _CtypesCalls), once the library is loaded
 
 
 def load():
-    """Load libnnv.so and the module beside it (building them first only if they do not exist).  torch is imported
+    """Load libnnv.so and the module beside it (each built first only if it does not exist).  torch is imported
     before the library so that both share one HIP runtime."""
     global _lib, _native
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  (loads the HIP runtime the library binds to)
-    if not (os.path.exists(LIB_PATH) and os.path.exists(MODULE_PATH)):
-        from .build import build
-        build()
+    if not os.path.exists(LIB_PATH):
+        _build.build()
     lib = ctypes.CDLL(LIB_PATH, use_errno=True)
     lib.nnv_layout_version.restype = c_int
     lib.nnv_status_string.restype = c_char_p
@@ -102,14 +104,25 @@ def load():
     lib.nnv_cache_write.argtypes = [c_char_p, POINTER(ConvDesc), c_int, c_void_p, c_void_p]
     lib.nnv_cache_read.restype = c_int
     lib.nnv_cache_read.argtypes = [c_char_p, POINTER(ConvDesc), c_int, c_void_p, c_int, c_void_p, POINTER(CacheIo)]
-    spec = importlib.util.spec_from_file_location("_nnvpy", MODULE_PATH)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
-    native.setup(ConvDesc, _fail, lambda: torch.cuda.current_stream().cuda_stream, torch.cuda.current_device if not hasattr(torch._C, "_cuda_getDevice")
-                 else torch._C._cuda_getDevice, getattr(torch._C, "_cuda_getCurrentRawStream", None))
-    _native = native
+    _native = _load_module(torch)
     _lib = lib
     return lib
+
+
+def _load_module(torch):
+    """The compiled module of this interpreter, or the same calls through ctypes."""
+    try:
+        if not os.path.exists(MODULE_PATH):
+            _build.build_module()
+        spec = importlib.util.spec_from_file_location("_nnvpy", MODULE_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"{e}; calling libnnv.so through ctypes, which costs some microseconds a call")
+        return _CtypesCalls
+    native.setup(ConvDesc, _fail, lambda: torch.cuda.current_stream().cuda_stream, getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),
+                 getattr(torch._C, "_cuda_getCurrentRawStream", None))
+    return native
 
 
 def _calls():
@@ -150,6 +163,68 @@ def _check(rc: int, where: str):
     if rc < 0:
         raise NnvError(rc, where)
     return rc
+
+
+def _array(ctype, items, n, convert=lambda v: v):
+    items = list(items)
+    if len(items) != n:
+        raise ValueError(f"{n} descriptors, but a list of {len(items)}")
+    return (ctype * n)(*[convert(v) for v in items])
+
+
+def _ptrs(tensors, n, null=False):
+    """Addresses of n tensors; None is a null pointer where `null` says so and an error elsewhere."""
+    return _array(c_void_p, tensors, n, lambda t: t if isinstance(t, int) or (null and t is None) else t.data_ptr())
+
+
+def _size(workspace, count=None):
+    if count is not None:
+        return count
+    return 0 if workspace is None else workspace.numel() * workspace.element_size()
+
+
+class _CtypesCalls:
+    """The functions of csrc/pymodule.cpp for an interpreter that has no compiled module."""
+
+    @staticmethod
+    def transform_weights(desc, kind, w_raw, w_tx, stream):
+        _check(load().nnv_transform_weights(byref(desc), kind, _ptr(w_raw), _ptr(w_tx), _stream(stream)), "nnv_transform_weights")
+
+    @staticmethod
+    def transform_weights_grouped(descs, kinds, w_raw, w_tx, stream):
+        n = len(descs)
+        _check(load().nnv_transform_weights_grouped(n, _array(ConvDesc, descs, n), _array(c_int, kinds, n), _ptrs(w_raw, n), _ptrs(w_tx, n),
+                                                    _stream(stream)), "nnv_transform_weights_grouped")
+
+    @staticmethod
+    def conv_forward(desc, kind, x, w_tx, bias, y, workspace, workspace_bytes, stream):
+        _check(load().nnv_conv_forward(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _ptr(workspace),
+                                       _size(workspace, workspace_bytes), _stream(stream)), "nnv_conv_forward")
+
+    @staticmethod
+    def conv_forward_relu(desc, kind, x, w_tx, bias, y, workspace, workspace_bytes, stream):
+        _check(load().nnv_conv_forward_relu(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _ptr(workspace),
+                                            _size(workspace, workspace_bytes), _stream(stream)), "nnv_conv_forward_relu")
+
+    @staticmethod
+    def conv_forward_static(desc, kind, x, w_tx, bias, y, stream):
+        _check(load().nnv_conv_forward_static(byref(desc), kind, _ptr(x), _ptr(w_tx), _ptr(bias), _ptr(y), _stream(stream)),
+               "nnv_conv_forward_static")
+
+    @staticmethod
+    def conv_forward_grouped(descs, kinds, x, w_tx, bias, y, workspace, workspace_bytes, flags, stream):
+        n = len(descs)
+        _check(load().nnv_conv_forward_grouped(n, _array(ConvDesc, descs, n), _array(c_int, kinds, n), _ptrs(x, n, True),
+                                               _ptrs(w_tx, n, True), None if bias is None else _ptrs(bias, n, True), _ptrs(y, n, True), _ptr(workspace),
+                                               _size(workspace, workspace_bytes), flags, _stream(stream)), "nnv_conv_forward_grouped")
+
+    @staticmethod
+    def cold_stack(descs, kinds, w_raw, w_tx, x, y, workspace, stage_layers, stream_exec, stream_tx):
+        n = len(descs)
+        se = _stream(stream_exec)
+        stx = se if stream_tx is None else _stream(stream_tx)
+        _check(load().nnv_cold_stack(n, _array(ConvDesc, descs, n), _array(c_int, kinds, n), _ptrs(w_raw, n), _ptrs(w_tx, n), _ptrs(x, n),
+                                     _ptrs(y, n), _ptr(workspace), _size(workspace), stage_layers, se, stx), "nnv_cold_stack")
 
 
 def nnv_layout_version() -> int:
