@@ -1273,7 +1273,7 @@ size_t im2col_workspace_bytes(const Geo &g) { return plan_im2col(g).xt_bytes; }
 template <bool HALF, int TM, int TN, int NBUF>
 static void launch_gemm_mode(int mode, const GemmParams &gp, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
     switch (mode) {
-        case 1: hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 1, NBUF>), grid, block, lds, st, gp); break;
+        case 1: if constexpr (!HALF || TM * TN < 4) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 1, NBUF>), grid, block, lds, st, gp); } break;
         case 3: hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 3, NBUF>), grid, block, lds, st, gp); break;
         case kModeTaps: if constexpr (HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, kModeTaps, NBUF>), grid, block, lds, st, gp); } break;
         case 5: if constexpr (!HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 5, NBUF>), grid, block, lds, st, gp); } break;
@@ -1287,13 +1287,16 @@ static void launch_gemm_variant(const GemmPlan &pl, const GemmParams &gp, dim3 g
     if (pl.tm == 4) {
         if constexpr (!HALF) hipLaunchKernelGGL((im2col_gemm_kernel<false, 4, 2, 3, 2>), grid, block, lds, st, gp);
     } else if (pl.tm == 2 && pl.tn == 2) launch_gemm_mode<HALF, 2, 2, 2>(pl.mode, gp, grid, block, lds, st);
-    else if (pl.tm == 2 && pl.tn == 1) {
-        if (!HALF && pl.nbuf >= 3) launch_gemm_mode<HALF, 2, 1, 3>(pl.mode, gp, grid, block, lds, st);
-        else launch_gemm_mode<HALF, 2, 1, 2>(pl.mode, gp, grid, block, lds, st);
+    else if constexpr (HALF) {      // rings of two only
+        if (pl.tm == 2) launch_gemm_mode<true, 2, 1, 2>(pl.mode, gp, grid, block, lds, st);
+        else launch_gemm_mode<true, 1, 1, 2>(pl.mode, gp, grid, block, lds, st);
+    } else if (pl.tm == 2) {
+        if (pl.nbuf >= 3) launch_gemm_mode<false, 2, 1, 3>(pl.mode, gp, grid, block, lds, st);
+        else launch_gemm_mode<false, 2, 1, 2>(pl.mode, gp, grid, block, lds, st);
     } else {
-        if (!HALF && pl.nbuf >= 4) launch_gemm_mode<HALF, 1, 1, 4>(pl.mode, gp, grid, block, lds, st);
-        else if (!HALF && pl.nbuf == 3) launch_gemm_mode<HALF, 1, 1, 3>(pl.mode, gp, grid, block, lds, st);
-        else launch_gemm_mode<HALF, 1, 1, 2>(pl.mode, gp, grid, block, lds, st);
+        if (pl.nbuf >= 4) launch_gemm_mode<false, 1, 1, 4>(pl.mode, gp, grid, block, lds, st);
+        else if (pl.nbuf == 3) launch_gemm_mode<false, 1, 1, 3>(pl.mode, gp, grid, block, lds, st);
+        else launch_gemm_mode<false, 1, 1, 2>(pl.mode, gp, grid, block, lds, st);
     }
 }
 
