@@ -674,7 +674,8 @@ static WinoPlan plan_wino(const Geo &g, int kind) {
     return p;
 }
 
-// Panels per tile of a tile GEMM: four (float32) unless that leaves more than a seventh of the rows empty.
+// Panels per tile of a tile GEMM: two, or four (float32) where that leaves at most a seventh more rows empty than two would (three
+// panels: as many).
 static int wino_tm(const WinoPlan &p, bool half, int most = 4) {
     if (half || most < 4) return std::min(most, p.K16 >= 2 ? 2 : 1);
     if (p.K16 >= 3 && ceil_div(p.K16, 4) * 4 * 100 <= ceil_div(p.K16, 2) * 2 * 115) return 4;
@@ -814,30 +815,27 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
     // F(4x4) 106 -> 108, float32 F(4x4) 175 -> 177, F(6x6) 196 -> 208).
     WinoPlan plans[kMaxWinoLayers];
     int order[kMaxWinoLayers];
-    long mfmas[kMaxWinoLayers], total = 0;
+    long mfmas[kMaxWinoLayers], total = 0, items = 0;
     for (int i = 0; i < n; ++i) {
         if ((geos[i].dtype == NNV_F16) != half || !wino_many_supported(geos[i], kind)) return hipErrorInvalidValue;
         plans[i] = plan_wino(geos[i], kind);
         const WinoPlan &p = plans[i];
-        total += (long)p.csteps * p.tn * p.alpha * p.alpha * p.K16 * p.nblk;
-        order[i] = i;
-    }
-    // Matrix instructions of the launch per SIMD.  Where it lies between 300 and 1250 (float32) the launch has items
-    // enough for its slots by itself, and a split costs more than the last items do: they are split beyond 512
-    // instructions only, elsewhere beyond 128 (float16: 96).  Measured with U in HBM, us a call, 128 / 512:
-    // F(2x2) ResNet-18-shaped stack 47.5 / 45.5, ResNet-50 52 / 50, F(4x4) GoogLeNet 37 / 32; AlexNet F(2x2) (232) 20 / 22.
-    // float32 F(4x4) and F(6x6) launches of fewer than 2000 keep the order of the layers: they are bound by U, and
-    // deep layers first put all of it in front of the arithmetic (ResNet-18 F(4x4) at batch 2 62 -> 60, F(6x6)
-    // 85 -> 82.5, ResNet-50 F(4x4) 69 -> 67; VGG-16, above the line, 198 sorted, 216 not).
-    const long per_simd = total / 1024;
-    for (int i = 0; i < n; ++i) {
-        const WinoPlan &p = plans[i];
         const int tm = wino_tm(p, half);
+        total += (long)p.csteps * p.tn * p.alpha * p.alpha * p.K16 * p.nblk;
+        items += (long)p.alpha * p.alpha * ceil_div(p.K16, tm) * p.nblk;
         // a step's panels come from HBM once per frequency, whatever the number of tile blocks that share them: at
         // four wavefronts per SIMD 256 bytes of them take as long as three matrix instructions (half: a quarter of that per KB)
         mfmas[i] = (long)p.csteps * std::max(tm * p.tn, (half ? 6 : 13) * tm / 4 / p.nblk);
+        order[i] = i;
     }
-    const long shortest = half ? 96 : per_simd >= 300 && per_simd < 1250 ? 512 : 128;
+    const long per_simd = total / 1024;      // matrix instructions of the launch per SIMD
+    // The shortest wavefront worth a split, in matrix instructions.  float32: 128 while the launch has fewer items than the
+    // chip has SIMDs (a split puts idle ones to work), else 512: wavefronts that have to queue gain nothing from being
+    // shorter.  Measured over 110 launches of six stacks at batch 1-6 and 80-320 pixels, weights from HBM, geometric means of
+    // 256 / 512 / 1024 against 128: up to 1008 items 1.02 / 1.06 / 1.12, 1472 to 4000 items 0.99 / 0.97 / 0.98, to 8000
+    // 0.99 / 0.98 / 0.99, beyond (per_simd / 6 rules) 1.00 / 1.00 / 1.01.  float16: 64 to 384 take the same time within
+    // 1-2 %, 32 costs a launch of few items 5 %.
+    const long shortest = half ? 96 : items < 1024 ? 128 : 512;
     const long most = std::max(shortest, per_simd / 6), least = per_simd / 4 / 4;
     int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) {
@@ -850,6 +848,9 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
             mfmas[i] *= runs[i];
         }
     }
+    // Longest first, except in float32 F(4x4) and F(6x6) launches of fewer than 2000 instructions per SIMD: they are bound by
+    // U, and deep layers first put all of it in front of the arithmetic.  Same 110 launches, sorted against not, geometric means: F(2x2)
+    // 0.99 (0.94-1.05), F(4x4) and F(6x6) below the line 1.01 (0.93-1.07), beyond it 0.98 (0.96-1.03).  float16: 0.98 (0.91-1.03).
     if (half || kind == NNV_WINO_F2 || per_simd >= 2000)
         std::stable_sort(order, order + n, [&](int a, int b) { return (mfmas[a] >> shifts[a]) > (mfmas[b] >> shifts[b]); });
     for (int o = 0; o < n; ++o) {
