@@ -115,7 +115,7 @@ SMALL = [
 
 @pytest.mark.parametrize("half", [False, True], ids=["f32", "f16"])
 def test_small_gemm_layers_in_one_call(env, half):
-    """23 layers (more than one launch carries): every filter mode, ragged tiles, batches, groups, split reductions."""
+    """Up to 29 layers in one launch (it carries 56): every filter mode, ragged tiles, batches, groups, split reductions."""
     nnv, torch = env
     cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, half, 700 + i) for i, l in enumerate(SMALL + SMALL[:6])
              if nnv.IM2COL_GEMM in applicable_kinds(l, half)]
@@ -161,7 +161,7 @@ def test_mixed_kinds_in_one_call(env):
                                        ("resnet18", True), ("vgg16", True)])
 def test_full_stacks_gemm_kind(env, name, half):
     """Whole stacks at full size, every layer the implicit GEMM can run, one grouped call.  In float16 the
-    small stacks run items a quarter as long as the VGG-16-shaped one; all channels-last copies are one launch."""
+    small stacks run items a third as long as the VGG-16-shaped one; the copies of x in octets are one launch."""
     nnv, torch = env
     cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, half, 220607446 + 3000 + i)
              for i, l in enumerate(stack(name)) if l.groups == 1]
@@ -316,6 +316,17 @@ def test_winograd_short_tile_block(env, kind, half):
         run_grouped(nnv, torch, [c])
 
 
+# float16 items of more than 96 matrix instructions are split over 2 or 4 wavefronts: from 800 channels up
+@pytest.mark.parametrize("kind", [2, 3], ids=["f2", "f4"])
+def test_winograd_float16_split_items(env, kind):
+    nnv, torch = env
+    layers = [Ly("two", 1024, 14, 14, 40, 3, 1, 1), Ly("two_ragged", 850, 9, 25, 64, 3, 1, 1), Ly("four", 2000, 10, 12, 72, 3, 1, 1),
+              Ly("one_panel", 1700, 7, 23, 16, 3, 1, 1, n=2), Ly("one_block", 1500, 7, 7, 33, 3, 1, 1), Ly("unsplit", 64, 14, 14, 64, 3, 1, 1)]
+    cases = [Case(nnv, torch, l, kind, True, 2900 + i, bias=(i % 2 == 0)) for i, l in enumerate(layers)]
+    run_grouped(nnv, torch, cases)
+    run_grouped(nnv, torch, cases, relu=True)
+
+
 def test_winograd_float16_runs_of_tile_blocks(env):
     """Short float16 F(2x2) items: several tile blocks one after the other per wavefront, the last run of a layer shorter
     than the others and, where the blocks of 16 tiles are odd in number, ending with a short block."""
@@ -326,8 +337,10 @@ def test_winograd_float16_runs_of_tile_blocks(env):
 
 
 @pytest.mark.parametrize("name,kind,half", [("resnet18", 2, False), ("resnet18", 3, False), ("resnet18", 5, False),
-                                            ("vgg16", 3, False), ("resnet50", 3, True), ("resnet50", 2, True)])
+                                            ("vgg16", 3, False), ("resnet50", 3, True), ("resnet50", 2, True),
+                                            ("vgg16", 2, True)])
 def test_full_stacks_winograd(env, name, kind, half):
+    """VGG-16 in float16 F(2x2) is the stack whose short items run several tile blocks each (3, 7 and 14)."""
     nnv, torch = env
     cases = [Case(nnv, torch, l, kind, half, 220607446 + 4000 + i) for i, l in enumerate(stack(name)) if l.winograd_ok
              and kind in applicable_kinds(l, half)]
