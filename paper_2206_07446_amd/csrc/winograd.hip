@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const WinoParams w) {
 // m is its operand of the m-th row block.  One 16-byte load replaces four, and V is stored so that the TN tile
 // blocks of a lane are neighbours too: 2 loads per 8 MFMAs instead of 6 (64 x 32 tile).
 // What bounds a launch now is U, V and M through the fabric: the tile GEMMs of a VGG-16-shaped F(4x4) stack move
-// 480 MB (U is 235) in 105 us, the rate of a plain copy; its pass took 207 us before, 175 now.  64 x 64 tiles
+// 497 MB (U is 235) in 110 us, 0.88 of the rate of a plain copy; its pass took 207 us before, 176 now.  64 x 64 tiles
 // (TN = 4) move less through L1 and took the same time there, 10 % more on a ResNet-18-shaped stack.
 // float16: fragments are 16 bytes per lane to begin with.
 typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
