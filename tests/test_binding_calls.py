@@ -1,5 +1,5 @@
 """The calls a program makes per pass, through the compiled module and through ctypes: what reaches the
-library and what is refused, without touching a GPU (every call here ends at an argument check)."""
+library and what is refused, without touching a GPU (every call but those of the last test ends at an argument check)."""
 import ctypes
 import sysconfig
 
@@ -133,3 +133,40 @@ def test_without_a_compiled_module_the_calls_go_through_ctypes(monkeypatch, tmp_
 
 def test_module_name_carries_the_interpreter():
     assert build.MODULE.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+@pytest.mark.gpu
+def test_both_routes_give_the_same_bytes(monkeypatch):
+    """Every call of the module on device tensors and the current stream, once compiled and once through ctypes."""
+    native, dev = binding._calls(), torch.device("cuda:0")
+    assert native is not binding._CtypesCalls
+    d = desc()
+    gen = torch.Generator(device=dev).manual_seed(31)
+    w = torch.randn(16 * 16 * 9, device=dev, generator=gen)
+    x = torch.rand(16 * 32 * 32, device=dev, generator=gen)
+    bias = torch.randn(16, device=dev, generator=gen)
+    kinds = [nnv.DIRECT, nnv.IM2COL_GEMM, nnv.WINO_F2, nnv.WINO_F4]
+    n = len(kinds)
+    sizes = [nnv.nnv_transformed_bytes(d, k) for k in kinds]
+
+    def outputs():
+        txs = [torch.zeros(s, dtype=torch.uint8, device=dev) for s in sizes]
+        ys = [torch.zeros(16 * 32 * 32, device=dev) for _ in range(5 * n)]
+        need = max([nnv.nnv_workspace_bytes(d, k) for k in kinds] + [nnv.nnv_conv_forward_grouped_workspace_bytes([d] * n, kinds)])
+        ws = torch.empty(need, dtype=torch.uint8, device=dev)
+        nnv.nnv_transform_weights_grouped([d] * n, kinds, [w] * n, txs)
+        one = torch.zeros_like(txs[2])
+        nnv.nnv_transform_weights(d, kinds[2], w, one)
+        for i, k in enumerate(kinds):
+            nnv.nnv_conv_forward(d, k, x, txs[i], bias, ys[i], ws)
+            nnv.nnv_conv_forward_relu(d, k, x, txs[i], None, ys[n + i], ws)
+            nnv.nnv_conv_forward_static(d, k, x, txs[i], bias, ys[2 * n + i])
+        nnv.nnv_conv_forward_grouped([d] * n, kinds, [x] * n, txs, [bias] * n, ys[3 * n:4 * n], ws, flags=nnv.FORWARD_RELU)
+        nnv.nnv_cold_stack([d] * n, kinds, [w] * n, [t.clone() for t in txs], [x] * n, ys[4 * n:], ws)
+        torch.cuda.synchronize()
+        return [t.cpu() for t in txs + [one] + ys]
+
+    compiled = outputs()
+    monkeypatch.setattr(binding, "_native", binding._CtypesCalls)
+    for a, b in zip(compiled, outputs()):
+        assert a.any() and torch.equal(a, b)
