@@ -304,7 +304,7 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
         if (b.cls != GroupedPlan::GEMM_ITEMS) continue;
         std::vector<Geo> bg;
         for (int i : b.layers) bg.push_back(geos[i]);
-        const int target = im2col_items_target((int)bg.size(), bg.data());
+        const ItemTarget target = im2col_items_target((int)bg.size(), bg.data());
         size_t off = 0;
         for (size_t j = 0; j < b.layers.size(); ++j) {
             b.offset[j] = off;

@@ -817,6 +817,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
     return make_rsrc(g.y, (uint32_t)g.N * (uint32_t)(g.K * g.P * g.Q) * (g.half_out ? 2u : 4u));
 }
 
+#include "tile_gemm.h"
+
 // One layer per launch: a workgroup of KS wavefronts owns one output tile, the wavefronts split
 // the channel blocks and add their partial sums through LDS in fixed order.
 // (the 32 x 32 tile is launched as one wavefront per workgroup only, and needs more than the 128
@@ -913,7 +915,10 @@ struct GemmItemRec {
     int H, W;
     uint16_t N, C, K, nsplit, sh, sw, ph, pw;
     uint8_t R, S, groups;
-    uint8_t mode : 3, tm : 3, relu : 1;
+    uint8_t mode : 3, tm : 3, relu : 1, tile : 1;
+    // tile = 1: items of whole workgroups (tile_gemm.h).  These layers have 3x3 filters, stride 1, square padding and one
+    // group; the fields that would say so hold the tile instead: S, groups: its rows and columns; sw, pw: tiles per
+    // row and per column of an image; tm: panels per wavefront, + 4 if it holds seven blocks of 16 pixels, not four.
 };
 static_assert(sizeof(GemmItemRec) == 64, "sixteen scalar registers");
 struct GemmItemTable {
@@ -990,13 +995,7 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
 typedef const __attribute__((address_space(4))) GemmItemTable *GemmItemTablePtr;
 
 // All of it is uniform: scalar arithmetic on one 64-byte scalar load.
-__device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItemTablePtr tbl, const int li, const bool half) {
-    GemmItemRec r;
-    const __attribute__((address_space(4))) uint32_t *src = (const __attribute__((address_space(4))) uint32_t *)&tbl->layer[li];
-    uint32_t d[sizeof(GemmItemRec) / 4];
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(GemmItemRec) / 4); ++i) d[i] = src[i];
-    __builtin_memcpy(&r, d, sizeof r);
+__device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItemTablePtr tbl, const GemmItemRec &r, const bool half) {
     GemmParams &g = L.g;
     g.x = r.x; g.wp = r.wp; g.bias = r.bias; g.y = r.y;
     g.N = r.N; g.C = r.C; g.H = r.H; g.W = r.W; g.K = r.K; g.R = r.R; g.S = r.S;
@@ -1023,8 +1022,52 @@ __device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItem
 
 constexpr int kItemWaves = 4;      // items per workgroup (one wavefront each)
 
-template <bool HALF, int NBUF = 2>
-__global__ __launch_bounds__(64 * kItemWaves, 3) void gemm_items_kernel(const GemmItemTable tbl_arg) {
+// The tile of a record with tile = 1.
+__device__ __forceinline__ void load_tile_layer(TileLayer &T, const GemmItemRec &r) {
+    T.x = static_cast<const float *>(r.x); T.wp = static_cast<const float *>(r.wp); T.bias = r.bias; T.y = static_cast<float *>(r.y);
+    T.N = r.N; T.C = r.C; T.H = r.H; T.W = r.W; T.K = r.K; T.pad = r.ph;
+    T.P = r.H + 2 * T.pad - 2;
+    T.Q = r.W + 2 * T.pad - 2;
+    T.K16 = (T.K + 15) >> 4;
+    T.cblocks = (T.C + 3) >> 2;
+    T.th = r.S; T.tw = r.groups; T.ntw = r.sw; T.nth = r.pw;
+    T.relu = r.relu;
+}
+__device__ __forceinline__ int tile_regs(const GemmItemRec &r) { return (r.tm & 3) * (r.tm & 4 ? 28 : 16); }      // accumulator registers of a wavefront
+
+__device__ __forceinline__ GemmItemRec load_item_rec(const GemmItemTablePtr tbl, const int li) {
+    GemmItemRec r;
+    const __attribute__((address_space(4))) uint32_t *src = (const __attribute__((address_space(4))) uint32_t *)&tbl->layer[li];
+    uint32_t d[sizeof(GemmItemRec) / 4];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(GemmItemRec) / 4); ++i) d[i] = src[i];
+    __builtin_memcpy(&r, d, sizeof r);
+    return r;
+}
+
+constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2;      // which whole-workgroup items a launch holds besides the others
+
+template <int TILE>
+__device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const GemmItemRec &r, const int local, char *lds) {
+    TileLayer T;
+    load_tile_layer(T, r);
+    // order: pixel tile fastest, then the range of channels, then the panels
+    const int ntiles = T.N * T.nth * T.ntw, nsplit = r.nsplit;
+    const int rest = __builtin_amdgcn_readfirstlane(local / ntiles), nt = local - rest * ntiles;
+    const int mt = __builtin_amdgcn_readfirstlane(rest / nsplit), ks = rest - mt * nsplit;
+    const int chunks = (T.C + kTileChannels - 1) / kTileChannels;
+    int per = chunks;
+    if (nsplit > 1) per = __builtin_amdgcn_readfirstlane((chunks + nsplit - 1) / nsplit);
+    const int c0 = ks * per, c1 = min(chunks, c0 + per);
+    float *part = nsplit == 1 ? nullptr : reinterpret_cast<float *>(tbl->part_base + (size_t)r.part256 * 256) + ((size_t)(mt * ntiles + nt) * nsplit + ks) * (size_t)(tile_regs(r) * 256);
+    if constexpr (TILE == kLargeTiles) tile_item<2, 7, true>(T, mt, nt, c0, c1, part, lds);
+    else if (r.tm == 5) tile_item<1, 7, false>(T, mt, nt, c0, c1, part, lds);
+    else tile_item<1, 4, false>(T, mt, nt, c0, c1, part, lds);
+}
+
+template <bool HALF, int TILE>
+__global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void gemm_items_kernel(const GemmItemTable tbl_arg) {
+    constexpr int NBUF = 2;
     const GemmItemTablePtr tbl = (GemmItemTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     // Workgroup i runs on XCD i % 8.  Groups of `group` consecutive items (neighbouring tiles of
     // one layer: they share a weight panel) are dealt to the XCDs in turn, so every XCD sees the
@@ -1043,9 +1086,19 @@ __global__ __launch_bounds__(64 * kItemWaves, 3) void gemm_items_kernel(const Ge
     if (item >= tbl->nitems) return;
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->item0[0], item, first);
+    const GemmItemRec rec = load_item_rec(tbl, li);
+    if constexpr (TILE != kNoTiles) {
+        __shared__ __align__(16) char tile_lds[TILE == kLargeTiles ? 2 * kTileBuffer : kTileBuffer];
+        // (every layer of such a launch starts with a workgroup of its own: all four wavefronts come here or none does)
+        if (TILE == kLargeTiles || rec.tile) {
+            run_tile_item<TILE>(tbl, rec, (item - first) / kItemWaves, tile_lds);
+            return;
+        }
+    }
     GemmItemLayer L;
-    load_item_layer(L, tbl, li, HALF);
+    load_item_layer(L, tbl, rec, HALF);
     const int local = item - first;
+    if (TILE != kNoTiles && local >= ((L.g.K16 + L.tm - 1) / L.tm) * L.ntn * L.nsplit) return;      // the layer's last workgroup is not full
     const int lane = threadIdx.x & 63;
     if (L.tm == 4) {
         if constexpr (!HALF) {
@@ -1081,16 +1134,67 @@ __global__ __launch_bounds__(64 * kItemWaves, 3) void gemm_items_kernel(const Ge
 
 __device__ static inline int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
 
+// Sum of nsplit partial values of four lanes, zs apart, in the order of the ranges; twelve loads in flight.
+__device__ __forceinline__ float4 sum_partials(const float4 *src, const size_t zs, const int nsplit) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int kInFlight = 12;
+    for (int z = 0; z < nsplit; z += kInFlight) {
+        // (ranges past the last one load the last one again and are not added)
+        float4 p[kInFlight];
+#pragma unroll
+        for (int i = 0; i < kInFlight; ++i) p[i] = src[(size_t)min(z + i, nsplit - 1) * zs];
+#pragma unroll
+        for (int i = 0; i < kInFlight; ++i)
+            if (z + i < nsplit) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
+    }
+    return v;
+}
+
+// The reduction of a layer whose items are whole workgroups: [tile][range][wavefront][register][lane].
+__device__ __forceinline__ void tile_reduce(const GemmItemTablePtr tbl, const GemmItemRec &r, const int blk) {
+    TileLayer T;
+    load_tile_layer(T, r);
+    const int regs = tile_regs(r), per_tile = regs * 256;        // a multiple of 1024: a workgroup stays in one tile
+    const int wgs = regs >> 2;                                   // workgroups per tile
+    const int tile = __builtin_amdgcn_readfirstlane(blk / wgs), e = (blk - tile * wgs) * 1024 + threadIdx.x * 4;
+    const float *part = reinterpret_cast<const float *>(tbl->part_base + (size_t)r.part256 * 256);
+    const float4 v = sum_partials(reinterpret_cast<const float4 *>(part + (size_t)tile * r.nsplit * per_tile + e), (size_t)per_tile / 4, r.nsplit);
+    const int wr = e >> 6, lane0 = e & 63;
+    const int wave = wr / regs, reg = wr - wave * regs;
+    const int tm = r.tm & 3, tn = r.tm & 4 ? 7 : 4;
+    const int blk16 = reg >> 2, j = reg & 3, m = blk16 / tn, t = blk16 - m * tn;
+    const int ntiles = T.N * T.nth * T.ntw;
+    const int mt = __builtin_amdgcn_readfirstlane(tile / ntiles), nt = tile - mt * ntiles;
+    const int rest = __builtin_amdgcn_readfirstlane(nt / T.ntw), img = __builtin_amdgcn_readfirstlane(rest / T.nth);
+    const TilePos at{img, (rest - img * T.nth) * T.th, (nt - rest * T.ntw) * T.tw, (mt * 4 + wave) * tm};
+    const int k = at.mb0 * 16 + gemm_row(true, tm, m, lane0 >> 4, j), n = t * 16 + (lane0 & 15);
+    const bool rok = k < T.K;
+    const float bv = T.bias && rok ? T.bias[k] : 0.f;
+    const int PQ = T.P * T.Q;
+    const SmallDiv by_tw(T.tw);
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc(T.y, (uint32_t)(T.N * T.K) * (uint32_t)PQ * 4u);
+    const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int pix = tile_out_pixel(T, at, by_tw, n + i);
+        gemm_store(yres, T.relu, false, rok && pix >= 0 ? (uint32_t)((img * T.K + k) * PQ + pix) * 4u : kOobOffset, bv, vv[i]);
+    }
+}
+
 // Adds the nsplit partial tiles of every split layer in the order of the ranges and stores y.
-// A thread owns four consecutive lanes of one accumulator register (16-byte loads); the loads of
-// twelve ranges are in flight at once, the additions keep the order of the ranges.
+// A thread owns four consecutive lanes of one accumulator register (16-byte loads).
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmItemTable tbl_arg) {
     const GemmItemTablePtr tbl = (GemmItemTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     const int b = blockIdx.x;
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->red0[0], b, first);      // the last layer that starts at or before b
+    const GemmItemRec rec = load_item_rec(tbl, li);
+    if (rec.tile) {
+        tile_reduce(tbl, rec, b - first);
+        return;
+    }
     GemmItemLayer L;
-    load_item_layer(L, tbl, li, tbl->half != 0);
+    load_item_layer(L, tbl, rec, tbl->half != 0);
     const int nreg = L.tm * 8;                                   // accumulator registers per lane: TM x 2 blocks x 4
     const int per_tile = nreg * 64;
     const int e = ((b - first) * 256 + threadIdx.x) * 4;          // over [tile][reg][lane]
@@ -1099,17 +1203,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmItemTable tb
     if (tile >= ceil_div_dev(L.g.K16, L.tm) * L.ntn) return;     // second half of the last workgroup of an odd tile count
     const float4 *src = reinterpret_cast<const float4 *>(L.part + (size_t)tile * L.nsplit * per_tile + rl);
     const size_t zs = (size_t)per_tile / 4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    constexpr int kInFlight = 12;
-    for (int z = 0; z < L.nsplit; z += kInFlight) {
-        // (ranges past the last one load the last one again and are not added)
-        float4 p[kInFlight];
-#pragma unroll
-        for (int i = 0; i < kInFlight; ++i) p[i] = src[(size_t)min(z + i, L.nsplit - 1) * zs];
-#pragma unroll
-        for (int i = 0; i < kInFlight; ++i)
-            if (z + i < L.nsplit) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
-    }
+    const float4 v = sum_partials(src, zs, L.nsplit);
     // the four values are rows (lane0 / 16) * 4 + jj of panel m, pixels (lane0 % 16) .. + 3 of block t
     const int mt = tile / L.ntn, nb = tile - mt * L.ntn;
     const int m = reg >> 3, t = (reg >> 2) & 1, jj = reg & 3;
@@ -1323,7 +1417,7 @@ static void launch_octets(const Geo &g, const GemmParams &gp, const void *x, voi
                        static_cast<__half *>(xt), g.c, g.h * g.w);
 }
 
-hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st) {
+static hipError_t launch_im2col_plain(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st) {
     const GemmPlan pl = plan_im2col(g);
     const bool half = g.dtype == NNV_F16;
     GemmParams gp = gemm_params(g, pl.mode, x, w, bias, y);
@@ -1347,8 +1441,30 @@ hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float
 }
 
 // ---- many layers in one launch: item plan of one layer
+// Tile of a layer whose items are whole workgroups (tile_gemm.h).
+struct TileShape {
+    int th, tw, nth, ntw;   // outputs of a tile, tiles per column and row of an image
+};
+
+// The fewest tiles of at most bn outputs whose patch fits, then the smallest patch; false if none does.
+static bool plan_tile_shape(const Geo &g, const int bn, TileShape *out) {
+    long best = LONG_MAX;
+    const int n0 = ceil_div(g.q, bn);
+    for (int n = n0; n < n0 + 4 && n <= g.q; ++n) {
+        const int tw = ceil_div(g.q, n), ntw = ceil_div(g.q, tw), pw = tw + 2;
+        const int rows = std::min({g.p, bn / tw, kTilePatch / pw - 2});
+        if (rows < 1) continue;
+        const int nth = ceil_div(g.p, rows), th = ceil_div(g.p, nth);
+        const long key = (long)nth * ntw * 1024 + (th + 2) * pw;
+        if (key < best && nth < 65536 && ntw < 65536) { best = key; *out = TileShape{th, tw, nth, ntw}; }
+    }
+    return best != LONG_MAX;
+}
+
 struct ItemPlan {
     int mode, tm, nmt, ntn, nsplit;
+    int tile, tn;           // tile: items of whole workgroups, 4 tm panels x tn blocks of 16 pixels
+    TileShape shape;
     int steps;              // k-steps of the whole reduction
     size_t part_bytes;      // partial tiles (0 if the layer is not split)
     size_t xt_bytes;        // float16 copy of x in octets of channels (0 if not needed)
@@ -1359,8 +1475,41 @@ struct ItemPlan {
 // stays small against the whole launch.
 constexpr int kItemSteps = 144;
 
-static ItemPlan plan_items(const Geo &g, const int item_steps) {
+// Layers that may run in items of whole workgroups: float32, 3x3, stride 1, and sizes that fill most of a tile: 48 input
+// channels (a chunk is 32), 33 output channels (a workgroup takes 64), two thirds of its pixels.
+// (SqueezeNet-shaped stack, the expand layers of 16 and 32 channels in tiles or not: 38.8 / 34.3 us.)
+static bool plan_tile(const Geo &g, ItemPlan *ip) {
+    if (g.dtype != NNV_F32 || g.groups != 1 || g.r != 3 || g.s != 3 || g.sh != 1 || g.sw != 1 || g.ph != g.pw || g.ph >= 65536) return false;
+    if (g.c < 48 || g.k < 33) return false;
+    TileShape wide{}, narrow{};
+    const bool okw = plan_tile_shape(g, 112, &wide), okn = plan_tile_shape(g, 64, &narrow);
+    if (!okw && !okn) return false;
+    const long nw = okw ? (long)wide.nth * wide.ntw * 7 : LONG_MAX, nn = okn ? (long)narrow.nth * narrow.ntw * 4 : LONG_MAX;
+    if (std::min(nw, nn) * 32 > 3L * g.p * g.q + 64) return false;
+    ip->tile = 1;
+    ip->tm = 1;
+    ip->tn = nw <= nn ? 7 : 4;
+    ip->shape = nw <= nn ? wide : narrow;
+    ip->nmt = ceil_div(g.k, 64);
+    ip->ntn = g.n * ip->shape.nth * ip->shape.ntw;
+    return true;
+}
+
+// ... its channels cut into ranges of about `chunks` chunks of 32
+static void split_tile(const Geo &g, const int chunks, ItemPlan *ip) {
+    const int all = ceil_div(g.c, kTileChannels);
+    const int per = ceil_div(all, ceil_div(all, std::min(all, chunks)));
+    ip->nsplit = ceil_div(all, per);
+    ip->steps = all * 9;
+    ip->part_bytes = ip->nsplit > 1 ? (size_t)ip->nmt * ip->ntn * ip->nsplit * (ip->tm * ip->tn * 1024) * sizeof(float) : 0;
+}
+
+static ItemPlan plan_items(const Geo &g, const ItemTarget target_len) {
     ItemPlan ip{};
+    if (target_len.chunks > 0 && plan_tile(g, &ip)) {
+        split_tile(g, target_len.chunks, &ip);
+        return ip;
+    }
     const GemmPlan pl = plan_im2col(g);
     const bool half = g.dtype == NNV_F16;
     ip.mode = pl.mode;
@@ -1389,10 +1538,10 @@ static ItemPlan plan_items(const Geo &g, const int item_steps) {
     int nunits = pl.mode == kModeTaps ? ceil_div(g.r * g.s, 4) : pl.mode == 0 ? cblocks * g.r * g.s : row ? cblocks * g.r : cblocks;
     int unit_steps = (pl.mode == 0 || pl.mode == kModeTaps) ? 1 : row ? pl.mode : g.r * g.s;
     int chunk_units = pl.mode == 1 ? (half ? 2 : 8) : 1;
-    int target = item_steps;
+    int target = target_len.steps;
     if (ip.tm == 4) {
         // a wide item does twice the MFMAs per k-step: somewhat fewer steps per item
-        target = std::max(9, item_steps * 3 / 4);
+        target = std::max(9, target * 3 / 4);
     }
     if (!half && pl.mode == 1) { nunits = ceil_div(cblocks, 4); unit_steps = 4; chunk_units = 1; }   // float32 1x1: the kernel splits whole chunks of 4 blocks
     const long steps = (long)nunits * unit_steps;
@@ -1423,59 +1572,77 @@ static ItemPlan plan_items(const Geo &g, const int item_steps) {
 constexpr int kItemStepsShortHalf = 48, kItemStepsMin = 48;
 constexpr int kItemsResident = 256 * 3 * kItemWaves;
 
-int im2col_items_target(int n, const Geo *geos) {
+// Items of whole workgroups: with W of them if each took one chunk (weighted by their blocks of pixels), an item takes W / 450, at least two
+// chunks: three workgroups fit a CU, and an item spends 5 us outside its products.  Launches of fewer than
+// 220 keep to single-wavefront items.  Measured over 30 launches of six stacks at batch 1-4 and 128-320 pixels, us at 1 / 2 / 4 / 8
+// chunks against none: W = 232 (AlexNet-shaped) 34 / 33 / 41 / 65 against 45, 803 (ResNet-18) 55 / 46 / 49 / 76 against 53, 1585 88 / 78 / 70 / 86
+// against 93, 3136 160 / 126 / 117 / 110 against 151, 7488 (VGG-16) 253 / 193 / 172 / 165 against 279; W = 154 (GoogLeNet, 128 x 160) 68 against 53.
+ItemTarget im2col_items_target(int n, const Geo *geos) {
+    ItemTarget target{kItemSteps, 0};
+    if (geos[0].dtype == NNV_F32) {
+        long w = 0;
+        for (int i = 0; i < n; ++i) {
+            ItemPlan ip{};
+            if (plan_tile(geos[i], &ip)) w += (long)ip.nmt * ip.ntn * ip.tn * ceil_div(geos[i].c, kTileChannels);
+        }
+        w /= 7;
+        if (w >= 220) target.chunks = std::max(2, (int)std::min((w + 449) / 450, 65536L));
+    }
     auto total_at = [&](int t) {
         long tot = 0;
         for (int i = 0; i < n; ++i) {
-            const ItemPlan p = plan_items(geos[i], t);
-            tot += (long)p.nmt * p.ntn * p.nsplit;
+            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks});
+            tot += (long)p.nmt * p.ntn * p.nsplit * (p.tile ? kItemWaves : 1);
         }
         return tot;
     };
     const long total = total_at(kItemSteps);
-    if (geos[0].dtype == NNV_F16) return total < 3L * kItemsResident ? kItemStepsShortHalf : kItemSteps;
+    if (geos[0].dtype == NNV_F16) {
+        if (total < 3L * kItemsResident) target.steps = kItemStepsShortHalf;
+        return target;
+    }
     constexpr long fit = (long)kItemsResident * 15 / 16;
-    int best = kItemSteps;
     if (total <= fit)
         for (int t = kItemSteps - 12; t >= kItemStepsMin; t -= 12) {
             if (total_at(t) > fit) break;
-            best = t;
+            target.steps = t;
         }
-    return best;
+    return target;
 }
 
 // The launch's 64-byte layer records hold filter sizes and groups in 8 bits, strides, pads and the
 // number of ranges in 16 (channels and images are below 2^16 everywhere).  Only a stride or a pad of 2^16
 // and more does not fit: such a layer is launched by itself.
 bool im2col_items_supported(const Geo &g) {
-    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, kItemStepsMin / 2).nsplit < 65536;
+    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0}).nsplit < 65536;
 }
 
-size_t im2col_items_workspace_bytes(const Geo &g, int target) {
+size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target) {
     const ItemPlan ip = plan_items(g, target);
     return align_up(ip.part_bytes, 256) + align_up(ip.xt_bytes, 256);
 }
 
-// Launches layers [0, n) (all of one storage type, n <= kMaxGemmLayers) as one item launch plus,
-// if any layer is split, one reduction launch.  ws[i] is layer i's own workspace region of
-// im2col_items_workspace_bytes(geos[i], im2col_items_target(n, geos)).
-hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
-                               void *const *y, void *const *ws, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (n > kMaxGemmLayers) return hipErrorInvalidValue;
+// One item launch of n planned layers of one storage type, with the copies of x in front of it and the reduction behind it
+// that they need; ws[i]: layer i's partial tiles and copy.
+static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, const void *const *x, const void *const *w,
+                                 const float *const *bias, void *const *y, void *const *ws, hipStream_t st) {
     const bool half = geos[0].dtype == NNV_F16;
     // Order: layers with the longest items first, so that the chip's last round of items is made
     // of the short ones.
-    ItemPlan plans[kMaxGemmLayers];
+    // (items of whole workgroups before the others: these fill what they leave)
     int order[kMaxGemmLayers];
-    for (int i = 0; i < n; ++i)
-        if ((geos[i].dtype == NNV_F16) != half) return hipErrorInvalidValue;
-    const int target = im2col_items_target(n, geos);
+    bool tiles = false;
     for (int i = 0; i < n; ++i) {
-        plans[i] = plan_items(geos[i], target);
         order[i] = i;
+        tiles = tiles || plans[i].tile;
     }
-    auto item_len = [&](int i) { return ceil_div(plans[i].steps, plans[i].nsplit) * plans[i].tm; };
+    // 128 x 112 outputs per workgroup: planned for single layers only, and that kernel runs no other items
+    const bool large = n == 1 && plans[0].tile && plans[0].tm == 2;
+    auto item_len = [&](int i) {
+        const ItemPlan &p = plans[i];
+        const long len = (long)ceil_div(p.steps, p.nsplit) * p.tm;
+        return p.tile ? (len * p.tn) << 20 : len;
+    };
     std::stable_sort(order, order + n, [&](int a, int b) { return item_len(a) > item_len(b); });
     GemmItemTable tbl{};
     OctetTable cl{};
@@ -1513,8 +1680,18 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
         L.nsplit = (uint16_t)ip.nsplit;
         L.mode = ip.mode;
         L.tm = ip.tm;
-        items += ip.nmt * ip.ntn * ip.nsplit;
-        if (ip.nsplit > 1) red += ceil_div(ip.nmt * ip.ntn * (ip.tm * 8), 16);     // 1024 values per workgroup
+        const int count = ip.nmt * ip.ntn * ip.nsplit;
+        if (ip.tile) {
+            L.tile = 1;
+            L.tm = ip.tm + (ip.tn == 7 ? 4 : 0);
+            L.S = (uint8_t)ip.shape.th; L.groups = (uint8_t)ip.shape.tw;
+            L.sw = (uint16_t)ip.shape.ntw; L.pw = (uint16_t)ip.shape.nth;
+            items += count * kItemWaves;
+            if (ip.nsplit > 1) red += ip.nmt * ip.ntn * (ip.tm * ip.tn);
+        } else {
+            items += tiles ? ceil_div(count, kItemWaves) * kItemWaves : count;
+            if (ip.nsplit > 1) red += ceil_div(ip.nmt * ip.ntn * (ip.tm * 8), 16);     // 1024 values per workgroup
+        }
     }
     for (int i = n; i < kMaxGemmLayers; ++i) tbl.item0[i] = tbl.red0[i] = INT_MAX;
     tbl.nitems = items;
@@ -1528,10 +1705,49 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
     }
     const int wgs = ceil_div(items, kItemWaves);
     const int per_xcd = ceil_div(ceil_div(wgs, tbl.group), 8) * tbl.group;
-    if (half) hipLaunchKernelGGL(gemm_items_kernel<true>, dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else hipLaunchKernelGGL(gemm_items_kernel<false>, dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    if (half) hipLaunchKernelGGL((gemm_items_kernel<true, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (large) hipLaunchKernelGGL((gemm_items_kernel<false, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (tiles) hipLaunchKernelGGL((gemm_items_kernel<false, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else hipLaunchKernelGGL((gemm_items_kernel<false, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     if (red > 0) hipLaunchKernelGGL(gemm_reduce_kernel, dim3(red), dim3(256), 0, st, tbl);
     return hipGetLastError();
+}
+
+// Launches layers [0, n) (all of one storage type, n <= kMaxGemmLayers) as one item launch plus,
+// if any layer is split, one reduction launch.  ws[i] is layer i's own workspace region of
+// im2col_items_workspace_bytes(geos[i], im2col_items_target(n, geos)).
+hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
+                               void *const *y, void *const *ws, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (n > kMaxGemmLayers) return hipErrorInvalidValue;
+    for (int i = 0; i < n; ++i)
+        if (geos[i].dtype != geos[0].dtype) return hipErrorInvalidValue;
+    const ItemTarget target = im2col_items_target(n, geos);
+    ItemPlan plans[kMaxGemmLayers];
+    for (int i = 0; i < n; ++i) plans[i] = plan_items(geos[i], target);
+    return launch_planned(n, geos, plans, x, w, bias, y, ws, st);
+}
+
+// A single layer in items of whole workgroups, its channels not split: from 200 items on (below, a CU's one item takes its whole
+// channel loop at the pace of one wavefront per SIMD).  Measured, us, without / with: 224 items 44.6 / 29.9 (128 channels at 112x112) and
+// 156 / 101 (512 at 4x28x28), 448 items 44.5 / 35 (64 at 224x224); 112 items 44 / 54 (256 at 56x56), 128 80 / 102 (512 at 8x14x14).
+// 128 x 112 outputs with two buffers in LDS where that leaves 260 items: 256 at 8x56x56 154 / 138, 2 x 96 -> 200 at 80x90 45 / 40; with 112
+// of them 101 / 138 (512 at 4x28x28).
+static bool plan_tile_single(const Geo &g, ItemPlan *ip) {
+    if (!plan_tile(g, ip) || (long)ip->nmt * ip->ntn < 200) return false;
+    const int K16 = ceil_div(g.k, 16), nmt = ceil_div(K16, 8);
+    if (ip->tn == 7 && (long)nmt * ip->ntn >= 260 && nmt * 8 * 100 <= ceil_div(K16, 4) * 4 * 115) {
+        ip->tm = 2;
+        ip->nmt = nmt;
+    }
+    split_tile(g, INT_MAX, ip);
+    return true;
+}
+
+hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st) {
+    ItemPlan tile{};
+    if (plan_tile_single(g, &tile)) return launch_planned(1, &g, &tile, &x, &w, bias ? &bias : nullptr, &y, &ws, st);
+    return launch_im2col_plain(g, x, w, bias, y, ws, st);
 }
 
 }  // namespace nnv
