@@ -819,8 +819,61 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
 
 #include "tile_gemm.h"
 
+// The KS partial tiles of a workgroup's tile nt meet in LDS: red[((nt * KS + ks) * NREG + reg) * 64 + lane].
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_put_partial(const floatx4 (&acc)[TM][TN], float *red, const int KS, const int place, const int lane) {
+    if (KS > 1) {
+        constexpr int NREG = TM * TN * 4;
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) red[(place * NREG + (m * TN + t) * 4 + j) * 64 + lane] = acc[m][t][j];
+    }
+}
+
+// ... and are added in fixed order; `share` of the tile's `sharers` wavefronts finishes the accumulator registers share,
+// share + sharers, ..  Lane holds rows 4 * slot + j, column col of each block.  A barrier lies between, for the whole workgroup.
+template <int TM, int TN, bool MIXED>
+__device__ __forceinline__ void gemm_finish(const GemmParams &g, const int mb0, const int KS, const int share, const int sharers, const int nt, const int lane,
+                                            const floatx4 (&acc)[TM][TN], const PixState<TN> &px, const float *red) {
+    constexpr int NREG = TM * TN * 4;
+    if (KS > 1) __syncthreads();
+    RowState<TM> rs;
+    gemm_rows<TM, MIXED>(g, mb0, lane >> 4, rs);
+    const __amdgpu_buffer_rsrc_t yres = gemm_y_rsrc(g);
+    const bool relu = g.relu, half_out = g.half_out;
+    uint32_t pixoff[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) pixoff[t] = gemm_pixel_offset(g, px.img[t], px.pq[t], px.valid[t]);
+#pragma unroll
+    for (int m = 0; m < TM; ++m) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int reg = (m * TN + t) * 4 + j;
+                if ((reg & (sharers - 1)) != share) continue;
+                float v = acc[m][t][j];
+                if (KS > 1) {
+                    v = 0.f;
+                    for (int z = 0; z < KS; ++z) v += red[((nt * KS + z) * NREG + reg) * 64 + lane];
+                }
+                // either offset may be the out-of-range constant 2^31; both at once would wrap to a small sum
+                const uint32_t off = rs.off[m][j] == kOobOffset ? kOobOffset : rs.off[m][j] + pixoff[t];
+                gemm_store(yres, relu, half_out, off, rs.bias[m][j], v);
+            }
+        }
+    }
+}
+
 // One layer per launch: a workgroup of KS wavefronts owns one output tile, the wavefronts split
 // the channel blocks and add their partial sums through LDS in fixed order.
+// What bounds such a launch is the vector memory path of its CUs beside the latency of the first loads.  float32 3x3 tiles run the
+// loop of the work items: one load carries the weights of both panels, and with a third of the registers the loads of a row do not queue
+// behind three chunks of others.  us, whole chunks of nine taps in rings of 2 to 4 -> rows in a ring of 3: 128 channels at 28x28
+// 8.1 -> 7.7, 512 at 7x7 14.7 -> 13.3, 512 -> 64 at 14x14 14.9 -> 12.5, 96 -> 100 at 20x30 8.9 -> 6.8.
 // (the 32 x 32 tile is launched as one wavefront per workgroup only, and needs more than the 128
 // registers a 16-wavefront workgroup leaves each lane)
 template <bool HALF, int TM, int TN, int MODE, int NBUF>
@@ -840,51 +893,13 @@ __global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void
     const int nb0 = (bx * tiles_per_wg + nt) * TN;
     floatx4 acc[TM][TN];
     PixState<TN> px;
-    constexpr bool MIXED = TM == 4;                       // float32 3x3 only
-    if constexpr (MIXED) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
+    constexpr bool ROWS3 = !HALF && MODE == 3 && (TM == 4 || TN == 1), MIXED = ROWS3;
+    if constexpr (ROWS3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(g, mb0, nb0, ks, KS, lane, acc, px);
 
-    // ---- sum the KS partial tiles through LDS: red[((nt * KS + ks) * NREG + reg) * 64 + lane]
-    constexpr int NREG = TM * TN * 4;
-    if (KS > 1) {
-#pragma unroll
-        for (int m = 0; m < TM; ++m)
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    red[((nt * KS + ks) * NREG + (m * TN + t) * 4 + j) * 64 + lane] = acc[m][t][j];
-        __syncthreads();
-    }
-    // epilogue: lane holds rows 4*slot + j, column col of each block; wavefront ks finishes the
-    // accumulator registers reg = ks, ks + KS, ...
-    RowState<TM> rs;
-    gemm_rows<TM, MIXED>(g, mb0, slot, rs);
-    const __amdgpu_buffer_rsrc_t yres = gemm_y_rsrc(g);
-    const bool relu = g.relu, half_out = g.half_out;
-    uint32_t pixoff[TN];
-#pragma unroll
-    for (int t = 0; t < TN; ++t) pixoff[t] = gemm_pixel_offset(g, px.img[t], px.pq[t], px.valid[t]);
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-#pragma unroll
-        for (int t = 0; t < TN; ++t) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int reg = (m * TN + t) * 4 + j;
-                if ((reg & (KS - 1)) != ks) continue;
-                float v = acc[m][t][j];
-                if (KS > 1) {
-                    v = 0.f;
-                    for (int z = 0; z < KS; ++z) v += red[((nt * KS + z) * NREG + reg) * 64 + lane];
-                }
-                // either offset may be the out-of-range constant 2^31; both at once would wrap to a small sum
-                const uint32_t off = rs.off[m][j] == kOobOffset ? kOobOffset : rs.off[m][j] + pixoff[t];
-                gemm_store(yres, relu, half_out, off, rs.bias[m][j], v);
-            }
-        }
-    }
+    gemm_put_partial<TM, TN>(acc, red, KS, nt * KS + ks, lane);
+    gemm_finish<TM, TN, MIXED>(g, mb0, KS, ks, KS, nt, lane, acc, px, red);
 }
 
 // ---------------------------------------------------------------- many layers in one launch
@@ -1344,7 +1359,14 @@ static GemmPlan plan_im2col(const Geo &g) {
     // (the float16 1x1 gather keeps eight loads per fragment in flight: no room for the 32x32 tile)
     if (tiles(2, 2) >= 4096 && !(half && pl.mode == 1)) { pl.tm = 2; pl.tn = 2; pl.ks_shift = 0; }
     else if (tiles(2, 1) >= 160) { pl.tm = 2; pl.tn = 1; pl.ks_shift = split_for(tiles(2, 1), 2048); }
-    else { pl.tm = 1; pl.tn = 1; pl.ks_shift = split_for(tiles(1, 1), 768); }
+    else {
+        pl.tm = 1; pl.tn = 1;
+        pl.ks_shift = split_for(tiles(1, 1), 768);
+        // float32 3x3, whose loop keeps fewer registers (two filter rows ahead): twice the wavefronts as long as each keeps 72 steps.
+        // us without / with, [channels, maps -> outputs]: [256, 14x14 -> 256] 9.6 / 8.0, [999, 12x32 -> 148] 27.5 / 20.7, [1024, 7x7 -> 1024] 39 /
+        // 26; below 72 steps [256, 2x7x7 -> 256] 8.4 / 8.9.
+        if (!half && pl.mode == 3 && pl.ks_shift < 3 && (tiles(1, 1) << pl.ks_shift) < 1536 && (((long)nunits * unit_steps) >> (pl.ks_shift + 1)) >= 72) ++pl.ks_shift;
+    }
     if (g.groups > 1 && kg16 % pl.tm != 0) {       // a wavefront's panels must belong to one group
         pl.tm = 1; pl.tn = 1;
         pl.ks_shift = split_for(tiles(1, 1), 2048);
@@ -1356,7 +1378,7 @@ static GemmPlan plan_im2col(const Geo &g) {
     pl.nbuf = 2;
     if (pl.tm == 1 && chunks >= 6) pl.nbuf = 4;
     else if (pl.tm * pl.tn <= 2 && chunks >= 3) pl.nbuf = 3;
-    if (half || pl.tm * pl.tn == 4) pl.nbuf = 2;
+    if (half || pl.tm * pl.tn == 4 || pl.mode == 3) pl.nbuf = 2;       // (float32 3x3: rings of three filter rows, gemm_accumulate_3x3)
     // float16 needs the copy of x in octets of channels, except for 1x1 filters (gathered from NCHW)
     pl.xt_bytes = (half && pl.mode != 1) ? align_up((size_t)g.n * g.h * g.w * copy_channels(g, pl.mode) * sizeof(__half), 256) : 0;
     return pl;
@@ -1368,7 +1390,7 @@ template <bool HALF, int TM, int TN, int NBUF>
 static void launch_gemm_mode(int mode, const GemmParams &gp, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
     switch (mode) {
         case 1: if constexpr (!HALF || TM * TN < 4) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 1, NBUF>), grid, block, lds, st, gp); } break;
-        case 3: hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 3, NBUF>), grid, block, lds, st, gp); break;
+        case 3: if constexpr (NBUF == 2) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 3, NBUF>), grid, block, lds, st, gp); } break;
         case kModeTaps: if constexpr (HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, kModeTaps, NBUF>), grid, block, lds, st, gp); } break;
         case 5: if constexpr (!HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 5, NBUF>), grid, block, lds, st, gp); } break;
         case 7: if constexpr (!HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 7, NBUF>), grid, block, lds, st, gp); } break;
