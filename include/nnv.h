@@ -223,12 +223,14 @@ int nnv_time_layer(const nnv_conv_desc *desc, nnv_kind kind, const float *w_raw,
  * by layer).  The layers are cut into stages of `stage_layers` consecutive layers
  * (<= 0: one stage holding all).  Each stage's weights are transformed in one grouped
  * launch on stream_tx; each layer's convolution runs on stream_exec once its stage
- * is transformed.  With stream_tx == stream_exec the same launches are issued in
+ * is transformed.  Within a stage, IM2COL_GEMM layers in float32 whose buffers show that
+ * neither reads or writes what the other writes may share a launch (the branches of a module, a
+ * residual block's projection); results are those of the layers one after the other, bit for bit.  With stream_tx == stream_exec the same launches are issued in
  * the same order on one stream: the unpipelined baseline.
  *   descs, kinds, w_raw, w_tx, x, y : HOST arrays of length n_layers (descriptors,
  *       kinds, device pointers); bias is not applied
  *   workspace : device, >= the largest nnv_workspace_bytes of the list, shared by
- *       all layers (their convolutions are serialised on stream_exec)
+ *       all layers that need it (these are serialised on stream_exec)
  * stream_tx first waits for the work already queued on stream_exec, and stream_exec
  * ends up waiting for everything issued on stream_tx, so the call may be captured
  * into a HIP graph from stream_exec; work the caller queues on either stream

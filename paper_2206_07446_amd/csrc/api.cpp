@@ -212,6 +212,76 @@ int forward_args(const nnv_conv_desc *desc, nnv_kind kind, const void *x, const 
     return NNV_OK;
 }
 
+// ---- the convolutions of a stage of a cold pass: layers that do not depend on one another share a launch where they can
+struct Span {
+    uintptr_t begin, end;
+    Span(const void *p, size_t n) : begin(reinterpret_cast<uintptr_t>(p)), end(begin + n) {}
+    bool meets(const Span &o) const { return begin < o.end && o.begin < end; }
+};
+
+// Executes layers [0, n) as one after the other would.  A layer's level is one above the highest of the earlier layers whose
+// output it reads or writes over, or whose input or weights it writes over; the mergeable layers of a level go out
+// in one launch.  Buffers that lie in the workspace follow no rule here: then one layer after the other.
+constexpr int kMergeWindow = 64;      // layers looked at together: at most 2016 pairs
+int forward_levels(int n, const Geo *geos, const nnv_kind *kinds, const void *const *x, void *const *w_tx, void *const *y, void *ws,
+                   size_t ws_size, hipStream_t st) {
+    int level[kMergeWindow], last = 0, mergeable = 0;
+    bool merge[kMergeWindow], plain = false;
+    for (int i = 0; i < n; ++i) {
+        level[i] = i;
+        merge[i] = kinds[i] == NNV_IM2COL_GEMM && im2col_layer_mergeable(geos[i]);
+        mergeable += merge[i] ? 1 : 0;
+    }
+    last = n - 1;
+    if (mergeable > 1) {
+        std::vector<Span> xs, wt, ys;
+        const Span scratch(ws, ws ? ws_size : 0);
+        for (int i = 0; i < n; ++i) {
+            const Geo &g = geos[i];
+            const size_t esz = g.dtype == NNV_F16 ? 2 : 4;
+            xs.emplace_back(x[i], (size_t)g.n * g.c * g.h * g.w * esz);
+            wt.emplace_back(w_tx[i], tx_bytes(g, kinds[i]));
+            ys.emplace_back(y[i], (size_t)g.n * g.k * g.p * g.q * esz);
+            plain = plain || scratch.meets(xs[i]) || scratch.meets(wt[i]) || scratch.meets(ys[i]);
+        }
+        last = 0;
+        for (int j = 0; j < n && !plain; ++j) {
+            level[j] = 0;
+            for (int i = 0; i < j; ++i)
+                if (level[i] >= level[j] && (ys[i].meets(xs[j]) || ys[i].meets(ys[j]) || ys[i].meets(wt[j]) || ys[j].meets(xs[i]) || ys[j].meets(wt[i])))
+                    level[j] = level[i] + 1;
+            last = std::max(last, level[j]);
+        }
+        if (plain) last = n - 1;
+    }
+    for (int v = 0; v <= last; ++v) {
+        std::vector<Geo> bg;
+        std::vector<const void *> bx, bw;
+        std::vector<void *> by;
+        int one = -1;
+        for (int i = 0; i < n; ++i) {
+            if (level[i] != v) continue;
+            if (merge[i]) {
+                bg.push_back(geos[i]); bx.push_back(x[i]); bw.push_back(w_tx[i]); by.push_back(y[i]);
+                one = i;
+                continue;
+            }
+            const int rc = forward_checked(geos[i], kinds[i], x[i], w_tx[i], nullptr, y[i], ws, st);
+            if (rc) return rc;
+        }
+        if (bg.size() == 1) {
+            const int rc = forward_checked(geos[one], kinds[one], x[one], w_tx[one], nullptr, y[one], ws, st);
+            if (rc) return rc;
+        }
+        for (size_t b = 0; bg.size() > 1 && b < bg.size(); b += kMaxMergedLayers) {
+            const int m = (int)std::min<size_t>(kMaxMergedLayers, bg.size() - b);
+            const hipError_t e = launch_im2col_layers(m, &bg[b], &bx[b], &bw[b], &by[b], st);
+            if (e != hipSuccess) return hip_fail(e);
+        }
+    }
+    return NNV_OK;
+}
+
 // Device address of nnv_static_scratch on the current device, looked up once per device.
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_lock;
@@ -546,8 +616,8 @@ int nnv_cold_stack(int n_layers, const nnv_conv_desc *descs, const nnv_kind *kin
             if (e != hipSuccess) { rc = hip_fail(e); break; }
         }
         const int b = s * per, n = std::min(per, n_layers - b);
-        for (int i = b; i < b + n && rc == NNV_OK; ++i)
-            rc = forward_checked(geos[i], kinds[i], x[i], w_tx[i], nullptr, y[i], workspace, se);
+        for (int i = b; i < b + n && rc == NNV_OK; i += kMergeWindow)
+            rc = forward_levels(std::min(kMergeWindow, b + n - i), &geos[i], kinds + i, x + i, w_tx + i, y + i, workspace, workspace_bytes, se);
     }
     if (two && rc != NNV_OK) {
         // an error cut the pass short: still join stream_tx back into stream_exec, so that a

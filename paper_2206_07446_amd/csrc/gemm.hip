@@ -1147,6 +1147,73 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
     }
 }
 
+// ---------------------------------------------------------------- several layers, each as its own launch would run it
+// Layers of a cold pass that do not depend on one another, in one launch: the tiles and the splits of the reduction are those of
+// im2col_gemm_kernel, and so are the results, bit for bit (a caller may not see whether a layer shared a launch).  What it
+// saves: a batch-1 layer leaves most of the chip idle for most of its 8-16 us.  Workgroups of eight wavefronts hold 8 / KS tiles, or one
+// of KS = 16, whose wavefronts then take two ranges each.  Every layer's blocks are a multiple of eight, so that the XCD of a
+// block does not depend on what else is in the launch.  Measured, us a cold pass of a stack (batch 1, 224 x 224), one launch a layer ->
+// this: ResNet-18-shaped 206 -> 127, ResNet-50 463 -> 320, GoogLeNet 362 -> 99, SqueezeNet 151 -> 59, AlexNet 76 -> 57; MobileNetV2 (a chain)
+// 224 -> 224.  Two workgroups per CU at 87 registers; held to 80 for a third one it takes as long.
+constexpr int kLayerWaves = 8;      // 1 << 3
+struct GemmLayersTable {
+    GemmParams g[kMaxMergedLayers];           // grid_nx, grid_ny: workgroups along the pixels, tiles along the panels
+    int block0[kMaxMergedLayers];             // first workgroup of each layer, INT_MAX beyond the last one
+    uint8_t variant[kMaxMergedLayers];        // mode + 8 if a tile has two panels
+};
+static_assert(sizeof(GemmLayersTable) <= 4096, "the table is passed by value as the kernel argument");
+typedef const __attribute__((address_space(4))) GemmLayersTable *GemmLayersTablePtr;
+
+template <int TM, int MODE, int NBUF>
+__device__ __forceinline__ void gemm_layer_block(const GemmParams &g, const int blk, float *red) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int KS = 1 << g.ks_shift, pshift = min(g.ks_shift, 3), per_tile = 1 << pshift, ks = wave & (per_tile - 1);
+    const int nt = wave >> pshift, tiles = kLayerWaves >> pshift;
+    const int total = g.grid_nx * g.grid_ny, per = (total + 7) >> 3, ltile = (blk & 7) * per + (blk >> 3);
+    if (ltile >= total) return;                            // whole workgroup: padding
+    const int div = g.m_major ? g.grid_nx : g.grid_ny, hi = __builtin_amdgcn_readfirstlane(ltile / div), lo = ltile - hi * div;
+    const int mb0 = (g.m_major ? hi : lo) * TM, nb0 = (g.m_major ? lo : hi) * tiles + nt;
+    floatx4 acc[TM][1];
+    PixState<1> px;
+#pragma nounroll
+    for (int z = ks; z < KS; z += per_tile) {
+        if constexpr (MODE == 3) gemm_accumulate_3x3<TM, 1>(g, mb0, nb0, z, KS, lane, acc, px);
+        else gemm_accumulate<false, TM, 1, MODE, NBUF>(g, mb0, nb0, z, KS, lane, acc, px);
+        gemm_put_partial<TM, 1>(acc, red, KS, nt * KS + z, lane);
+    }
+    gemm_finish<TM, 1, MODE == 3>(g, mb0, KS, ks, per_tile, nt, lane, acc, px, red);
+}
+
+__global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const GemmLayersTable tbl_arg) {
+    __shared__ __align__(16) float red[16 * 8 * 64];       // KS = 16, two panels
+    const GemmLayersTablePtr tbl = (GemmLayersTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
+    int first;
+    const int li = table_find<kMaxMergedLayers>(&tbl->block0[0], (int)blockIdx.x, first);
+    GemmParams g;
+    {
+        static_assert(sizeof(GemmParams) % 4 == 0, "copied word by word");
+        const __attribute__((address_space(4))) uint32_t *src = (const __attribute__((address_space(4))) uint32_t *)&tbl->g[li];
+        uint32_t d[sizeof(GemmParams) / 4];
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(GemmParams) / 4); ++i) d[i] = src[i];
+        __builtin_memcpy(&g, d, sizeof g);
+    }
+    const int blk = (int)blockIdx.x - first;
+    switch (tbl->variant[li]) {
+        case 1: gemm_layer_block<1, 1, 2>(g, blk, red); break;
+        case 3: gemm_layer_block<1, 3, 2>(g, blk, red); break;
+        case 5: gemm_layer_block<1, 5, 2>(g, blk, red); break;
+        case 7: gemm_layer_block<1, 7, 2>(g, blk, red); break;
+        case 0: gemm_layer_block<1, 0, 2>(g, blk, red); break;
+        case 9: gemm_layer_block<2, 1, 2>(g, blk, red); break;
+        case 11: gemm_layer_block<2, 3, 2>(g, blk, red); break;
+        case 13: gemm_layer_block<2, 5, 2>(g, blk, red); break;
+        case 15: gemm_layer_block<2, 7, 2>(g, blk, red); break;
+        default: gemm_layer_block<2, 0, 2>(g, blk, red); break;
+    }
+}
+
 __device__ static inline int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
 
 // Sum of nsplit partial values of four lanes, zs apart, in the order of the ranges; twelve loads in flight.
@@ -1764,6 +1831,48 @@ static bool plan_tile_single(const Geo &g, ItemPlan *ip) {
     }
     split_tile(g, INT_MAX, ip);
     return true;
+}
+
+// Layers that gemm_layers_kernel may run: float32 with the small tiles of im2col_gemm_kernel.
+bool im2col_layer_mergeable(const Geo &g) {
+    ItemPlan tile{};
+    if (g.dtype != NNV_F32 || plan_tile_single(g, &tile)) return false;
+    const GemmPlan pl = plan_im2col(g);
+    return pl.tn == 1 && pl.tm <= 2 && pl.ks_shift <= 4;
+}
+
+// n <= kMaxMergedLayers mergeable layers, none of which reads or writes what another one writes: one launch, results as by launch_im2col.
+hipError_t launch_im2col_layers(int n, const Geo *geos, const void *const *x, const void *const *w, void *const *y, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (n > kMaxMergedLayers) return hipErrorInvalidValue;
+    GemmPlan plans[kMaxMergedLayers];
+    int order[kMaxMergedLayers];
+    long work[kMaxMergedLayers];         // about the k-steps of a wavefront
+    for (int i = 0; i < n; ++i) {
+        plans[i] = plan_im2col(geos[i]);
+        order[i] = i;
+        work[i] = (long)ceil_div(geos[i].cg, 4) * geos[i].r * geos[i].s >> std::min(plans[i].ks_shift, 3);
+    }
+    std::stable_sort(order, order + n, [&](int a, int b) { return work[a] > work[b]; });
+    GemmLayersTable tbl{};
+    long blocks = 0;
+    for (int o = 0; o < n; ++o) {
+        const int i = order[o];
+        const GemmPlan &pl = plans[i];
+        GemmParams &gp = tbl.g[o];
+        gp = gemm_params(geos[i], pl.mode, x[i], w[i], nullptr, y[i]);
+        gp.ks_shift = pl.ks_shift;
+        gp.grid_nx = ceil_div(ceil_div(gp.npix, 16), kLayerWaves >> std::min(pl.ks_shift, 3));
+        gp.grid_ny = ceil_div(gp.K16, pl.tm);
+        gp.m_major = gp.w_bytes >= gp.x_bytes;
+        tbl.variant[o] = (uint8_t)(pl.mode + (pl.tm == 2 ? 8 : 0));
+        tbl.block0[o] = (int)blocks;
+        blocks += xcd_grid(gp.grid_nx * gp.grid_ny);
+        if (blocks >= (1L << 30)) return hipErrorInvalidValue;
+    }
+    for (int o = n; o < kMaxMergedLayers; ++o) tbl.block0[o] = INT_MAX;
+    hipLaunchKernelGGL(gemm_layers_kernel, dim3((unsigned)blocks), dim3(64 * kLayerWaves), 0, st, tbl);
+    return hipGetLastError();
 }
 
 hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st) {

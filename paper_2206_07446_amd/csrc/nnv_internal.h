@@ -96,6 +96,12 @@ size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target);
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w,
                                const float *const *bias, void *const *y, void *const *ws, hipStream_t st);
 
+// Several IM2COL_GEMM layers without bias that do not depend on one another, in one launch whose results are those of
+// launch_im2col on each of them, bit for bit (at most kMaxMergedLayers, each mergeable).
+constexpr int kMaxMergedLayers = 24;
+bool im2col_layer_mergeable(const Geo &g);
+hipError_t launch_im2col_layers(int n, const Geo *geos, const void *const *x, const void *const *w, void *const *y, hipStream_t st);
+
 size_t wino_workspace_bytes(const Geo &g, int kind);
 // Many layers of one Winograd kind and storage type in three launches (see winograd.hip).
 constexpr int kMaxWinoLayers = 20;
