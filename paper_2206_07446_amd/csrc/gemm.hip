@@ -1696,6 +1696,21 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
             if (total_at(t) > fit) break;
             target.steps = t;
         }
+    // float32, whatever their number: no item longer than a SIMD's share of the launch's matrix instructions, or the launch ends with
+    // a few long items (the deep layers of a mobile network: 20 us each, and all others are done after 12).  us a call, items of 144 steps
+    // or what the rule above chose / this: MobileNetV2-shaped plan 47 / 40, MobileNetV1 44 / 42, ResNet-18 at batch 2, 150 x 187 74 / 63;
+    // shares longer than the items change nothing (ResNet-50, SqueezeNet, where items of 72 cost 9 %).
+    double share = 0;                   // in steps of a panel
+    int longest[5] = {0, 0, 0, 0, 0};   // steps of the longest reduction among the layers of 1, 2 and 4 panels per tile
+    for (int i = 0; i < n; ++i) {
+        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks});
+        if (p.tile) continue;
+        share += (double)p.nmt * p.ntn * p.steps * p.tm / 1024;
+        longest[p.tm] = std::max(longest[p.tm], p.steps);
+    }
+    for (int tm : {1, 2, 4})
+        if ((double)longest[tm] * tm > share)
+            while (target.steps > kItemStepsMin && target.steps * (tm == 4 ? 0.75 : 1.0) * tm > share) target.steps -= 12;
     return target;
 }
 
