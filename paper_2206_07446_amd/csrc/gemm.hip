@@ -931,9 +931,9 @@ struct GemmItemRec {
     uint16_t N, C, K, nsplit, sh, sw, ph, pw;
     uint8_t R, S, groups;
     uint8_t mode : 3, tm : 3, relu : 1, tile : 1;
-    // tile = 1: items of whole workgroups (tile_gemm.h).  These layers have 3x3 filters, stride 1, square padding and one
-    // group; the fields that would say so hold the tile instead: S, groups: its rows and columns; sw, pw: tiles per
-    // row and per column of an image; tm: panels per wavefront, + 4 if it holds seven blocks of 16 pixels, not four.
+    // tile = 1: items of whole workgroups (tile_gemm.h), all of one group.  tm: panels per wavefront, + 4 if it holds seven blocks of 16 pixels, not
+    // four.  mode: 3, 3x3 filters at equal strides (sh) and pads (ph), the fields that are free hold the tile: S, groups: its rows and columns; sw, pw: tiles
+    // per row and per column of an image.  1, 1x1 filters.  kModeTaps, few channels, not split: the tile's rows and columns * 256 in part256.
 };
 static_assert(sizeof(GemmItemRec) == 64, "sixteen scalar registers");
 struct GemmItemTable {
@@ -1038,15 +1038,28 @@ __device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItem
 constexpr int kItemWaves = 4;      // items per workgroup (one wavefront each)
 
 // The tile of a record with tile = 1.
-__device__ __forceinline__ void load_tile_layer(TileLayer &T, const GemmItemRec &r) {
-    T.x = static_cast<const float *>(r.x); T.wp = static_cast<const float *>(r.wp); T.bias = r.bias; T.y = static_cast<float *>(r.y);
+__device__ __forceinline__ void load_tile_layer(TileLayer &T, const GemmItemRec &r, const bool half) {
+    T.x = r.x; T.wp = r.wp; T.bias = r.bias; T.y = r.y;
     T.N = r.N; T.C = r.C; T.H = r.H; T.W = r.W; T.K = r.K; T.pad = r.ph;
-    T.P = r.H + 2 * T.pad - 2;
-    T.Q = r.W + 2 * T.pad - 2;
     T.K16 = (T.K + 15) >> 4;
-    T.cblocks = (T.C + 3) >> 2;
-    T.th = r.S; T.tw = r.groups; T.ntw = r.sw; T.nth = r.pw;
+    T.cblocks = half ? (T.C + 31) >> 5 : (T.C + 3) >> 2;
     T.relu = r.relu;
+    if (!half || r.mode == 3) {
+        T.st = half ? r.sh : 1;
+        T.P = (half && T.st == 2 ? (r.H + 2 * T.pad - 3) >> 1 : r.H + 2 * T.pad - 3) + 1;
+        T.Q = (half && T.st == 2 ? (r.W + 2 * T.pad - 3) >> 1 : r.W + 2 * T.pad - 3) + 1;
+        T.th = r.S; T.tw = r.groups; T.ntw = r.sw; T.nth = r.pw;
+        return;
+    }
+    T.R = r.R; T.S = r.S; T.sh = r.sh; T.sw = r.sw; T.padw = r.pw;
+    T.P = (r.H + 2 * T.pad - T.R) / T.sh + 1;
+    T.Q = (r.W + 2 * T.padw - T.S) / T.sw + 1;
+    T.th = T.tw = T.nth = T.ntw = 1;
+    if (r.mode == kModeTaps) {
+        T.th = r.part256 & 255; T.tw = r.part256 >> 8;         // (not split)
+        T.nth = (T.P + T.th - 1) / T.th;
+        T.ntw = (T.Q + T.tw - 1) / T.tw;
+    }
 }
 __device__ __forceinline__ int tile_regs(const GemmItemRec &r) { return (r.tm & 3) * (r.tm & 4 ? 28 : 16); }      // accumulator registers of a wavefront
 
@@ -1062,12 +1075,17 @@ __device__ __forceinline__ GemmItemRec load_item_rec(const GemmItemTablePtr tbl,
 
 constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2;      // which whole-workgroup items a launch holds besides the others
 
-template <int TILE>
+__device__ __forceinline__ int one_tiles(const TileLayer &T, const GemmItemRec &r) {
+    const int px = r.tm & 4 ? 112 : 64;
+    return __builtin_amdgcn_readfirstlane((T.N * T.P * T.Q + px - 1) / px);
+}
+
+template <bool HALF, int TILE>
 __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const GemmItemRec &r, const int local, char *lds) {
     TileLayer T;
-    load_tile_layer(T, r);
+    load_tile_layer(T, r, HALF);
     // order: pixel tile fastest, then the range of channels, then the panels
-    const int ntiles = T.N * T.nth * T.ntw, nsplit = r.nsplit;
+    const int ntiles = HALF && r.mode == 1 ? one_tiles(T, r) : T.N * T.nth * T.ntw, nsplit = r.nsplit;
     const int rest = __builtin_amdgcn_readfirstlane(local / ntiles), nt = local - rest * ntiles;
     const int mt = __builtin_amdgcn_readfirstlane(rest / nsplit), ks = rest - mt * nsplit;
     const int chunks = (T.C + kTileChannels - 1) / kTileChannels;
@@ -1075,9 +1093,29 @@ __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const 
     if (nsplit > 1) per = __builtin_amdgcn_readfirstlane((chunks + nsplit - 1) / nsplit);
     const int c0 = ks * per, c1 = min(chunks, c0 + per);
     float *part = nsplit == 1 ? nullptr : reinterpret_cast<float *>(tbl->part_base + (size_t)r.part256 * 256) + ((size_t)(mt * ntiles + nt) * nsplit + ks) * (size_t)(tile_regs(r) * 256);
-    if constexpr (TILE == kLargeTiles) tile_item<2, 7, true>(T, mt, nt, c0, c1, part, lds);
-    else if (r.tm == 5) tile_item<1, 7, false>(T, mt, nt, c0, c1, part, lds);
-    else tile_item<1, 4, false>(T, mt, nt, c0, c1, part, lds);
+    if constexpr (HALF && TILE != kLargeTiles) {
+        if (r.mode == kModeTaps) {
+            if (r.tm == 5) few_item<7>(T, mt, nt, lds);
+            else few_item<4>(T, mt, nt, lds);
+            return;
+        }
+        if (r.mode == 3 && r.sh == 2) {
+            tile_item<true, 1, 4, true, kTilePatch2 / 64>(T, mt, nt, c0, c1, part, lds);
+            return;
+        }
+        if (r.mode == 1) {
+            switch (r.tm) {
+                case 6: one_item<2, 7, true>(T, mt, nt, c0, c1, part, lds); break;
+                case 5: one_item<1, 7, true>(T, mt, nt, c0, c1, part, lds); break;
+                case 2: one_item<2, 4, false>(T, mt, nt, c0, c1, part, lds); break;
+                default: one_item<1, 4, false>(T, mt, nt, c0, c1, part, lds); break;
+            }
+            return;
+        }
+    }
+    if constexpr (TILE == kLargeTiles) tile_item<HALF, 2, 7, true>(T, mt, nt, c0, c1, part, lds);
+    else if (r.tm == 5) tile_item<HALF, 1, 7, false>(T, mt, nt, c0, c1, part, lds);
+    else tile_item<HALF, 1, 4, false>(T, mt, nt, c0, c1, part, lds);
 }
 
 template <bool HALF, int TILE>
@@ -1103,10 +1141,10 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
     const int li = table_find<kMaxGemmLayers>(&tbl->item0[0], item, first);
     const GemmItemRec rec = load_item_rec(tbl, li);
     if constexpr (TILE != kNoTiles) {
-        __shared__ __align__(16) char tile_lds[TILE == kLargeTiles ? 2 * kTileBuffer : kTileBuffer];
+        __shared__ __align__(16) char tile_lds[HALF ? (TILE == kLargeTiles ? 8 * kTilePatch * 16 : 8 * kTilePatch2 * 16) : TILE == kLargeTiles ? 2 * kTileBuffer : kTileBuffer];
         // (every layer of such a launch starts with a workgroup of its own: all four wavefronts come here or none does)
         if (TILE == kLargeTiles || rec.tile) {
-            run_tile_item<TILE>(tbl, rec, (item - first) / kItemWaves, tile_lds);
+            run_tile_item<HALF, TILE>(tbl, rec, (item - first) / kItemWaves, tile_lds);
             return;
         }
     }
@@ -1233,9 +1271,9 @@ __device__ __forceinline__ float4 sum_partials(const float4 *src, const size_t z
 }
 
 // The reduction of a layer whose items are whole workgroups: [tile][range][wavefront][register][lane].
-__device__ __forceinline__ void tile_reduce(const GemmItemTablePtr tbl, const GemmItemRec &r, const int blk) {
+__device__ __forceinline__ void tile_reduce(const GemmItemTablePtr tbl, const GemmItemRec &r, const int blk, const bool half) {
     TileLayer T;
-    load_tile_layer(T, r);
+    load_tile_layer(T, r, half);
     const int regs = tile_regs(r), per_tile = regs * 256;        // a multiple of 1024: a workgroup stays in one tile
     const int wgs = regs >> 2;                                   // workgroups per tile
     const int tile = __builtin_amdgcn_readfirstlane(blk / wgs), e = (blk - tile * wgs) * 1024 + threadIdx.x * 4;
@@ -1245,21 +1283,28 @@ __device__ __forceinline__ void tile_reduce(const GemmItemTablePtr tbl, const Ge
     const int wave = wr / regs, reg = wr - wave * regs;
     const int tm = r.tm & 3, tn = r.tm & 4 ? 7 : 4;
     const int blk16 = reg >> 2, j = reg & 3, m = blk16 / tn, t = blk16 - m * tn;
-    const int ntiles = T.N * T.nth * T.ntw;
+    const bool one = half && r.mode == 1;
+    const int ntiles = one ? one_tiles(T, r) : T.N * T.nth * T.ntw;
     const int mt = __builtin_amdgcn_readfirstlane(tile / ntiles), nt = tile - mt * ntiles;
-    const int rest = __builtin_amdgcn_readfirstlane(nt / T.ntw), img = __builtin_amdgcn_readfirstlane(rest / T.nth);
+    const int rest = one ? 0 : __builtin_amdgcn_readfirstlane(nt / T.ntw), img = one ? 0 : __builtin_amdgcn_readfirstlane(rest / T.nth);
     const TilePos at{img, (rest - img * T.nth) * T.th, (nt - rest * T.ntw) * T.tw, (mt * 4 + wave) * tm};
-    const int k = at.mb0 * 16 + gemm_row(true, tm, m, lane0 >> 4, j), n = t * 16 + (lane0 & 15);
+    const int k = at.mb0 * 16 + gemm_row(!half, tm, m, lane0 >> 4, j), n = t * 16 + (lane0 & 15);
     const bool rok = k < T.K;
     const float bv = T.bias && rok ? T.bias[k] : 0.f;
     const int PQ = T.P * T.Q;
     const SmallDiv by_tw(T.tw);
-    const __amdgpu_buffer_rsrc_t yres = make_rsrc(T.y, (uint32_t)(T.N * T.K) * (uint32_t)PQ * 4u);
+    const uint32_t esz = half ? 2u : 4u;
+    const __amdgpu_buffer_rsrc_t yres = make_rsrc(T.y, (uint32_t)(T.N * T.K) * (uint32_t)PQ * esz);
     const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int pix = tile_out_pixel(T, at, by_tw, n + i);
-        gemm_store(yres, T.relu, false, rok && pix >= 0 ? (uint32_t)((img * T.K + k) * PQ + pix) * 4u : kOobOffset, bv, vv[i]);
+        uint32_t off;
+        if (one) off = one_out_offset(T, nt * (tn * 16) + one_pixel(tn == 7, tn, t, (lane0 & 15) + i));
+        else {
+            const int pix = tile_out_pixel(T, at, by_tw, n + i);
+            off = pix >= 0 ? (uint32_t)(img * T.K * PQ + pix) * esz : kOobOffset;
+        }
+        gemm_store(yres, T.relu, half, rok && off != kOobOffset ? off + (uint32_t)(k * PQ) * esz : kOobOffset, bv, vv[i]);
     }
 }
 
@@ -1272,7 +1317,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmItemTable tb
     const int li = table_find<kMaxGemmLayers>(&tbl->red0[0], b, first);      // the last layer that starts at or before b
     const GemmItemRec rec = load_item_rec(tbl, li);
     if (rec.tile) {
-        tile_reduce(tbl, rec, b - first);
+        tile_reduce(tbl, rec, b - first, tbl->half != 0);
         return;
     }
     GemmItemLayer L;
@@ -1536,15 +1581,17 @@ struct TileShape {
 };
 
 // The fewest tiles of at most bn outputs whose patch fits, then the smallest patch; false if none does.
-static bool plan_tile_shape(const Geo &g, const int bn, TileShape *out) {
+static bool plan_tile_shape(const Geo &g, const int bn, const int patch, TileShape *out) {
     long best = LONG_MAX;
     const int n0 = ceil_div(g.q, bn);
     for (int n = n0; n < n0 + 4 && n <= g.q; ++n) {
-        const int tw = ceil_div(g.q, n), ntw = ceil_div(g.q, tw), pw = tw + 2;
-        const int rows = std::min({g.p, bn / tw, kTilePatch / pw - 2});
+        const int tw = ceil_div(g.q, n), ntw = ceil_div(g.q, tw);
+        const long pw = (long)(tw - 1) * g.sw + g.s;
+        int rows = std::min(g.p, bn / tw);
+        while (rows > 0 && ((rows - 1L) * g.sh + g.r) * pw > patch) --rows;
         if (rows < 1) continue;
         const int nth = ceil_div(g.p, rows), th = ceil_div(g.p, nth);
-        const long key = (long)nth * ntw * 1024 + (th + 2) * pw;
+        const long key = (long)nth * ntw * 4096 + ((th - 1L) * g.sh + g.r) * pw;
         if (key < best && nth < 65536 && ntw < 65536) { best = key; *out = TileShape{th, tw, nth, ntw}; }
     }
     return best != LONG_MAX;
@@ -1564,40 +1611,93 @@ struct ItemPlan {
 // stays small against the whole launch.
 constexpr int kItemSteps = 144;
 
-// Layers that may run in items of whole workgroups: float32, 3x3, stride 1, and sizes that fill most of a tile: 48 input
+// Layers that may run in items of whole workgroups: 3x3, stride 1 (float16: or 2), and sizes that fill most of a tile: 48 input
 // channels (a chunk is 32), 33 output channels (a workgroup takes 64), two thirds of its pixels.
 // (SqueezeNet-shaped stack, the expand layers of 16 and 32 channels in tiles or not: 38.8 / 34.3 us.)
 static bool plan_tile(const Geo &g, ItemPlan *ip) {
-    if (g.dtype != NNV_F32 || g.groups != 1 || g.r != 3 || g.s != 3 || g.sh != 1 || g.sw != 1 || g.ph != g.pw || g.ph >= 65536) return false;
+    if (g.groups != 1 || g.r != 3 || g.s != 3 || g.sh != g.sw || g.ph != g.pw || g.ph >= 65536) return false;
+    if (g.sh != 1 && (g.sh != 2 || g.dtype != NNV_F16)) return false;
     if (g.c < 48 || g.k < 33) return false;
     TileShape wide{}, narrow{};
-    const bool okw = plan_tile_shape(g, 112, &wide), okn = plan_tile_shape(g, 64, &narrow);
+    const bool okw = g.sh == 1 && plan_tile_shape(g, 112, kTilePatch, &wide), okn = plan_tile_shape(g, 64, g.sh == 1 ? kTilePatch : kTilePatch2, &narrow);
     if (!okw && !okn) return false;
     const long nw = okw ? (long)wide.nth * wide.ntw * 7 : LONG_MAX, nn = okn ? (long)narrow.nth * narrow.ntw * 4 : LONG_MAX;
     if (std::min(nw, nn) * 32 > 3L * g.p * g.q + 64) return false;
     ip->tile = 1;
+    ip->mode = 3;
+    ip->tm = 1;
+    const int K16 = ceil_div(g.k, 16);
+    ip->tn = nw <= nn ? 7 : 4;
+    ip->shape = nw <= nn ? wide : narrow;
+    ip->nmt = ceil_div(K16, 4 * ip->tm);
+    ip->ntn = g.n * ip->shape.nth * ip->shape.ntw;
+    return true;
+}
+
+// ... and float16 layers of 1x1 filters, under the same rule (one_item).  128 channels per item unless 64 leave fewer empty.
+static bool plan_one(const Geo &g, ItemPlan *ip) {
+    if (g.dtype != NNV_F16 || g.groups != 1 || g.r != 1 || g.s != 1 || g.sh >= 65536 || g.sw >= 65536 || g.ph >= 65536 || g.pw >= 65536) return false;
+    if (g.c < 48 || g.k < 33) return false;
+    const bool pairs = g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0 && (g.h * g.w) % 2 == 0;
+    const int bn = pairs ? 112 : 64, npix = g.n * g.p * g.q;
+    if (2L * ceil_div(npix, bn) * bn > 3L * npix + 64) return false;
+    const int K16 = ceil_div(g.k, 16);
+    ip->tile = 1;
+    ip->mode = 1;
+    ip->tm = ceil_div(K16, 8) * 8 * 100 <= ceil_div(K16, 4) * 4 * 115 ? 2 : 1;
+    ip->tn = pairs ? 7 : 4;
+    ip->nmt = ceil_div(K16, 4 * ip->tm);
+    ip->ntn = ceil_div(npix, bn);
+    return true;
+}
+
+// ... and float16 layers of up to eight channels (few_item).
+static bool plan_few(const Geo &g, ItemPlan *ip) {
+    if (g.dtype != NNV_F16 || g.groups != 1 || g.c > kTapsMaxChannels || g.r * g.s < 2 || g.sh >= 65536 || g.sw >= 65536 || g.ph >= 65536 || g.pw >= 65536) return false;
+    TileShape wide{}, narrow{};
+    const bool okw = plan_tile_shape(g, 112, kFewPatch, &wide), okn = plan_tile_shape(g, 64, kFewPatch, &narrow);
+    if (!okw && !okn) return false;
+    const long nw = okw ? (long)wide.nth * wide.ntw * 7 : LONG_MAX, nn = okn ? (long)narrow.nth * narrow.ntw * 4 : LONG_MAX;
+    if (std::min(nw, nn) * 32 > 3L * g.p * g.q + 64) return false;
+    ip->tile = 1;
+    ip->mode = kModeTaps;
     ip->tm = 1;
     ip->tn = nw <= nn ? 7 : 4;
     ip->shape = nw <= nn ? wide : narrow;
     ip->nmt = ceil_div(g.k, 64);
     ip->ntn = g.n * ip->shape.nth * ip->shape.ntw;
+    ip->nsplit = 1;
+    ip->steps = ceil_div(g.r * g.s, 4);
     return true;
 }
 
 // ... its channels cut into ranges of about `chunks` chunks of 32
 static void split_tile(const Geo &g, const int chunks, ItemPlan *ip) {
     const int all = ceil_div(g.c, kTileChannels);
-    const int per = ceil_div(all, ceil_div(all, std::min(all, chunks)));
+    const int most = std::min(all, chunks), n = g.dtype == NNV_F16 ? std::max(1, (all + most / 2) / most) : ceil_div(all, most);
+    const int per = ceil_div(all, n);
     ip->nsplit = ceil_div(all, per);
-    ip->steps = all * 9;
+    ip->steps = all * g.r * g.s;
     ip->part_bytes = ip->nsplit > 1 ? (size_t)ip->nmt * ip->ntn * ip->nsplit * (ip->tm * ip->tn * 1024) * sizeof(float) : 0;
 }
 
-static ItemPlan plan_items(const Geo &g, const ItemTarget target_len) {
+// The layer in items of whole workgroups, before its channels are cut (tile = 0: it has none).
+static ItemPlan plan_whole(const Geo &g) {
     ItemPlan ip{};
-    if (target_len.chunks > 0 && plan_tile(g, &ip)) {
-        split_tile(g, target_len.chunks, &ip);
-        return ip;
+    if (!plan_tile(g, &ip) && !plan_one(g, &ip)) plan_few(g, &ip);
+    return ip;
+}
+
+// whole: plan_whole(g), which a caller that plans a layer several times keeps.
+static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const ItemPlan *whole = nullptr) {
+    ItemPlan ip{};
+    if (target_len.chunks > 0 || target_len.few) {
+        ip = whole ? *whole : plan_whole(g);
+        if (ip.tile && (ip.mode == kModeTaps ? target_len.few : target_len.chunks > 0)) {
+            if (ip.mode != kModeTaps) split_tile(g, ip.mode == 1 ? 4 * target_len.chunks : target_len.chunks, &ip);
+            return ip;
+        }
+        ip = ItemPlan{};
     }
     const GemmPlan pl = plan_im2col(g);
     const bool half = g.dtype == NNV_F16;
@@ -1666,21 +1766,37 @@ constexpr int kItemsResident = 256 * 3 * kItemWaves;
 // 220 keep to single-wavefront items.  Measured over 30 launches of six stacks at batch 1-4 and 128-320 pixels, us at 1 / 2 / 4 / 8
 // chunks against none: W = 232 (AlexNet-shaped) 34 / 33 / 41 / 65 against 45, 803 (ResNet-18) 55 / 46 / 49 / 76 against 53, 1585 88 / 78 / 70 / 86
 // against 93, 3136 160 / 126 / 117 / 110 against 151, 7488 (VGG-16) 253 / 193 / 172 / 165 against 279; W = 154 (GoogLeNet, 128 x 160) 68 against 53.
+// float16, W in chunks of 3x3 filters of 64 x 112 outputs, four chunks of 1x1 filters to one: below 600 single-wavefront items; else the channels stay whole
+// if no layer has more than 12 chunks (48 of 1x1 filters), since partial tiles and the launch that adds them cost 6 us, and otherwise a range is W / 330 chunks, at
+// least four: an item of 512 channels takes 24 us.  us a call at 0 / 4 / 8 / 12 or more chunks, none longer than 12: W = 662 (AlexNet-shaped, 2x211x317) 25 / 29 / 29 / 23, 1273
+// (GoogLeNet, 3x210x173) 64 / 66 / 58 / 58, 1380 (MobileNetV1, 3x273x258) 48 / 39 / 35 / 35; longer: 983 (ResNet-18) 38 / 23 / 31 / 31, 1381 (ResNet-18, 295x215) 38 / 27 / 30 / 37, 3374
+// (ResNet-50, 301x227) 72 / 60 / 55 / 63, 5085 (ResNet-50, 2x217x257) 103 / 85 / 74 / 69, 7488 (VGG-16) 92 / 80 / 69 / 59; W = 197 (SqueezeNet, 2x132x119) 16 / 22 / 22 / 22.
+// Layers of few channels are items of workgroups where that saves the launch that copies x, not beside other copies (MobileNetV2-shaped plan 50 / 44;
+// ResNet-18 at 4x108x114, whose last layers keep their copy, 30 / 36).
 ItemTarget im2col_items_target(int n, const Geo *geos) {
-    ItemTarget target{kItemSteps, 0};
-    if (geos[0].dtype == NNV_F32) {
-        long w = 0;
-        for (int i = 0; i < n; ++i) {
-            ItemPlan ip{};
-            if (plan_tile(geos[i], &ip)) w += (long)ip.nmt * ip.ntn * ip.tn * ceil_div(geos[i].c, kTileChannels);
-        }
-        w /= 7;
-        if (w >= 220) target.chunks = std::max(2, (int)std::min((w + 449) / 450, 65536L));
+    ItemTarget target{kItemSteps, 0, false};
+    ItemPlan whole[kMaxGemmLayers];
+    long w = 0;                      // in chunks of 1x1 filters of 64 x 16 outputs
+    int longest_whole = 0;           // reduction, in chunks of 1x1 filters
+    for (int i = 0; i < n; ++i) {
+        whole[i] = plan_whole(geos[i]);
+        if (!whole[i].tile || whole[i].mode == kModeTaps) continue;
+        const int chunks = ceil_div(geos[i].c, kTileChannels) * (whole[i].mode == 3 ? 4 : 1);
+        w += (long)whole[i].nmt * whole[i].ntn * whole[i].tn * chunks;
+        longest_whole = std::max(longest_whole, chunks);
     }
+    w /= 28;
+    if (geos[0].dtype == NNV_F16) {
+        if (w >= 600) target.chunks = longest_whole <= 48 ? 12 : (int)std::min(std::max(4L, w / 330), 65536L);
+        // (decided last: plans without `few` first)
+        bool copies = false;
+        for (int i = 0; i < n && !copies; ++i) copies = whole[i].mode != kModeTaps && plan_items(geos[i], target, &whole[i]).xt_bytes > 0;
+        target.few = !copies;
+    } else if (w >= 220) target.chunks = std::max(2, (int)std::min((w + 449) / 450, 65536L));
     auto total_at = [&](int t) {
         long tot = 0;
         for (int i = 0; i < n; ++i) {
-            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks});
+            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks, target.few}, &whole[i]);
             tot += (long)p.nmt * p.ntn * p.nsplit * (p.tile ? kItemWaves : 1);
         }
         return tot;
@@ -1703,7 +1819,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     double share = 0;                   // in steps of a panel
     int longest[5] = {0, 0, 0, 0, 0};   // steps of the longest reduction among the layers of 1, 2 and 4 panels per tile
     for (int i = 0; i < n; ++i) {
-        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks});
+        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks, false}, &whole[i]);
         if (p.tile) continue;
         share += (double)p.nmt * p.ntn * p.steps * p.tm / 1024;
         longest[p.tm] = std::max(longest[p.tm], p.steps);
@@ -1718,7 +1834,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
 // number of ranges in 16 (channels and images are below 2^16 everywhere).  Only a stride or a pad of 2^16
 // and more does not fit: such a layer is launched by itself.
 bool im2col_items_supported(const Geo &g) {
-    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0}).nsplit < 65536;
+    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0, false}).nsplit < 65536;
 }
 
 size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target) {
@@ -1741,13 +1857,14 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
         tiles = tiles || plans[i].tile;
     }
     // 128 x 112 outputs per workgroup: planned for single layers only, and that kernel runs no other items
-    const bool large = n == 1 && plans[0].tile && plans[0].tm == 2;
+    const bool large = n == 1 && plans[0].tile && plans[0].mode == 3 && plans[0].tm == 2;
     auto item_len = [&](int i) {
         const ItemPlan &p = plans[i];
         // float16: a step that gathers pixels from NCHW takes about four times as long as one that reads octets, one that reads pairs half as
         // long again (ResNet-50-shaped stack, in that order or by steps alone: 54 / 59 us)
         const long cost = !half ? 1 : p.mode == 1 ? 16 : p.mode == kModePairs ? 6 : 4;
         const long len = (long)ceil_div(p.steps, p.nsplit) * p.tm * cost;
+        if (p.tile && half) return (long)ceil_div(p.steps, p.nsplit) * (p.mode == 1 ? 2 : 1) << 20;
         return p.tile ? (len * p.tn) << 20 : len;
     };
     std::stable_sort(order, order + n, [&](int a, int b) { return item_len(a) > item_len(b); });
@@ -1791,8 +1908,11 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
         if (ip.tile) {
             L.tile = 1;
             L.tm = ip.tm + (ip.tn == 7 ? 4 : 0);
-            L.S = (uint8_t)ip.shape.th; L.groups = (uint8_t)ip.shape.tw;
-            L.sw = (uint16_t)ip.shape.ntw; L.pw = (uint16_t)ip.shape.nth;
+            if (ip.mode == kModeTaps) L.part256 = (uint32_t)(ip.shape.th + ip.shape.tw * 256);
+            else if (ip.mode == 3) {
+                L.S = (uint8_t)ip.shape.th; L.groups = (uint8_t)ip.shape.tw;
+                L.sw = (uint16_t)ip.shape.ntw; L.pw = (uint16_t)ip.shape.nth;
+            }
             items += count * kItemWaves;
             if (ip.nsplit > 1) red += ip.nmt * ip.ntn * (ip.tm * ip.tn);
         } else {
@@ -1812,7 +1932,9 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     }
     const int wgs = ceil_div(items, kItemWaves);
     const int per_xcd = ceil_div(ceil_div(wgs, tbl.group), 8) * tbl.group;
-    if (half) hipLaunchKernelGGL((gemm_items_kernel<true, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    if (half && large) hipLaunchKernelGGL((gemm_items_kernel<true, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (half && tiles) hipLaunchKernelGGL((gemm_items_kernel<true, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (half) hipLaunchKernelGGL((gemm_items_kernel<true, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (large) hipLaunchKernelGGL((gemm_items_kernel<false, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (tiles) hipLaunchKernelGGL((gemm_items_kernel<false, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else hipLaunchKernelGGL((gemm_items_kernel<false, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
@@ -1835,15 +1957,25 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
     return launch_planned(n, geos, plans, x, w, bias, y, ws, st);
 }
 
-// A single layer in items of whole workgroups, its channels not split: from 200 items on (below, a CU's one item takes its whole
+// A single layer in items of whole workgroups, its channels not split.  float32: from 200 items on (below, a CU's one item takes its whole
 // channel loop at the pace of one wavefront per SIMD).  Measured, us, without / with: 224 items 44.6 / 29.9 (128 channels at 112x112) and
 // 156 / 101 (512 at 4x28x28), 448 items 44.5 / 35 (64 at 224x224); 112 items 44 / 54 (256 at 56x56), 128 80 / 102 (512 at 8x14x14).
 // 128 x 112 outputs with two buffers in LDS where that leaves 260 items: 256 at 8x56x56 154 / 138, 2 x 96 -> 200 at 80x90 45 / 40; with 112
 // of them 101 / 138 (512 at 4x28x28).
+// float16, in items of 64 output channels: 3x3 from 100 on (us without / with, items: 256 at 8x56x56, 896: 76 / 39; 512 at 4x28x28, 224: 66 / 27; 64 at
+// 4x56x56, 112: 10.2 / 8.3; stride 2, 64 at 112x112 -> 128, 100: 8.6 / 8.3; below: 96 at 56x56 -> 160, 84: 10.0 / 9.8; 128 at 56x56, 56: 10.3 / 12.7), 1x1
+// from 340 on (512 at 8x56x56 / 2 -> 512, 784: 32 / 16; 64 at 4x56x56 -> 256, 448: 11.3 / 8.6; 300 at 4x33x33, 345: 12.0 / 10.2; below: 500 -> 100 at 100x100, 180:
+// 15.2 / 15.8), few channels from 200 on if one row of tiles holds all 33 to 64 panels' channels (3x3 at 224x224 -> 64, 448: 10.3 / 8.3; 7x7 / 2 there, 112: 8.1 /
+// 8.6; 5x5 -> 200: 17.8 / 20.1).  3x3 with 128 x 112 outputs where those of 64 would be at most one to a CU (512 at 4x28x28 32 -> 27,
+// 128 at 112x112 12.7 -> 10.8; 128 at 5x56x56, 280: 14.1 against 16.4, 256 at 8x56x56 39 against 48: two wavefronts per SIMD, not three).
 static bool plan_tile_single(const Geo &g, ItemPlan *ip) {
-    if (!plan_tile(g, ip) || (long)ip->nmt * ip->ntn < 200) return false;
     const int K16 = ceil_div(g.k, 16), nmt = ceil_div(K16, 8);
-    if (ip->tn == 7 && (long)nmt * ip->ntn >= 260 && nmt * 8 * 100 <= ceil_div(K16, 4) * 4 * 115) {
+    const bool fits = nmt * 8 * 100 <= ceil_div(K16, 4) * 4 * 115;       // 128 channels per item leave no more empty than 64
+    if (plan_few(g, ip)) return g.k > 32 && g.k <= 64 && ip->ntn >= 200;
+    if (!plan_tile(g, ip) && !plan_one(g, ip)) return false;
+    const long items = (long)ip->nmt * ip->ntn * ip->tm;
+    if (items < (g.dtype == NNV_F32 ? 200 : ip->mode == 3 ? 100 : 340)) return false;
+    if (fits && ip->mode == 3 && ip->tn == 7 && (g.dtype == NNV_F32 ? (long)nmt * ip->ntn >= 260 : items <= 256)) {
         ip->tm = 2;
         ip->nmt = nmt;
     }

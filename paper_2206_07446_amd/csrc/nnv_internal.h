@@ -89,8 +89,9 @@ hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float
 // layer i's own region of im2col_items_workspace_bytes(geos[i], im2col_items_target(n, geos)) bytes.
 constexpr int kMaxGemmLayers = 56;
 bool im2col_items_supported(const Geo &g);
-// Length of the items of a launch: k-steps of a single-wavefront item, chunks of channels of a whole workgroup's (0: none of these).
-struct ItemTarget { int steps, chunks; };
+// Length of the items of a launch: k-steps of a single-wavefront item, chunks of 32 channels of a whole workgroup's (0: none of these); few: float16
+// layers of few channels in items of workgroups.
+struct ItemTarget { int steps, chunks; bool few; };
 ItemTarget im2col_items_target(int n, const Geo *geos);
 size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target);
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w,
