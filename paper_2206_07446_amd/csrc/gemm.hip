@@ -1156,6 +1156,7 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
     if (L.tm == 4) {
         if constexpr (!HALF) {
             if (L.mode == 3) gemm_item<false, 4, 3, NBUF>(L, local, lane);
+            else if (L.mode == 7) gemm_item<false, 4, 7, NBUF>(L, local, lane);
             else gemm_item<false, 4, 1, NBUF>(L, local, lane);
         } else {
             if (L.mode == kModePairs) gemm_item<true, 4, kModePairs>(L, local, lane);
@@ -1720,6 +1721,8 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Item
         ip.xt_bytes = align_up((size_t)g.n * g.h * g.w * copy_channels(g, ip.mode) * sizeof(__half), 256);
     }
     if (pl.mode == kModeTaps && (kg16 % 4 == 0 || kg16 >= 12)) ip.tm = 4;
+    // float32 7x7: four where the launch wants them (im2col_items_target)
+    if (target_len.wide && !half && g.groups == 1 && pl.mode == 7 && kg16 % 4 == 0) ip.tm = 4;
     ip.nmt = ceil_div(K16, ip.tm);
     ip.ntn = ceil_div(ceil_div(g.n * g.p * g.q, 16), 2);
     const int cblocks = half ? ceil_div(g.cg, 32) : ceil_div(g.cg, 4);
@@ -1774,7 +1777,7 @@ constexpr int kItemsResident = 256 * 3 * kItemWaves;
 // Layers of few channels are items of workgroups where that saves the launch that copies x, not beside other copies (MobileNetV2-shaped plan 50 / 44;
 // ResNet-18 at 4x108x114, whose last layers keep their copy, 30 / 36).
 ItemTarget im2col_items_target(int n, const Geo *geos) {
-    ItemTarget target{kItemSteps, 0, false};
+    ItemTarget target{kItemSteps, 0, false, false};
     ItemPlan whole[kMaxGemmLayers];
     long w = 0;                      // in chunks of 1x1 filters of 64 x 16 outputs
     int longest_whole = 0;           // reduction, in chunks of 1x1 filters
@@ -1796,7 +1799,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     auto total_at = [&](int t) {
         long tot = 0;
         for (int i = 0; i < n; ++i) {
-            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks, target.few}, &whole[i]);
+            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks, target.few, target.wide}, &whole[i]);
             tot += (long)p.nmt * p.ntn * p.nsplit * (p.tile ? kItemWaves : 1);
         }
         return tot;
@@ -1819,7 +1822,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     double share = 0;                   // in steps of a panel
     int longest[5] = {0, 0, 0, 0, 0};   // steps of the longest reduction among the layers of 1, 2 and 4 panels per tile
     for (int i = 0; i < n; ++i) {
-        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks, false}, &whole[i]);
+        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks, false, target.wide}, &whole[i]);
         if (p.tile) continue;
         share += (double)p.nmt * p.ntn * p.steps * p.tm / 1024;
         longest[p.tm] = std::max(longest[p.tm], p.steps);
@@ -1827,6 +1830,12 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     for (int tm : {1, 2, 4})
         if ((double)longest[tm] * tm > share)
             while (target.steps > kItemStepsMin && target.steps * (tm == 4 ? 0.75 : 1.0) * tm > share) target.steps -= 12;
+    // Launches of between one and one and a half times the items that are resident at once end with a round that fills the chip in part: there the
+    // 7x7 layers, whose items are many and bound by their gathers of pixels, take four panels per tile (half the items and gathers).  us a call without / with, items:
+    // ResNet-18-shaped stack 48.7 / 45.6 (224x224, 3344), 52.0 / 48.1 (180x256, 3660), 57.1 / 53.2 (2x150x150, 3660), 61.7 / 62.8 (260x270, 3786), GoogLeNet 88.2 / 86.5
+    // (300x280, 3963); outside: ResNet-50 70 / 74 (150x190, 5537), ResNet-18 36.4 / 39.8 (120x110, 2414).
+    const long items = total_at(target.steps);
+    target.wide = items > kItemsResident && items <= kItemsResident * 3L / 2;
     return target;
 }
 
@@ -1834,7 +1843,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
 // number of ranges in 16 (channels and images are below 2^16 everywhere).  Only a stride or a pad of 2^16
 // and more does not fit: such a layer is launched by itself.
 bool im2col_items_supported(const Geo &g) {
-    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0, false}).nsplit < 65536;
+    return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0, false, false}).nsplit < 65536;
 }
 
 size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target) {

@@ -90,8 +90,8 @@ hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float
 constexpr int kMaxGemmLayers = 56;
 bool im2col_items_supported(const Geo &g);
 // Length of the items of a launch: k-steps of a single-wavefront item, chunks of 32 channels of a whole workgroup's (0: none of these); few: float16
-// layers of few channels in items of workgroups.
-struct ItemTarget { int steps, chunks; bool few; };
+// layers of few channels in items of workgroups; wide: float32 7x7 layers with four panels per tile.
+struct ItemTarget { int steps, chunks; bool few, wide; };
 ItemTarget im2col_items_target(int n, const Geo *geos);
 size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target);
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w,

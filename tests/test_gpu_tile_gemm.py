@@ -63,6 +63,15 @@ def test_grouped_ranges(env):
     run_grouped(nnv, torch, [Case(nnv, torch, l, nnv.IM2COL_GEMM, False, 60 + i, bias=i % 2 == 0) for i, l in enumerate(layers)])
 
 
+@pytest.mark.parametrize("ks", [(64, 64, 64, 64), (64, 128, 64), (192, 64, 48)])
+def test_wide_7x7(env, ks):
+    """7x7 layers in a launch of one to one and a half times as many items as are resident at once: four panels per tile."""
+    nnv, torch = env
+    layers = [ConvLayer(f"w{i}", (3, 5, 4, 3)[i], (224, 201, 223, 224)[i], (224, 230, 225, 224)[i], k, 7, 7, 2, (3, 0, 3, 2)[i]) for i, k in enumerate(ks)]
+    layers += [Ly(32, 14, 14, 64), ConvLayer("pw", 96, 14, 14, 64, 1, 1, 1, 0)]
+    run_grouped(nnv, torch, [Case(nnv, torch, l, nnv.IM2COL_GEMM, False, 80 + i, bias=i % 2 == 0) for i, l in enumerate(layers)], big=True)
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.395e38, 1e-38])
 @pytest.mark.parametrize("grouped", [False, True])
 def test_values_beyond_bfloat16(env, value, grouped):
