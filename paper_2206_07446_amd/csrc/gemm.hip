@@ -1192,18 +1192,18 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
 // saves: a batch-1 layer leaves most of the chip idle for most of its 8-16 us.  Workgroups of eight wavefronts hold 8 / KS tiles, or one
 // of KS = 16, whose wavefronts then take two ranges each.  Every layer's blocks are a multiple of eight, so that the XCD of a
 // block does not depend on what else is in the launch.  Measured, us a cold pass of a stack (batch 1, 224 x 224), one launch a layer ->
-// this: ResNet-18-shaped 206 -> 127, ResNet-50 463 -> 320, GoogLeNet 362 -> 99, SqueezeNet 151 -> 59, AlexNet 76 -> 57; MobileNetV2 (a chain)
-// 224 -> 224.  Two workgroups per CU at 87 registers; held to 80 for a third one it takes as long.
+// this: ResNet-18-shaped 206 -> 126, ResNet-50 463 -> 318, GoogLeNet 362 -> 94, SqueezeNet 151 -> 53, AlexNet 76 -> 57; MobileNetV2 (a chain)
+// 224 -> 221.  Two workgroups per CU; with fewer registers, for a third one, it takes as long.
 constexpr int kLayerWaves = 8;      // 1 << 3
 struct GemmLayersTable {
     GemmParams g[kMaxMergedLayers];           // grid_nx, grid_ny: workgroups along the pixels, tiles along the panels
     int block0[kMaxMergedLayers];             // first workgroup of each layer, INT_MAX beyond the last one
-    uint8_t variant[kMaxMergedLayers];        // mode + 8 if a tile has two panels
+    uint8_t variant[kMaxMergedLayers];        // mode + 8 if a tile has two panels, + 16 if two blocks of pixels
 };
 static_assert(sizeof(GemmLayersTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) GemmLayersTable *GemmLayersTablePtr;
 
-template <int TM, int MODE, int NBUF>
+template <int TM, int TN, int MODE>
 __device__ __forceinline__ void gemm_layer_block(const GemmParams &g, const int blk, float *red) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1212,16 +1212,16 @@ __device__ __forceinline__ void gemm_layer_block(const GemmParams &g, const int 
     const int total = g.grid_nx * g.grid_ny, per = (total + 7) >> 3, ltile = (blk & 7) * per + (blk >> 3);
     if (ltile >= total) return;                            // whole workgroup: padding
     const int div = g.m_major ? g.grid_nx : g.grid_ny, hi = __builtin_amdgcn_readfirstlane(ltile / div), lo = ltile - hi * div;
-    const int mb0 = (g.m_major ? hi : lo) * TM, nb0 = (g.m_major ? lo : hi) * tiles + nt;
-    floatx4 acc[TM][1];
-    PixState<1> px;
+    const int mb0 = (g.m_major ? hi : lo) * TM, nb0 = ((g.m_major ? lo : hi) * tiles + nt) * TN;
+    floatx4 acc[TM][TN];
+    PixState<TN> px;
 #pragma nounroll
     for (int z = ks; z < KS; z += per_tile) {
-        if constexpr (MODE == 3) gemm_accumulate_3x3<TM, 1>(g, mb0, nb0, z, KS, lane, acc, px);
-        else gemm_accumulate<false, TM, 1, MODE, NBUF>(g, mb0, nb0, z, KS, lane, acc, px);
-        gemm_put_partial<TM, 1>(acc, red, KS, nt * KS + z, lane);
+        if constexpr (MODE == 3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, z, KS, lane, acc, px);
+        else gemm_accumulate<false, TM, TN, MODE, 2>(g, mb0, nb0, z, KS, lane, acc, px);
+        gemm_put_partial<TM, TN>(acc, red, KS, nt * KS + z, lane);
     }
-    gemm_finish<TM, 1, MODE == 3>(g, mb0, KS, ks, per_tile, nt, lane, acc, px, red);
+    gemm_finish<TM, TN, MODE == 3>(g, mb0, KS, ks, per_tile, nt, lane, acc, px, red);
 }
 
 __global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const GemmLayersTable tbl_arg) {
@@ -1239,18 +1239,19 @@ __global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const 
         __builtin_memcpy(&g, d, sizeof g);
     }
     const int blk = (int)blockIdx.x - first;
+#define NNV_LAYER_BLOCK(V, TM, TN)                                     \
+    case V + 1: gemm_layer_block<TM, TN, 1>(g, blk, red); break;       \
+    case V + 3: gemm_layer_block<TM, TN, 3>(g, blk, red); break;       \
+    case V + 5: gemm_layer_block<TM, TN, 5>(g, blk, red); break;       \
+    case V + 7: gemm_layer_block<TM, TN, 7>(g, blk, red); break;       \
+    case V: gemm_layer_block<TM, TN, 0>(g, blk, red); break;
     switch (tbl->variant[li]) {
-        case 1: gemm_layer_block<1, 1, 2>(g, blk, red); break;
-        case 3: gemm_layer_block<1, 3, 2>(g, blk, red); break;
-        case 5: gemm_layer_block<1, 5, 2>(g, blk, red); break;
-        case 7: gemm_layer_block<1, 7, 2>(g, blk, red); break;
-        case 0: gemm_layer_block<1, 0, 2>(g, blk, red); break;
-        case 9: gemm_layer_block<2, 1, 2>(g, blk, red); break;
-        case 11: gemm_layer_block<2, 3, 2>(g, blk, red); break;
-        case 13: gemm_layer_block<2, 5, 2>(g, blk, red); break;
-        case 15: gemm_layer_block<2, 7, 2>(g, blk, red); break;
-        default: gemm_layer_block<2, 0, 2>(g, blk, red); break;
+        NNV_LAYER_BLOCK(0, 1, 1)
+        NNV_LAYER_BLOCK(8, 2, 1)
+        NNV_LAYER_BLOCK(16, 1, 2)
+        NNV_LAYER_BLOCK(24, 2, 2)
     }
+#undef NNV_LAYER_BLOCK
 }
 
 __device__ static inline int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
@@ -2014,17 +2015,28 @@ hipError_t launch_im2col_layers(int n, const Geo *geos, const void *const *x, co
     }
     std::stable_sort(order, order + n, [&](int a, int b) { return work[a] > work[b]; });
     GemmLayersTable tbl{};
+    auto blocks_of = [&](int i, int tn) {
+        const int tiles = ceil_div(ceil_div(geos[i].n * geos[i].p * geos[i].q, 16 * tn), kLayerWaves >> std::min(plans[i].ks_shift, 3));
+        return (long)xcd_grid(tiles * ceil_div(geos[i].groups * ceil_div(geos[i].kg, 16), plans[i].tm));
+    };
     long blocks = 0;
+    for (int i = 0; i < n; ++i) blocks += blocks_of(i, 1);
+    // More workgroups than twice what is resident at once: two blocks of pixels per tile (a load of weights feeds twice the products; the sums are
+    // the same).  us a cold pass, one block / two: SqueezeNet-shaped stack 58.1 / 52.9, GoogLeNet 98.5 / 94.1 (levels of 1800 to 3300 workgroups); in launches of 700 to 1000 it
+    // leaves SIMDs idle: ResNet-18 126 / 139.
+    const bool wide = blocks > 4 * 256;
+    blocks = 0;
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
         const GemmPlan &pl = plans[i];
         GemmParams &gp = tbl.g[o];
         gp = gemm_params(geos[i], pl.mode, x[i], w[i], nullptr, y[i]);
         gp.ks_shift = pl.ks_shift;
-        gp.grid_nx = ceil_div(ceil_div(gp.npix, 16), kLayerWaves >> std::min(pl.ks_shift, 3));
+        const int tn = wide && pl.ks_shift <= 3 ? 2 : 1;         // (KS = 16: the partial tiles would not fit)
+        gp.grid_nx = ceil_div(ceil_div(gp.npix, 16 * tn), kLayerWaves >> std::min(pl.ks_shift, 3));
         gp.grid_ny = ceil_div(gp.K16, pl.tm);
         gp.m_major = gp.w_bytes >= gp.x_bytes;
-        tbl.variant[o] = (uint8_t)(pl.mode + (pl.tm == 2 ? 8 : 0));
+        tbl.variant[o] = (uint8_t)(pl.mode + (pl.tm == 2 ? 8 : 0) + (tn == 2 ? 16 : 0));
         tbl.block0[o] = (int)blocks;
         blocks += xcd_grid(gp.grid_nx * gp.grid_ny);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;

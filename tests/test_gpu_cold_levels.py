@@ -64,6 +64,23 @@ def test_independent_layers(env, stage):
         assert (b[-128:] == 7.0).all(), f"{l}: write past y"
 
 
+@pytest.mark.parametrize("copies", [1, 4])
+def test_launch_of_many_workgroups(env, copies):
+    """Few workgroups, and more than twice what is resident at once, which take two blocks of pixels per tile: odd numbers of
+    blocks, ragged last ones, every chunking mode."""
+    nnv, torch = env
+    layers = [Ly(64, 56, 64), Ly(96, 55, 96, 1), Ly(32, 57, 48, 5), Ly(3, 111, 64, 7, 2), Ly(20, 56, 40, 4, 1, 2), Ly(128, 33, 200, n=2, w=31)] * copies
+    kinds = [nnv.IM2COL_GEMM] * len(layers)
+    descs, raw, xs, wt, ws = tensors(nnv, torch, layers, kinds)
+    ys = [[torch.full((l.n * l.k * l.p * l.q + 128,), 7.0, device="cuda") for l in layers] for _ in range(2)]
+    one_by_one(nnv, torch, descs, kinds, raw, wt, xs, ys[0], ws)
+    nnv.nnv_cold_stack(descs, kinds, raw, wt, xs, ys[1], ws, 0)
+    torch.cuda.synchronize()
+    for l, a, b in zip(layers, *ys):
+        assert torch.equal(a, b), l
+        assert (b[-128:] == 7.0).all(), f"{l}: write past y"
+
+
 def build_shared(torch, how, layers, xs):
     """Inputs and outputs of a list of 32-channel 14x14 layers that share memory in the given way."""
     n = layers[0].c * layers[0].h * layers[0].w
