@@ -14,6 +14,7 @@
 //   16-byte loads.  For 1x1 filters (most layers of the bottleneck and inverted-residual
 //   networks) that copy would cost a launch of its own, as long as the layer itself: there a
 //   lane gathers its 8 channels straight from NCHW with eight 2-byte loads per fragment.
+//   Layers large enough to fill workgroups (and float32 3x3 ones) run in items that share pixels through LDS instead (tile_gemm.h).
 //
 // Batch-1 layers put one or two wavefronts on a SIMD, and a lone wavefront issues one
 // instruction every four cycles: the k-loop must be almost nothing but loads and MFMAs.
@@ -1755,7 +1756,7 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Item
 // otherwise), and a float16 step moves eight times the channels of a float32 one.  Measured (us, one
 // call, items of 36 / 48 / 144 steps): ResNet-18-shaped stack 48.2 / 48.3 / 62.7, AlexNet 26.6 / 27.2 / 36.5,
 // GoogLeNet 60.2 / 55.8 / 56.0, SqueezeNet 43.7 / 43.5 / 43.8; above the line (10840 items of 144 steps or
-// more) ResNet-50 78.7 / 77.7 / 77.0 and VGG-16 179 / 178 / 162.
+// more) ResNet-50 78.7 / 77.7 / 77.0 and VGG-16 179 / 178 / 162 (all of them before 3x3 and 1x1 layers ran in items of workgroups).
 // float32: a launch whose items all fit the chip at once (kItemsResident, less a sixteenth: a launch
 // that fills every slot was measured slower than one that leaves a few free) takes the shortest
 // item length, in steps of 12 down to kItemStepsMin, with which they still do: the launch lasts as
@@ -1871,7 +1872,7 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     auto item_len = [&](int i) {
         const ItemPlan &p = plans[i];
         // float16: a step that gathers pixels from NCHW takes about four times as long as one that reads octets, one that reads pairs half as
-        // long again (ResNet-50-shaped stack, in that order or by steps alone: 54 / 59 us)
+        // long again (ResNet-50-shaped stack without items of workgroups, in that order or by steps alone: 54 / 59 us)
         const long cost = !half ? 1 : p.mode == 1 ? 16 : p.mode == kModePairs ? 6 : 4;
         const long len = (long)ceil_div(p.steps, p.nsplit) * p.tm * cost;
         if (p.tile && half) return (long)ceil_div(p.steps, p.nsplit) * (p.mode == 1 ? 2 : 1) << 20;
