@@ -32,13 +32,13 @@ VALU_F32_PEAK_TFLOPS = 157.3  # float32 vector peak of the data sheet (loops of 
 # the digest below; once a source file changes, `traffic` is reported as null until the counters
 # are taken again.
 MEASURED_TRAFFIC = {
-    "csrc_sha256_16": "bc5d856573856346",
+    "csrc_sha256_16": "72623ec81fc30426",
     "MB_per_step": {
         "transform": (44.9, 262.9),
-        "direct": (77.7, 10.2),
-        "im2col_gemm": (97.5, 23.0),
+        "direct": (77.6, 10.2),
+        "im2col_gemm": (94.2, 23.2),
         "wino_f2": (132.8, 51.0),
-        "wino_f4": (211.6, 38.5),
+        "wino_f4": (210.9, 38.5),
     },
 }
 
@@ -47,7 +47,7 @@ KIND_LABEL = {0: "direct", 1: "im2col_gemm", 2: "wino_f2", 3: "wino_f4", 4: "dep
 PHASE_KERNELS = {
     "transform": "transform_kernel (grouped weight transformation, all kinds)",
     "direct": "direct_conv_many_klane_kernel<float> (direct convolution of all layers in one launch, lanes along the output channels, vector ALU)",
-    "im2col_gemm": "gemm_items_kernel + gemm_reduce_kernel (implicit GEMM work items of all layers, float32 MFMA)",
+    "im2col_gemm": "gemm_items_kernel + gemm_reduce_kernel (implicit GEMM work items of all layers, float32 MFMA; 3x3 stride-1 layers bfloat16 MFMA, three parts per float32)",
     "wino_f2": "wino_f2: wino_input_many + wino_gemm_many (float32 MFMA) + wino_output_many",
     "wino_f4": "wino_f4: wino_input_many + wino_gemm_many (float32 MFMA) + wino_output_many",
 }
