@@ -374,11 +374,12 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
         if (b.cls != GroupedPlan::GEMM_ITEMS) continue;
         std::vector<Geo> bg;
         for (int i : b.layers) bg.push_back(geos[i]);
-        const ItemTarget target = im2col_items_target((int)bg.size(), bg.data());
+        std::vector<size_t> bytes(bg.size());
+        im2col_items_workspace_bytes((int)bg.size(), bg.data(), bytes.data());
         size_t off = 0;
         for (size_t j = 0; j < b.layers.size(); ++j) {
             b.offset[j] = off;
-            off += align_up(im2col_items_workspace_bytes(bg[j], target), 256);
+            off += align_up(bytes[j], 256);
         }
         gp.bytes = std::max(gp.bytes, off);
     }

@@ -1593,12 +1593,18 @@ static bool plan_tile_shape(const Geo &g, const int bn, const int patch, TileSha
         int rows = std::min(g.p, bn / tw);
         while (rows > 0 && ((rows - 1L) * g.sh + g.r) * pw > patch) --rows;
         if (rows < 1) continue;
-        const int nth = ceil_div(g.p, rows), th = ceil_div(g.p, nth);
+        const int nth = ceil_div(g.p, rows);
+        if ((long)nth * ntw * 4096 >= best) continue;
+        const int th = ceil_div(g.p, nth);
         const long key = (long)nth * ntw * 4096 + ((th - 1L) * g.sh + g.r) * pw;
         if (key < best && nth < 65536 && ntw < 65536) { best = key; *out = TileShape{th, tw, nth, ntw}; }
     }
     return best != LONG_MAX;
 }
+
+// Length of the items of a launch: k-steps of a single-wavefront item, chunks of 32 channels of a whole workgroup's (0: none of these); few: float16
+// layers of few channels in items of workgroups; wide: float32 7x7 layers with four panels per tile.
+struct ItemTarget { int steps, chunks; bool few, wide; };
 
 struct ItemPlan {
     int mode, tm, nmt, ntn, nsplit;
@@ -1691,18 +1697,23 @@ static ItemPlan plan_whole(const Geo &g) {
     return ip;
 }
 
-// whole: plan_whole(g), which a caller that plans a layer several times keeps.
-static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const ItemPlan *whole = nullptr) {
+// What does not depend on the target, for callers that plan a layer several times.
+struct LayerPlan {
+    ItemPlan whole;
+    GemmPlan gemm;
+};
+
+static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const LayerPlan *known = nullptr) {
     ItemPlan ip{};
     if (target_len.chunks > 0 || target_len.few) {
-        ip = whole ? *whole : plan_whole(g);
+        ip = known ? known->whole : plan_whole(g);
         if (ip.tile && (ip.mode == kModeTaps ? target_len.few : target_len.chunks > 0)) {
             if (ip.mode != kModeTaps) split_tile(g, ip.mode == 1 ? 4 * target_len.chunks : target_len.chunks, &ip);
             return ip;
         }
         ip = ItemPlan{};
     }
-    const GemmPlan pl = plan_im2col(g);
+    const GemmPlan pl = known ? known->gemm : plan_im2col(g);
     const bool half = g.dtype == NNV_F16;
     ip.mode = pl.mode;
     ip.xt_bytes = pl.xt_bytes;
@@ -1723,7 +1734,7 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Item
         ip.xt_bytes = align_up((size_t)g.n * g.h * g.w * copy_channels(g, ip.mode) * sizeof(__half), 256);
     }
     if (pl.mode == kModeTaps && (kg16 % 4 == 0 || kg16 >= 12)) ip.tm = 4;
-    // float32 7x7: four where the launch wants them (im2col_items_target)
+    // float32 7x7: four where the launch wants them (items_target)
     if (target_len.wide && !half && g.groups == 1 && pl.mode == 7 && kg16 % 4 == 0) ip.tm = 4;
     ip.nmt = ceil_div(K16, ip.tm);
     ip.ntn = ceil_div(ceil_div(g.n * g.p * g.q, 16), 2);
@@ -1778,16 +1789,17 @@ constexpr int kItemsResident = 256 * 3 * kItemWaves;
 // (ResNet-50, 301x227) 72 / 60 / 55 / 63, 5085 (ResNet-50, 2x217x257) 103 / 85 / 74 / 69, 7488 (VGG-16) 92 / 80 / 69 / 59; W = 197 (SqueezeNet, 2x132x119) 16 / 22 / 22 / 22.
 // Layers of few channels are items of workgroups where that saves the launch that copies x, not beside other copies (MobileNetV2-shaped plan 50 / 44;
 // ResNet-18 at 4x108x114, whose last layers keep their copy, 30 / 36).
-ItemTarget im2col_items_target(int n, const Geo *geos) {
+// known: filled in for n layers.
+static ItemTarget items_target(int n, const Geo *geos, LayerPlan *known) {
     ItemTarget target{kItemSteps, 0, false, false};
-    ItemPlan whole[kMaxGemmLayers];
     long w = 0;                      // in chunks of 1x1 filters of 64 x 16 outputs
     int longest_whole = 0;           // reduction, in chunks of 1x1 filters
     for (int i = 0; i < n; ++i) {
-        whole[i] = plan_whole(geos[i]);
-        if (!whole[i].tile || whole[i].mode == kModeTaps) continue;
-        const int chunks = ceil_div(geos[i].c, kTileChannels) * (whole[i].mode == 3 ? 4 : 1);
-        w += (long)whole[i].nmt * whole[i].ntn * whole[i].tn * chunks;
+        known[i] = LayerPlan{plan_whole(geos[i]), plan_im2col(geos[i])};
+        const ItemPlan &whole = known[i].whole;
+        if (!whole.tile || whole.mode == kModeTaps) continue;
+        const int chunks = ceil_div(geos[i].c, kTileChannels) * (whole.mode == 3 ? 4 : 1);
+        w += (long)whole.nmt * whole.ntn * whole.tn * chunks;
         longest_whole = std::max(longest_whole, chunks);
     }
     w /= 28;
@@ -1795,13 +1807,13 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
         if (w >= 600) target.chunks = longest_whole <= 48 ? 12 : (int)std::min(std::max(4L, w / 330), 65536L);
         // (decided last: plans without `few` first)
         bool copies = false;
-        for (int i = 0; i < n && !copies; ++i) copies = whole[i].mode != kModeTaps && plan_items(geos[i], target, &whole[i]).xt_bytes > 0;
+        for (int i = 0; i < n && !copies; ++i) copies = known[i].whole.mode != kModeTaps && plan_items(geos[i], target, &known[i]).xt_bytes > 0;
         target.few = !copies;
     } else if (w >= 220) target.chunks = std::max(2, (int)std::min((w + 449) / 450, 65536L));
     auto total_at = [&](int t) {
         long tot = 0;
         for (int i = 0; i < n; ++i) {
-            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks, target.few, target.wide}, &whole[i]);
+            const ItemPlan p = plan_items(geos[i], ItemTarget{t, target.chunks, target.few, target.wide}, &known[i]);
             tot += (long)p.nmt * p.ntn * p.nsplit * (p.tile ? kItemWaves : 1);
         }
         return tot;
@@ -1812,11 +1824,15 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
         return target;
     }
     constexpr long fit = (long)kItemsResident * 15 / 16;
+    long items = total;                 // at target.steps
     if (total <= fit)
         for (int t = kItemSteps - 12; t >= kItemStepsMin; t -= 12) {
-            if (total_at(t) > fit) break;
+            const long at = total_at(t);
+            if (at > fit) break;
             target.steps = t;
+            items = at;
         }
+    const int fitting = target.steps;
     // float32, whatever their number: no item longer than a SIMD's share of the launch's matrix instructions, or the launch ends with
     // a few long items (the deep layers of a mobile network: 20 us each, and all others are done after 12).  us a call, items of 144 steps
     // or what the rule above chose / this: MobileNetV2-shaped plan 47 / 40, MobileNetV1 44 / 42, ResNet-18 at batch 2, 150 x 187 74 / 63;
@@ -1824,7 +1840,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     double share = 0;                   // in steps of a panel
     int longest[5] = {0, 0, 0, 0, 0};   // steps of the longest reduction among the layers of 1, 2 and 4 panels per tile
     for (int i = 0; i < n; ++i) {
-        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks, false, target.wide}, &whole[i]);
+        const ItemPlan p = plan_items(geos[i], ItemTarget{kItemSteps, target.chunks, false, target.wide}, &known[i]);
         if (p.tile) continue;
         share += (double)p.nmt * p.ntn * p.steps * p.tm / 1024;
         longest[p.tm] = std::max(longest[p.tm], p.steps);
@@ -1836,7 +1852,7 @@ ItemTarget im2col_items_target(int n, const Geo *geos) {
     // 7x7 layers, whose items are many and bound by their gathers of pixels, take four panels per tile (half the items and gathers).  us a call without / with, items:
     // ResNet-18-shaped stack 48.7 / 45.6 (224x224, 3344), 52.0 / 48.1 (180x256, 3660), 57.1 / 53.2 (2x150x150, 3660), 61.7 / 62.8 (260x270, 3786), GoogLeNet 88.2 / 86.5
     // (300x280, 3963); outside: ResNet-50 70 / 74 (150x190, 5537), ResNet-18 36.4 / 39.8 (120x110, 2414).
-    const long items = total_at(target.steps);
+    if (target.steps != fitting) items = total_at(target.steps);
     target.wide = items > kItemsResident && items <= kItemsResident * 3L / 2;
     return target;
 }
@@ -1848,9 +1864,14 @@ bool im2col_items_supported(const Geo &g) {
     return g.sh < 65536 && g.sw < 65536 && g.ph < 65536 && g.pw < 65536 && plan_items(g, ItemTarget{kItemStepsMin / 2, 0, false, false}).nsplit < 65536;
 }
 
-size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target) {
-    const ItemPlan ip = plan_items(g, target);
-    return align_up(ip.part_bytes, 256) + align_up(ip.xt_bytes, 256);
+void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes) {
+    if (n <= 0 || n > kMaxGemmLayers) return;
+    LayerPlan known[kMaxGemmLayers];
+    const ItemTarget target = items_target(n, geos, known);
+    for (int i = 0; i < n; ++i) {
+        const ItemPlan ip = plan_items(geos[i], target, &known[i]);
+        bytes[i] = align_up(ip.part_bytes, 256) + align_up(ip.xt_bytes, 256);
+    }
 }
 
 // One item launch of n planned layers of one storage type, with the copies of x in front of it and the reduction behind it
@@ -1955,16 +1976,17 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
 
 // Launches layers [0, n) (all of one storage type, n <= kMaxGemmLayers) as one item launch plus,
 // if any layer is split, one reduction launch.  ws[i] is layer i's own workspace region of
-// im2col_items_workspace_bytes(geos[i], im2col_items_target(n, geos)).
+// im2col_items_workspace_bytes of these layers.
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
                                void *const *y, void *const *ws, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     if (n > kMaxGemmLayers) return hipErrorInvalidValue;
     for (int i = 0; i < n; ++i)
         if (geos[i].dtype != geos[0].dtype) return hipErrorInvalidValue;
-    const ItemTarget target = im2col_items_target(n, geos);
+    LayerPlan known[kMaxGemmLayers];
+    const ItemTarget target = items_target(n, geos, known);
     ItemPlan plans[kMaxGemmLayers];
-    for (int i = 0; i < n; ++i) plans[i] = plan_items(geos[i], target);
+    for (int i = 0; i < n; ++i) plans[i] = plan_items(geos[i], target, &known[i]);
     return launch_planned(n, geos, plans, x, w, bias, y, ws, st);
 }
 

@@ -86,14 +86,10 @@ hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float
 
 // Many independent IM2COL_GEMM layers (one storage type, at most kMaxGemmLayers) in one launch of
 // single-wavefront work items, plus one reduction launch if a layer's channels are split; ws[i] is
-// layer i's own region of im2col_items_workspace_bytes(geos[i], im2col_items_target(n, geos)) bytes.
+// layer i's own region of im2col_items_workspace_bytes.
 constexpr int kMaxGemmLayers = 56;
 bool im2col_items_supported(const Geo &g);
-// Length of the items of a launch: k-steps of a single-wavefront item, chunks of 32 channels of a whole workgroup's (0: none of these); few: float16
-// layers of few channels in items of workgroups; wide: float32 7x7 layers with four panels per tile.
-struct ItemTarget { int steps, chunks; bool few, wide; };
-ItemTarget im2col_items_target(int n, const Geo *geos);
-size_t im2col_items_workspace_bytes(const Geo &g, ItemTarget target);
+void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes);      // of each of the layers of a launch
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w,
                                const float *const *bias, void *const *y, void *const *ws, hipStream_t st);
 
