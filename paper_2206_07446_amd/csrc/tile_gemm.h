@@ -9,9 +9,10 @@
 //     at most 2^-23 of the product and of either sign.  h h' and the small terms have an accumulator each, so a long sum rounds its large part
 //     once per 32 channels and tap instead of once per channel.  Relative 2-norm of the error against float64, random
 //     data, this / one chain of float32 products: 3.7e-8 / 1.0e-7 over 32 terms, 1.3e-7 / 4.4e-7 over 576, 4.1e-7 / 1.2e-6
-//     over 4608.  Values that bfloat16 cannot hold (infinite, NaN, rounded up to infinity) leave a sum that is not finite, and
-//     parts below 2^-126, which the matrix unit takes for zero, matter only in sums of tiny values: a wavefront that finds a sum
-//     not finite, or not zero and below 2^-60, computes its tile once more with float32 products (tile_exact).
+//     over 4608.  The matrix unit takes bfloat16 below 2^-126 for zero, so both operands are taken times 2^23 and the sums times 2^-46:
+//     a part of any float32, being a multiple of 2^-149, is then zero or at least 2^-126, and what products lose is below 2^-172 each, no sum of
+//     which a float32 shows.  Operands that bfloat16 cannot hold (infinite, NaN, from 2^105 on) and sums from 2^82 on leave a scaled sum that
+//     is not finite: a wavefront that finds one computes its tile once more with float32 products (tile_exact).
 //   * the four wavefronts of a workgroup share the pixels of a tile: 32 channels of the patch of x are split once, laid
 //     down in LDS and read by all wavefronts and all filter taps; each wavefront reads and splits the weights of its own
 //     output channels only.
@@ -50,7 +51,11 @@ struct TileLayer {
     int relu;
 };
 
-__device__ __forceinline__ void bf3_split(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+// Both operands are taken times 2^23, the sums times 2^-46: whatever part of a float32 is not zero is then at least 2^-126.
+constexpr float kTileScale = 0x1p23f, kTileUnscale = 0x1p-46f;
+
+__device__ __forceinline__ void bf3_split(const float x, const float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+    const float a = x * kTileScale, b = y * kTileScale;
     // (the empty statements keep the compiler from converting a second time for the value it shifts out)
     const bf16x2 hp = {(__bf16)a, (__bf16)b};
     h = __builtin_bit_cast(uint32_t, hp);
@@ -257,7 +262,7 @@ __device__ __forceinline__ void tile_accumulate(const TileLayer &g, const TilePo
     }
 }
 
-// The same sums with float32 products, every operand straight from memory: for tiles whose result is not finite.
+// The same sums with float32 products, every operand straight from memory: for tiles whose scaled sums are not finite.
 template <int TM, int TN>
 __device__ __forceinline__ void tile_exact(const TileLayer &g, const TilePos &at, const int c0, const int c1, floatx4 (&acc)[TM][TN]) {
     constexpr int QM = 16 / TM;
@@ -473,20 +478,16 @@ __device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, cons
         floatx4 acs[TM][TN];
         tile_accumulate<TM, TN, DOUBLE>(g, at, c0, c1, lds, acc, acs);
         float z = 0.f;                    // NaN if any sum is not finite
-        uint32_t least = 0xffffffffu;     // twice the bits of the smallest one that is not zero, less one
 #pragma unroll
         for (int m = 0; m < TM; ++m)
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
                 acc[m][t] += acs[m][t];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    z = fmaf(acc[m][t][j], 0.f, z);
-                    least = min(least, (__builtin_bit_cast(uint32_t, acc[m][t][j]) << 1) - 1u);
-                }
+                for (int j = 0; j < 4; ++j) z = fmaf(acc[m][t][j], 0.f, z);
+                acc[m][t] *= kTileUnscale;
             }
-        constexpr uint32_t kTiny = (127u - 60u) << 24;      // 2^-60
-        if (__ballot(z != 0.f || least < kTiny) != 0) tile_exact<TM, TN>(g, at, c0, c1, acc);
+        if (__ballot(z != 0.f) != 0) tile_exact<TM, TN>(g, at, c0, c1, acc);
     }
     __builtin_amdgcn_s_setprio(3);
     if (part) {

@@ -113,3 +113,48 @@ def test_values_beyond_bfloat16(env, value, grouped):
         near = fin & ~far
         if near.any():
             assert (np.abs(got[near] - ref[near]) <= 1e-5 * np.abs(ref[near])).all()
+
+
+def run_alone_or_grouped(nnv, torch, case, grouped):
+    """The case's output with its present x and w, alone or as the first of a grouped call."""
+    case.xd = torch.from_numpy(case.x).to("cuda")
+    nnv.nnv_transform_weights(case.desc, case.kind, torch.from_numpy(case.w).to("cuda"), case.wt)
+    if not grouped:
+        return forward(nnv, torch, case)
+    all_ = [case, *(Case(nnv, torch, Ly(64, 56, 56, 128), nnv.IM2COL_GEMM, False, 70 + i) for i in range(4))]
+    descs, kinds = [c.desc for c in all_], [c.kind for c in all_]
+    need = nnv.nnv_conv_forward_grouped_workspace_bytes(descs, kinds)
+    ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+    nnv.nnv_conv_forward_grouped(descs, kinds, [c.xd for c in all_], [c.wt for c in all_], None, [c.y for c in all_], ws, need, 0)
+    torch.cuda.synchronize()
+    return case.result()
+
+
+def scaled(rng, shape, exponent):
+    """Magnitudes in [2^exponent, 2^(exponent + 1)], either sign."""
+    return (rng.uniform(1.0, 2.0, shape) * rng.choice((-1.0, 1.0), shape) * 2.0 ** exponent).astype(np.float32)
+
+
+# 128 x 112 outputs with two buffers, 64 x 112 outputs
+RANGES = [Ly(64, 56, 56, 256, n=6), Ly(64, 150, 150, 64)]
+
+
+@pytest.mark.parametrize("layer", RANGES, ids=[l.name for l in RANGES])
+@pytest.mark.parametrize("ex,ew", [(-126, 80), (80, -126), (-140, 100), (100, -140), (-112, 60), (-75, -75), (-90, -40), (110, -100), (-100, 110), (60, 40)])
+@pytest.mark.parametrize("part", [1, 2])
+def test_operand_ranges(env, layer, ex, ew, part):
+    """Small pixels beside large weights and the reverse, subnormal ones, products that underflow, sums that nearly overflow; in every
+    channel (part 1) or in every second one beside ordinary values of about the same product (part 2)."""
+    nnv, torch = env
+    rng = np.random.default_rng(1000 + ex)
+    case = Case(nnv, torch, layer, nnv.IM2COL_GEMM, False, 5)
+    case.x, case.w = scaled(rng, case.x.shape, ex), scaled(rng, case.w.shape, ew)
+    if part == 2:
+        case.x[:, ::2] = scaled(rng, case.x[:, ::2].shape, (ex + ew) // 2)
+        case.w[:, ::2] = scaled(rng, case.w[:, ::2].shape, ex + ew - (ex + ew) // 2)
+    got = run_alone_or_grouped(nnv, torch, case, part == 2 and layer.n == 1)
+    ref = cdirect.conv2d_direct_c(case.x, case.w, 1, layer.pad, 1)
+    # as test_single, and half of the smallest number where the result is subnormal; products are rounded to it in float32
+    chunks = -(-layer.c // 32)
+    err = np.linalg.norm(got - ref)
+    assert err <= 4 * 2.0 ** -24 * np.sqrt(18 * chunks) * np.linalg.norm(ref) + 2.0 ** -149 * np.sqrt(ref.size), f"{err / np.linalg.norm(ref):.2e}"
