@@ -5,9 +5,10 @@
 // cycles for 1024 FMAs, a bfloat16 16x16x32 one 16 cycles for 8192) and the vector memory path of a CU, which every operand
 // fragment passes once per wavefront and filter tap.  Here
 //   * a float32 is the exact sum of three bfloat16 (8 + 8 + 8 significant bits, each rounded to nearest), x = h + m + l,
-//     and a product of two of them six bfloat16 products: h h' + (h m' + m h') + (m m' + h l' + l h'); what is left out is
-//     at most 2^-23 of the product and of either sign.  h h' and the small terms have an accumulator each, so a long sum rounds its large part
-//     once per 32 channels and tap instead of once per channel.  Relative 2-norm of the error against float64, random
+//     and a product of two of them eight bfloat16 products: h h' + (h m' + m h') + (m m' + h l' + l h') + (m l' + l m'); l l', what is left
+//     out, is at most 2^-34 of the product, a thousandth of what rounding the product to float32 takes.  h h' and the small terms have an accumulator each,
+//     so a long sum rounds its large part once per 32 channels and tap instead of once per channel.  Sums of one product, 115 million of them: at
+//     most 5.99e-8 of it away from it, a float32 product 5.96e-8 (with six products, m l' and l m' left out, 1.09e-7).  Relative 2-norm of the error against float64, random
 //     data, this / one chain of float32 products: 3.7e-8 / 1.0e-7 over 32 terms, 1.3e-7 / 4.4e-7 over 576, 4.1e-7 / 1.2e-6
 //     over 4608.  The matrix unit takes bfloat16 below 2^-126 for zero, so both operands are taken times 2^23 and the sums times 2^-46:
 //     a part of any float32, being a multiple of 2^-149, is then zero or at least 2^-126, and what products lose is below 2^-172 each, no sum of
@@ -227,13 +228,13 @@ __device__ __forceinline__ void tile_accumulate(const TileLayer &g, const TilePo
 #define NNV_BF(X) __builtin_bit_cast(bf16x8, X)
 #define NNV_TILE_MFMA(X, Y, Z) \
     _Pragma("unroll") for (int m = 0; m < TM; ++m) Z[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(NNV_BF(af[sa][m].X), NNV_BF(bf[sb].Y), Z[m][t], 0, 0, 0);
-                NNV_TILE_MFMA(l, h, acs) NNV_TILE_MFMA(h, h, acc) NNV_TILE_MFMA(m, h, acs)
-                NNV_TILE_MFMA(m, m, acs) NNV_TILE_MFMA(h, m, acs) NNV_TILE_MFMA(h, l, acs)
+                NNV_TILE_MFMA(l, m, acs) NNV_TILE_MFMA(m, l, acs) NNV_TILE_MFMA(l, h, acs) NNV_TILE_MFMA(h, h, acc)
+                NNV_TILE_MFMA(m, h, acs) NNV_TILE_MFMA(m, m, acs) NNV_TILE_MFMA(h, m, acs) NNV_TILE_MFMA(h, l, acs)
 #undef NNV_TILE_MFMA
 #undef NNV_BF
                 // (vector instructions dealt out over the products)
 #pragma unroll
-                for (int i = 0; i < 6 * TM; ++i) {
+                for (int i = 0; i < 8 * TM; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
                 }

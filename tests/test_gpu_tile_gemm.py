@@ -158,3 +158,25 @@ def test_operand_ranges(env, layer, ex, ew, part):
     chunks = -(-layer.c // 32)
     err = np.linalg.norm(got - ref)
     assert err <= 4 * 2.0 ** -24 * np.sqrt(18 * chunks) * np.linalg.norm(ref) + 2.0 ** -149 * np.sqrt(ref.size), f"{err / np.linalg.norm(ref):.2e}"
+
+
+@pytest.mark.parametrize("grouped", [False, True])
+def test_single_products(env, grouped):
+    """Outputs of one product each, all others being zero: no less exact than a float32 product."""
+    nnv, torch = env
+    layer = Ly(64, 150, 150, 64)
+    rng = np.random.default_rng(77)
+    case = Case(nnv, torch, layer, nnv.IM2COL_GEMM, False, 5)
+    case.x = scaled(rng, case.x.shape, 0)
+    w = scaled(rng, case.w.shape, 0)
+    case.w = np.zeros_like(w)
+    for k in range(layer.k):
+        c, r, s = k * 5 % 64, k % 3, k // 3 % 3
+        case.w[k, c, r, s] = w[k, c, r, s]
+    got = run_alone_or_grouped(nnv, torch, case, grouped)
+    ref = cdirect.conv2d_direct_c(case.x, case.w, 1, 1, 1)
+    # half an ulp of the result, and a few roundings of its part below 2^-8
+    bound = 2.0 ** -24 * (1 + 2.0 ** -5)
+    worst = np.abs(got - ref)[ref != 0] / np.abs(ref)[ref != 0]
+    assert worst.max() <= bound, f"{worst.max():.3e}"
+    assert (got[ref == 0] == 0).all()
