@@ -1,7 +1,7 @@
 // Work items of whole workgroups (included by gemm.hip): float32 3x3 layers at stride 1 on the bfloat16 matrix cores; float16 3x3, 1x1 and few-channel
 // layers (further down).
 //
-// float32.  // What bounds the single-wavefront items of gemm.hip on such layers is the float32 matrix pipe (a 16x16x4 product runs 32
+// float32.  What bounds the single-wavefront items of gemm.hip on such layers is the float32 matrix pipe (a 16x16x4 product runs 32
 // cycles for 1024 FMAs, a bfloat16 16x16x32 one 16 cycles for 8192) and the vector memory path of a CU, which every operand
 // fragment passes once per wavefront and filter tap.  Here
 //   * a float32 is the exact sum of three bfloat16 (8 + 8 + 8 significant bits, each rounded to nearest), x = h + m + l,
@@ -13,7 +13,9 @@
 //     over 4608.  The matrix unit takes bfloat16 below 2^-126 for zero, so both operands are taken times 2^23 and the sums times 2^-46:
 //     a part of any float32, being a multiple of 2^-149, is then zero or at least 2^-126, and what products lose is below 2^-172 each, no sum of
 //     which a float32 shows.  Operands that bfloat16 cannot hold (infinite, NaN, from 2^105 on) and sums from 2^82 on leave a scaled sum that
-//     is not finite: a wavefront that finds one computes its tile once more with float32 products (tile_exact).
+//     is not finite: a workgroup that finds one computes its tile once more with float32 products (tile_accumulate_float; us a call with
+//     ordinary values / one infinite pixel / every sum not finite: 256 channels at 8x56x56 165 / 285 / 405, 512 at 4x28x28 112 / 270 / 270, 64 at 224x224
+//     38 / 45 / 93; each wavefront for itself, its operands straight from memory, took 480 / 605, 1290 / 1290 and 75 / 140).
 //   * the four wavefronts of a workgroup share the pixels of a tile: 32 channels of the patch of x are split once, laid
 //     down in LDS and read by all wavefronts and all filter taps; each wavefront reads and splits the weights of its own
 //     output channels only.
@@ -263,34 +265,68 @@ __device__ __forceinline__ void tile_accumulate(const TileLayer &g, const TilePo
     }
 }
 
-// The same sums with float32 products, every operand straight from memory: for tiles whose scaled sums are not finite.
+// The same sums with float32 products, for tiles whose sums are not finite.  All four wavefronts call it with the same tile and range,
+// and none reads lds any more.  The patch of a chunk is laid down as it is, [slot][pixel][8 channels].
 template <int TM, int TN>
-__device__ __forceinline__ void tile_exact(const TileLayer &g, const TilePos &at, const int c0, const int c1, floatx4 (&acc)[TM][TN]) {
-    constexpr int QM = 16 / TM;
+__device__ __forceinline__ void tile_accumulate_float(const TileLayer &g, const TilePos &at, const int c0, const int c1, char *lds, floatx4 (&acc)[TM][TN]) {
+    constexpr int NT = kTilePatch / 64, QM = 16 / TM;
+    constexpr uint32_t SUB = kTilePatch * 32;
+    static_assert(4 * SUB <= kTileBuffer, "the patch fits");
     const int lane = threadIdx.x & 63, col = lane & 15, slot = lane >> 4;
-    const SmallDiv by_tw(g.tw);
-    const __amdgpu_buffer_rsrc_t xres = make_rsrc(g.x, (uint32_t)(g.N * g.C) * (uint32_t)(g.H * g.W) * 4u);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pw = g.tw + 2, npatch = pw * (g.th + 2), HW = g.H * g.W;
+    const SmallDiv by_pw(pw), by_tw(g.tw);
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(g.x, (uint32_t)(g.N * g.C) * (uint32_t)HW * 4u);
     const __amdgpu_buffer_rsrc_t wres = make_rsrc(g.wp, (uint32_t)g.K16 * (uint32_t)g.cblocks * (9 * 256u));
     const uint32_t a_voff = at.mb0 + col / QM < g.K16
         ? (uint32_t)(col / QM) * (uint32_t)g.cblocks * (9 * 256u) + (uint32_t)slot * 64u + (uint32_t)(col % QM) * (4u * TM) : kOobOffset;
+    const uint32_t a_base = (uint32_t)at.mb0 * (uint32_t)g.cblocks * 9u;
 #pragma unroll
     for (int m = 0; m < TM; ++m)
 #pragma unroll
         for (int t = 0; t < TN; ++t) acc[m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int cb = c0 * 8; cb < min(c1 * 8, g.cblocks); ++cb) {
-        const int c = cb * 4 + slot;
+    for (int ch = c0; ch < c1; ++ch) {
+        __syncthreads();            // all have read the chunk before
 #pragma unroll 1
-        for (int rs = 0; rs < 9; ++rs) {
-            const auto a = buf_load_floats<TM>(wres, a_voff, ((uint32_t)at.mb0 * (uint32_t)g.cblocks * 9u + (uint32_t)(cb * 9 + rs)) * 256u);
+        for (int j = 0; j < NT; ++j) {
+            const int f = j * 64 + lane, r = by_pw(f), c = f - r * pw;
+            const int ih = at.p0 - g.pad + r, iw = at.q0 - g.pad + c;
+            const bool in = f < npatch && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+            floatx4 v[2];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int cc = (ch * 8 + i) * 4 + wave;
+                v[i >> 2][i & 3] = buf_load<float>(xres, in && cc < g.C ? (uint32_t)((at.img * g.C + cc) * HW + ih * g.W + iw) * 4u : kOobOffset, 0u);
+            }
+            floatx4 *o = reinterpret_cast<floatx4 *>(lds + wave * SUB + f * 32);
+            o[0] = v[0];
+            o[1] = v[1];
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int row = 0; row < 3; ++row) {
+            typename FloatVec<TM>::type a[3][8];
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int cb = ch * 8 + i;          // past the last channel block: zeros, as its pixels are
+                    a[s][i] = buf_load_floats<TM>(wres, cb < g.cblocks ? a_voff : kOobOffset, (a_base + (uint32_t)(min(cb, g.cblocks - 1) * 9 + row * 3 + s)) * 256u);
+                }
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
-                const int n = t * 16 + col, r = by_tw(n), q = n - r * g.tw;
-                const int ih = at.p0 + r - g.pad + rs / 3, iw = at.q0 + q - g.pad + rs % 3;
-                const bool ok = r < g.th && c < g.C && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
-                const float b = buf_load<float>(xres, ok ? (uint32_t)(((at.img * g.C + c) * g.H + ih) * g.W + iw) * 4u : kOobOffset, 0u);
+                const int n = t * 16 + col, r = by_tw(n), c = n - r * g.tw;
+                const char *pix = lds + slot * SUB + (r < g.th ? ((r + row) * pw + c) * 32 : 0);
 #pragma unroll
-                for (int m = 0; m < TM; ++m) acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(a, m), b, acc[m][t], 0, 0, 0);
+                for (int s = 0; s < 3; ++s) {
+                    const floatx4 b[2] = {reinterpret_cast<const floatx4 *>(pix + s * 32)[0], reinterpret_cast<const floatx4 *>(pix + s * 32)[1]};
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int m = 0; m < TM; ++m)
+                            acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(a[s][i], m), b[i >> 2][i & 3], acc[m][t], 0, 0, 0);
+                }
             }
         }
     }
@@ -488,7 +524,13 @@ __device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, cons
                 for (int j = 0; j < 4; ++j) z = fmaf(acc[m][t][j], 0.f, z);
                 acc[m][t] *= kTileUnscale;
             }
-        if (__ballot(z != 0.f) != 0) tile_exact<TM, TN>(g, at, c0, c1, acc);
+        // (a workgroup's wavefronts decide together: the float32 products share the patch as well.  The products end with a barrier, so that
+        // lds may be written.)
+        int *bad = reinterpret_cast<int *>(lds);
+        const bool mine = __ballot(z != 0.f) != 0;
+        if (lane == 0) bad[wave] = mine;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(bad[0] | bad[1] | bad[2] | bad[3]) != 0) tile_accumulate_float<TM, TN>(g, at, c0, c1, lds, acc);
     }
     __builtin_amdgcn_s_setprio(3);
     if (part) {

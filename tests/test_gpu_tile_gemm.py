@@ -180,3 +180,19 @@ def test_single_products(env, grouped):
     worst = np.abs(got - ref)[ref != 0] / np.abs(ref)[ref != 0]
     assert worst.max() <= bound, f"{worst.max():.3e}"
     assert (got[ref == 0] == 0).all()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_values_in_ranges_of_channels(env, value):
+    """A launch that splits the channels: the range with the value in it, and it alone, has sums that are not finite."""
+    nnv, torch = env
+    case = Case(nnv, torch, Ly(352, 14, 14, 512), nnv.IM2COL_GEMM, False, 9)
+    case.x[0, 300, 13, 0] = case.x[0, 3, 5, 5] = value
+    case.w[7] = 0.0          # nothing but products with zero: NaN
+    got = run_alone_or_grouped(nnv, torch, case, True)
+    with np.errstate(invalid="ignore"):
+        ref = cdirect.conv2d_direct_c(case.x, case.w, 1, 1, 1)
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    inf, fin = np.isinf(ref), np.isfinite(ref)
+    assert (got[inf] == ref[inf]).all()
+    assert np.abs(got[fin] - ref[fin]).max() <= 1e-4 * np.abs(ref[fin]).max()
