@@ -1990,25 +1990,30 @@ hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, con
     return launch_planned(n, geos, plans, x, w, bias, y, ws, st);
 }
 
-// A single layer in items of whole workgroups, its channels not split.  float32: from 200 items on (below, a CU's one item takes its whole
-// channel loop at the pace of one wavefront per SIMD).  Measured, us, without / with: 224 items 44.6 / 29.9 (128 channels at 112x112) and
-// 156 / 101 (512 at 4x28x28), 448 items 44.5 / 35 (64 at 224x224); 112 items 44 / 54 (256 at 56x56), 128 80 / 102 (512 at 8x14x14).
-// 128 x 112 outputs with two buffers in LDS where that leaves 260 items: 256 at 8x56x56 154 / 138, 2 x 96 -> 200 at 80x90 45 / 40; with 112
-// of them 101 / 138 (512 at 4x28x28).
-// float16, in items of 64 output channels: 3x3 from 100 on (us without / with, items: 256 at 8x56x56, 896: 76 / 39; 512 at 4x28x28, 224: 66 / 27; 64 at
-// 4x56x56, 112: 10.2 / 8.3; stride 2, 64 at 112x112 -> 128, 100: 8.6 / 8.3; below: 96 at 56x56 -> 160, 84: 10.0 / 9.8; 128 at 56x56, 56: 10.3 / 12.7), 1x1
-// from 340 on (512 at 8x56x56 / 2 -> 512, 784: 32 / 16; 64 at 4x56x56 -> 256, 448: 11.3 / 8.6; 300 at 4x33x33, 345: 12.0 / 10.2; below: 500 -> 100 at 100x100, 180:
-// 15.2 / 15.8), few channels from 200 on if one row of tiles holds all 33 to 64 panels' channels (3x3 at 224x224 -> 64, 448: 10.3 / 8.3; 7x7 / 2 there, 112: 8.1 /
-// 8.6; 5x5 -> 200: 17.8 / 20.1).  3x3 with 128 x 112 outputs where those of 64 would be at most one to a CU (512 at 4x28x28 32 -> 27,
-// 128 at 112x112 12.7 -> 10.8; 128 at 5x56x56, 280: 14.1 against 16.4, 256 at 8x56x56 39 against 48: two wavefronts per SIMD, not three).
+// A single layer in items of whole workgroups, its channels not split: an item takes the whole channel loop, so that there have to be enough of
+// them.  The lines stand where a sweep of 590 layers changes sides (48-2048 channels, planes of 7x7 to 224x224, batches of 1-16, half of the sizes those of networks,
+// half random; weights and pixels from HBM; geometric means of the time without / with such items, in brackets the smallest and largest):
+//   float32, by items of 64 channels x 16 pixels (an item holds 7 or 4 of them): 7 x 140-179 items 0.92 (0.74-1.06), 180-199 1.06 (0.98-1.20), 200-229 1.22 (0.95-1.35), 280-399
+//     1.15 (0.90-1.28), above 1.33 (0.97-1.72); 4 x 250-299 0.80 (0.64-1.01), 300-349 0.88 (0.72-1.15), 350-399 1.00 (0.85-1.19), 400-499 1.10 (0.89-1.29), above 1.14 (0.83-1.47).
+//   float16 3x3, items: 1-59 0.81 (0.48-1.03), 80-99 1.07 (0.87-1.58), 100-119 1.17 (0.94-1.46), 120-199 1.40 (1.13-2.21), above 1.43 (1.10-2.27); stride 2:
+//     100-130 0.89 (0.76-1.11), 168 1.14, 200-299 1.24 (1.00-1.36), above 1.28 (1.09-1.58).
+//   float16 1x1: 150-199 0.84 (0.73-0.96), 200-249 0.97 (0.83-1.51), 250-299 1.13 (0.97-1.47), 300-339 1.23 (1.07-1.70), above 1.52 (0.95-2.50); at stride 2 200-249 1.22 (0.95-1.60).
+//   float16 few channels, if one row of tiles holds all 33 to 64 panels' channels: below 70 1.00 (0.94-1.06), 100-199 1.09 (1.07-1.12), above 1.14 (0.99-1.29);
+//     fewer channels 1.03 (0.80-1.20), more 1.02 (0.84-1.26).
+// 128 x 112 outputs (times of 64 x 112 / 128 x 112): float32, with two buffers, two workgroups per CU and not three: where they all fit the chip and
+// those of 64 need a second round, 1.03 (1.00-1.07, 29 layers; 256 channels at 8x56x56 189 / 177 us); fewer 0.87, more 0.82-1.00.  float16 3x3, whose LDS reads
+// they halve: where those of 64 would share CUs, 257-449 items 1.11 (1.04-1.25), 450-999 1.17 (1.02-1.30), more 1.08 (0.99-1.16; 256 channels at 8x56x56
+// 51 / 41 us); one to a CU 0.86 (0.78-0.92, 52 layers; 512 at 4x28x28 27 / 31 us).
 static bool plan_tile_single(const Geo &g, ItemPlan *ip) {
+    const bool half = g.dtype == NNV_F16;
     const int K16 = ceil_div(g.k, 16), nmt = ceil_div(K16, 8);
     const bool fits = nmt * 8 * 100 <= ceil_div(K16, 4) * 4 * 115;       // 128 channels per item leave no more empty than 64
-    if (plan_few(g, ip)) return g.k > 32 && g.k <= 64 && ip->ntn >= 200;
+    if (plan_few(g, ip)) return g.k > 32 && g.k <= 64 && ip->ntn >= 100;
     if (!plan_tile(g, ip) && !plan_one(g, ip)) return false;
     const long items = (long)ip->nmt * ip->ntn * ip->tm;
-    if (items < (g.dtype == NNV_F32 ? 200 : ip->mode == 3 ? 100 : 340)) return false;
-    if (fits && ip->mode == 3 && ip->tn == 7 && (g.dtype == NNV_F32 ? (long)nmt * ip->ntn >= 260 : items <= 256)) {
+    if (half ? items < (ip->mode == 1 ? 250 : g.sh == 1 ? 80 : 160) : items * ip->tn < 200 * 7) return false;
+    constexpr int kChipSmall = 256 * 3, kChipLarge = 256 * 2;            // workgroups resident at once
+    if (fits && ip->mode == 3 && ip->tn == 7 && (half ? items > 256 : items > kChipSmall && (long)nmt * ip->ntn <= kChipLarge)) {
         ip->tm = 2;
         ip->nmt = nmt;
     }

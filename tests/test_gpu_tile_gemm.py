@@ -29,12 +29,13 @@ def forward(nnv, torch, case, relu=False):
     return case.result()
 
 
-# at least 200 items of 64 x 112 (or 64 x 64) outputs: such layers take the path by themselves
+# at least 200 items of 64 x 112 outputs or 350 of 64 x 64: such layers take the path by themselves (65 channels at 110 x 7x7 stay just below)
 SINGLE = [
     Ly(48, 150, 150, 64), Ly(49, 113, 200, 65, pad=0), Ly(64, 58, 61, 400, n=2), Ly(63, 40, 41, 127, pad=2, n=6),
     Ly(96, 9, 9, 130, n=70), Ly(65, 7, 7, 128, n=110), Ly(128, 224, 113, 33), Ly(70, 1, 300, 500, n=10),
-    # 128 x 112 outputs with two buffers
-    Ly(64, 56, 56, 256, n=6), Ly(100, 57, 83, 250, n=3),
+    Ly(65, 7, 7, 128, n=180), Ly(64, 56, 56, 256, n=6), Ly(100, 57, 83, 250, n=3),
+    # 128 x 112 outputs with two buffers: at most 512 items, where 64 x 112 would be more than 768
+    Ly(64, 56, 56, 256, n=8), Ly(49, 41, 54, 245, n=11), Ly(70, 41, 54, 249, n=10),
 ]
 
 
@@ -136,7 +137,7 @@ def scaled(rng, shape, exponent):
 
 
 # 128 x 112 outputs with two buffers, 64 x 112 outputs
-RANGES = [Ly(64, 56, 56, 256, n=6), Ly(64, 150, 150, 64)]
+RANGES = [Ly(64, 56, 56, 256, n=8), Ly(64, 150, 150, 64)]
 
 
 @pytest.mark.parametrize("layer", RANGES, ids=[l.name for l in RANGES])

@@ -22,10 +22,11 @@ def Few(c, h, w, k, r, stride, pad=None, n=1):
     return ConvLayer(f"f{c}_{n}x{h}x{w}_k{k}_r{r}s{stride}", c, h, w, k, r, r, stride, r // 2 if pad is None else pad, 1, n)
 
 
-# enough tiles for the path by themselves; the last three 128 x 112 outputs
+# enough tiles for the path by themselves; from the sixth on 128 x 112 outputs, but for 100 channels at 57x83, whose tiles hold 64 pixels
 SINGLE = [
     Ly(48, 150, 150, 64), Ly(49, 113, 200, 65, pad=0), Ly(63, 40, 41, 127, pad=2, n=6), Ly(96, 9, 9, 130, n=70), Ly(70, 1, 300, 500, n=10),
     Ly(64, 56, 56, 256, n=6), Ly(100, 57, 83, 250, n=3), Ly(33 * 2, 28, 28, 512, n=7),
+    Ly(49, 41, 54, 245, n=5), Ly(100, 27, 41, 375, pad=0, n=7),
 ]
 
 
