@@ -1773,15 +1773,18 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Laye
 // item length, in steps of 12 down to kItemStepsMin, with which they still do: the launch lasts as
 // long as an item, and the free slots would stay idle.  Measured (us, one call, 48 / 72 / 144 steps):
 // AlexNet-shaped stack 35.8 / 42.8 / 63.3, SqueezeNet 42.2 / 37.6 / 38.3; launches above the line keep the long
-// items: ResNet-18 (2882 items) 65.7 / 62.9 / 52.1, ResNet-50 131 / 111 / 98, MobileNetV1 48 / 46 / 44.
+// items: ResNet-18 65.7 / 62.9 / 52.1, ResNet-50 131 / 111 / 98, MobileNetV1 48 / 46 / 44 (all of them before 3x3 layers ran in items of workgroups,
+// and before the share of a SIMD counted, below, by which the ResNet-18-shaped launch takes items of 60 steps).
 constexpr int kItemStepsShortHalf = 48, kItemStepsMin = 48;
 constexpr int kItemsResident = 256 * 3 * kItemWaves;
 
 // Items of whole workgroups: with W of them if each took one chunk (weighted by their blocks of pixels), an item takes W / 450, at least two
 // chunks: three workgroups fit a CU, and an item spends 5 us outside its products.  Launches of fewer than
-// 220 keep to single-wavefront items.  Measured over 30 launches of six stacks at batch 1-4 and 128-320 pixels, us at 1 / 2 / 4 / 8
-// chunks against none: W = 232 (AlexNet-shaped) 34 / 33 / 41 / 65 against 45, 803 (ResNet-18) 55 / 46 / 49 / 76 against 53, 1585 88 / 78 / 70 / 86
-// against 93, 3136 160 / 126 / 117 / 110 against 151, 7488 (VGG-16) 253 / 193 / 172 / 165 against 279; W = 154 (GoogLeNet, 128 x 160) 68 against 53.
+// 220 keep to single-wavefront items.  Measured over 50 launches of five stacks at batch 1-4 and 96-320 pixels, us at 1 / 2 / 4 / 8
+// chunks against none: W = 232 (AlexNet-shaped) 35 / 34 / 41 / 67 against 43, 803 (ResNet-18) 59 / 48 / 54 / 83 against 56, 995 (ResNet-50) 106 / 101 / 98 / 119
+// against 106, 2146 (ResNet-18, 3x162x237) 126 / 112 / 103 / 105 against 116, 7488 (VGG-16) 285 / 233 / 211 / 203 (16: 198) against 296; below, W = 216 (GoogLeNet, 201 x 134)
+// 53 / 59 / 86 / 100 against 60.  Taken together 4 % over the best of 0, 1, 2, 3, 4, 6, 8 and 16 for each launch; no other line, divisor or least range tried came below 3 %
+// (three chunks at least: ResNet-18 48 -> 53).  The worst: W = 397 (AlexNet, 2x225x156), 60 where three chunks give 42 and fill the chip once.
 // float16, W in chunks of 3x3 filters of 64 x 112 outputs, four chunks of 1x1 filters to one: below 600 single-wavefront items; else the channels stay whole
 // if no layer has more than 12 chunks (48 of 1x1 filters), since partial tiles and the launch that adds them cost 6 us, and otherwise a range is W / 330 chunks, at
 // least four: an item of 512 channels takes 24 us.  us a call at 0 / 4 / 8 / 12 or more chunks, none longer than 12: W = 662 (AlexNet-shaped, 2x211x317) 25 / 29 / 29 / 23, 1273
@@ -1849,9 +1852,10 @@ static ItemTarget items_target(int n, const Geo *geos, LayerPlan *known) {
         if ((double)longest[tm] * tm > share)
             while (target.steps > kItemStepsMin && target.steps * (tm == 4 ? 0.75 : 1.0) * tm > share) target.steps -= 12;
     // Launches of between one and one and a half times the items that are resident at once end with a round that fills the chip in part: there the
-    // 7x7 layers, whose items are many and bound by their gathers of pixels, take four panels per tile (half the items and gathers).  us a call without / with, items:
-    // ResNet-18-shaped stack 48.7 / 45.6 (224x224, 3344), 52.0 / 48.1 (180x256, 3660), 57.1 / 53.2 (2x150x150, 3660), 61.7 / 62.8 (260x270, 3786), GoogLeNet 88.2 / 86.5
-    // (300x280, 3963); outside: ResNet-50 70 / 74 (150x190, 5537), ResNet-18 36.4 / 39.8 (120x110, 2414).
+    // 7x7 layers, whose items are many and bound by their gathers of pixels, take four panels per tile (half the items and gathers).  54 launches of three stacks at
+    // batch 1-3 and 96-320 pixels, times without / with (geometric means, in brackets the smallest and largest), by items over those resident: 0.66-0.9 0.98 (0.92-1.03), 1.0-1.5 1.02
+    // (0.95-1.08; ResNet-18-shaped stack at 192x253 55.0 / 51.0 us, at 318x182 62.4 / 65.3), 1.5-1.9 0.97 (0.93-1.02), 2.0-2.5 1.00 (0.98-1.01), more 1.01 (0.98-1.03):
+    // a partly filled round counts while it is the second.
     if (target.steps != fitting) items = total_at(target.steps);
     target.wide = items > kItemsResident && items <= kItemsResident * 3L / 2;
     return target;

@@ -21,10 +21,10 @@
 //     output channels only.
 // What bounds it now: large layers the power limit (256 channels at 8x56x56 take 20 % less time when the pixels are zeros),
 // small launches the issue of vector instructions beside the products (a 16x16x32 product leaves room for one, splitting
-// takes one for each) and 5 us of an item before its first and after its last product.  Measured, us a call,
-// single-wavefront kernels -> this: 256 channels at 8x56x56 252 -> 134 (221 TFLOP/s), 512 at 4x28x28 156 -> 101, 64 at 224x224
-// 44.5 -> 35, VGG-16-shaped stack 278 -> 166, ResNet-50 100 -> 85, ResNet-18 50.4 -> 41.6, AlexNet 45 -> 33.  (32x32x16 products
-// leave room for four vector instructions, but blocks of 32 pixels fill a row of 28 or 56 worse: 256 channels at 8x56x56 156.
+// takes one for each) and 5 us of an item before its first and after its last product.  Measured, us a call with weights and pixels from HBM,
+// single-wavefront kernels -> this: 256 channels at 8x56x56 253 -> 177 (165 in a row of calls, 179 TFLOP/s), 512 at 4x28x28 156 -> 125, 128 at 112x112
+// 44.7 -> 33.2, 64 at 224x224 44.7 -> 40.7; VGG-16-shaped stack 296 -> 197, ResNet-50 106 -> 98, ResNet-18 56 -> 48.5, AlexNet 43 -> 34.  (32x32x16 products
+// leave room for four vector instructions, but blocks of 32 pixels fill a row of 28 or 56 worse: 256 channels at 8x56x56 with six products 156 against 134.
 // 1x1 layers lose: a chunk of theirs is one tap, over before the next chunk has arrived.)
 //
 // Patch in LDS: [part h, m, l][channel slot c % 4][pixel][8 channels], 16 bytes per pixel and slot, so that the 16
