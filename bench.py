@@ -47,11 +47,11 @@ KIND_LABEL = {0: "direct", 1: "im2col_gemm", 2: "wino_f2", 3: "wino_f4", 4: "dep
 PHASE_KERNELS = {
     "transform": "transform_kernel (grouped weight transformation, all kinds)",
     "direct": "direct_conv_many_klane_kernel<float> (direct convolution of all layers in one launch, lanes along the output channels, vector ALU)",
-    "im2col_gemm": "gemm_items_kernel + gemm_reduce_kernel (implicit GEMM work items of all layers, float32 MFMA; 3x3 stride-1 layers bfloat16 MFMA, three parts per float32)",
+    "im2col_gemm": "gemm_items_kernel (implicit GEMM work items of all layers, float32 MFMA; 3x3 stride-1 layers bfloat16 MFMA, three parts per float32)",
     "wino_f2": "wino_f2: wino_input_many + wino_gemm_many (float32 MFMA) + wino_output_many",
     "wino_f4": "wino_f4: wino_input_many + wino_gemm_many (float32 MFMA) + wino_output_many",
 }
-PHASE_LAUNCHES = {"transform": 1, "direct": 1, "im2col_gemm": 2, "wino_f2": 3, "wino_f4": 3}
+PHASE_LAUNCHES = {"transform": 1, "direct": 1, "im2col_gemm": 1, "wino_f2": 3, "wino_f4": 3}
 
 
 def csrc_digest():
@@ -406,7 +406,7 @@ def main():
                           "transform_bytes_per_step": sum(p.transform_bytes for p in pairs)}))
         return
 
-    # A step is ten kernel launches in five calls (the grouped transformation, then one grouped
+    # A step is nine kernel launches in five calls (the grouped transformation, then one grouped
     # forward call per kernel kind), issued eagerly on torch's current stream: the GPU needs about
     # 0.35 ms for them, the host far less to enqueue them, so the queue never runs dry and the
     # events recorded between the calls split the step into its phases.

@@ -160,7 +160,7 @@ int nnv_conv_forward_relu(const nnv_conv_desc *desc, nnv_kind kind, const void *
  * layer (Algorithm 1's input, Section 3.3, Table 2), and a batch-1 layer alone neither fills
  * the GPU nor outlasts its own launch: IM2COL_GEMM layers of one storage type share one
  * launch of work items (output tile x range of the reduction; a wavefront each, or a workgroup each for
- * layers large enough) and one reduction launch (float16: one more, which makes copies of inputs in octets
+ * layers large enough; float16: and one more, which makes copies of inputs in octets
  * of channels, where a layer of a wavefront per item has a filter larger than 1x1); Winograd layers of one kind and storage type share three launches (all
  * input transforms, all tile GEMMs, all output transforms), except those nnv_conv_forward
  * runs as one fused kernel; DEPTHWISE layers of one storage type share one launch; DIRECT

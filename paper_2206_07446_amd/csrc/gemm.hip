@@ -818,6 +818,69 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
     return make_rsrc(g.y, (uint32_t)g.N * (uint32_t)(g.K * g.P * g.Q) * (g.half_out ? 2u : 4u));
 }
 
+// ---- reductions cut into ranges: the partial sums of a tile meet in the workspace, and the wavefront or workgroup that stores the last of them adds
+// them up, in the order of the ranges, and stores y.  A launch of its own for that took 4-6.5 us behind all items; here most tiles are added up while others
+// are still multiplied.  What is left of it is latency, one trip to memory for the stores, one or two for the word of arrivals, one per few ranges.  us a call, launch / this:
+// ResNet-18-shaped stack 39.2 / 36.5, MobileNetV2-shaped plan 33.6 / 30.0, ResNet-50 in float16 39.1 / 34.5.
+// Nothing in the workspace has to be cleared: a tile's word of arrivals counts while its upper 48 bits are kSplitMark, any other content means that
+// nobody has arrived, and the last one clears it.  The partial sums are stored through to memory and read past the caches that other
+// XCDs do not share (sc1, the scope of one GPU); a wavefront waits for its stores before it, or the workgroup's first thread, arrives.
+struct SplitTile {
+    char *tile;         // [range][wavefront][block of 16 x 16][lane] floatx4, then the word of arrivals in 256 bytes
+    int ks, n;          // which range; ranges in all (1: the item stores y itself)
+};
+constexpr int kSplitScope = 16;                         // sc1
+constexpr unsigned long long kSplitMark = 0x7fa5c3e996b1ull;
+constexpr size_t kSplitWord = 256;
+
+// One thread; true for the last of n.  (Every exchange that fails means that another arrival's went through, and there are n of them.)
+__device__ __forceinline__ bool split_arrive(char *word, const int n) {
+    unsigned long long *w = reinterpret_cast<unsigned long long *>(word);
+    unsigned long long seen = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) {
+        const int before = seen >> 16 == kSplitMark ? (int)(seen & 0xffff) : 0;
+        const bool last = before + 1 >= n;
+        if (__hip_atomic_compare_exchange_strong(w, &seen, last ? 0ull : kSplitMark << 16 | (unsigned long long)(before + 1), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return last;
+    }
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void split_put(const floatx4 (&acc)[TM][TN], const __amdgpu_buffer_rsrc_t res, const uint32_t off) {
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[m][t]), res, off + (m * TN + t) * 1024u, 0u, kSplitScope);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// acc = the sum of n partial sums `stride` bytes apart, as many of them on their way as registers allow.
+template <int TM, int TN>
+__device__ __forceinline__ void split_sum(floatx4 (&acc)[TM][TN], const __amdgpu_buffer_rsrc_t res, const uint32_t off, const uint32_t stride, const int n) {
+    constexpr int NB = TM * TN, G = NB >= 12 ? 2 : NB >= 7 ? 3 : 6;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b / TN][b % TN] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int z = 0; z < n; z += G) {
+        // (ranges past the last one load the last one again and are not added)
+        floatx4 p[G][NB];
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                p[i][b] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(res, off + b * 1024u, (uint32_t)min(z + i, n - 1) * stride, kSplitScope));
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+            if (z + i < n) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b / TN][b % TN] += p[i][b];
+            }
+    }
+}
+
 #include "tile_gemm.h"
 
 // The KS partial tiles of a workgroup's tile nt meet in LDS: red[((nt * KS + ks) * NREG + reg) * 64 + lane].
@@ -911,10 +974,10 @@ __global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void
 // nsplit ranges its reduction is cut into, the ranges sized so that items of different layers
 // take about the same time.  The chip's dispatcher balances the items over the CUs; two to four
 // items are resident per SIMD, so one item's addressing and first loads run under another's
-// MFMAs.  A split layer's items store partial tiles, which a second launch adds in fixed order.
+// MFMAs.  A split layer's items store partial tiles; the last of a tile's items adds them in fixed order.
 struct GemmItemLayer {
     GemmParams g;
-    float *part;        // partial tiles of a split layer (workspace): [tile][split][reg][lane]
+    char *part;         // partial tiles of a split layer (workspace)
     int ntn;            // tiles along the pixels
     int nsplit;         // ranges of the reduction (1: the item stores y itself)
     int mode, tm;       // chunking mode (ModeT); 16-row panels per tile (1, 2 or 4)
@@ -939,13 +1002,11 @@ struct GemmItemRec {
 static_assert(sizeof(GemmItemRec) == 64, "sixteen scalar registers");
 struct GemmItemTable {
     GemmItemRec layer[kMaxGemmLayers];
-    // first item / first reduction workgroup of each layer, INT_MAX beyond the last layer: a
-    // workgroup finds its layer by counting the entries it has reached (table_find)
-    int item0[kMaxGemmLayers], red0[kMaxGemmLayers];
+    // first item of each layer, INT_MAX beyond the last layer: a workgroup finds its layer by counting the entries it has reached (table_find)
+    int item0[kMaxGemmLayers];
     char *part_base;
     int nitems;
     int group;          // consecutive items handed to one XCD
-    int half;           // float16 storage
 };
 static_assert(sizeof(GemmItemTable) <= 4096, "the table is passed by value as the kernel argument");
 
@@ -963,7 +1024,17 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
     else if constexpr (!HALF && MODE == 1) gemm_accumulate_1x1<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     __builtin_amdgcn_s_setprio(3);
-    if (L.nsplit == 1) {
+    if (L.nsplit > 1) {
+        constexpr uint32_t BYTES = TM * TN * 1024;
+        char *tile = L.part + (size_t)(mt * L.ntn + nb) * ((size_t)L.nsplit * BYTES + kSplitWord);
+        const __amdgpu_buffer_rsrc_t res = make_rsrc(tile, (uint32_t)L.nsplit * BYTES);
+        split_put<TM, TN>(acc, res, (uint32_t)ks * BYTES + (uint32_t)lane * 16u);
+        int last = 0;
+        if (lane == 0) last = split_arrive(tile + (size_t)L.nsplit * BYTES, L.nsplit);
+        if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+        split_sum<TM, TN>(acc, res, (uint32_t)lane * 16u, BYTES, L.nsplit);
+    }
+    {
         RowState<TM> rs;
         gemm_rows<TM, !HALF && (MODE == 1 || MODE == 3)>(L.g, mt * TM, lane >> 4, rs);
         const __amdgpu_buffer_rsrc_t yres = gemm_y_rsrc(L.g);
@@ -992,15 +1063,6 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
                     const uint32_t off = rs.off[m][j] == kOobOffset ? kOobOffset : rs.off[m][j] + pixoff[t];
                     gemm_store(yres, relu, half_out, off, rs.bias[m][j], acc[m][t][j]);
                 }
-    } else {
-        constexpr int NREG = TM * TN * 4;
-        float *o = L.part + ((size_t)(mt * L.ntn + nb) * L.nsplit + ks) * (NREG * 64) + lane;
-#pragma unroll
-        for (int m = 0; m < TM; ++m)
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[((m * TN + t) * 4 + j) * 64] = acc[m][t][j];
     }
 }
 
@@ -1030,7 +1092,7 @@ __device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItem
     L.mode = r.mode;
     gemm_derived(g, half, r.mode);
     g.relu = r.relu;
-    L.part = reinterpret_cast<float *>(tbl->part_base + (size_t)r.part256 * 256);
+    L.part = tbl->part_base + (size_t)r.part256 * 256;
     L.ntn = (g.npix + 31) >> 5;
     L.nsplit = r.nsplit;
     L.tm = r.tm;
@@ -1093,7 +1155,7 @@ __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const 
     int per = chunks;
     if (nsplit > 1) per = __builtin_amdgcn_readfirstlane((chunks + nsplit - 1) / nsplit);
     const int c0 = ks * per, c1 = min(chunks, c0 + per);
-    float *part = nsplit == 1 ? nullptr : reinterpret_cast<float *>(tbl->part_base + (size_t)r.part256 * 256) + ((size_t)(mt * ntiles + nt) * nsplit + ks) * (size_t)(tile_regs(r) * 256);
+    const SplitTile sp{tbl->part_base + (size_t)r.part256 * 256 + (size_t)(mt * ntiles + nt) * ((size_t)nsplit * (tile_regs(r) * 1024u) + kSplitWord), ks, nsplit};
     if constexpr (HALF && TILE != kLargeTiles) {
         if (r.mode == kModeTaps) {
             if (r.tm == 5) few_item<7>(T, mt, nt, lds);
@@ -1101,22 +1163,22 @@ __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const 
             return;
         }
         if (r.mode == 3 && r.sh == 2) {
-            tile_item<true, 1, 4, true, kTilePatch2 / 64>(T, mt, nt, c0, c1, part, lds);
+            tile_item<true, 1, 4, true, kTilePatch2 / 64>(T, mt, nt, c0, c1, sp, lds);
             return;
         }
         if (r.mode == 1) {
             switch (r.tm) {
-                case 6: one_item<2, 7, true>(T, mt, nt, c0, c1, part, lds); break;
-                case 5: one_item<1, 7, true>(T, mt, nt, c0, c1, part, lds); break;
-                case 2: one_item<2, 4, false>(T, mt, nt, c0, c1, part, lds); break;
-                default: one_item<1, 4, false>(T, mt, nt, c0, c1, part, lds); break;
+                case 6: one_item<2, 7, true>(T, mt, nt, c0, c1, sp, lds); break;
+                case 5: one_item<1, 7, true>(T, mt, nt, c0, c1, sp, lds); break;
+                case 2: one_item<2, 4, false>(T, mt, nt, c0, c1, sp, lds); break;
+                default: one_item<1, 4, false>(T, mt, nt, c0, c1, sp, lds); break;
             }
             return;
         }
     }
-    if constexpr (TILE == kLargeTiles) tile_item<HALF, 2, 7, true>(T, mt, nt, c0, c1, part, lds);
-    else if (r.tm == 5) tile_item<HALF, 1, 7, false>(T, mt, nt, c0, c1, part, lds);
-    else tile_item<HALF, 1, 4, false>(T, mt, nt, c0, c1, part, lds);
+    if constexpr (TILE == kLargeTiles) tile_item<HALF, 2, 7, true>(T, mt, nt, c0, c1, sp, lds);
+    else if (r.tm == 5) tile_item<HALF, 1, 7, false>(T, mt, nt, c0, c1, sp, lds);
+    else tile_item<HALF, 1, 4, false>(T, mt, nt, c0, c1, sp, lds);
 }
 
 template <bool HALF, int TILE>
@@ -1253,111 +1315,6 @@ __global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const 
         NNV_LAYER_BLOCK(24, 2, 2)
     }
 #undef NNV_LAYER_BLOCK
-}
-
-__device__ static inline int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
-
-// Sum of nsplit partial values of four lanes, zs apart, in the order of the ranges; twelve loads in flight.
-__device__ __forceinline__ float4 sum_partials(const float4 *src, const size_t zs, const int nsplit) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    constexpr int kInFlight = 12;
-    for (int z = 0; z < nsplit; z += kInFlight) {
-        // (ranges past the last one load the last one again and are not added)
-        float4 p[kInFlight];
-#pragma unroll
-        for (int i = 0; i < kInFlight; ++i) p[i] = src[(size_t)min(z + i, nsplit - 1) * zs];
-#pragma unroll
-        for (int i = 0; i < kInFlight; ++i)
-            if (z + i < nsplit) { v.x += p[i].x; v.y += p[i].y; v.z += p[i].z; v.w += p[i].w; }
-    }
-    return v;
-}
-
-// The reduction of a layer whose items are whole workgroups: [tile][range][wavefront][register][lane].
-__device__ __forceinline__ void tile_reduce(const GemmItemTablePtr tbl, const GemmItemRec &r, const int blk, const bool half) {
-    TileLayer T;
-    load_tile_layer(T, r, half);
-    const int regs = tile_regs(r), per_tile = regs * 256;        // a multiple of 1024: a workgroup stays in one tile
-    const int wgs = regs >> 2;                                   // workgroups per tile
-    const int tile = __builtin_amdgcn_readfirstlane(blk / wgs), e = (blk - tile * wgs) * 1024 + threadIdx.x * 4;
-    const float *part = reinterpret_cast<const float *>(tbl->part_base + (size_t)r.part256 * 256);
-    const float4 v = sum_partials(reinterpret_cast<const float4 *>(part + (size_t)tile * r.nsplit * per_tile + e), (size_t)per_tile / 4, r.nsplit);
-    const int wr = e >> 6, lane0 = e & 63;
-    const int wave = wr / regs, reg = wr - wave * regs;
-    const int tm = r.tm & 3, tn = r.tm & 4 ? 7 : 4;
-    const int blk16 = reg >> 2, j = reg & 3, m = blk16 / tn, t = blk16 - m * tn;
-    const bool one = half && r.mode == 1;
-    const int ntiles = one ? one_tiles(T, r) : T.N * T.nth * T.ntw;
-    const int mt = __builtin_amdgcn_readfirstlane(tile / ntiles), nt = tile - mt * ntiles;
-    const int rest = one ? 0 : __builtin_amdgcn_readfirstlane(nt / T.ntw), img = one ? 0 : __builtin_amdgcn_readfirstlane(rest / T.nth);
-    const TilePos at{img, (rest - img * T.nth) * T.th, (nt - rest * T.ntw) * T.tw, (mt * 4 + wave) * tm};
-    const int k = at.mb0 * 16 + gemm_row(!half, tm, m, lane0 >> 4, j), n = t * 16 + (lane0 & 15);
-    const bool rok = k < T.K;
-    const float bv = T.bias && rok ? T.bias[k] : 0.f;
-    const int PQ = T.P * T.Q;
-    const SmallDiv by_tw(T.tw);
-    const uint32_t esz = half ? 2u : 4u;
-    const __amdgpu_buffer_rsrc_t yres = make_rsrc(T.y, (uint32_t)(T.N * T.K) * (uint32_t)PQ * esz);
-    const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t off;
-        if (one) off = one_out_offset(T, nt * (tn * 16) + one_pixel(tn == 7, tn, t, (lane0 & 15) + i));
-        else {
-            const int pix = tile_out_pixel(T, at, by_tw, n + i);
-            off = pix >= 0 ? (uint32_t)(img * T.K * PQ + pix) * esz : kOobOffset;
-        }
-        gemm_store(yres, T.relu, half, rok && off != kOobOffset ? off + (uint32_t)(k * PQ) * esz : kOobOffset, bv, vv[i]);
-    }
-}
-
-// Adds the nsplit partial tiles of every split layer in the order of the ranges and stores y.
-// A thread owns four consecutive lanes of one accumulator register (16-byte loads).
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmItemTable tbl_arg) {
-    const GemmItemTablePtr tbl = (GemmItemTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
-    const int b = blockIdx.x;
-    int first;
-    const int li = table_find<kMaxGemmLayers>(&tbl->red0[0], b, first);      // the last layer that starts at or before b
-    const GemmItemRec rec = load_item_rec(tbl, li);
-    if (rec.tile) {
-        tile_reduce(tbl, rec, b - first, tbl->half != 0);
-        return;
-    }
-    GemmItemLayer L;
-    load_item_layer(L, tbl, rec, tbl->half != 0);
-    const int nreg = L.tm * 8;                                   // accumulator registers per lane: TM x 2 blocks x 4
-    const int per_tile = nreg * 64;
-    const int e = ((b - first) * 256 + threadIdx.x) * 4;          // over [tile][reg][lane]
-    const int tile = e / per_tile, rl = e - tile * per_tile;
-    const int reg = rl >> 6, lane0 = rl & 63;
-    if (tile >= ceil_div_dev(L.g.K16, L.tm) * L.ntn) return;     // second half of the last workgroup of an odd tile count
-    const float4 *src = reinterpret_cast<const float4 *>(L.part + (size_t)tile * L.nsplit * per_tile + rl);
-    const size_t zs = (size_t)per_tile / 4;
-    const float4 v = sum_partials(src, zs, L.nsplit);
-    // the four values are rows (lane0 / 16) * 4 + jj of panel m, pixels (lane0 % 16) .. + 3 of block t
-    const int mt = tile / L.ntn, nb = tile - mt * L.ntn;
-    const int m = reg >> 3, t = (reg >> 2) & 1, jj = reg & 3;
-    const int PQ = L.g.P * L.g.Q, Kg = L.g.Kg, npix = L.g.npix;
-    const bool relu = L.g.relu, half_out = L.g.half_out;
-    const float *bias = L.g.bias;
-    const __amdgpu_buffer_rsrc_t yres = gemm_y_rsrc(L.g);
-    const int mb0 = mt * L.tm, grp = mb0 / L.g.kg16, mbl = mb0 - grp * L.g.kg16;
-    const int kl = mbl * 16 + gemm_row(!half_out && (L.mode == 1 || L.mode == 3), L.tm, m, lane0 >> 4, jj);
-    const int k = grp * Kg + kl;
-    const bool rok = kl < Kg;
-    const float bv = (bias && rok) ? bias[k] : 0.f;
-    const uint32_t esz = half_out ? 2u : 4u;
-    const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = (lane0 & 15) + i;
-        const int n = nb * 32 + (L.mode == kModePairs && half_out ? c * 2 + t : t * 16 + c);
-        const bool valid = rok && n < npix;
-        const int nn = valid ? n : 0;
-        const int img = nn / PQ;
-        const uint32_t off = valid ? ((uint32_t)(img * L.g.K + k) * (uint32_t)PQ + (uint32_t)(nn - img * PQ)) * esz : kOobOffset;
-        gemm_store(yres, relu, half_out, off, bv, vv[i]);
-    }
 }
 
 // half NCHW -> half [N][cpad / 8][H][W][8]: octets of channels, zero padded to a multiple of 32.
@@ -1687,7 +1644,7 @@ static void split_tile(const Geo &g, const int chunks, ItemPlan *ip) {
     const int per = ceil_div(all, n);
     ip->nsplit = ceil_div(all, per);
     ip->steps = all * g.r * g.s;
-    ip->part_bytes = ip->nsplit > 1 ? (size_t)ip->nmt * ip->ntn * ip->nsplit * (ip->tm * ip->tn * 1024) * sizeof(float) : 0;
+    ip->part_bytes = ip->nsplit > 1 ? (size_t)ip->nmt * ip->ntn * (ip->nsplit * (size_t)(ip->tm * ip->tn * 4096) + kSplitWord) : 0;
 }
 
 // The layer in items of whole workgroups, before its channels are cut (tile = 0: it has none).
@@ -1757,7 +1714,7 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Laye
     // ranges are ceil(nunits / nsplit) units long: drop ranges that would come out empty
     const int per = ceil_div(nunits, (int)nsplit);
     ip.nsplit = ceil_div(nunits, per);
-    ip.part_bytes = ip.nsplit > 1 ? (size_t)ip.nmt * ip.ntn * ip.nsplit * (ip.tm * 8) * 64 * sizeof(float) : 0;
+    ip.part_bytes = ip.nsplit > 1 ? (size_t)ip.nmt * ip.ntn * (ip.nsplit * (size_t)(ip.tm * 2048) + kSplitWord) : 0;
     return ip;
 }
 
@@ -1786,7 +1743,7 @@ constexpr int kItemsResident = 256 * 3 * kItemWaves;
 // 53 / 59 / 86 / 100 against 60.  Taken together 4 % over the best of 0, 1, 2, 3, 4, 6, 8 and 16 for each launch; no other line, divisor or least range tried came below 3 %
 // (three chunks at least: ResNet-18 48 -> 53).  The worst: W = 397 (AlexNet, 2x225x156), 60 where three chunks give 42 and fill the chip once.
 // float16, W in chunks of 3x3 filters of 64 x 112 outputs, four chunks of 1x1 filters to one: below 600 single-wavefront items; else the channels stay whole
-// if no layer has more than 12 chunks (48 of 1x1 filters), since partial tiles and the launch that adds them cost 6 us, and otherwise a range is W / 330 chunks, at
+// if no layer has more than 12 chunks (48 of 1x1 filters), since partial tiles and their sums cost 3 us (6 when a launch added them), and otherwise a range is W / 330 chunks, at
 // least four: an item of 512 channels takes 24 us.  us a call at 0 / 4 / 8 / 12 or more chunks, none longer than 12: W = 662 (AlexNet-shaped, 2x211x317) 25 / 29 / 29 / 23, 1273
 // (GoogLeNet, 3x210x173) 64 / 66 / 58 / 58, 1380 (MobileNetV1, 3x273x258) 48 / 39 / 35 / 35; longer: 983 (ResNet-18) 38 / 23 / 31 / 31, 1381 (ResNet-18, 295x215) 38 / 27 / 30 / 37, 3374
 // (ResNet-50, 301x227) 72 / 60 / 55 / 63, 5085 (ResNet-50, 2x217x257) 103 / 85 / 74 / 69, 7488 (VGG-16) 92 / 80 / 69 / 59; W = 197 (SqueezeNet, 2x132x119) 16 / 22 / 22 / 22.
@@ -1878,8 +1835,7 @@ void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes) {
     }
 }
 
-// One item launch of n planned layers of one storage type, with the copies of x in front of it and the reduction behind it
-// that they need; ws[i]: layer i's partial tiles and copy.
+// One item launch of n planned layers of one storage type, with the copies of x in front of it that they need; ws[i]: layer i's partial tiles and copy.
 static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, const void *const *x, const void *const *w,
                                  const float *const *bias, void *const *y, void *const *ws, hipStream_t st) {
     const bool half = geos[0].dtype == NNV_F16;
@@ -1906,7 +1862,7 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     std::stable_sort(order, order + n, [&](int a, int b) { return item_len(a) > item_len(b); });
     GemmItemTable tbl{};
     OctetTable cl{};
-    int items = 0, red = 0, ncl = 0, clblocks = 0;
+    int items = 0, ncl = 0, clblocks = 0;
     char *base = static_cast<char *>(ws[0]);
     for (int i = 1; i < n; ++i) base = std::min(base, static_cast<char *>(ws[i]));
     for (int o = 0; o < n; ++o) {
@@ -1936,7 +1892,6 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
         }
         L.part256 = (uint32_t)((region - base) / 256);
         tbl.item0[o] = items;
-        tbl.red0[o] = red;
         L.nsplit = (uint16_t)ip.nsplit;
         L.mode = ip.mode;
         L.tm = ip.tm;
@@ -1950,16 +1905,13 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
                 L.sw = (uint16_t)ip.shape.ntw; L.pw = (uint16_t)ip.shape.nth;
             }
             items += count * kItemWaves;
-            if (ip.nsplit > 1) red += ip.nmt * ip.ntn * (ip.tm * ip.tn);
         } else {
             items += tiles ? ceil_div(count, kItemWaves) * kItemWaves : count;
-            if (ip.nsplit > 1) red += ceil_div(ip.nmt * ip.ntn * (ip.tm * 8), 16);     // 1024 values per workgroup
         }
     }
-    for (int i = n; i < kMaxGemmLayers; ++i) tbl.item0[i] = tbl.red0[i] = INT_MAX;
+    for (int i = n; i < kMaxGemmLayers; ++i) tbl.item0[i] = INT_MAX;
     tbl.nitems = items;
     tbl.group = 2;       // workgroups (of kItemWaves items) handed to one XCD in a row
-    tbl.half = half;
     tbl.part_base = base;
     if (ncl > 0) {
         for (int i = ncl; i < kMaxGemmLayers; ++i) cl.block0[i] = INT_MAX;
@@ -1974,12 +1926,11 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     else if (large) hipLaunchKernelGGL((gemm_items_kernel<false, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (tiles) hipLaunchKernelGGL((gemm_items_kernel<false, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else hipLaunchKernelGGL((gemm_items_kernel<false, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    if (red > 0) hipLaunchKernelGGL(gemm_reduce_kernel, dim3(red), dim3(256), 0, st, tbl);
     return hipGetLastError();
 }
 
-// Launches layers [0, n) (all of one storage type, n <= kMaxGemmLayers) as one item launch plus,
-// if any layer is split, one reduction launch.  ws[i] is layer i's own workspace region of
+// Launches layers [0, n) (all of one storage type, n <= kMaxGemmLayers) as one item launch, with a
+// launch of copies in front if a float16 layer reads one.  ws[i] is layer i's own workspace region of
 // im2col_items_workspace_bytes of these layers.
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
                                void *const *y, void *const *ws, hipStream_t st) {

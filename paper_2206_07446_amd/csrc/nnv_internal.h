@@ -85,8 +85,7 @@ size_t im2col_workspace_bytes(const Geo &g);
 hipError_t launch_im2col(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st);
 
 // Many independent IM2COL_GEMM layers (one storage type, at most kMaxGemmLayers) in one launch of
-// work items, of single wavefronts or whole workgroups (tile_gemm.h), plus one launch in front if a float16 layer reads a copy of x and one
-// reduction launch if a layer's channels are split; ws[i] is layer i's own region of im2col_items_workspace_bytes.
+// work items, of single wavefronts or whole workgroups (tile_gemm.h), plus one launch in front if a float16 layer reads a copy of x; ws[i] is layer i's own region of im2col_items_workspace_bytes.
 constexpr int kMaxGemmLayers = 56;
 bool im2col_items_supported(const Geo &g);
 void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes);      // of each of the layers of a launch

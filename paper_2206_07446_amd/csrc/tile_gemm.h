@@ -448,16 +448,19 @@ __device__ __forceinline__ void tile_accumulate_half(const TileLayer &g, const T
     chunk_of(std::false_type{}, c1 - 1);
 }
 
-// A wavefront's sums of one range, [register][lane].
+// The sums of a tile whose reduction is cut, added by whichever of its workgroups (or wavefronts) is done last.  true: acc holds them.
 template <int TM, int TN>
-__device__ __forceinline__ void tile_put_partial(const floatx4 (&acc)[TM][TN], float *part, const int wave, const int lane) {
-    float *o = part + (size_t)wave * (TM * TN * 256) + lane;
-#pragma unroll
-    for (int m = 0; m < TM; ++m)
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[((m * TN + t) * 4 + j) * 64] = acc[m][t][j];
+__device__ __forceinline__ bool tile_fold(const SplitTile &sp, const int wave, const int lane, char *lds, floatx4 (&acc)[TM][TN]) {
+    const uint32_t bytes = 4 * TM * TN * 1024, mine = (uint32_t)wave * (TM * TN * 1024) + (uint32_t)lane * 16u;
+    const __amdgpu_buffer_rsrc_t res = make_rsrc(sp.tile, (uint32_t)sp.n * bytes);
+    split_put<TM, TN>(acc, res, (uint32_t)sp.ks * bytes + mine);
+    __syncthreads();                // (and none reads lds any more)
+    int *flag = reinterpret_cast<int *>(lds);
+    if (threadIdx.x == 0) flag[0] = split_arrive(sp.tile + (size_t)sp.n * bytes, sp.n);
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(flag[0]) == 0) return false;
+    split_sum<TM, TN>(acc, res, mine, bytes, sp.n);
+    return true;
 }
 
 // Bias, clamp and store; off: offsets of the lane's pixels in channel 0 of their image, or out of range.  PAIRS: blocks 2 i and 2 i + 1
@@ -501,9 +504,9 @@ __device__ __forceinline__ uint32_t one_out_offset(const TileLayer &g, const int
     return (uint32_t)(img * g.K * PQ + n - img * PQ) * 2u;
 }
 
-// One work item: tile (mt, nt) over the chunks [c0, c1); part: where its sums go if the layer's channels are split, else null.
+// One work item: tile (mt, nt) over the chunks [c0, c1).
 template <bool HALF, int TM, int TN, bool DOUBLE, int NT = 3>
-__device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, const int nt, const int c0, const int c1, float *part, char *lds) {
+__device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, const int nt, const int c0, const int c1, const SplitTile sp, char *lds) {
     const int lane = threadIdx.x & 63, col = lane & 15, slot = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rest = nt / g.ntw, img = rest / g.nth;
@@ -533,9 +536,9 @@ __device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, cons
         if (__builtin_amdgcn_readfirstlane(bad[0] | bad[1] | bad[2] | bad[3]) != 0) tile_accumulate_float<TM, TN>(g, at, c0, c1, lds, acc);
     }
     __builtin_amdgcn_s_setprio(3);
-    if (part) {
-        tile_put_partial<TM, TN>(acc, part, wave, lane);
-        return;
+    // (tiles of 128 channels are not split; the float16 one's compiler spills 672 bytes per lane if no branch stands between its loop and its stores)
+    if constexpr (HALF || TM == 1) {
+        if (sp.n > 1 && !tile_fold<TM, TN>(sp, wave, lane, lds, acc)) return;
     }
     const SmallDiv by_tw(g.tw);
     uint32_t off[TN];
@@ -553,7 +556,7 @@ __device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, cons
 // are in LDS, the next ones on their way to registers; a chunk is TM TN products only, so that less in flight would wait for memory.
 constexpr int kOneChunks = 4;
 template <int TM, int TN, bool PAIRS>
-__device__ __forceinline__ void one_item(const TileLayer &g, const int mt, const int nt, const int c0, const int c1, float *part, char *lds) {
+__device__ __forceinline__ void one_item(const TileLayer &g, const int mt, const int nt, const int c0, const int c1, const SplitTile sp, char *lds) {
     static_assert(PAIRS ? TN <= 8 : TN <= 4, "a wavefront's 64 lanes cover the pixels");
     constexpr uint32_t SUB = TN * 256, CHUNK = 4 * SUB;
     const int lane = threadIdx.x & 63, col = lane & 15, slot = lane >> 4;
@@ -666,10 +669,7 @@ __device__ __forceinline__ void one_item(const TileLayer &g, const int mt, const
     }
     chunks_of(std::false_type{}, ch);
     __builtin_amdgcn_s_setprio(3);
-    if (part) {
-        tile_put_partial<TM, TN>(acc, part, wave, lane);
-        return;
-    }
+    if (sp.n > 1 && !tile_fold<TM, TN>(sp, wave, lane, lds, acc)) return;
     uint32_t off[TN];
 #pragma unroll
     for (int t = 0; t < TN; ++t) off[t] = one_out_offset(g, n0 + one_pixel(PAIRS, TN, t, col));

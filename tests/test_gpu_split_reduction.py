@@ -1,0 +1,87 @@
+"""Reductions cut into ranges whose partial sums meet in the workspace: the last item of a tile adds them, whatever the workspace held
+before, call after call and in replays of a graph."""
+import pytest
+
+from nnv_workloads import ConvLayer
+from test_gpu_grouped import Case, PAD
+from test_gpu_tile_gemm import env  # noqa: F401
+from test_gpu_tile_gemm_f16 import check as check_f16
+
+pytestmark = pytest.mark.gpu
+
+
+def Ly(c, h, k, r=3, stride=1, n=1, w=None, groups=1):
+    return ConvLayer(f"s{c}_{n}x{h}x{w or h}_k{k}_r{r}s{stride}g{groups}", c, h, w or h, k, r, r, stride, r // 2, groups, n)
+
+
+# two ranges and as many as the channels allow, every sort of item: workgroups of 64 x 112 and 64 x 64 outputs (3x3; 1x1 in pairs of pixels and alone), wavefronts
+# of one, two and four panels, ragged last panels, pixels and ranges
+LAYERS = {
+    "f32": [Ly(64, 56, 64), Ly(128, 28, 128), Ly(256, 14, 250), Ly(512, 7, 512), Ly(500, 14, 60), Ly(256, 14, 512, 3, 2), Ly(512, 14, 96, 1), Ly(300, 9, 16, 1),
+            Ly(130, 13, 20, 3, 2), Ly(96, 14, 48, 5), Ly(20, 30, 64, 7, 2), Ly(256, 14, 96, groups=2), Ly(520, 5, 30, 1, n=3)],
+    "f16": [Ly(512, 7, 512), Ly(1024, 14, 256, 1), Ly(2048, 7, 512, 1), Ly(1024, 7, 70, 1), Ly(512, 14, 512, 3, 2), Ly(512, 14, 250, n=2), Ly(2048, 8, 100, 1),
+            Ly(1024, 14, 130, 1, 2), Ly(256, 14, 40, 5), Ly(1152, 7, 24, 1), Ly(320, 3, 20, 1), Ly(768, 4, 48)],
+}
+
+
+@pytest.mark.parametrize("dtype", list(LAYERS))
+def test_any_workspace(env, dtype):  # noqa: F811
+    nnv, torch = env
+    half = dtype == "f16"
+    # (copies of the list: float16 layers run in workgroups from some number of items on)
+    layers = LAYERS[dtype] * (3 if half else 1)
+    cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, half, 300 + i, bias=i % 2 == 0) for i, l in enumerate(layers)]
+    descs, kinds = [c.desc for c in cases], [c.kind for c in cases]
+    need = nnv.nnv_conv_forward_grouped_workspace_bytes(descs, kinds)
+    assert need > 0
+    print("grouped call:", dtype, [l.name for l in layers], flush=True)
+    wsbuf = torch.zeros(need + 2 * PAD, dtype=torch.uint8, device="cuda")
+    ws = wsbuf[PAD:PAD + need]
+
+    def call(stream=None):
+        nnv.nnv_conv_forward_grouped(descs, kinds, [c.xd for c in cases], [c.wt for c in cases], [c.bd for c in cases], [c.y for c in cases], ws, need,
+                                     nnv.FORWARD_RELU, stream=stream)
+
+    first = None
+    for fill in ("zeros", "ones", "noise", "as the last call left it", "shifted"):
+        if fill == "ones":
+            wsbuf.fill_(255)
+        elif fill == "noise":
+            ws[:need // 4 * 4].view(torch.float32).normal_()
+        elif fill == "shifted":             # partial sums where the words of arrivals were
+            ws.copy_(torch.roll(ws.clone(), 4096 + 16))
+        wsbuf[:PAD] = 0x5A
+        wsbuf[PAD + need:] = 0x5A
+        for c in cases:
+            c.y.fill_(0x7F)
+        call()
+        torch.cuda.synchronize()
+        assert (wsbuf[:PAD] == 0x5A).all() and (wsbuf[PAD + need:] == 0x5A).all(), "write outside the workspace"
+        if first is None:
+            first = [c.ybuf.clone() for c in cases]
+            for c in cases:
+                if half:
+                    check_f16(torch, c, c.result())
+                else:
+                    l = c.layer
+                    ref = torch.nn.functional.conv2d(c.xd.cpu().double(), torch.from_numpy(c.w).double(), None if c.bd is None else c.bd.cpu().double(), stride=l.stride,
+                                                     padding=l.pad, groups=l.groups).clamp(min=0).numpy()
+                    # every sum of the chain rounds by at most 2^-24 of the sum of |x w|, which |x| <= 1 and He-normal weights keep below the bound here
+                    most = float(torch.from_numpy(c.w).abs().flatten(1).sum(1).max()) + 1
+                    bound = 2.0 ** -24 * (l.c // l.groups * l.r * l.s / 4 + 64) * most
+                    assert abs(c.result() - ref).max() <= bound, l.name
+        for c, f in zip(cases, first):
+            assert torch.equal(c.ybuf, f), (fill, c.layer.name)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call(side)
+    for i in range(3):
+        for c in cases:
+            c.y.fill_(0x7F)
+        if i == 1:
+            ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        for c, f in zip(cases, first):
+            assert torch.equal(c.ybuf, f), ("replay", i, c.layer.name)
