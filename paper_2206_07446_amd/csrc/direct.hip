@@ -12,6 +12,7 @@
 #include <type_traits>
 #include "nnv_internal.h"
 #include "buf.h"
+#include "depthwise.h"
 
 namespace nnv {
 
@@ -1069,10 +1070,6 @@ hipError_t launch_direct(const Geo &g, const void *x, const float *w, const floa
 
 // ------------------------------------------------------------------ depthwise 3x3 / 5x5
 
-struct DwParams {
-    int N, C, H, W, st, ph, pw, P, Q, relu;
-};
-
 template <typename T, int FS>
 __device__ __forceinline__ void depthwise_block(const T *__restrict__ x, const T *__restrict__ wp,
                                                 const float *__restrict__ bias, T *__restrict__ y, const DwParams &d,
@@ -1113,14 +1110,7 @@ __global__ __launch_bounds__(256) void depthwise_kernel(const T *__restrict__ x,
     depthwise_block<T, FS>(x, wp, bias, y, d, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// ---- many depthwise layers in one launch (a MobileNet-style network has 13-17 of them, each a few
-// microseconds of work).  y of a layer is one contiguous [N*C][P*Q] array: a thread owns
-// kDwPerThread outputs of that flat array (stride 256, so every store of a wavefront is one
-// contiguous run whatever the plane size: 7x7 planes fill the lanes like 112x112 ones), finds
-// channel and pixel by division, and reads the channel's taps with ordinary (cached) loads.
-// Two outputs per thread for 3x3 and one for 5x5 keep the kernel at 8 wavefronts per SIMD: what
-// bounds these small layers is how many loads the chip has in flight, not a thread's own pace.
-__host__ __device__ constexpr int dw_per_thread(int fs) { return fs == 3 ? 2 : 1; }
+// ---- many depthwise layers in one launch (a MobileNet-style network has 13-17 of them, each a few microseconds of work): depthwise.h
 struct DwLayer {
     const void *x, *w;
     const float *bias;
@@ -1137,48 +1127,6 @@ struct DwTable {
 static_assert(sizeof(DwTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) DwTable *DwTablePtr;
 
-template <typename T, int FS, bool RAW>
-__device__ __forceinline__ void depthwise_flat_block(const T *__restrict__ x, const void *__restrict__ wv,
-                                                     const float *__restrict__ bias, T *__restrict__ y,
-                                                     const DwParams &d, const int blk) {
-    constexpr int kDwPerThread = dw_per_thread(FS);
-    const int PQ = d.P * d.Q, total = d.N * d.C * PQ;
-    int o[kDwPerThread], pq[kDwPerThread], c[kDwPerThread], plane[kDwPerThread];
-    float acc[kDwPerThread];
-#pragma unroll
-    for (int i = 0; i < kDwPerThread; ++i) {
-        o[i] = (blk * kDwPerThread + i) * 256 + threadIdx.x;
-        const int oo = o[i] < total ? o[i] : 0;
-        plane[i] = oo / PQ;                        // image * C + channel
-        pq[i] = oo - plane[i] * PQ;
-        c[i] = d.N == 1 ? plane[i] : plane[i] % d.C;
-        acc[i] = bias ? bias[c[i]] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < kDwPerThread; ++i) {
-        const int p = pq[i] / d.Q, q = pq[i] - p * d.Q;
-        const T *wc = static_cast<const T *>(wv) + (size_t)(c[i] >> 5) * (FS * FS * 32) + (c[i] & 31);
-        const float *wr = static_cast<const float *>(wv) + (size_t)c[i] * (FS * FS);
-        const T *xc = x + (size_t)plane[i] * d.H * d.W;
-        const int ih0 = p * d.st - d.ph, iw0 = q * d.st - d.pw;
-#pragma unroll
-        for (int r = 0; r < FS; ++r) {
-            const int ih = ih0 + r;
-            const bool rok = ih >= 0 && ih < d.H;
-#pragma unroll
-            for (int s2 = 0; s2 < FS; ++s2) {
-                const int iw = iw0 + s2;
-                const bool ok = rok && iw >= 0 && iw < d.W;
-                const float xv = ok ? ld<T>(xc, (size_t)ih * d.W + iw) : 0.f;
-                acc[i] = fmaf(xv, RAW ? wr[r * FS + s2] : ld<T>(wc, (r * FS + s2) * 32), acc[i]);
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kDwPerThread; ++i)
-        if (o[i] < total) st<T>(y, (size_t)o[i], act(acc[i], d.relu));
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void depthwise_many_kernel(const DwTable tbl_arg) {
     const DwTablePtr tbl = (DwTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1193,15 +1141,7 @@ __global__ __launch_bounds__(256) void depthwise_many_kernel(const DwTable tbl_a
 #pragma unroll
         for (int k = 0; k < (int)(sizeof(DwLayer) / 4); ++k) dst[k] = src[k];
     }
-    const T *x = static_cast<const T *>(L.x);
-    T *y = static_cast<T *>(L.y);
-    if (L.raw) {
-        if (L.fs == 5) depthwise_flat_block<T, 5, true>(x, L.w, L.bias, y, L.d, b - first);
-        else depthwise_flat_block<T, 3, true>(x, L.w, L.bias, y, L.d, b - first);
-    } else {
-        if (L.fs == 5) depthwise_flat_block<T, 5, false>(x, L.w, L.bias, y, L.d, b - first);
-        else depthwise_flat_block<T, 3, false>(x, L.w, L.bias, y, L.d, b - first);
-    }
+    depthwise_workgroup<T>(L.x, L.w, L.bias, L.y, L.d, L.fs, L.raw != 0, b - first);
 }
 
 hipError_t launch_depthwise_many(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
@@ -1220,7 +1160,7 @@ hipError_t launch_depthwise_many(int n, const Geo *geos, const void *const *x, c
         L.fs = g.r;
         L.raw = raw ? 1 : 0;
         tbl.block0[i] = (int)blocks;
-        blocks += ((long)g.n * g.c * g.p * g.q + 256 * dw_per_thread(g.r) - 1) / (256 * dw_per_thread(g.r));
+        blocks += dw_workgroups(L.d);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxDwLayers; ++i) tbl.block0[i] = INT_MAX;
