@@ -163,7 +163,8 @@ int nnv_conv_forward_relu(const nnv_conv_desc *desc, nnv_kind kind, const void *
  * layers large enough; float16: and one more, which makes copies of inputs in octets
  * of channels, where a layer of a wavefront per item has a filter larger than 1x1); Winograd layers of one kind and storage type share three launches (all
  * input transforms, all tile GEMMs, all output transforms), except those nnv_conv_forward
- * runs as one fused kernel; DEPTHWISE layers of one storage type share one launch; DIRECT
+ * runs as one fused kernel; DEPTHWISE layers of one storage type share one launch, that of the
+ * IM2COL_GEMM items of that type where there are any and the depthwise layers are not too large; DIRECT
  * layers with groups = 1 and a square 1x1, 3x3, 5x5 or 7x7 filter share up to three (one of
  * them for the layers that run with the lanes along the output channels: K a multiple of 64 and
  * a 3x3 filter with C a multiple of 4, a 1x1 filter with C a multiple of 16, each at stride 1 or

@@ -314,6 +314,7 @@ struct GroupedPlan {
         int kind;                   // WINO_MANY: the Winograd kind of the batch
         std::vector<int> layers;
         std::vector<size_t> offset; // workspace offset of each layer's region
+        std::vector<int> depthwise; // GEMM_ITEMS: depthwise layers that ride along
     };
     std::vector<Batch> batches;
     size_t bytes = 0;
@@ -329,7 +330,7 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
     // all at once - and one or two layers through them take 2-5 times as long as their own launches
     // (measured: a 512-channel 7x7 layer 30 against 15 us through the item GEMM).
     auto collect = [&](int cls, int kind, int cap, int least, auto pick, auto region_bytes) {
-        GroupedPlan::Batch cur{cls, kind, {}, {}};
+        GroupedPlan::Batch cur{cls, kind, {}, {}, {}};
         size_t off = 0;
         auto close = [&]() {
             if ((int)cur.layers.size() >= least) { gp.bytes = std::max(gp.bytes, off); gp.batches.push_back(cur); }
@@ -370,6 +371,27 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
                     [&](int i) { return kinds[i] == kind && same_type(i) && wino_many_supported(geos[i], kind); },
                     [&](int i) { return ws_bytes(geos[i], kind); });
     }
+    // Depthwise layers ride along with an item launch of their storage type: the items leave half of the memory path idle and end one by one, and a launch
+    // less is 4 us.  Up to kMostDepthwise workgroups of them, ten rounds of what the item kernel's registers let the chip hold; more do better in a launch of
+    // their own, seven wavefronts per SIMD instead of three.  us a call, apart / together, [workgroups]: ShuffleNet-shaped [460] 23.5 / 19.8, MobileNetV1 [1970] 38.1 / 29.0,
+    // MobileNetV2 [2350] 32.3 / 27.4, float16 28.1 / 20.9, EfficientNet-B0 [2370] 49.9 / 45.0, MobileNetV2 in float16 at batch 2 [4700] 38.0 / 33.4 and 3 [7050] 49.8 / 48.2,
+    // EfficientNet-B0 at batch 3 [7120] 105 / 100; beyond the line MobileNetV2 at batch 4 [9400] 98 / 98, float16 69 / 70.6, at 4x320x320 [18600] 176 / 182, float16 125 / 133.
+    constexpr long kMostDepthwise = 7680;
+    for (GroupedPlan::Batch &d : gp.batches) {
+        if (d.cls != GroupedPlan::DW_MANY && d.cls != GroupedPlan::DW_RAW_MANY) continue;
+        for (GroupedPlan::Batch &b : gp.batches) {
+            if (b.cls != GroupedPlan::GEMM_ITEMS || geos[b.layers[0]].dtype != geos[d.layers[0]].dtype) continue;
+            if ((int)(b.layers.size() + b.depthwise.size() + d.layers.size()) > kMaxGemmLayers) continue;
+            long items = 0;
+            for (int i : b.depthwise) items += depthwise_items(geos[i]);
+            for (int i : d.layers) items += depthwise_items(geos[i]);
+            if (items > kMostDepthwise) continue;
+            b.depthwise.insert(b.depthwise.end(), d.layers.begin(), d.layers.end());
+            d.layers.clear();
+            break;
+        }
+    }
+    gp.batches.erase(std::remove_if(gp.batches.begin(), gp.batches.end(), [](const GroupedPlan::Batch &b) { return b.layers.empty(); }), gp.batches.end());
     for (GroupedPlan::Batch &b : gp.batches) {
         if (b.cls != GroupedPlan::GEMM_ITEMS) continue;
         std::vector<Geo> bg;
@@ -385,7 +407,7 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
     }
     for (int i = 0; i < n; ++i) {
         if (taken[i]) continue;
-        gp.batches.push_back(GroupedPlan::Batch{GroupedPlan::SINGLE, kinds[i], {i}, {0}});
+        gp.batches.push_back(GroupedPlan::Batch{GroupedPlan::SINGLE, kinds[i], {i}, {0}, {}});
         gp.bytes = std::max(gp.bytes, ws_bytes(geos[i], kinds[i]));
     }
     return gp;
@@ -517,20 +539,22 @@ int nnv_conv_forward_grouped(int n_layers, const nnv_conv_desc *descs, const nnv
             if (rc) return rc;
             continue;
         }
-        const int m = (int)b.layers.size();
-        std::vector<Geo> bg(m);
-        std::vector<const void *> bx(m), bw(m);
-        std::vector<const float *> bb(m);
-        std::vector<void *> by(m), bws(m);
-        for (int j = 0; j < m; ++j) {
-            const int i = b.layers[j];
+        const int m = (int)b.layers.size(), ndw = (int)b.depthwise.size();
+        std::vector<Geo> bg(m + ndw);
+        std::vector<const void *> bx(m + ndw), bw(m + ndw);
+        std::vector<const float *> bb(m + ndw);
+        std::vector<void *> by(m + ndw), bws(m);
+        std::vector<char> raw(ndw);
+        for (int j = 0; j < m + ndw; ++j) {
+            const int i = j < m ? b.layers[j] : b.depthwise[j - m];
             bg[j] = geos[i]; bx[j] = x[i]; bw[j] = w_tx[i]; bb[j] = bias ? bias[i] : nullptr; by[j] = y[i];
-            bws[j] = static_cast<char *>(workspace) + b.offset[j];
+            if (j < m) bws[j] = static_cast<char *>(workspace) + b.offset[j];
+            else raw[j - m] = kinds[i] == NNV_DIRECT;
         }
         hipError_t e = hipSuccess;
         switch (b.cls) {
             case GroupedPlan::GEMM_ITEMS:
-                e = launch_im2col_items(m, bg.data(), bx.data(), bw.data(), bb.data(), by.data(), bws.data(), st);
+                e = launch_im2col_items(m, bg.data(), bx.data(), bw.data(), bb.data(), by.data(), bws.data(), st, ndw, raw.data());
                 break;
             case GroupedPlan::WINO_MANY:
                 e = launch_wino_many(m, bg.data(), b.kind, bx.data(), bw.data(), bb.data(), by.data(), bws.data(), st);

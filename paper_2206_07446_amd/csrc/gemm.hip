@@ -29,6 +29,7 @@
 #include <climits>
 #include "nnv_internal.h"
 #include "buf.h"
+#include "depthwise.h"
 
 namespace nnv {
 
@@ -998,6 +999,7 @@ struct GemmItemRec {
     // tile = 1: items of whole workgroups (tile_gemm.h), all of one group.  tm: panels per wavefront, + 4 if it holds seven blocks of 16 pixels, not
     // four.  mode: 3, 3x3 filters at equal strides (sh) and pads (ph), the fields that are free hold the tile: S, groups: its rows and columns; sw, pw: tiles
     // per row and per column of an image.  1, 1x1 filters.  kModeTaps, few channels, not split: the tile's rows and columns * 256 in part256.
+    // 0, a depthwise layer (depthwise.h), R x R; groups: its filters are untransformed.
 };
 static_assert(sizeof(GemmItemRec) == 64, "sixteen scalar registers");
 struct GemmItemTable {
@@ -1136,11 +1138,19 @@ __device__ __forceinline__ GemmItemRec load_item_rec(const GemmItemTablePtr tbl,
     return r;
 }
 
-constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2;      // which whole-workgroup items a launch holds besides the others
+constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2, kDepthwise = 3;      // which whole-workgroup items a launch holds besides the others (1: depthwise ones, too)
 
 __device__ __forceinline__ int one_tiles(const TileLayer &T, const GemmItemRec &r) {
     const int px = r.tm & 4 ? 112 : 64;
     return __builtin_amdgcn_readfirstlane((T.N * T.P * T.Q + px - 1) / px);
+}
+
+template <bool HALF>
+__device__ __forceinline__ void run_depthwise_item(const GemmItemRec &r, const int blk) {
+    DwParams d{r.N, r.C, r.H, r.W, r.sh, r.ph, r.pw, 0, 0, r.relu};
+    d.P = (d.st == 2 ? (d.H + 2 * d.ph - r.R) >> 1 : d.H + 2 * d.ph - r.R) + 1;
+    d.Q = (d.st == 2 ? (d.W + 2 * d.pw - r.R) >> 1 : d.W + 2 * d.pw - r.R) + 1;
+    depthwise_workgroup<typename std::conditional<HALF, __half, float>::type>(r.x, r.wp, r.bias, r.y, d, r.R, r.groups != 0, blk);
 }
 
 template <bool HALF, int TILE>
@@ -1203,7 +1213,14 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->item0[0], item, first);
     const GemmItemRec rec = load_item_rec(tbl, li);
-    if constexpr (TILE != kNoTiles) {
+    if constexpr (TILE == kDepthwise || TILE == kTiles) {
+        if (rec.tile && rec.mode == 0) {
+            __builtin_amdgcn_s_setprio(0);
+            run_depthwise_item<HALF>(rec, (item - first) / kItemWaves);
+            return;
+        }
+    }
+    if constexpr (TILE == kTiles || TILE == kLargeTiles) {
         __shared__ __align__(16) char tile_lds[HALF ? (TILE == kLargeTiles ? 8 * kTilePatch * 16 : 8 * kTilePatch2 * 16) : TILE == kLargeTiles ? 2 * kTileBuffer : kTileBuffer];
         // (every layer of such a launch starts with a workgroup of its own: all four wavefronts come here or none does)
         if (TILE == kLargeTiles || rec.tile) {
@@ -1818,6 +1835,11 @@ static ItemTarget items_target(int n, const Geo *geos, LayerPlan *known) {
     return target;
 }
 
+long depthwise_items(const Geo &g) {
+    if (g.ph >= 65536 || g.pw >= 65536) return LONG_MAX / kMaxGemmLayers;
+    return dw_workgroups(DwParams{g.n, g.c, g.h, g.w, g.sh, g.ph, g.pw, g.p, g.q, 0});
+}
+
 // The launch's 64-byte layer records hold filter sizes and groups in 8 bits, strides, pads and the
 // number of ranges in 16 (channels and images are below 2^16 everywhere).  Only a stride or a pad of 2^16
 // and more does not fit: such a layer is launched by itself.
@@ -1836,8 +1858,9 @@ void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes) {
 }
 
 // One item launch of n planned layers of one storage type, with the copies of x in front of it that they need; ws[i]: layer i's partial tiles and copy.
+// Behind them ndw depthwise layers (geos, x, w, bias, y [n ..]; raw: their filters are untransformed).
 static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, const void *const *x, const void *const *w,
-                                 const float *const *bias, void *const *y, void *const *ws, hipStream_t st) {
+                                 const float *const *bias, void *const *y, void *const *ws, hipStream_t st, int ndw = 0, const char *raw = nullptr) {
     const bool half = geos[0].dtype == NNV_F16;
     // Order: layers with the longest items first, so that the chip's last round of items is made
     // of the short ones.
@@ -1906,10 +1929,23 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
             }
             items += count * kItemWaves;
         } else {
-            items += tiles ? ceil_div(count, kItemWaves) * kItemWaves : count;
+            items += tiles || ndw > 0 ? ceil_div(count, kItemWaves) * kItemWaves : count;
         }
     }
-    for (int i = n; i < kMaxGemmLayers; ++i) tbl.item0[i] = INT_MAX;
+    for (int i = n; i < n + ndw; ++i) {
+        const Geo &g = geos[i];
+        GemmItemRec &L = tbl.layer[i];
+        L.x = x[i]; L.wp = w[i]; L.bias = bias ? bias[i] : nullptr; L.y = y[i];
+        L.H = g.h; L.W = g.w;
+        L.N = (uint16_t)g.n; L.C = (uint16_t)g.c;
+        L.sh = (uint16_t)g.sh; L.ph = (uint16_t)g.ph; L.pw = (uint16_t)g.pw;
+        L.R = (uint8_t)g.r; L.groups = raw[i - n] ? 1 : 0;
+        L.relu = g.relu ? 1 : 0;
+        L.tile = 1;
+        tbl.item0[i] = items;
+        items += (int)dw_workgroups(DwParams{g.n, g.c, g.h, g.w, g.sh, g.ph, g.pw, g.p, g.q, 0}) * kItemWaves;
+    }
+    for (int i = n + ndw; i < kMaxGemmLayers; ++i) tbl.item0[i] = INT_MAX;
     tbl.nitems = items;
     tbl.group = 2;       // workgroups (of kItemWaves items) handed to one XCD in a row
     tbl.part_base = base;
@@ -1922,9 +1958,11 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     const int per_xcd = ceil_div(ceil_div(wgs, tbl.group), 8) * tbl.group;
     if (half && large) hipLaunchKernelGGL((gemm_items_kernel<true, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (half && tiles) hipLaunchKernelGGL((gemm_items_kernel<true, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (half && ndw > 0) hipLaunchKernelGGL((gemm_items_kernel<true, kDepthwise>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (half) hipLaunchKernelGGL((gemm_items_kernel<true, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (large) hipLaunchKernelGGL((gemm_items_kernel<false, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else if (tiles) hipLaunchKernelGGL((gemm_items_kernel<false, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    else if (ndw > 0) hipLaunchKernelGGL((gemm_items_kernel<false, kDepthwise>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     else hipLaunchKernelGGL((gemm_items_kernel<false, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
     return hipGetLastError();
 }
@@ -1933,16 +1971,16 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
 // launch of copies in front if a float16 layer reads one.  ws[i] is layer i's own workspace region of
 // im2col_items_workspace_bytes of these layers.
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w, const float *const *bias,
-                               void *const *y, void *const *ws, hipStream_t st) {
+                               void *const *y, void *const *ws, hipStream_t st, int ndw, const char *raw) {
     if (n <= 0) return hipSuccess;
-    if (n > kMaxGemmLayers) return hipErrorInvalidValue;
-    for (int i = 0; i < n; ++i)
+    if (n + ndw > kMaxGemmLayers) return hipErrorInvalidValue;
+    for (int i = 0; i < n + ndw; ++i)
         if (geos[i].dtype != geos[0].dtype) return hipErrorInvalidValue;
     LayerPlan known[kMaxGemmLayers];
     const ItemTarget target = items_target(n, geos, known);
     ItemPlan plans[kMaxGemmLayers];
     for (int i = 0; i < n; ++i) plans[i] = plan_items(geos[i], target, &known[i]);
-    return launch_planned(n, geos, plans, x, w, bias, y, ws, st);
+    return launch_planned(n, geos, plans, x, w, bias, y, ws, st, ndw, raw);
 }
 
 // A single layer in items of whole workgroups, its channels not split: an item takes the whole channel loop, so that there have to be enough of

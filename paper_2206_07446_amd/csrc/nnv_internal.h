@@ -90,7 +90,11 @@ constexpr int kMaxGemmLayers = 56;
 bool im2col_items_supported(const Geo &g);
 void im2col_items_workspace_bytes(int n, const Geo *geos, size_t *bytes);      // of each of the layers of a launch
 hipError_t launch_im2col_items(int n, const Geo *geos, const void *const *x, const void *const *w,
-                               const float *const *bias, void *const *y, void *const *ws, hipStream_t st);
+                               const float *const *bias, void *const *y, void *const *ws, hipStream_t st, int ndw = 0, const char *raw = nullptr);
+// Behind the n layers, ndw depthwise ones of the same storage type may ride along (n + ndw <= kMaxGemmLayers, n > 0): geos, x, w, bias and y go on
+// with them, ws does not; raw[j]: filters of the j-th untransformed.
+// depthwise_items: workgroups of a layer (more than any launch should take where a layer record cannot hold it).
+long depthwise_items(const Geo &g);
 
 // Several IM2COL_GEMM layers without bias that do not depend on one another, in one launch whose results are those of
 // launch_im2col on each of them, bit for bit (at most kMaxMergedLayers, each mergeable).
