@@ -67,6 +67,8 @@ constexpr int kModeTaps = 4, kTapsMaxChannels = 8;
 // ... and of the work items of float16 1x1 layers of many channels whose pixels cannot be read in pairs
 // (gemm_accumulate_octets); fewer channel blocks or output panels than this are gathered from NCHW.
 constexpr int kModeOctets = 6, kOctetsMinBlocks = 16, kOctetsMinPanels = 32;
+// ... and of float32 3x3 layers whose pixels go through LDS (gemm_accumulate_patch; single layers and those of a cold pass).
+constexpr int kModePatch = 8;
 
 // The parameters that follow from a layer's sizes, its storage type and its chunking mode.
 __host__ __device__ inline void gemm_derived(GemmParams &g, const bool half, const int mode) {
@@ -420,6 +422,92 @@ __device__ __forceinline__ void gemm_accumulate_3x3(const GemmParams &g, const i
             load_row(1, cb + 1);
             __builtin_amdgcn_sched_barrier(0);
             compute_row(2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// The same sums, in the same order, for 3x3 filters at stride 1 with one column of padding: the pixels of a tile go through LDS.
+// What bounds the smallest tile is the vector memory path of its CU: a product takes a fragment of weights and a gather of 16 pixels x 4 planes, and
+// the nine taps gather the same pixels nine times.  Outputs n and n + 1 of a row lie over neighbouring inputs, so that the three rows of input under 16 outputs are
+// 18 entries each, whatever the width of the image: a wavefront reads them with one load per channel, lays them down in a buffer of its own and takes the taps
+// from there, 4 loads for four channels instead of 36.  Taps left and right of the image read an entry that is always zero.  Three channel blocks of
+// weights and pixels are on their way.
+constexpr int kPatchRow = 20, kPatchZero = 18;          // entries of a row; the one that is zero
+constexpr int kPatchChannel = 80;                       // floats from channel to channel: neighbouring slots in different banks
+constexpr int kPatchFloats = 2 * 4 * kPatchChannel;     // of a wavefront: two buffers of four channels
+__device__ __forceinline__ void gemm_accumulate_patch(const GemmParams &g, const int mb0, const int nb0, const int ks, const int nsplit, const int lane,
+                                                      float *lds, floatx4 (&acc)[1][1], PixState<1> &px) {
+    constexpr int D = 3;
+    const int slot = lane >> 4, j = lane & 15;
+    uint32_t xo, at[3];             // the lane's entry of a channel, its taps of filter row 0
+    {
+        const int r = lane / kPatchRow, e = lane - r * kPatchRow, v = nb0 * 16 - 1 + e;
+        const bool live = r < 3 && e < kPatchZero && v >= 0 && v < g.npix;
+        const int n = live ? v : 0, PQ = g.P * g.Q;
+        const int img = g.N == 1 ? 0 : n / PQ, pq = n - img * PQ, p = pq / g.Q, q = pq - p * g.Q, ih = p - g.ph + r;
+        xo = live && (unsigned)ih < (unsigned)g.H ? (uint32_t)(((img * g.C + (mb0 / g.kg16) * g.Cg) * g.H + ih) * g.W + q) * 4u : kOobOffset;
+        int ih0[1], iw0[1], xbase[1];
+        gemm_pixels<1>(g, mb0, nb0, lane, px, ih0, iw0, xbase);
+        at[0] = slot * kPatchChannel + (iw0[0] < 0 ? kPatchZero : j);
+        at[1] = slot * kPatchChannel + j + 1;
+        at[2] = slot * kPatchChannel + (iw0[0] + 2 >= g.W ? kPatchZero : j + 2);
+    }
+    const int cblocks = g.cblocks;
+    const int per = (cblocks + nsplit - 1) / nsplit;
+    const int cb_begin = min(cblocks, ks * per), cb_end = min(cblocks, cb_begin + per);
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(g.x, g.x_bytes), zres = make_rsrc(g.x, 0u);
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(g.wp, g.w_bytes);
+    const uint32_t a_voff = gemm_a_offset<1>(g, mb0, lane, (uint32_t)cblocks * 9u);
+    const uint32_t a_base = (uint32_t)mb0 * (uint32_t)cblocks * 9u;
+    const uint32_t plane = g.cb_stride >> 2;
+    float a[D][9], xr[D][4];
+    // (blocks past the range: the last one again, not used)
+    auto load_a = [&](const int d, int cb) __attribute__((always_inline)) {
+        cb = min(cb, cb_end - 1);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) a[d][i] = buf_load<float>(wres, a_voff + i % 3 * 256u, (a_base + (uint32_t)cb * 9u + i / 3 * 3) * 256u);
+    };
+    auto load_x = [&](const int d, int cb) __attribute__((always_inline)) {
+        cb = min(cb, cb_end - 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool ok = cb * 4 + c < g.Cg;             // uniform
+            xr[d][c] = buf_load<float>(ok ? xres : zres, xo, ok ? (uint32_t)cb * g.cb_stride + c * plane : 0u);
+        }
+    };
+    auto put = [&](const int d, const uint32_t buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) lds[buf + c * kPatchChannel + lane] = xr[d][c];
+    };
+    acc[0][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (cb_begin >= cb_end) return;
+    // The pixels of block b, in registers b % D, go to LDS one block ahead: the registers are free when block b begins.
+    load_x(0, cb_begin);
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) {
+        load_a(d, cb_begin + d);
+        load_x(d + 1, cb_begin + d + 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    uint32_t cur = 0;
+    put(0, 0);
+    for (int cb = cb_begin; cb < cb_end; cb += D) {
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            if (i > 0 && cb + i >= cb_end) break;
+            float b[9];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) b[k] = lds[cur + at[k % 3] + k / 3 * kPatchRow];
+            load_a((i + D - 1) % D, cb + i + D - 1);
+            load_x(i, cb + i + D);
+            __builtin_amdgcn_sched_barrier(0);
+            cur = cur ? 0 : 4 * kPatchChannel;
+            put((i + 1) % D, cur);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], b[k], acc[0][0], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -958,8 +1046,11 @@ __global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void
     const int nb0 = (bx * tiles_per_wg + nt) * TN;
     floatx4 acc[TM][TN];
     PixState<TN> px;
-    constexpr bool ROWS3 = !HALF && MODE == 3 && (TM == 4 || TN == 1), MIXED = ROWS3;
-    if constexpr (ROWS3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
+    constexpr bool ROWS3 = !HALF && MODE == 3 && (TM == 4 || TN == 1), PATCH = MODE == kModePatch, MIXED = ROWS3 || PATCH;
+    if constexpr (PATCH) {
+        gemm_accumulate_patch(g, mb0, nb0, ks, KS, lane, red + wave * kPatchFloats, acc, px);
+        if (KS > 1) __syncthreads();                                     // the partial sums take the place of the pixels
+    } else if constexpr (ROWS3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(g, mb0, nb0, ks, KS, lane, acc, px);
 
@@ -1272,13 +1363,18 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
 // saves: a batch-1 layer leaves most of the chip idle for most of its 8-16 us.  Workgroups of eight wavefronts hold 8 / KS tiles, or one
 // of KS = 16, whose wavefronts then take two ranges each.  Every layer's blocks are a multiple of eight, so that the XCD of a
 // block does not depend on what else is in the launch.  Measured, us a cold pass of a stack (batch 1, 224 x 224), one launch a layer ->
-// this: ResNet-18-shaped 206 -> 126, ResNet-50 463 -> 318, GoogLeNet 362 -> 94, SqueezeNet 151 -> 53, AlexNet 76 -> 57; MobileNetV2 (a chain)
+// this: ResNet-18-shaped 206 -> 113, ResNet-50 463 -> 296, GoogLeNet 362 -> 89, SqueezeNet 151 -> 52, AlexNet 76 -> 51; MobileNetV2 (a chain)
 // 224 -> 221.  Two workgroups per CU; with fewer registers, for a third one, it takes as long.
+// What bounds a launch of such layers is the sum of their wavefronts, each of them mostly latency, over what the chip holds at once: a
+// wavefront whose share of the products would be below the chip's average takes a tile of two panels, then two blocks of pixels as well (the sums stay the same).  us a cold pass, tiles as
+// alone (two blocks of pixels in launches of more than 1024 workgroups) / this: ResNet-18 123 / 113, ResNet-50 318 / 296, AlexNet 57 / 51, GoogLeNet 94 / 89 (2x130x300 139 / 128).
 constexpr int kLayerWaves = 8;      // 1 << 3
+constexpr int kLayerResident = 256 * 2 * kLayerWaves;       // wavefronts
+constexpr int kLayerRed = 16 * 8 * 64;      // partial tiles: KS = 16, two panels, or KS = 8, two and two blocks of pixels
 struct GemmLayersTable {
     GemmParams g[kMaxMergedLayers];           // grid_nx, grid_ny: workgroups along the pixels, tiles along the panels
     int block0[kMaxMergedLayers];             // first workgroup of each layer, INT_MAX beyond the last one
-    uint8_t variant[kMaxMergedLayers];        // mode + 8 if a tile has two panels, + 16 if two blocks of pixels
+    uint8_t variant[kMaxMergedLayers];        // mode + 16 if a tile has two panels, + 32 if two blocks of pixels
 };
 static_assert(sizeof(GemmLayersTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) GemmLayersTable *GemmLayersTablePtr;
@@ -1298,14 +1394,15 @@ __device__ __forceinline__ void gemm_layer_block(const GemmParams &g, const int 
 #pragma nounroll
     for (int z = ks; z < KS; z += per_tile) {
         if constexpr (MODE == 3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, z, KS, lane, acc, px);
+        else if constexpr (MODE == kModePatch) gemm_accumulate_patch(g, mb0, nb0, z, KS, lane, red + kLayerRed + wave * kPatchFloats, acc, px);
         else gemm_accumulate<false, TM, TN, MODE, 2>(g, mb0, nb0, z, KS, lane, acc, px);
         gemm_put_partial<TM, TN>(acc, red, KS, nt * KS + z, lane);
     }
-    gemm_finish<TM, TN, MODE == 3>(g, mb0, KS, ks, per_tile, nt, lane, acc, px, red);
+    gemm_finish<TM, TN, MODE == 3 || MODE == kModePatch>(g, mb0, KS, ks, per_tile, nt, lane, acc, px, red);
 }
 
 __global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const GemmLayersTable tbl_arg) {
-    __shared__ __align__(16) float red[16 * 8 * 64];       // KS = 16, two panels
+    __shared__ __align__(16) float red[kLayerRed + kLayerWaves * kPatchFloats];
     const GemmLayersTablePtr tbl = (GemmLayersTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     int first;
     const int li = table_find<kMaxMergedLayers>(&tbl->block0[0], (int)blockIdx.x, first);
@@ -1327,9 +1424,10 @@ __global__ __launch_bounds__(64 * kLayerWaves, 4) void gemm_layers_kernel(const 
     case V: gemm_layer_block<TM, TN, 0>(g, blk, red); break;
     switch (tbl->variant[li]) {
         NNV_LAYER_BLOCK(0, 1, 1)
-        NNV_LAYER_BLOCK(8, 2, 1)
-        NNV_LAYER_BLOCK(16, 1, 2)
-        NNV_LAYER_BLOCK(24, 2, 2)
+        NNV_LAYER_BLOCK(16, 2, 1)
+        NNV_LAYER_BLOCK(32, 1, 2)
+        NNV_LAYER_BLOCK(48, 2, 2)
+        case kModePatch: gemm_layer_block<1, 1, kModePatch>(g, blk, red); break;
     }
 #undef NNV_LAYER_BLOCK
 }
@@ -1418,7 +1516,8 @@ static GemmPlan plan_im2col(const Geo &g) {
     auto tiles = [&](int tm, int tn) { return (long)ceil_div(K16, tm) * ceil_div(npix16, tn); };
     // Batch-1 layers are latency-bound.  What pays (measured on ResNet-18-shaped layers): the
     // 32x32 tile only with thousands of tiles; the 32x16 tile while it still leaves >= 160 tiles,
-    // its units split over KS wavefronts up to ~2048 wavefronts; else the 16x16 tile with a
+    // its units split over KS wavefronts up to ~2048 wavefronts (1536 for float32 3x3, whose wavefronts of two channel blocks are mostly start: 64 channels at 56x56
+    // 7.6 -> 7.0 us, 128 at 28x28 7.6 -> 7.2, 64 at 56x56 -> 128 at stride 2 7.7 -> 6.8; 48 layers by 1 % on average); else the 16x16 tile with a
     // moderate split (>= 768 wavefronts) and a deeper register ring, because its few workgroups
     // stream the weights from HBM and each CU keeps only so many misses in flight.
     auto split_for = [&](long t, long target) {
@@ -1447,7 +1546,7 @@ static GemmPlan plan_im2col(const Geo &g) {
     }
     // (the float16 1x1 gather keeps eight loads per fragment in flight: no room for the 32x32 tile)
     if (tiles(2, 2) >= 4096 && !(half && pl.mode == 1)) { pl.tm = 2; pl.tn = 2; pl.ks_shift = 0; }
-    else if (tiles(2, 1) >= 160) { pl.tm = 2; pl.tn = 1; pl.ks_shift = split_for(tiles(2, 1), 2048); }
+    else if (tiles(2, 1) >= 160) { pl.tm = 2; pl.tn = 1; pl.ks_shift = split_for(tiles(2, 1), !half && pl.mode == 3 ? 1536 : 2048); }
     else {
         pl.tm = 1; pl.tn = 1;
         pl.ks_shift = split_for(tiles(1, 1), 768);
@@ -1475,12 +1574,23 @@ static GemmPlan plan_im2col(const Geo &g) {
 
 size_t im2col_workspace_bytes(const Geo &g) { return plan_im2col(g).xt_bytes; }
 
+// Where the pixels of a tile go through LDS (gemm_accumulate_patch): tiles of 16 x 16 whose wavefronts have enough channels to make up for a longer start.  us a layer alone, gathered /
+// through LDS, [channel blocks of a wavefront, channels, maps -> outputs]: [8, 256, 14x14 -> 256] 7.3 / 7.8, [9, 306, 4x26x30 -> 37] 20.2 / 21.5, [16, 512, 7x7 -> 512] 11.9 / 11.5,
+// [16, 1024, 7x7 -> 1024] 20.9 / 19.0, [13, 836, 2x8x9 -> 23] 17.9 / 16.3, [24, 770, 2x16x14 -> 154] 29.2 / 25.2, [14, 462, 2x33x26 -> 25] 13.4 / 11.0.  Tiles of two panels gain
+// nothing (60 outputs of 318 channels at 73x75 27.6 / 30.3), nor does stride 2, whose rows are twice as long (256, 14x14 -> 512 8.4 / 9.6).
+constexpr int kPatchMinBlocks = 12;
+static bool patch_pays(const Geo &g, const GemmPlan &pl) {
+    if (g.dtype != NNV_F32 || pl.mode != 3 || pl.tm * pl.tn != 1 || g.sh != 1 || g.sw != 1 || g.pw != 1) return false;
+    return ceil_div(g.cg, 4) >> pl.ks_shift >= kPatchMinBlocks;
+}
+
 template <bool HALF, int TM, int TN, int NBUF>
 static void launch_gemm_mode(int mode, const GemmParams &gp, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
     switch (mode) {
         case 1: if constexpr (!HALF || TM * TN < 4) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 1, NBUF>), grid, block, lds, st, gp); } break;
         case 3: if constexpr (NBUF == 2) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 3, NBUF>), grid, block, lds, st, gp); } break;
         case kModeTaps: if constexpr (HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, kModeTaps, NBUF>), grid, block, lds, st, gp); } break;
+        case kModePatch: if constexpr (!HALF && NBUF == 2 && TM * TN == 1) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, kModePatch, NBUF>), grid, block, lds, st, gp); } break;
         case 5: if constexpr (!HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 5, NBUF>), grid, block, lds, st, gp); } break;
         case 7: if constexpr (!HALF) { hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 7, NBUF>), grid, block, lds, st, gp); } break;
         default: hipLaunchKernelGGL((im2col_gemm_kernel<HALF, TM, TN, 0, NBUF>), grid, block, lds, st, gp); break;
@@ -1529,7 +1639,7 @@ static void launch_octets(const Geo &g, const GemmParams &gp, const void *x, voi
 }
 
 static hipError_t launch_im2col_plain(const Geo &g, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st) {
-    const GemmPlan pl = plan_im2col(g);
+    GemmPlan pl = plan_im2col(g);
     const bool half = g.dtype == NNV_F16;
     GemmParams gp = gemm_params(g, pl.mode, x, w, bias, y);
     gp.ks_shift = pl.ks_shift;
@@ -1545,7 +1655,11 @@ static hipError_t launch_im2col_plain(const Geo &g, const void *x, const void *w
     gp.grid_ny = ceil_div(gp.K16, pl.tm);
     gp.m_major = gp.w_bytes >= gp.x_bytes;
     dim3 grid(xcd_grid(gp.grid_nx * gp.grid_ny), 1, 1);
-    const size_t lds = KS > 1 ? (size_t)waves * pl.tm * pl.tn * 4 * 64 * sizeof(float) : 0;
+    size_t lds = KS > 1 ? (size_t)waves * pl.tm * pl.tn * 4 * 64 * sizeof(float) : 0;
+    if (patch_pays(g, pl)) {
+        pl.mode = kModePatch;
+        lds = std::max(lds, (size_t)waves * kPatchFloats * sizeof(float));
+    }
     if (half) launch_gemm_variant<true>(pl, gp, grid, dim3(64 * waves), lds, st);
     else launch_gemm_variant<false>(pl, gp, grid, dim3(64 * waves), lds, st);
     return hipGetLastError();
@@ -2027,37 +2141,36 @@ hipError_t launch_im2col_layers(int n, const Geo *geos, const void *const *x, co
     if (n <= 0) return hipSuccess;
     if (n > kMaxMergedLayers) return hipErrorInvalidValue;
     GemmPlan plans[kMaxMergedLayers];
-    int order[kMaxMergedLayers];
-    long work[kMaxMergedLayers];         // about the k-steps of a wavefront
+    int order[kMaxMergedLayers], tn[kMaxMergedLayers];
+    long work[kMaxMergedLayers];         // about the products of a wavefront
+    long all = 0;
+    auto products = [&](int i) { return (long)ceil_div(geos[i].cg, 4) * geos[i].r * geos[i].s; };
     for (int i = 0; i < n; ++i) {
         plans[i] = plan_im2col(geos[i]);
         order[i] = i;
-        work[i] = (long)ceil_div(geos[i].cg, 4) * geos[i].r * geos[i].s >> std::min(plans[i].ks_shift, 3);
+        all += products(i) * ceil_div(geos[i].n * geos[i].p * geos[i].q, 16) * geos[i].groups * ceil_div(geos[i].kg, 16);
+    }
+    for (int i = 0; i < n; ++i) {
+        GemmPlan &pl = plans[i];
+        tn[i] = 1;
+        work[i] = products(i) * pl.tm >> std::min(pl.ks_shift, 3);
+        if (work[i] < all / kLayerResident && pl.tm == 1 && ceil_div(geos[i].kg, 16) % 2 == 0) { pl.tm = 2; work[i] *= 2; }
+        if (work[i] < all / kLayerResident && pl.ks_shift <= 3) { tn[i] = 2; work[i] *= 2; }       // (KS = 16: the partial tiles would not fit)
     }
     std::stable_sort(order, order + n, [&](int a, int b) { return work[a] > work[b]; });
     GemmLayersTable tbl{};
-    auto blocks_of = [&](int i, int tn) {
-        const int tiles = ceil_div(ceil_div(geos[i].n * geos[i].p * geos[i].q, 16 * tn), kLayerWaves >> std::min(plans[i].ks_shift, 3));
-        return (long)xcd_grid(tiles * ceil_div(geos[i].groups * ceil_div(geos[i].kg, 16), plans[i].tm));
-    };
     long blocks = 0;
-    for (int i = 0; i < n; ++i) blocks += blocks_of(i, 1);
-    // More workgroups than twice what is resident at once: two blocks of pixels per tile (a load of weights feeds twice the products; the sums are
-    // the same).  us a cold pass, one block / two: SqueezeNet-shaped stack 58.1 / 52.9, GoogLeNet 98.5 / 94.1 (levels of 1800 to 3300 workgroups); in launches of 700 to 1000 it
-    // leaves SIMDs idle: ResNet-18 126 / 139.
-    const bool wide = blocks > 4 * 256;
-    blocks = 0;
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
         const GemmPlan &pl = plans[i];
         GemmParams &gp = tbl.g[o];
         gp = gemm_params(geos[i], pl.mode, x[i], w[i], nullptr, y[i]);
         gp.ks_shift = pl.ks_shift;
-        const int tn = wide && pl.ks_shift <= 3 ? 2 : 1;         // (KS = 16: the partial tiles would not fit)
-        gp.grid_nx = ceil_div(ceil_div(gp.npix, 16 * tn), kLayerWaves >> std::min(pl.ks_shift, 3));
+        gp.grid_nx = ceil_div(ceil_div(gp.npix, 16 * tn[i]), kLayerWaves >> std::min(pl.ks_shift, 3));
         gp.grid_ny = ceil_div(gp.K16, pl.tm);
         gp.m_major = gp.w_bytes >= gp.x_bytes;
-        tbl.variant[o] = (uint8_t)(pl.mode + (pl.tm == 2 ? 8 : 0) + (tn == 2 ? 16 : 0));
+        const int mode = tn[i] == 1 && patch_pays(geos[i], pl) ? kModePatch : pl.mode;
+        tbl.variant[o] = (uint8_t)(mode + (pl.tm == 2 ? 16 : 0) + (tn[i] == 2 ? 32 : 0));
         tbl.block0[o] = (int)blocks;
         blocks += xcd_grid(gp.grid_nx * gp.grid_ny);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;
