@@ -914,18 +914,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
 // Nothing in the workspace has to be cleared: a tile's word of arrivals counts while its upper 48 bits are kSplitMark, any other content means that
 // nobody has arrived, and the last one clears it.  The partial sums are stored through to memory and read past the caches that other
 // XCDs do not share (sc1, the scope of one GPU); a wavefront waits for its stores before it, or the workgroup's first thread, arrives.
+// More than kSplitMost ranges go in two steps, groups of them first: one wavefront takes 1.5 us for every three ranges of a 64 x 32 tile (ResNet-18-shaped stack at 130x111, whose
+// 512-channel layers have 43, 42.2 -> 30.7 us a call; a launch behind the items took 34.3).
 struct SplitTile {
-    char *tile;         // [range][wavefront][block of 16 x 16][lane] floatx4, then the word of arrivals in 256 bytes
+    char *tile;         // [range][wavefront][block of 16 x 16][lane] floatx4, then the words of arrivals in 256 bytes: of the tile, of its groups
     int ks, n;          // which range; ranges in all (1: the item stores y itself)
 };
 constexpr int kSplitScope = 16;                         // sc1
 constexpr unsigned long long kSplitMark = 0x7fa5c3e996b1ull;
 constexpr size_t kSplitWord = 256;
+constexpr int kSplitMost = 12, kSplitGroup = 6, kSplitGroups = 31;
 
-// One thread; true for the last of n.  (Every exchange that fails means that another arrival's went through, and there are n of them.)
-__device__ __forceinline__ bool split_arrive(char *word, const int n) {
+__device__ __forceinline__ unsigned long long split_look(const char *word) {
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(word), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// One thread, which has looked at the word before (on its way beside the partial sums); true for the last of n.  (Every exchange that fails means that
+// another arrival's went through since, and there are n of them.)
+__device__ __forceinline__ bool split_arrive(char *word, const int n, unsigned long long seen) {
     unsigned long long *w = reinterpret_cast<unsigned long long *>(word);
-    unsigned long long seen = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (;;) {
         const int before = seen >> 16 == kSplitMark ? (int)(seen & 0xffff) : 0;
         const bool last = before + 1 >= n;
@@ -947,7 +953,7 @@ __device__ __forceinline__ void split_put(const floatx4 (&acc)[TM][TN], const __
 
 // acc = the sum of n partial sums `stride` bytes apart, as many of them on their way as registers allow.
 template <int TM, int TN>
-__device__ __forceinline__ void split_sum(floatx4 (&acc)[TM][TN], const __amdgpu_buffer_rsrc_t res, const uint32_t off, const uint32_t stride, const int n) {
+__device__ __forceinline__ void split_sum(floatx4 (&acc)[TM][TN], const __amdgpu_buffer_rsrc_t res, const uint32_t off, const uint32_t first, const uint32_t stride, const int n) {
     constexpr int NB = TM * TN, G = NB >= 12 ? 2 : NB >= 7 ? 3 : 6;
     asm volatile("" ::: "memory");
 #pragma unroll
@@ -960,13 +966,50 @@ __device__ __forceinline__ void split_sum(floatx4 (&acc)[TM][TN], const __amdgpu
         for (int i = 0; i < G; ++i)
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                p[i][b] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(res, off + b * 1024u, (uint32_t)min(z + i, n - 1) * stride, kSplitScope));
+                p[i][b] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(res, off + b * 1024u, first + (uint32_t)min(z + i, n - 1) * stride, kSplitScope));
 #pragma unroll
         for (int i = 0; i < G; ++i)
             if (z + i < n) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b / TN][b % TN] += p[i][b];
             }
+    }
+}
+
+// The sums of a tile whose reduction is cut, added by whichever of its wavefronts (WG: workgroups of four) is done last.  true: acc holds them.
+// mine: the lane's place in a range; lds: WG, of the workgroup, no longer read by any of its wavefronts once they are here.
+template <bool WG, int TM, int TN>
+__device__ __forceinline__ bool split_fold(const SplitTile &sp, const uint32_t mine, char *lds, floatx4 (&acc)[TM][TN]) {
+    constexpr uint32_t BYTES = (WG ? 4 : 1) * TM * TN * 1024;
+    const __amdgpu_buffer_rsrc_t res = make_rsrc(sp.tile, (uint32_t)sp.n * BYTES);
+    char *words = sp.tile + (size_t)sp.n * BYTES;
+    const int size = sp.n <= kSplitMost ? sp.n : max(kSplitGroup, (sp.n + kSplitGroups - 1) / kSplitGroups);      // ranges of a group
+    const int groups = (sp.n + size - 1) / size, grp = sp.ks / size;
+    const bool one = WG ? threadIdx.x == 0 : (threadIdx.x & 63) == 0;
+    // a group's ranges, unless there is one group only; then the groups' sums, each where its first range was
+    int at = sp.ks, first = grp * size, step = 1, n = min(size, sp.n - first);
+    char *word = words + (groups > 1 ? 8 + 8 * grp : 0);
+#pragma unroll 1
+    for (;;) {
+        unsigned long long seen = 0;
+        if (one) seen = split_look(word);
+        split_put<TM, TN>(acc, res, (uint32_t)at * BYTES + mine);
+        int last = 0;
+        if constexpr (WG) {
+            int *flag = reinterpret_cast<int *>(lds);
+            __syncthreads();
+            if (one) flag[0] = split_arrive(word, n, seen);
+            __syncthreads();
+            last = flag[0];
+        } else if (one) last = split_arrive(word, n, seen);
+        if (__builtin_amdgcn_readfirstlane(last) == 0) return false;
+        split_sum<TM, TN>(acc, res, mine, (uint32_t)first * BYTES, (uint32_t)step * BYTES, n);
+        if (word == words) return true;
+        word = words;
+        at = first;
+        first = 0;
+        step = size;
+        n = groups;
     }
 }
 
@@ -1118,14 +1161,8 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     __builtin_amdgcn_s_setprio(3);
     if (L.nsplit > 1) {
-        constexpr uint32_t BYTES = TM * TN * 1024;
-        char *tile = L.part + (size_t)(mt * L.ntn + nb) * ((size_t)L.nsplit * BYTES + kSplitWord);
-        const __amdgpu_buffer_rsrc_t res = make_rsrc(tile, (uint32_t)L.nsplit * BYTES);
-        split_put<TM, TN>(acc, res, (uint32_t)ks * BYTES + (uint32_t)lane * 16u);
-        int last = 0;
-        if (lane == 0) last = split_arrive(tile + (size_t)L.nsplit * BYTES, L.nsplit);
-        if (__builtin_amdgcn_readfirstlane(last) == 0) return;
-        split_sum<TM, TN>(acc, res, (uint32_t)lane * 16u, BYTES, L.nsplit);
+        const SplitTile sp{L.part + (size_t)(mt * L.ntn + nb) * ((size_t)L.nsplit * (TM * TN * 1024) + kSplitWord), ks, L.nsplit};
+        if (!split_fold<false, TM, TN>(sp, (uint32_t)lane * 16u, nullptr, acc)) return;
     }
     {
         RowState<TM> rs;
@@ -1229,7 +1266,9 @@ __device__ __forceinline__ GemmItemRec load_item_rec(const GemmItemTablePtr tbl,
     return r;
 }
 
-constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2, kDepthwise = 3;      // which whole-workgroup items a launch holds besides the others (1: depthwise ones, too)
+// Which whole-workgroup items a launch holds besides the others.  (A kernel with all of them is 25-30 KB longer than one without depthwise
+// items, which costs launches that have none 2-4 %.)
+constexpr int kNoTiles = 0, kTiles = 1, kLargeTiles = 2, kDepthwise = 3, kTilesDepthwise = 4;
 
 __device__ __forceinline__ int one_tiles(const TileLayer &T, const GemmItemRec &r) {
     const int px = r.tm & 4 ? 112 : 64;
@@ -1244,19 +1283,19 @@ __device__ __forceinline__ void run_depthwise_item(const GemmItemRec &r, const i
     depthwise_workgroup<typename std::conditional<HALF, __half, float>::type>(r.x, r.wp, r.bias, r.y, d, r.R, r.groups != 0, blk);
 }
 
-template <bool HALF, int TILE>
+template <bool HALF, int TILE, bool SPLIT>
 __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const GemmItemRec &r, const int local, char *lds) {
     TileLayer T;
     load_tile_layer(T, r, HALF);
     // order: pixel tile fastest, then the range of channels, then the panels
-    const int ntiles = HALF && r.mode == 1 ? one_tiles(T, r) : T.N * T.nth * T.ntw, nsplit = r.nsplit;
+    const int ntiles = HALF && r.mode == 1 ? one_tiles(T, r) : T.N * T.nth * T.ntw, nsplit = SPLIT ? r.nsplit : 1;
     const int rest = __builtin_amdgcn_readfirstlane(local / ntiles), nt = local - rest * ntiles;
     const int mt = __builtin_amdgcn_readfirstlane(rest / nsplit), ks = rest - mt * nsplit;
     const int chunks = (T.C + kTileChannels - 1) / kTileChannels;
     int per = chunks;
     if (nsplit > 1) per = __builtin_amdgcn_readfirstlane((chunks + nsplit - 1) / nsplit);
     const int c0 = ks * per, c1 = min(chunks, c0 + per);
-    const SplitTile sp{tbl->part_base + (size_t)r.part256 * 256 + (size_t)(mt * ntiles + nt) * ((size_t)nsplit * (tile_regs(r) * 1024u) + kSplitWord), ks, nsplit};
+    const SplitTile sp{tbl->part_base + (size_t)r.part256 * 256 + (size_t)(mt * ntiles + nt) * ((size_t)nsplit * (tile_regs(r) * 1024u) + kSplitWord), ks, SPLIT ? nsplit : 1};
     if constexpr (HALF && TILE != kLargeTiles) {
         if (r.mode == kModeTaps) {
             if (r.tm == 5) few_item<7>(T, mt, nt, lds);
@@ -1282,7 +1321,7 @@ __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const 
     else tile_item<HALF, 1, 4, false>(T, mt, nt, c0, c1, sp, lds);
 }
 
-template <bool HALF, int TILE>
+template <bool HALF, int TILE, bool SPLIT>
 __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void gemm_items_kernel(const GemmItemTable tbl_arg) {
     constexpr int NBUF = 2;
     const GemmItemTablePtr tbl = (GemmItemTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1304,23 +1343,24 @@ __global__ __launch_bounds__(64 * kItemWaves, TILE == kLargeTiles ? 2 : 3) void 
     int first;
     const int li = table_find<kMaxGemmLayers>(&tbl->item0[0], item, first);
     const GemmItemRec rec = load_item_rec(tbl, li);
-    if constexpr (TILE == kDepthwise || TILE == kTiles) {
+    if constexpr (TILE == kDepthwise || TILE == kTilesDepthwise) {
         if (rec.tile && rec.mode == 0) {
             __builtin_amdgcn_s_setprio(0);
             run_depthwise_item<HALF>(rec, (item - first) / kItemWaves);
             return;
         }
     }
-    if constexpr (TILE == kTiles || TILE == kLargeTiles) {
+    if constexpr (TILE == kTiles || TILE == kTilesDepthwise || TILE == kLargeTiles) {
         __shared__ __align__(16) char tile_lds[HALF ? (TILE == kLargeTiles ? 8 * kTilePatch * 16 : 8 * kTilePatch2 * 16) : TILE == kLargeTiles ? 2 * kTileBuffer : kTileBuffer];
         // (every layer of such a launch starts with a workgroup of its own: all four wavefronts come here or none does)
         if (TILE == kLargeTiles || rec.tile) {
-            run_tile_item<HALF, TILE>(tbl, rec, (item - first) / kItemWaves, tile_lds);
+            run_tile_item<HALF, TILE, SPLIT>(tbl, rec, (item - first) / kItemWaves, tile_lds);
             return;
         }
     }
     GemmItemLayer L;
     load_item_layer(L, tbl, rec, HALF);
+    if (!SPLIT) L.nsplit = 1;
     const int local = item - first;
     if (TILE != kNoTiles && local >= ((L.g.K16 + L.tm - 1) / L.tm) * L.ntn * L.nsplit) return;      // the layer's last workgroup is not full
     const int lane = threadIdx.x & 63;
@@ -1865,6 +1905,7 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Laye
 // and before the share of a SIMD counted, below, by which the ResNet-18-shaped launch takes items of 60 steps).
 constexpr int kItemStepsShortHalf = 48, kItemStepsMin = 48;
 constexpr int kItemsResident = 256 * 3 * kItemWaves;
+constexpr int kMostChunks = 6;
 
 // Items of whole workgroups: with W of them if each took one chunk (weighted by their blocks of pixels), an item takes W / 450, at least two
 // chunks: three workgroups fit a CU, and an item spends 5 us outside its products.  Launches of fewer than
@@ -1909,12 +1950,23 @@ static ItemTarget items_target(int n, const Geo *geos, LayerPlan *known) {
         }
         return tot;
     };
-    const long total = total_at(kItemSteps);
+    long total = total_at(kItemSteps);
     if (geos[0].dtype == NNV_F16) {
         if (total < 3L * kItemsResident) target.steps = kItemStepsShortHalf;
         return target;
     }
     constexpr long fit = (long)kItemsResident * 15 / 16;
+    // One and a half times what is resident at most, where longer ranges of workgroups make that one round: an item whose partial sums have to meet holds its place for another
+    // 3-5 us, and those of a second, partly filled round wait for it.  us a call without / with, of 52 launches of four stacks those that change: AlexNet-shaped stack at 2x314x246
+    // 81 / 65, 3x224x200 76 / 61, 4x200x180 83 / 65.
+    if (target.chunks > 0 && total > kItemsResident && total <= kItemsResident * 3L / 2) {
+        const int chunks = target.chunks;
+        for (; target.chunks < kMostChunks && total > fit; ++target.chunks, total = total_at(kItemSteps)) {}
+        if (total > fit) {
+            target.chunks = chunks;
+            total = total_at(kItemSteps);
+        }
+    }
     long items = total;                 // at target.steps
     if (total <= fit)
         for (int t = kItemSteps - 12; t >= kItemStepsMin; t -= 12) {
@@ -2070,14 +2122,19 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     }
     const int wgs = ceil_div(items, kItemWaves);
     const int per_xcd = ceil_div(ceil_div(wgs, tbl.group), 8) * tbl.group;
-    if (half && large) hipLaunchKernelGGL((gemm_items_kernel<true, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (half && tiles) hipLaunchKernelGGL((gemm_items_kernel<true, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (half && ndw > 0) hipLaunchKernelGGL((gemm_items_kernel<true, kDepthwise>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (half) hipLaunchKernelGGL((gemm_items_kernel<true, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (large) hipLaunchKernelGGL((gemm_items_kernel<false, kLargeTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (tiles) hipLaunchKernelGGL((gemm_items_kernel<false, kTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else if (ndw > 0) hipLaunchKernelGGL((gemm_items_kernel<false, kDepthwise>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
-    else hipLaunchKernelGGL((gemm_items_kernel<false, kNoTiles>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl);
+    const bool split = std::any_of(plans, plans + n, [](const ItemPlan &ip) { return ip.nsplit > 1; });
+#define NNV_ITEMS(HALF, TILE, SPLIT) hipLaunchKernelGGL((gemm_items_kernel<HALF, TILE, SPLIT>), dim3(per_xcd * 8), dim3(64 * kItemWaves), 0, st, tbl)
+#define NNV_ITEMS_OF(HALF)                                           \
+    if (large) NNV_ITEMS(HALF, kLargeTiles, HALF);                   \
+    else if (tiles && ndw > 0) NNV_ITEMS(HALF, kTilesDepthwise, true); \
+    else if (ndw > 0) NNV_ITEMS(HALF, kDepthwise, true);             \
+    else if (tiles && split) NNV_ITEMS(HALF, kTiles, true);          \
+    else if (tiles) NNV_ITEMS(HALF, kTiles, false);                  \
+    else if (split) NNV_ITEMS(HALF, kNoTiles, true);                 \
+    else NNV_ITEMS(HALF, kNoTiles, false);
+    if (half) { NNV_ITEMS_OF(true) } else { NNV_ITEMS_OF(false) }
+#undef NNV_ITEMS_OF
+#undef NNV_ITEMS
     return hipGetLastError();
 }
 

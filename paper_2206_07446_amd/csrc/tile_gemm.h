@@ -448,21 +448,6 @@ __device__ __forceinline__ void tile_accumulate_half(const TileLayer &g, const T
     chunk_of(std::false_type{}, c1 - 1);
 }
 
-// The sums of a tile whose reduction is cut, added by whichever of its workgroups (or wavefronts) is done last.  true: acc holds them.
-template <int TM, int TN>
-__device__ __forceinline__ bool tile_fold(const SplitTile &sp, const int wave, const int lane, char *lds, floatx4 (&acc)[TM][TN]) {
-    const uint32_t bytes = 4 * TM * TN * 1024, mine = (uint32_t)wave * (TM * TN * 1024) + (uint32_t)lane * 16u;
-    const __amdgpu_buffer_rsrc_t res = make_rsrc(sp.tile, (uint32_t)sp.n * bytes);
-    split_put<TM, TN>(acc, res, (uint32_t)sp.ks * bytes + mine);
-    __syncthreads();                // (and none reads lds any more)
-    int *flag = reinterpret_cast<int *>(lds);
-    if (threadIdx.x == 0) flag[0] = split_arrive(sp.tile + (size_t)sp.n * bytes, sp.n);
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(flag[0]) == 0) return false;
-    split_sum<TM, TN>(acc, res, mine, bytes, sp.n);
-    return true;
-}
-
 // Bias, clamp and store; off: offsets of the lane's pixels in channel 0 of their image, or out of range.  PAIRS: blocks 2 i and 2 i + 1
 // hold neighbouring pixels of an even number (one_pixel).
 template <bool HALF, int TM, int TN, bool PAIRS = false>
@@ -538,7 +523,7 @@ __device__ __forceinline__ void tile_item(const TileLayer &g, const int mt, cons
     __builtin_amdgcn_s_setprio(3);
     // (tiles of 128 channels are not split; the float16 one's compiler spills 672 bytes per lane if no branch stands between its loop and its stores)
     if constexpr (HALF || TM == 1) {
-        if (sp.n > 1 && !tile_fold<TM, TN>(sp, wave, lane, lds, acc)) return;
+        if (sp.n > 1 && !split_fold<true, TM, TN>(sp, (uint32_t)wave * (TM * TN * 1024) + (uint32_t)lane * 16u, lds, acc)) return;
     }
     const SmallDiv by_tw(g.tw);
     uint32_t off[TN];
@@ -669,7 +654,7 @@ __device__ __forceinline__ void one_item(const TileLayer &g, const int mt, const
     }
     chunks_of(std::false_type{}, ch);
     __builtin_amdgcn_s_setprio(3);
-    if (sp.n > 1 && !tile_fold<TM, TN>(sp, wave, lane, lds, acc)) return;
+    if (sp.n > 1 && !split_fold<true, TM, TN>(sp, (uint32_t)wave * (TM * TN * 1024) + (uint32_t)lane * 16u, lds, acc)) return;
     uint32_t off[TN];
 #pragma unroll
     for (int t = 0; t < TN; ++t) off[t] = one_out_offset(g, n0 + one_pixel(PAIRS, TN, t, col));

@@ -23,13 +23,18 @@ LAYERS = {
             Ly(1024, 14, 130, 1, 2), Ly(256, 14, 40, 5), Ly(1152, 7, 24, 1), Ly(320, 3, 20, 1), Ly(768, 4, 48)],
 }
 
+# ranges in groups (more than twelve of them): wavefronts of 4, 2 and 1 panels, the last group a single range or short; workgroups
+LAYERS["f32 groups"] = [Ly(512, 5, 512, w=4), Ly(1024, 4, 40), Ly(700, 3, 16), Ly(400, 6, 130, 5), Ly(1000, 4, 64, 1), Ly(512, 4, 24, 3, 2), Ly(470, 2, 80)]
+LAYERS["f32 groups, workgroups"] = [Ly(1100, 14, 128), Ly(900, 7, 100, n=4), Ly(64, 20, 64), Ly(832, 8, 70)] * 2
+LAYERS["f16 groups"] = [Ly(2048, 3, 16), Ly(2048, 2, 40), Ly(1500, 3, 24, 5), Ly(2000, 3, 20, 1)]
+
 
 @pytest.mark.parametrize("dtype", list(LAYERS))
 def test_any_workspace(env, dtype):  # noqa: F811
     nnv, torch = env
-    half = dtype == "f16"
+    half = dtype.startswith("f16")
     # (copies of the list: float16 layers run in workgroups from some number of items on)
-    layers = LAYERS[dtype] * (3 if half else 1)
+    layers = LAYERS[dtype] * (3 if dtype == "f16" else 1)
     cases = [Case(nnv, torch, l, nnv.IM2COL_GEMM, half, 300 + i, bias=i % 2 == 0) for i, l in enumerate(layers)]
     descs, kinds = [c.desc for c in cases], [c.kind for c in cases]
     need = nnv.nnv_conv_forward_grouped_workspace_bytes(descs, kinds)
