@@ -116,7 +116,7 @@ int nnv_kind_supported(const nnv_conv_desc *desc, nnv_kind kind);
 size_t nnv_transformed_bytes(const nnv_conv_desc *desc, nnv_kind kind);
 
 /* Bytes of scratch nnv_conv_forward needs for `kind` (may be 0: DIRECT, DEPTHWISE, float32
- * IM2COL_GEMM, and float32 WINO_F2/F4 on layers that run as one fused kernel; the other
+ * IM2COL_GEMM, and float32 WINO_F2/F4 on layers of many tiles and few channels; the other
  * Winograd layers keep their transformed input V and the tile products M there). */
 size_t nnv_workspace_bytes(const nnv_conv_desc *desc, nnv_kind kind);
 
@@ -162,8 +162,8 @@ int nnv_conv_forward_relu(const nnv_conv_desc *desc, nnv_kind kind, const void *
  * launch of work items (output tile x range of the reduction; a wavefront each, or a workgroup each for
  * layers large enough; float16: and one more, which makes copies of inputs in octets
  * of channels, where a layer of a wavefront per item has a filter larger than 1x1); Winograd layers of one kind and storage type share three launches (all
- * input transforms, all tile GEMMs, all output transforms), except those nnv_conv_forward
- * runs as one fused kernel; DEPTHWISE layers of one storage type share one launch, that of the
+ * input transforms, all tile GEMMs, all output transforms), except float32 F2 and F4 ones that
+ * do better as one fused kernel, which share a launch of it; DEPTHWISE layers of one storage type share one launch, that of the
  * IM2COL_GEMM items of that type where there are any and the depthwise layers are not too large; DIRECT
  * layers with groups = 1 and a square 1x1, 3x3, 5x5 or 7x7 filter share up to three (one of
  * them for the layers that run with the lanes along the output channels: K a multiple of 64 and

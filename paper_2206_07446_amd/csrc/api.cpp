@@ -308,7 +308,7 @@ int static_scratch(void **out) {
 // Layers of one launch run concurrently, so each needs a workspace region of its own; launches
 // follow one another on the stream, so the regions of different launches overlap.
 struct GroupedPlan {
-    enum Class { SINGLE = 0, GEMM_ITEMS = 1, WINO_MANY = 2, DIRECT_MANY = 3, DW_MANY = 4, DW_RAW_MANY = 5 };
+    enum Class { SINGLE = 0, GEMM_ITEMS = 1, WINO_MANY = 2, DIRECT_MANY = 3, DW_MANY = 4, DW_RAW_MANY = 5, WINO_FUSED = 6 };
     struct Batch {
         int cls;
         int kind;                   // WINO_MANY: the Winograd kind of the batch
@@ -366,6 +366,31 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
         collect(GroupedPlan::DW_RAW_MANY, NNV_DIRECT, kMaxDwLayers, 2,
                 [&](int i) { return kinds[i] == NNV_DIRECT && same_type(i) && supported(geos[i], NNV_DEPTHWISE); },
                 [&](int) { return (size_t)0; });
+        // The workspace holds every Winograd layer's region, also of those that run fused: which ones do depends on all layers of the call, and
+        // a workspace for many layers has to be enough for some of them.
+        for (int kind : {NNV_WINO_F2, NNV_WINO_F4, NNV_WINO_F6}) {
+            std::vector<char> fused(n, 0);
+            std::vector<int> part;
+            size_t off = 0;
+            auto close = [&]() {
+                std::vector<Geo> pg;
+                for (int i : part) pg.push_back(geos[i]);
+                std::vector<char> pf(part.size(), 0);
+                if (part.size() > 1) wino_fused_layers((int)part.size(), pg.data(), kind, pf.data());      // (one layer: runs by itself)
+                for (size_t j = 0; j < part.size(); ++j) fused[part[j]] = pf[j];
+                part.clear(); off = 0;
+            };
+            for (int i = 0; i < n; ++i) {
+                if (kinds[i] != kind || !same_type(i)) continue;
+                if (!wino_many_supported(geos[i], kind)) { fused[i] = !half && kind != NNV_WINO_F6 && ws_bytes(geos[i], kind) == 0; continue; }
+                off += align_up(ws_bytes(geos[i], kind), 256);
+                gp.bytes = std::max(gp.bytes, off);
+                part.push_back(i);
+                if ((int)part.size() == kMaxWinoLayers) close();
+            }
+            close();
+            collect(GroupedPlan::WINO_FUSED, kind, kMaxWinoLayers, 1, [&](int i) { return fused[i] != 0; }, [&](int) { return (size_t)0; });
+        }
         for (int kind : {NNV_WINO_F2, NNV_WINO_F4, NNV_WINO_F6})
             collect(GroupedPlan::WINO_MANY, kind, kMaxWinoLayers, 2,
                     [&](int i) { return kinds[i] == kind && same_type(i) && wino_many_supported(geos[i], kind); },
@@ -555,6 +580,9 @@ int nnv_conv_forward_grouped(int n_layers, const nnv_conv_desc *descs, const nnv
         switch (b.cls) {
             case GroupedPlan::GEMM_ITEMS:
                 e = launch_im2col_items(m, bg.data(), bx.data(), bw.data(), bb.data(), by.data(), bws.data(), st, ndw, raw.data());
+                break;
+            case GroupedPlan::WINO_FUSED:
+                e = launch_wino_fused(m, bg.data(), b.kind, bx.data(), bw.data(), bb.data(), by.data(), st);
                 break;
             case GroupedPlan::WINO_MANY:
                 e = launch_wino_many(m, bg.data(), b.kind, bx.data(), bw.data(), bb.data(), by.data(), bws.data(), st);

@@ -108,6 +108,11 @@ constexpr int kMaxWinoLayers = 20;
 bool wino_many_supported(const Geo &g, int kind);
 hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const *x, const void *const *U,
                             const float *const *bias, void *const *y, void *const *ws, hipStream_t st);
+// Several layers of one kind that run as one fused kernel (see winograd.hip), without a workspace.
+// wino_fused_layers: which of n layers of one kind and storage type (n <= kMaxWinoLayers) run so in one call.
+void wino_fused_layers(int n, const Geo *geos, int kind, char *fused);
+hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const *x, const void *const *U,
+                             const float *const *bias, void *const *y, hipStream_t st);
 hipError_t launch_wino(const Geo &g, int kind, const void *x, const void *w, const float *bias, void *y, void *ws, hipStream_t st);
 
 }  // namespace nnv

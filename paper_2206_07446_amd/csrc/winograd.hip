@@ -9,11 +9,12 @@
 //   3. output transform  Y = A^T M A, clipped to P x Q, plus bias        (vector ALU)
 // V and M live in the caller's workspace.  float16 storage keeps U, V and y in half
 // precision; the transforms and the accumulation are float32.
-// float32 F(2x2) / F(4x4) layers with many tiles and few channels run instead as ONE kernel
-// (wino_fused_kernel below) that keeps V and M in registers and needs no workspace.
+// float32 F(2x2) / F(4x4) layers with many tiles for their channels run instead as ONE kernel
+// (wino_fused_kernel below) that keeps V in LDS and M in registers.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
+#include <vector>
 #include "nnv_internal.h"
 #include "buf.h"
 #include "wino_consts.h"
@@ -81,7 +82,7 @@ __device__ __forceinline__ void patch_load(float (&d)[M + 2][M + 2], const __amd
 #pragma unroll
             for (int i = 0; i < 2; ++i) d[u][1 + M / 4 * 4 + i] = v[i];
         }
-        d[u][0] = buf_load<float>(xres, has_edge ? o + (uint32_t)edge * 4u : kOobOffset, has_edge ? soff : 0u);
+        d[u][0] = buf_load<float>(xres, has_edge ? o + (uint32_t)edge * 4u : kOobOffset, soff);
     }
 }
 template <int M>
@@ -571,134 +572,216 @@ __global__ __launch_bounds__(64 * kWinoItemWaves, 5) void wino_gemm_many_kernel(
 #undef NNV_WINO_ITEM
 }
 
-// ---- fused variant (float32, F(2x2) and F(4x4)): all three steps in one kernel, no workspace.
-// On layers with many tiles and few output channels the three-kernel route spends most of its
-// time writing and re-reading V and M.  Here a wavefront owns 16 tiles x 16 output channels.
-// Per step of 4 input channels every lane transforms the patch of one (tile, channel) pair in
-// registers: lane (tile l%16, channel l/16) then holds, for every frequency, exactly its element
-// of the B operand of the 16x16x4 MFMA.  The alpha^2 accumulators stay in registers and the
-// output transform is applied to them in place (accumulator register j of lane l is output
-// channel 4*(l/16)+j of tile l%16).  The input transform is repeated by every 16-channel block
-// of K, which is what restricts this route to layers with few output channels.
-template <int SET>
-__global__ __launch_bounds__(256) void wino_fused_kernel(const WinoParams w) {
+// ---- fused variant (float32, F(2x2) and F(4x4)): all three steps in one kernel, V and M never in memory.
+// A workgroup owns 16 TN tiles x 16 TM output channels at all frequencies, FW of them per wavefront.  A chunk is 4 / TN steps of four input channels:
+// while the products of a chunk run, four wavefronts transform the patches of the next one, each those of one step and one block of 16 tiles, lane (tile
+// l % 16, channel l / 16), and lay them down in LDS as ready-made operand fragments.  U comes from L2 in the layout of the tile GEMM, a load per TM TN
+// products, requested a chunk ahead.  At the end the frequencies meet in LDS, a row block at a time, and a thread transforms and stores one tile.
+// What bounds it is the matrix cores, at three quarters of the rate of a large product while a workgroup per CU is resident: a chunk of F(4x4) (16 channels) takes 3.0 us,
+// 1.9 of them products at 2.4 GHz; 2.7 without the transforms, as long without the loads of U.  Patches in single elements held the vector memory path
+// instead (4.4 us).  F(4x4) has twelve wavefronts for the products and four of their own for the transforms: one wavefront that did both would wait for
+// patches whenever it waits for U, since loads come back in order (5.0 us).  F(2x2), with four times fewer elements in a patch, has eight that do both; twelve,
+// one workgroup per CU instead of two, take a VGG-16-shaped stack from 166 to 200 us.  32 x 32 tiles (TM = TN = 2) for F(4x4), half the loads of U and twice the transforms: 3.9 us a chunk.
+constexpr int kWinoFusedTiles[2] = {2, 1};        // blocks of 16 tiles of a workgroup: F(2x2), F(4x4)
+constexpr int kWinoFusedFreqs[2] = {2, 3};        // frequencies of a wavefront
+constexpr int kWinoFusedOwn[2] = {0, 4};          // wavefronts that only transform (0: the first four do both)
+constexpr int wino_fused_threads(int set) { return ((set == 0 ? 16 : 36) / kWinoFusedFreqs[set] + kWinoFusedOwn[set]) * 64; }
+template <int SET, int TM, int TN, bool WIDE>
+__device__ __forceinline__ void wino_fused_block(const WinoParams &w, const int blk, float *lds) {
     using Wm = WinoMat<SET>;
-    constexpr int A = Wm::A, M = Wm::M, AA = A * A;
-    const int lane = threadIdx.x & 63;
+    constexpr int A = Wm::A, M = Wm::M, AA = A * A, FW = kWinoFusedFreqs[SET], WAVES = AA / FW, OWN = kWinoFusedOwn[SET], STEPS = 4 / TN, QM = 16 / TM;
+    static_assert(AA % FW == 0 && WAVES >= 8 && STEPS % 2 == 0, "the first four wavefronts transform, eight store");
+    constexpr int kBuffer = AA * 256;                     // floats: a chunk of V, or a row block of M of 16 tiles
+    const int lane = threadIdx.x & 63, col = lane & 15, slot = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // logical order: tile blocks fastest, so neighbouring workgroups share U; the four
-    // wavefronts of a workgroup share the patches (same tiles, four blocks of output channels)
-    const int lwg = xcd_logical_tile(w.gemm_wgs_per_xi);
-    if (lwg < 0) return;
-    const int T16 = (w.T + 15) >> 4;
-    const int kbg = lwg / T16, tb = lwg - kbg * T16;
-    const int kb = kbg * 4 + wave;
-    if (kb >= w.K16) return;
-    const int col = lane & 15, slot = lane >> 4;
-    const int t = tb * 16 + col;
-    const bool live = t < w.T;
+    const int nt = ((w.Tpad >> 4) + TN - 1) / TN;
+    const int kbt = blk / nt, tb = blk - kbt * nt, kb0 = kbt * TM;       // tile blocks fastest: neighbours share U
     const __amdgpu_buffer_rsrc_t xres = make_rsrc(w.x, w.x_bytes);
     const __amdgpu_buffer_rsrc_t ures = make_rsrc(w.U, w.u_bytes);
-    const uint32_t plane4 = (uint32_t)(w.H * w.W) * 16u;     // bytes of 4 channel planes
-    // per-lane byte offsets of the patch rows and columns in channel `slot`; a step adds its
-    // channel base as the scalar offset.  Rows and columns in the zero padding (and every row of
-    // a surplus tile) carry 2^30 instead, which puts the sum beyond the end of x (x is smaller
-    // than 2^30 bytes on this route), so those elements read as zero.
+    const int jt = wave % TN, js = (wave & 3) / TN;             // the block of tiles and the step of a chunk that this wavefront transforms
+    // Byte offsets of the patch's rows and columns in channel `slot`.  Those in the zero padding, of tiles past the end and of
+    // missing channels carry 2^30 each, beyond the end of x (smaller than 2^30 bytes on this route): their elements read as zero.
     constexpr uint32_t kOut = 0x40000000u;
-    uint32_t rowoff[A], coloff[A];
+    const uint32_t plane4 = (uint32_t)(w.H * w.W) * 16u;  // bytes of 4 channel planes
+    uint32_t rowoff[A];
+    int tj;
     {
-        const int tt = live ? t : 0;
-        const int per = w.th * w.tw;
+        const int t = (tb * TN + jt) * 16 + col;
+        const bool live = t < w.T;
+        const int tt = live ? t : 0, per = w.th * w.tw;
         const int img = tt / per, rem = tt - img * per;
-        const int ti = rem / w.tw, tj = rem - ti * w.tw;
-        const int ih0 = ti * M - w.ph, iw0 = tj * M - w.pw;
+        const int ti = rem / w.tw, ih0 = ti * M - w.ph;
+        tj = rem - ti * w.tw;
         const int base = (img * w.C + slot) * w.H * w.W;
 #pragma unroll
         for (int u = 0; u < A; ++u) {
             const int ih = ih0 + u;
-            rowoff[u] = (live && (unsigned)ih < (unsigned)w.H) ? (uint32_t)(base + ih * w.W) * 4u : kOut;
+            rowoff[u] = live && (unsigned)ih < (unsigned)w.H ? (uint32_t)(base + ih * w.W) * 4u : kOut;
         }
+    }
+    const uint32_t panel = (uint32_t)w.csteps * 256u;
+    const uint32_t a_voff = kb0 + col / QM < w.K16 ? (uint32_t)(col / QM) * panel + (uint32_t)slot * 64u + (uint32_t)(col % QM) * (4u * TM) : kOobOffset;
+    const uint32_t a_xi = (uint32_t)w.K16 * panel, a_base = (uint32_t)(wave * FW) * a_xi + (uint32_t)kb0 * panel;
+    typename FloatVec<TM>::type a[STEPS][FW];   // of the steps s, s + 1, ...
+    float d[A][A];
+    // (steps past the last one read as zero, both operands: one path through the loop keeps one set of accumulators)
+    auto load_a = [&](const int p, const int f, const int s) __attribute__((always_inline)) {
+        a[p][f] = buf_load_floats<TM>(ures, s < w.csteps ? a_voff : kOobOffset, a_base + (uint32_t)f * a_xi + (s < w.csteps ? (uint32_t)s * 256u : 0u));
+    };
+    auto load_patch = [&](const int ch) __attribute__((always_inline)) {
+        const int s = ch * STEPS + js;                    // (past the last step: nothing)
+        const uint32_t miss = s * 4 + slot < w.C ? 0u : kOut, soff = s < w.csteps ? (uint32_t)s * plane4 : 0u;
+        if constexpr (WIDE) patch_load<M>(d, xres, tj, w.tw, lane, [&](int u) __attribute__((always_inline)) { return rowoff[u] + miss; }, soff);
+        else {
+#pragma unroll
+            for (int v = 0; v < A; ++v) {
+                const int iw = tj * M - w.pw + v;
+                const uint32_t coloff = (unsigned)iw < (unsigned)w.W ? (uint32_t)iw * 4u : kOut;
+#pragma unroll
+                for (int u = 0; u < A; ++u) d[u][v] = buf_load<float>(xres, rowoff[u] + miss + coloff, soff);
+            }
+        }
+    };
+    auto put_patch = [&](const int ch) __attribute__((always_inline)) {
+        float *o = lds + (ch & 1) * kBuffer + (js * AA * 64 + lane) * TN + jt;
+        if constexpr (WIDE) patch_finish<M>(d, tj, w.tw, w.W);
+        // column by column in place, then row by row: few registers beside the patch itself
 #pragma unroll
         for (int v = 0; v < A; ++v) {
-            const int iw = iw0 + v;
-            coloff[v] = (unsigned)iw < (unsigned)w.W ? (uint32_t)iw * 4u : kOut;
+            float in[A][1], out[A][1];
+#pragma unroll
+            for (int u = 0; u < A; ++u) in[u][0] = d[u][v];
+            NNV_MATMUL_LEFT(Wm::BT, A, A, 1, in, out)
+#pragma unroll
+            for (int u = 0; u < A; ++u) d[u][v] = out[u][0];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int u = 0; u < A; ++u) {
+            float in[1][A], out[1][A];
+#pragma unroll
+            for (int v = 0; v < A; ++v) in[0][v] = d[u][v];
+            NNV_MATMUL_RIGHT_T(Wm::BT, 1, A, A, in, out)
+#pragma unroll
+            for (int v = 0; v < A; ++v) o[(u * A + v) * 64 * TN] = out[0][v];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    floatx4 acc[FW][TM][TN];
+#pragma unroll
+    for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) acc[f][m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int chunks = (w.csteps + STEPS - 1) / STEPS;
+    auto chunk_loop = [&](auto transforms, auto multiplies) __attribute__((always_inline)) {
+        constexpr bool T = decltype(transforms)::value, P = decltype(multiplies)::value;
+        if constexpr (T) {
+            load_patch(0);
+            __builtin_amdgcn_sched_barrier(0);
+            put_patch(0);
+            load_patch(1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (P) {
+#pragma unroll
+            for (int f = 0; f < STEPS * FW; ++f) load_a(f / FW, f % FW, f / FW);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        for (int ch = 0; ch < chunks; ++ch) {
+            if constexpr (T) {
+                put_patch(ch + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                    load_patch(ch + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const float *vb = lds + (ch & 1) * kBuffer + (wave * FW * 64 + lane) * TN;
+            if constexpr (P) {
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) {
+                    typename FloatVec<TN>::type b[FW];
+#pragma unroll
+                    for (int f = 0; f < FW; ++f) b[f] = *reinterpret_cast<const typename FloatVec<TN>::type *>(vb + (i * AA + f) * 64 * TN);
+#pragma unroll
+                    for (int f = 0; f < FW; ++f) {
+#pragma unroll
+                        for (int m = 0; m < TM; ++m)
+#pragma unroll
+                            for (int t = 0; t < TN; ++t)
+                                acc[f][m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(a[i][f], m), float_of<TN>(b[f], t), acc[f][m][t], 0, 0, 0);
+                        load_a(i, f, (ch + 1) * STEPS + i);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    };
+    // A loop for each role, so that no wavefront waits for what it does not use; all pass 1 + chunks barriers.
+    if (wave >= WAVES) __builtin_amdgcn_s_setprio(3);
+    if (wave >= WAVES) chunk_loop(std::true_type{}, std::false_type{});
+    else if (OWN == 0 && wave < 4) chunk_loop(std::true_type{}, std::true_type{});
+    else chunk_loop(std::false_type{}, std::true_type{});
+    // Row i = 4 slot + j of row block m is row TM (i % QM) + m of panel i / QM.  Two row blocks at a time, four wavefronts each.
+    constexpr int Q = TM * TN;
+#pragma unroll
+    for (int q0 = 0; q0 < Q; q0 += 2) {
+        if (q0 > 0) __syncthreads();
+#pragma unroll
+        for (int q = q0; q < q0 + 2 && q < Q; ++q)
+#pragma unroll
+            for (int f = 0; f < FW && wave < WAVES; ++f)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) lds[(q & 1) * kBuffer + (wave * FW + f) * 256 + j * 64 + lane] = acc[f][q / TN][q % TN][j];
+        __syncthreads();
+        const int q = q0 + (wave >> 2), row = slot * 4 + (wave & 3);
+        const int k = (kb0 + row / QM) * 16 + TM * (row % QM) + q / TN, tile = (tb * TN + q % TN) * 16 + col;
+        if (wave < 8 && q < Q && k < w.K && tile < w.T) {
+            const float *in_lds = lds + (wave >> 2) * kBuffer + (wave & 3) * 64 + lane;
+            float in[A][A], tmp[M][A], Y[M][M];
+#pragma unroll
+            for (int u = 0; u < A; ++u)
+#pragma unroll
+                for (int v = 0; v < A; ++v) in[u][v] = in_lds[(u * A + v) * 256];
+            NNV_MATMUL_LEFT(Wm::AT, M, A, A, in, tmp)
+            NNV_MATMUL_RIGHT_T(Wm::AT, M, A, M, tmp, Y)
+            wino_store_tile<M, false>(w, Y, tile, k);
         }
     }
-    const uint32_t a_voff = lane * 4u;
-    const uint32_t a_base = (uint32_t)kb * w.csteps;          // fragment index at frequency 0, step 0
-    const uint32_t a_xi = (uint32_t)w.K16 * w.csteps;         // fragments per frequency
-    floatx4 acc[AA];
+}
+
+struct WinoFusedTable {
+    WinoParams layer[kMaxWinoLayers];
+    int block0[kMaxWinoLayers];
+    int tm[kMaxWinoLayers];
+    int n;
+};
+static_assert(sizeof(WinoFusedTable) <= 4096, "the table is passed by value as the kernel argument");
+typedef const __attribute__((address_space(4))) WinoFusedTable *WinoFusedTablePtr;
+template <int SET, bool WIDE>
+__global__ __launch_bounds__(wino_fused_threads(SET)) void wino_fused_kernel(const WinoFusedTable tbl_arg) {
+    constexpr int A = WinoMat<SET>::A, TN = kWinoFusedTiles[SET];
+    __shared__ __align__(16) float lds[2 * A * A * 256];
+    const WinoFusedTablePtr tbl = (WinoFusedTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int G = kWinoGroup;
+    const int i = blockIdx.x, xcd = i & 7, j = i >> 3;
+    const int wg = ((j / G) * 8 + xcd) * G + j % G;
+    if (wg >= tbl->n) return;
+    int first;
+    const int li = table_find<kMaxWinoLayers>(&tbl->block0[0], wg, first);
+    WinoParams w;
+    {
+        const __attribute__((address_space(4))) uint32_t *src = (const __attribute__((address_space(4))) uint32_t *)&tbl->layer[li];
+        uint32_t *dst = reinterpret_cast<uint32_t *>(&w);
 #pragma unroll
-    for (int i = 0; i < AA; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // Everything a step needs is requested one step earlier.  Patches alternate between two
-    // register sets; the U fragment of frequency i is re-requested for the next step right
-    // after the MFMA that consumed it, into the same register.  Loads complete in order, and
-    // the order of issue is patch(s), U(s), patch(s+1), U(s+1), ..., so waiting for one of
-    // them never waits for anything requested later.  The scheduling barriers keep that order.
-    float d[2][A][A], a[AA];
-    const int full = w.C >> 2;                                // steps whose 4 channels all exist
-    const int last = w.csteps - 1;
-    auto load_patch = [&](int buf, int s) __attribute__((always_inline)) {
-        const uint32_t soff = (uint32_t)s * plane4;
-#pragma unroll
-        for (int u = 0; u < A; ++u)
-#pragma unroll
-            for (int v = 0; v < A; ++v) d[buf][u][v] = buf_load<float>(xres, rowoff[u] + coloff[v], soff);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto load_a = [&](int i, int s) __attribute__((always_inline)) {
-        a[i] = buf_load<float>(ures, a_voff, (a_base + (uint32_t)i * a_xi + s) * 256u);
-    };
-    auto step = [&](int buf, int s) __attribute__((always_inline)) {
-        float tmp[A][A], V[A][A];
-        NNV_MATMUL_LEFT(Wm::BT, A, A, A, d[buf], tmp)
-        NNV_MATMUL_RIGHT_T(Wm::BT, A, A, A, tmp, V)
-        const int sn = min(s + 1, last);
-#pragma unroll
-        for (int i = 0; i < AA; ++i) {
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], V[i / A][i % A], acc[i], 0, 0, 0);
-            load_a(i, sn);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    if (full > 0) load_patch(0, 0);
-#pragma unroll
-    for (int i = 0; i < AA; ++i) load_a(i, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (full > 0) {
-        int s = 0;
-        for (; s + 2 <= full; s += 2) {
-            load_patch(1, s + 1);
-            step(0, s);
-            load_patch(0, min(s + 2, full - 1));
-            step(1, s + 1);
-        }
-        if (s < full) step(0, s);
+        for (int k = 0; k < (int)(sizeof(WinoParams) / 4); ++k) dst[k] = src[k];
     }
-    if (w.C & 3) {
-        // last step of a channel count that is not a multiple of 4: lanes of missing channels read zero
-        const bool cok = full * 4 + slot < w.C;
-        const uint32_t soff = (uint32_t)full * plane4;
-#pragma unroll
-        for (int u = 0; u < A; ++u)
-#pragma unroll
-            for (int v = 0; v < A; ++v) d[0][u][v] = buf_load<float>(xres, cok ? rowoff[u] + coloff[v] : kOobOffset, soff);
-        __builtin_amdgcn_sched_barrier(0);
-        step(0, full);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int k = kb * 16 + slot * 4 + j;
-        if (!live || k >= w.K) continue;
-        float m[A][A], tmp[M][A], Y[M][M];
-#pragma unroll
-        for (int u = 0; u < A; ++u)
-#pragma unroll
-            for (int v = 0; v < A; ++v) m[u][v] = acc[u * A + v][j];
-        NNV_MATMUL_LEFT(Wm::AT, M, A, A, m, tmp)
-        NNV_MATMUL_RIGHT_T(Wm::AT, M, A, M, tmp, Y)
-        wino_store_tile<M, false>(w, Y, t, k);
-    }
+    const int tm = tbl->tm[li];
+    if (tm == 4) wino_fused_block<SET, 4, TN, WIDE>(w, wg - first, lds);
+    else if (tm == 2) wino_fused_block<SET, 2, TN, WIDE>(w, wg - first, lds);
+    else wino_fused_block<SET, 1, TN, WIDE>(w, wg - first, lds);
 }
 
 // ---------------------------------------------------------------- host side
@@ -738,21 +821,30 @@ static int wino_tm(const WinoPlan &p, bool half, int most = 4) {
     return p.K16 >= 2 ? 2 : 1;
 }
 
-// The fused kernel repeats the input transform (and the strided patch loads, which dominate its
-// time) once per 16 output channels and runs one or two wavefronts per SIMD, so it pays only
-// where the three-kernel route is dominated by launch floors and by its V and M round trips.
-// The choice compares two estimates fitted to a sweep over 48..224-pixel planes, 4..64 input
-// and 16..128 output channels (they pick the faster route, or one within 5 %, at every point):
-//   fused = 4 us + y / 2.3 TB/s + channel steps x time per step x max(1, workgroups / 256);
-//           a step takes 0.47 us (F(2x2)) or 1.9 us (F(4x4)) for a lone wavefront on a CU and
-//           0.16 / 0.5 us more for each further wavefront of the workgroup
-//   three = 8 us + 2 (V + M) / 3 TB/s
-// e.g. 3 -> 64 channels at 224x224, F(4x4): 11 us fused against 32 us; 64 -> 64 at 56x56,
-// F(2x2): 21 us fused against 13 us.  Outside the swept range the three kernels are kept.
-static bool wino_fused(const Geo &g, int kind, const WinoPlan &p) {
-    if (g.dtype != NNV_F32 || (kind != NNV_WINO_F2 && kind != NNV_WINO_F4)) return false;
-    const size_t x_bytes = (size_t)g.n * g.c * g.h * g.w * 4;
-    if (p.T16 < 32 || p.K16 > 8 || p.csteps > 16 || x_bytes >= ((size_t)1 << 30)) return false;
+// Which layers run as the fused kernel.  The three launches are bound by V and M, written and read in between, and by U; the fused kernel reads U once per block
+// of tiles, from L2, and has no parallelism along the channels: a layer of many channels on few tiles is one long chain.  Both are estimated,
+// in us, and a launch of several layers takes those of at most so many channel steps that the sum is least, by 5 % (wino_fused_layers).  A layer whose
+// channel steps the three launches would split keeps them: added up in one chain, 512 channels are 1.4 to 2 times further from the exact sums.
+//   three = base + (V + M) / in_out + max((V + M + U) / gemm, operations / rate)                                (sums over the layers)
+//   fused = start + max(workgroups / 256 x (chunks x chunk + each), longest (chunks x chunk x lone) + first)
+// MB and MFLOP over us; chunk: that of 64 outputs (less: its part for fewer).  Fitted to 144 single layers (3-512 channels, 8-512 outputs, 7-224 pixels,
+// batch 1-8) and 26 launches of four stacks at batch 1-4 and 96-320 pixels, weights and pixels from HBM; geometric means of the chosen over the best of both: single
+// layers F(2x2) 1.005 (the best over three launches 0.85), F(4x4) 1.007 (0.92).  us a call, three launches / chosen (the best line): VGG-16-shaped stack F(2x2) at 3x115x114
+// 183 / 141 (141), F(4x4) 1x263x191 179 / 146 (146), 2x166x278 306 / 263 (251); ResNet-18 F(2x2) 3x222x177 82 / 74 (74), F(4x4) 1x227x172 50.5 / 50.5 (50.5; all fused 107); SqueezeNet
+// F(4x4) 4x157x241 37 / 32 (31).  One layer, three / fused: F(4x4), 64 channels at 224x224 35.7 / 23.1, 256 at 112x112 68 / 58, at 56x56 24.8 / 56; F(2x2), 128 at 112x112 44 / 30.
+struct WinoRates {
+    double base, in_out, gemm, rate, start, chunk, each, lone, less, first;
+};
+constexpr WinoRates kWinoRates[2] = {{11.0, 4.4, 13.8, 89.0, 0.0, 1.34, 7.8, 1.12, 0.455, 6.5}, {10.7, 2.8, 6.1, 104.0, 7.5, 4.1, 8.5, 0.835, 0.40, 0.7}};
+
+static bool wino_fused_able(const Geo &g, int kind) {
+    return g.dtype == NNV_F32 && (kind == NNV_WINO_F2 || kind == NNV_WINO_F4) && (size_t)g.n * g.c * g.h * g.w * 4 < ((size_t)1 << 30);
+}
+
+// Layers with many tiles and few channels and outputs, which have no workspace and so no other route (the lines are those of an
+// estimate of their own: what a program is told to allocate stays the same).
+static bool wino_no_workspace(const Geo &g, int kind, const WinoPlan &p) {
+    if (!wino_fused_able(g, kind) || p.T16 < 32 || p.K16 > 8 || p.csteps > 16) return false;
     const double wgs = (double)p.T16 * ceil_div(p.K16, 4);
     const double rounds = wgs > 256.0 ? wgs / 256.0 : 1.0;
     const int waves = p.K16 < 4 ? p.K16 : 4;
@@ -763,17 +855,109 @@ static bool wino_fused(const Geo &g, int kind, const WinoPlan &p) {
     return fused_us < three_us;
 }
 
-size_t wino_workspace_bytes(const Geo &g, int kind) {
-    const WinoPlan p = plan_wino(g, kind);
-    if (wino_fused(g, kind, p)) return 0;
-    return p.v_bytes + p.m_bytes;
+// Panels per workgroup of the fused kernel.
+static int wino_fused_panels(const WinoPlan &p) { return p.K16 >= 3 ? 4 : p.K16; }
+
+// Panels per tile of a layer's own tile GEMM, and over how many (1 << shift) wavefronts its channel steps are split.
+// Latency-bound at batch 1 (measured on ResNet-18-shaped layers): the largest wavefront tile that still leaves >= 768 wavefronts; then
+// the channel steps are split over the wavefronts of a workgroup towards ~4 per SIMD, keeping >= 16 steps each.
+struct WinoSplit { int tm, shift; };
+static WinoSplit wino_split(const WinoPlan &p, bool half) {
+    const long aa = (long)p.alpha * p.alpha;
+    int tm = wino_tm(p, half);
+    while (tm > 1 && aa * ceil_div(p.K16, tm) * p.nblk < 768) tm = tm == 4 ? wino_tm(p, half, 2) : 1;
+    int shift = 0;
+    const long tiles = (long)ceil_div(p.K16, tm) * p.nblk;
+    while (shift < 4 && ((aa * tiles) << shift) < 4096 && (p.csteps >> (shift + 1)) >= (half ? 4 : 16)) ++shift;
+    return {tm, shift};
 }
 
-template <int SET>
-static hipError_t launch_wino_fused(const WinoPlan &p, WinoParams &w, hipStream_t st) {
-    w.gemm_wgs_per_xi = p.T16 * ceil_div(p.K16, 4);
-    hipLaunchKernelGGL((wino_fused_kernel<SET>), dim3(xcd_grid(w.gemm_wgs_per_xi)), dim3(256), 0, st, w);
-    return hipGetLastError();
+// The channel steps of the layers of one launch: split over 1 << shifts[i] wavefronts; runs[i]: tile blocks per item; mfmas[i]: matrix instructions of an
+// item.  Returns those of the launch per SIMD.
+// An item's wavefront should not outlast its share of the launch: matrix instructions of an item against
+// those of the launch per SIMD; the channel steps of longer items are split over 2 or 4 wavefronts, and the
+// layers with the longest wavefronts go first (but see below).  float16 F(2x2) items much shorter than a wavefront slot's
+// share (four per SIMD) take several tile blocks one after the other (VGG-16-shaped stack 163 -> 157 us; the same on
+// F(4x4) 106 -> 108, float32 F(4x4) 175 -> 177, F(6x6) 196 -> 208).
+static long wino_many_split(int n, const WinoPlan *plans, int kind, bool half, long *mfmas, int *shifts, int *runs) {
+    long total = 0, items = 0;
+    for (int i = 0; i < n; ++i) {
+        const WinoPlan &p = plans[i];
+        const int tm = wino_tm(p, half);
+        total += (long)p.csteps * p.tn * p.alpha * p.alpha * p.K16 * p.nblk;
+        items += (long)p.alpha * p.alpha * ceil_div(p.K16, tm) * p.nblk;
+        // a step's panels come from HBM once per frequency, whatever the number of tile blocks that share them: at
+        // four wavefronts per SIMD 256 bytes of them take as long as three matrix instructions (half: a quarter of that per KB)
+        mfmas[i] = (long)p.csteps * std::max(tm * p.tn, (half ? 6 : 13) * tm / 4 / p.nblk);
+    }
+    const long per_simd = total / 1024;      // matrix instructions of the launch per SIMD
+    // The shortest wavefront worth a split, in matrix instructions.  float32: 128 while the launch has fewer items than the
+    // chip has SIMDs (a split puts idle ones to work), else 512: wavefronts that have to queue gain nothing from being
+    // shorter.  Measured over 110 launches of six stacks at batch 1-6 and 80-320 pixels, weights from HBM, geometric means of
+    // 256 / 512 / 1024 against 128: up to 1008 items 1.02 / 1.06 / 1.12, 1472 to 4000 items 0.99 / 0.97 / 0.98, to 8000
+    // 0.99 / 0.98 / 0.99, beyond (per_simd / 6 rules) 1.00 / 1.00 / 1.01.  float16: 64 to 384 take the same time within
+    // 1-2 %, 32 costs a launch of few items 5 %.
+    const long shortest = half ? 96 : items < 1024 ? 128 : 512;
+    const long most = std::max(shortest, per_simd / 6), least = per_simd / 4 / 4;
+    for (int i = 0; i < n; ++i) {
+        shifts[i] = 0;
+        while (shifts[i] < 2 && (mfmas[i] >> shifts[i]) > most && (plans[i].csteps >> (shifts[i] + 1)) >= (half ? 2 : 8)) ++shifts[i];
+        runs[i] = 1;
+        if (half && kind == NNV_WINO_F2 && shifts[i] == 0 && mfmas[i] < least) {
+            const int r = (int)std::min<long>(least / mfmas[i], plans[i].nblk);
+            runs[i] = ceil_div(plans[i].nblk, ceil_div(plans[i].nblk, r));      // equal runs
+            mfmas[i] *= runs[i];
+        }
+    }
+    return per_simd;
+}
+
+void wino_fused_layers(int n, const Geo *geos, int kind, char *fused) {
+    std::fill(fused, fused + n, 0);
+    if (n > kMaxWinoLayers || (kind != NNV_WINO_F2 && kind != NNV_WINO_F4)) return;
+    const WinoRates &r = kWinoRates[kind == NNV_WINO_F2 ? 0 : 1];
+    const int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
+    struct Cost { int steps; double three, work, chain; };
+    Cost cost[kMaxWinoLayers];
+    WinoPlan plans[kMaxWinoLayers];
+    for (int i = 0; i < n; ++i) plans[i] = plan_wino(geos[i], kind);
+    long mfmas[kMaxWinoLayers];
+    int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
+    if (n > 1) wino_many_split(n, plans, kind, geos[0].dtype == NNV_F16, mfmas, shifts, runs);
+    else shifts[0] = wino_split(plans[0], geos[0].dtype == NNV_F16).shift;
+    std::vector<int> lines{0};
+    for (int i = 0; i < n; ++i) {
+        const WinoPlan &p = plans[i];
+        const int tm = wino_fused_panels(p);
+        const double aa = (double)p.alpha * p.alpha, vm = (double)(p.v_bytes + p.m_bytes) * 1e-6, u = aa * p.K16 * p.csteps * 256e-6;
+        const double chunks = (double)ceil_div(p.csteps, 4 / tn) * r.chunk * (tm == 4 ? 1.0 : r.less);
+        const double ops = 2.0 * aa * p.csteps * 4 * p.K16 * 16 * p.Tpad * 1e-6;
+        const bool able = wino_fused_able(geos[i], kind);
+        const int steps = able && wino_no_workspace(geos[i], kind, p) ? 0 : able && shifts[i] == 0 ? p.csteps : INT_MAX;
+        cost[i] = Cost{steps, vm / r.in_out + std::max((vm + u) / r.gemm, ops / r.rate),
+                       (double)ceil_div(p.T16, tn) * ceil_div(p.K16, tm) / 256.0 * (chunks + r.each), chunks * r.lone};
+        if (steps != INT_MAX) lines.push_back(steps);
+    }
+    std::sort(lines.begin(), lines.end());
+    lines.erase(std::unique(lines.begin(), lines.end()), lines.end());
+    int best = 0;
+    double best_us = 0;
+    for (int line : lines) {
+        double three = 0, work = 0, chain = 0;
+        for (int i = 0; i < n; ++i) {
+            if (cost[i].steps > line) three += cost[i].three;
+            else { work += cost[i].work; chain = std::max(chain, cost[i].chain); }
+        }
+        const double us = (three > 0 ? r.base + three : 0.0) + (work > 0 ? r.start + std::max(work, chain + r.first) : 0.0);
+        if (line == 0 || us < 0.95 * best_us) { best = line; best_us = us; }
+    }
+    for (int i = 0; i < n; ++i) fused[i] = cost[i].steps <= best;
+}
+
+size_t wino_workspace_bytes(const Geo &g, int kind) {
+    const WinoPlan p = plan_wino(g, kind);
+    if (wino_no_workspace(g, kind, p)) return 0;
+    return p.v_bytes + p.m_bytes;
 }
 
 template <bool HALF>
@@ -801,15 +985,10 @@ static hipError_t launch_wino_t(const Geo &g, const WinoPlan &p, WinoParams &w, 
         hipLaunchKernelGGL((wino_input_kernel<SET, HALF>), grid, dim3(bt), 0, st, w);
     }
     {
-        // latency-bound at batch 1 (measured on ResNet-18-shaped layers): the largest wavefront
-        // tile that still leaves >= 768 wavefronts; then split the channel steps over the
-        // wavefronts of a workgroup towards ~4 per SIMD, keeping >= 16 steps each
         const long aa = (long)p.alpha * p.alpha;
-        int tm = wino_tm(p, HALF);
-        while (tm > 1 && aa * ceil_div(p.K16, tm) * p.nblk < 768) tm = tm == 4 ? wino_tm(p, HALF, 2) : 1;
-        int shift = 0;
+        const WinoSplit sp = wino_split(p, HALF);
+        const int tm = sp.tm, shift = sp.shift;
         const long tiles = (long)ceil_div(p.K16, tm) * p.nblk;
-        while (shift < 4 && ((aa * tiles) << shift) < 4096 && (p.csteps >> (shift + 1)) >= (HALF ? 4 : 16)) ++shift;
         w.ks_shift = shift;
         w.gemm_wgs_per_xi = (int)tiles;
         const int waves = 1 << shift;
@@ -844,7 +1023,7 @@ static WinoParams wino_params(const Geo &g, const WinoPlan &p, const void *x, co
 
 bool wino_many_supported(const Geo &g, int kind) {
     const WinoPlan p = plan_wino(g, kind);
-    return !wino_fused(g, kind, p) && p.T16 <= (1 << 20) && p.K16 <= 65535;
+    return !wino_no_workspace(g, kind, p) && p.T16 <= (1 << 20) && p.K16 <= 65535;
 }
 
 template <int SET, bool HALF>
@@ -855,8 +1034,8 @@ static void launch_wino_many_t(const WinoTable &tbl, hipStream_t st) {
     hipLaunchKernelGGL((wino_output_many_kernel<SET, HALF>), dim3(tbl.n_out), dim3(256), 0, st, tbl);
 }
 
-// Layers [0, n) of one Winograd kind and storage type (n <= kMaxWinoLayers, none of them on the
-// fused route) in three launches; ws[i] is layer i's own region of wino_workspace_bytes.
+// Layers [0, n) of one Winograd kind and storage type (n <= kMaxWinoLayers, all of them with a
+// workspace) in three launches; ws[i] is layer i's own region of wino_workspace_bytes.
 hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const *x, const void *const *U,
                             const float *const *bias, void *const *y, void *const *ws, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -864,46 +1043,16 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
     const bool half = geos[0].dtype == NNV_F16;
     WinoTable tbl{};
     long n_in = 0, n_gemm = 0, n_out = 0;
-    // An item's wavefront should not outlast its share of the launch: matrix instructions of an item against
-    // those of the launch per SIMD; the channel steps of longer items are split over 2 or 4 wavefronts, and the
-    // layers with the longest wavefronts go first (but see below).  float16 F(2x2) items much shorter than a wavefront slot's
-    // share (four per SIMD) take several tile blocks one after the other (VGG-16-shaped stack 163 -> 157 us; the same on
-    // F(4x4) 106 -> 108, float32 F(4x4) 175 -> 177, F(6x6) 196 -> 208).
     WinoPlan plans[kMaxWinoLayers];
     int order[kMaxWinoLayers];
-    long mfmas[kMaxWinoLayers], total = 0, items = 0;
+    long mfmas[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) {
         if ((geos[i].dtype == NNV_F16) != half || !wino_many_supported(geos[i], kind)) return hipErrorInvalidValue;
         plans[i] = plan_wino(geos[i], kind);
-        const WinoPlan &p = plans[i];
-        const int tm = wino_tm(p, half);
-        total += (long)p.csteps * p.tn * p.alpha * p.alpha * p.K16 * p.nblk;
-        items += (long)p.alpha * p.alpha * ceil_div(p.K16, tm) * p.nblk;
-        // a step's panels come from HBM once per frequency, whatever the number of tile blocks that share them: at
-        // four wavefronts per SIMD 256 bytes of them take as long as three matrix instructions (half: a quarter of that per KB)
-        mfmas[i] = (long)p.csteps * std::max(tm * p.tn, (half ? 6 : 13) * tm / 4 / p.nblk);
         order[i] = i;
     }
-    const long per_simd = total / 1024;      // matrix instructions of the launch per SIMD
-    // The shortest wavefront worth a split, in matrix instructions.  float32: 128 while the launch has fewer items than the
-    // chip has SIMDs (a split puts idle ones to work), else 512: wavefronts that have to queue gain nothing from being
-    // shorter.  Measured over 110 launches of six stacks at batch 1-6 and 80-320 pixels, weights from HBM, geometric means of
-    // 256 / 512 / 1024 against 128: up to 1008 items 1.02 / 1.06 / 1.12, 1472 to 4000 items 0.99 / 0.97 / 0.98, to 8000
-    // 0.99 / 0.98 / 0.99, beyond (per_simd / 6 rules) 1.00 / 1.00 / 1.01.  float16: 64 to 384 take the same time within
-    // 1-2 %, 32 costs a launch of few items 5 %.
-    const long shortest = half ? 96 : items < 1024 ? 128 : 512;
-    const long most = std::max(shortest, per_simd / 6), least = per_simd / 4 / 4;
     int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
-    for (int i = 0; i < n; ++i) {
-        shifts[i] = 0;
-        while (shifts[i] < 2 && (mfmas[i] >> shifts[i]) > most && (plans[i].csteps >> (shifts[i] + 1)) >= (half ? 2 : 8)) ++shifts[i];
-        runs[i] = 1;
-        if (half && kind == NNV_WINO_F2 && shifts[i] == 0 && mfmas[i] < least) {
-            const int r = (int)std::min<long>(least / mfmas[i], plans[i].nblk);
-            runs[i] = ceil_div(plans[i].nblk, ceil_div(plans[i].nblk, r));      // equal runs
-            mfmas[i] *= runs[i];
-        }
-    }
+    const long per_simd = wino_many_split(n, plans, kind, half, mfmas, shifts, runs);
     // Longest first, except in float32 F(4x4) and F(6x6) launches of fewer than 2000 instructions per SIMD: they are bound by
     // U, and deep layers first put all of it in front of the arithmetic.  Same 110 launches, sorted against not, geometric means: F(2x2)
     // 0.99 (0.94-1.05), F(4x4) and F(6x6) below the line 1.01 (0.93-1.07), beyond it 0.98 (0.96-1.03).  float16: 0.98 (0.91-1.03).
@@ -936,16 +1085,46 @@ hipError_t launch_wino_many(int n, const Geo *geos, int kind, const void *const 
     return hipGetLastError();
 }
 
+// Layers [0, n) on the fused route, of one kind (n <= kMaxWinoLayers), in one launch; the layers of the longest workgroups first.
+hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const *x, const void *const *U, const float *const *bias, void *const *y, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (n > kMaxWinoLayers) return hipErrorInvalidValue;
+    WinoFusedTable tbl{};
+    int order[kMaxWinoLayers];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order, order + n, [&](int a, int b) { return geos[a].c > geos[b].c; });
+    const int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
+    long blocks = 0;
+    for (int o = 0; o < n; ++o) {
+        const int i = order[o];
+        const WinoPlan p = plan_wino(geos[i], kind);
+        if (!wino_fused_able(geos[i], kind)) return hipErrorInvalidValue;
+        tbl.layer[o] = wino_params(geos[i], p, x[i], U[i], bias ? bias[i] : nullptr, y[i], nullptr);
+        tbl.tm[o] = wino_fused_panels(p);
+        tbl.block0[o] = (int)blocks;
+        blocks += (long)ceil_div(p.T16, tn) * ceil_div(p.K16, tbl.tm[o]);
+        if (blocks >= (1L << 30)) return hipErrorInvalidValue;
+    }
+    for (int i = n; i < kMaxWinoLayers; ++i) tbl.block0[i] = INT_MAX;
+    tbl.n = (int)blocks;
+    const dim3 grid((unsigned)(((blocks + 8 * kWinoGroup - 1) / (8 * kWinoGroup)) * 8 * kWinoGroup));
+    const bool wide = std::all_of(geos, geos + n, [](const Geo &g) { return g.pw == 1; });
+#define NNV_WINO_FUSED(SET, WIDE) hipLaunchKernelGGL((wino_fused_kernel<SET, WIDE>), grid, dim3(wino_fused_threads(SET)), 0, st, tbl)
+    if (kind == NNV_WINO_F2) { if (wide) NNV_WINO_FUSED(0, true); else NNV_WINO_FUSED(0, false); }
+    else { if (wide) NNV_WINO_FUSED(1, true); else NNV_WINO_FUSED(1, false); }
+#undef NNV_WINO_FUSED
+    return hipGetLastError();
+}
+
 hipError_t launch_wino(const Geo &g, int kind, const void *x, const void *U, const float *bias, void *y, void *ws,
                        hipStream_t st) {
     const WinoPlan p = plan_wino(g, kind);
+    char fused = 0;
+    wino_fused_layers(1, &g, kind, &fused);
+    if (fused) return launch_wino_fused(1, &g, kind, &x, &U, &bias, &y, st);
     if (p.T16 > 65535 * 16 || p.K16 > 65535) return hipErrorInvalidValue;
     WinoParams w = wino_params(g, p, x, U, bias, y, ws);
     const int set = wino_set(kind, g.dtype);
-    if (wino_fused(g, kind, p)) {
-        if (set == WS_F2) return launch_wino_fused<0>(p, w, st);
-        return launch_wino_fused<1>(p, w, st);
-    }
     if (set == WS_F2) {
         if (g.dtype == NNV_F16) return launch_wino_t<0, true>(g, p, w, st);
         return launch_wino_t<0, false>(g, p, w, st);

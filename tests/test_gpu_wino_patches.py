@@ -2,6 +2,7 @@
 (no padding along the rows), whose patches are read element by element: the same sums, bit for bit."""
 import pytest
 
+from nnv_testlib import conv_tolerance
 from nnv_workloads import ConvLayer
 
 pytestmark = pytest.mark.gpu
@@ -19,7 +20,9 @@ def env():
 # (images, channels, height, width, outputs, padding rows): rows of one tile, of one partly outside, of 15, 16 and 17 tiles and more; rows of tiles that begin inside
 # a row of lanes; images of odd sizes, whose last elements are the end of x; channels that fill no step
 SHAPES = [(1, 5, 3, 1, 16, 1), (1, 8, 1, 3, 20, 1), (2, 19, 7, 7, 33, 1), (3, 6, 9, 13, 16, 1), (1, 17, 12, 31, 48, 0), (1, 4, 5, 64, 70, 1), (1, 33, 6, 67, 64, 2),
-          (2, 16, 14, 35, 65, 1), (1, 7, 30, 101, 24, 1), (1, 70, 11, 130, 40, 1), (4, 64, 56, 56, 64, 1), (1, 12, 150, 149, 96, 1)]
+          (2, 16, 14, 35, 65, 1), (1, 7, 30, 101, 24, 1), (1, 70, 11, 130, 40, 1), (4, 64, 56, 56, 64, 1), (1, 12, 150, 149, 96, 1),
+          # layers of many tiles, all three steps in one kernel: one, two and four panels of outputs and a ragged fifth, one to many chunks of channels and ragged last ones
+          (1, 1, 200, 201, 9, 1), (1, 22, 180, 190, 16, 1), (1, 30, 224, 225, 24, 1), (2, 40, 150, 170, 33, 1), (1, 64, 224, 224, 64, 1), (1, 121, 223, 190, 70, 1), (5, 96, 110, 90, 130, 0)]
 
 
 def forward(nnv, torch, kind, layers, grouped):
@@ -64,4 +67,9 @@ def test_wide_loads(env, kind, grouped):
         carried.append((n, c, h, w + 2, k, ph, 0, torch.nn.functional.pad(x, (1, 1)).contiguous(), raw))
     a, b = forward(nnv, torch, kind, padded, grouped), forward(nnv, torch, kind, carried, grouped)
     for l, u, v in zip(padded, a, b):
+        n, c, h, w, k, ph = l[:6]
+        ref = torch.nn.functional.conv2d(l[7].double().cpu(), l[8].double().cpu().reshape(k, c, 3, 3), None, padding=(ph, 1)).flatten()
+        ok = torch.isfinite(ref)
+        # the bound on |y - y64| / max |y| that all tests of this library hold a kind to
+        assert (u.cpu().double() - ref)[ok].abs().max() <= conv_tolerance(kind, False) * ref[ok].abs().max() or not torch.isfinite(l[7]).all(), l[:6]
         assert torch.equal(torch.nan_to_num(u, 3e38, 2e38, 1e38), torch.nan_to_num(v, 3e38, 2e38, 1e38)), l[:6]
