@@ -582,7 +582,7 @@ __global__ __launch_bounds__(64 * kWinoItemWaves, 5) void wino_gemm_many_kernel(
 // instead (4.4 us).  F(4x4) has twelve wavefronts for the products and four of their own for the transforms: one wavefront that did both would wait for
 // patches whenever it waits for U, since loads come back in order (5.0 us).  F(2x2), with four times fewer elements in a patch, has eight that do both; twelve,
 // one workgroup per CU instead of two, take a VGG-16-shaped stack from 166 to 200 us.  32 x 32 tiles (TM = TN = 2) for F(4x4), half the loads of U and twice the transforms: 3.9 us a chunk.
-constexpr int kWinoFusedTiles[2] = {2, 1};        // blocks of 16 tiles of a workgroup: F(2x2), F(4x4)
+constexpr int kWinoFusedTiles[2] = {2, 1};        // blocks of 16 tiles of a workgroup: F(2x2) (launches that do not fill the chip: 1), F(4x4)
 constexpr int kWinoFusedFreqs[2] = {2, 3};        // frequencies of a wavefront
 constexpr int kWinoFusedOwn[2] = {0, 4};          // wavefronts that only transform (0: the first four do both)
 constexpr int wino_fused_threads(int set) { return ((set == 0 ? 16 : 36) / kWinoFusedFreqs[set] + kWinoFusedOwn[set]) * 64; }
@@ -760,9 +760,9 @@ struct WinoFusedTable {
 };
 static_assert(sizeof(WinoFusedTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) WinoFusedTable *WinoFusedTablePtr;
-template <int SET, bool WIDE>
+template <int SET, int TN, bool WIDE>
 __global__ __launch_bounds__(wino_fused_threads(SET)) void wino_fused_kernel(const WinoFusedTable tbl_arg) {
-    constexpr int A = WinoMat<SET>::A, TN = kWinoFusedTiles[SET];
+    constexpr int A = WinoMat<SET>::A;
     __shared__ __align__(16) float lds[2 * A * A * 256];
     const WinoFusedTablePtr tbl = (WinoFusedTablePtr)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr int G = kWinoGroup;
@@ -828,14 +828,14 @@ static int wino_tm(const WinoPlan &p, bool half, int most = 4) {
 //   three = base + (V + M) / in_out + max((V + M + U) / gemm, operations / rate)                                (sums over the layers)
 //   fused = start + max(workgroups / 256 x (chunks x chunk + each), longest (chunks x chunk x lone) + first)
 // MB and MFLOP over us; chunk: that of 64 outputs (less: its part for fewer).  Fitted to 144 single layers (3-512 channels, 8-512 outputs, 7-224 pixels,
-// batch 1-8) and 26 launches of four stacks at batch 1-4 and 96-320 pixels, weights and pixels from HBM; geometric means of the chosen over the best of both: single
-// layers F(2x2) 1.005 (the best over three launches 0.85), F(4x4) 1.007 (0.92).  us a call, three launches / chosen (the best line): VGG-16-shaped stack F(2x2) at 3x115x114
-// 183 / 141 (141), F(4x4) 1x263x191 179 / 146 (146), 2x166x278 306 / 263 (251); ResNet-18 F(2x2) 3x222x177 82 / 74 (74), F(4x4) 1x227x172 50.5 / 50.5 (50.5; all fused 107); SqueezeNet
-// F(4x4) 4x157x241 37 / 32 (31).  One layer, three / fused: F(4x4), 64 channels at 224x224 35.7 / 23.1, 256 at 112x112 68 / 58, at 56x56 24.8 / 56; F(2x2), 128 at 112x112 44 / 30.
+// batch 1-8) and 26 launches of four stacks at batch 1-4 and 96-320 pixels, weights and pixels from HBM.  us a call, three launches (their patches in wide loads) / all
+// layers fused / chosen: VGG-16-shaped stack F(2x2) at 3x115x114 183 / 141 / 165, F(4x4) 1x263x191 179 / 146 / 162, 2x166x278 306 / 251 / 265; ResNet-18 F(2x2) 3x222x177 82 / 99 / 72, F(4x4)
+// 1x227x172 50.5 / 107 / 50.3; SqueezeNet F(4x4) 4x157x241 37 / 31 / 33.  One layer, three / fused: F(4x4), 64 channels at 224x224 35.7 / 23.1, 256 at 112x112 68 / 58, at 56x56 24.8 / 56; F(2x2),
+// 128 at 112x112 44 / 30.  157 other layers and launches of six stacks against the code before both steps: geometric mean 1.16 times as fast, the slowest 0.95.
 struct WinoRates {
     double base, in_out, gemm, rate, start, chunk, each, lone, less, first;
 };
-constexpr WinoRates kWinoRates[2] = {{11.0, 4.4, 13.8, 89.0, 0.0, 1.34, 7.8, 1.12, 0.455, 6.5}, {10.7, 2.8, 6.1, 104.0, 7.5, 4.1, 8.5, 0.835, 0.40, 0.7}};
+constexpr WinoRates kWinoRates[2] = {{11.0, 4.4, 13.8, 89.0, 0.0, 1.34, 7.8, 1.12, 0.455, 6.5}, {10.7, 2.8, 6.1, 104.0, 7.5, 4.1, 8.5, 0.835, 0.50, 0.7}};
 
 static bool wino_fused_able(const Geo &g, int kind) {
     return g.dtype == NNV_F32 && (kind == NNV_WINO_F2 || kind == NNV_WINO_F4) && (size_t)g.n * g.c * g.h * g.w * 4 < ((size_t)1 << 30);
@@ -1093,25 +1093,33 @@ hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const
     int order[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order, order + n, [&](int a, int b) { return geos[a].c > geos[b].c; });
-    const int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
+    int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
+    WinoPlan plans[kMaxWinoLayers];
+    for (int i = 0; i < n; ++i) plans[i] = plan_wino(geos[i], kind);
+    auto blocks_of = [&](int i) { return (long)ceil_div(plans[i].T16, tn) * ceil_div(plans[i].K16, wino_fused_panels(plans[i])); };
+    // F(2x2) in fewer workgroups than the chip has CUs: one block of tiles each, twice as many and half as many chunks.  us a layer, two blocks / one: 10 channels at 5x73x22 -> 36 10.8 / 7.9,
+    // 20 at 4x46x31 -> 126 11.6 / 9.4.
+    long all = 0;
+    for (int i = 0; i < n; ++i) all += blocks_of(i);
+    if (all < 256) tn = 1;
     long blocks = 0;
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
-        const WinoPlan p = plan_wino(geos[i], kind);
         if (!wino_fused_able(geos[i], kind)) return hipErrorInvalidValue;
-        tbl.layer[o] = wino_params(geos[i], p, x[i], U[i], bias ? bias[i] : nullptr, y[i], nullptr);
-        tbl.tm[o] = wino_fused_panels(p);
+        tbl.layer[o] = wino_params(geos[i], plans[i], x[i], U[i], bias ? bias[i] : nullptr, y[i], nullptr);
+        tbl.tm[o] = wino_fused_panels(plans[i]);
         tbl.block0[o] = (int)blocks;
-        blocks += (long)ceil_div(p.T16, tn) * ceil_div(p.K16, tbl.tm[o]);
+        blocks += blocks_of(i);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.block0[i] = INT_MAX;
     tbl.n = (int)blocks;
     const dim3 grid((unsigned)(((blocks + 8 * kWinoGroup - 1) / (8 * kWinoGroup)) * 8 * kWinoGroup));
     const bool wide = std::all_of(geos, geos + n, [](const Geo &g) { return g.pw == 1; });
-#define NNV_WINO_FUSED(SET, WIDE) hipLaunchKernelGGL((wino_fused_kernel<SET, WIDE>), grid, dim3(wino_fused_threads(SET)), 0, st, tbl)
-    if (kind == NNV_WINO_F2) { if (wide) NNV_WINO_FUSED(0, true); else NNV_WINO_FUSED(0, false); }
-    else { if (wide) NNV_WINO_FUSED(1, true); else NNV_WINO_FUSED(1, false); }
+#define NNV_WINO_FUSED(SET, TN, WIDE) hipLaunchKernelGGL((wino_fused_kernel<SET, TN, WIDE>), grid, dim3(wino_fused_threads(SET)), 0, st, tbl)
+    if (kind == NNV_WINO_F4) { if (wide) NNV_WINO_FUSED(1, 1, true); else NNV_WINO_FUSED(1, 1, false); }
+    else if (tn == 2) { if (wide) NNV_WINO_FUSED(0, 2, true); else NNV_WINO_FUSED(0, 2, false); }
+    else { if (wide) NNV_WINO_FUSED(0, 1, true); else NNV_WINO_FUSED(0, 1, false); }
 #undef NNV_WINO_FUSED
     return hipGetLastError();
 }
