@@ -349,7 +349,10 @@ __device__ __forceinline__ uint32_t gemm_a_offset(const GemmParams &g, const int
     return mb0 + panel < g.K16 ? (uint32_t)panel * panel_steps * 256u + (uint32_t)slot * 64u + (uint32_t)(col % QM) * (4u * TM) : kOobOffset;
 }
 
-template <int TM, int TN>
+// CHAINS = 2: the products go to two sets of sums in turn, added at the end.  Single layers and those of a cold pass take two: a sum of half as many products
+// at a time is nearer to the exact one (64 channels at 56x56 -> 64, relative 2-norm of the error, one chain / two: 2.17e-7 / 1.60e-7), which is what lets a layer's reduction be cut
+// into fewer wavefronts (plan_im2col).
+template <int TM, int TN, int CHAINS>
 __device__ __forceinline__ void gemm_accumulate_3x3(const GemmParams &g, const int mb0, const int nb0, const int ks,
                                                     const int nsplit, const int lane, floatx4 (&acc)[TM][TN],
                                                     PixState<TN> &px) {
@@ -376,6 +379,7 @@ __device__ __forceinline__ void gemm_accumulate_3x3(const GemmParams &g, const i
     const uint32_t a_base = (uint32_t)mb0 * (uint32_t)cblocks * 9u;
     typename FloatVec<TM>::type a[3][3];
     float b[3][3][TN];
+    floatx4 sum[CHAINS][TM][TN];
     auto load_row = [&](const int r, int cb) __attribute__((always_inline)) {
         cb = max(min(cb, cb_end - 1), 0);          // past the range: re-read valid data that is not used
         const bool partial = g.c_rem != 0 && cb == cblocks - 1;     // uniform
@@ -398,13 +402,17 @@ __device__ __forceinline__ void gemm_accumulate_3x3(const GemmParams &g, const i
 #pragma unroll
             for (int m = 0; m < TM; ++m)
 #pragma unroll
-                for (int t = 0; t < TN; ++t)
-                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(a[r][sx], m), b[r][sx][t], acc[m][t], 0, 0, 0);
+                for (int t = 0; t < TN; ++t) {
+                    floatx4 &to = sum[(r * 3 + sx) % CHAINS][m][t];
+                    to = __builtin_amdgcn_mfma_f32_16x16x4f32(float_of<TM>(a[r][sx], m), b[r][sx][t], to, 0, 0, 0);
+                }
     };
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
+    for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-        for (int t = 0; t < TN; ++t) acc[m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) sum[c][m][t] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (cb_begin < cb_end) {
         load_row(0, cb_begin);
         load_row(1, cb_begin);
@@ -425,9 +433,13 @@ __device__ __forceinline__ void gemm_accumulate_3x3(const GemmParams &g, const i
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int t = 0; t < TN; ++t) acc[m][t] = CHAINS == 2 ? sum[0][m][t] + sum[CHAINS - 1][m][t] : sum[0][m][t];
 }
 
-// The same sums, in the same order, for 3x3 filters at stride 1 with one column of padding: the pixels of a tile go through LDS.
+// The same sums, in the same order and the same two chains, for 3x3 filters at stride 1 with one column of padding: the pixels of a tile go through LDS.
 // What bounds the smallest tile is the vector memory path of its CU: a product takes a fragment of weights and a gather of 16 pixels x 4 planes, and
 // the nine taps gather the same pixels nine times.  Outputs n and n + 1 of a row lie over neighbouring inputs, so that the three rows of input under 16 outputs are
 // 18 entries each, whatever the width of the image: a wavefront reads them with one load per channel, lays them down in a buffer of its own and takes the taps
@@ -481,6 +493,7 @@ __device__ __forceinline__ void gemm_accumulate_patch(const GemmParams &g, const
         for (int c = 0; c < 4; ++c) lds[buf + c * kPatchChannel + lane] = xr[d][c];
     };
     acc[0][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
     if (cb_begin >= cb_end) return;
     // The pixels of block b, in registers b % D, go to LDS one block ahead: the registers are free when block b begins.
     load_x(0, cb_begin);
@@ -507,10 +520,14 @@ __device__ __forceinline__ void gemm_accumulate_patch(const GemmParams &g, const
             put((i + 1) % D, cur);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], b[k], acc[0][0], 0, 0, 0);
+            for (int k = 0; k < 9; ++k) {
+                floatx4 &to = k % 2 ? odd : acc[0][0];
+                to = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], b[k], to, 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    acc[0][0] += odd;
 }
 
 // 1x1 filters: a chunk is four channel blocks, three chunks form the ring.
@@ -1093,7 +1110,7 @@ __global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void
     if constexpr (PATCH) {
         gemm_accumulate_patch(g, mb0, nb0, ks, KS, lane, red + wave * kPatchFloats, acc, px);
         if (KS > 1) __syncthreads();                                     // the partial sums take the place of the pixels
-    } else if constexpr (ROWS3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
+    } else if constexpr (ROWS3) gemm_accumulate_3x3<TM, TN, TM * TN <= 2 ? 2 : 1>(g, mb0, nb0, ks, KS, lane, acc, px);
     else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(g, mb0, nb0, ks, KS, lane, acc, px);
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(g, mb0, nb0, ks, KS, lane, acc, px);
 
@@ -1153,7 +1170,7 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
     const int ks = rest % L.nsplit, mt = rest / L.nsplit;       // order: tile row, range, tile column (fastest)
     floatx4 acc[TM][TN];
     PixState<TN> px;
-    if constexpr (!HALF && MODE == 3) gemm_accumulate_3x3<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
+    if constexpr (!HALF && MODE == 3) gemm_accumulate_3x3<TM, TN, 1>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (MODE == kModeOctets) gemm_accumulate_octets<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (MODE == kModeTaps) gemm_accumulate_taps<TM, TN>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     else if constexpr (MODE == kModePairs) gemm_accumulate_pairs<TM>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
@@ -1433,7 +1450,7 @@ __device__ __forceinline__ void gemm_layer_block(const GemmParams &g, const int 
     PixState<TN> px;
 #pragma nounroll
     for (int z = ks; z < KS; z += per_tile) {
-        if constexpr (MODE == 3) gemm_accumulate_3x3<TM, TN>(g, mb0, nb0, z, KS, lane, acc, px);
+        if constexpr (MODE == 3) gemm_accumulate_3x3<TM, TN, 2>(g, mb0, nb0, z, KS, lane, acc, px);
         else if constexpr (MODE == kModePatch) gemm_accumulate_patch(g, mb0, nb0, z, KS, lane, red + kLayerRed + wave * kPatchFloats, acc, px);
         else gemm_accumulate<false, TM, TN, MODE, 2>(g, mb0, nb0, z, KS, lane, acc, px);
         gemm_put_partial<TM, TN>(acc, red, KS, nt * KS + z, lane);
@@ -1557,7 +1574,8 @@ static GemmPlan plan_im2col(const Geo &g) {
     // Batch-1 layers are latency-bound.  What pays (measured on ResNet-18-shaped layers): the
     // 32x32 tile only with thousands of tiles; the 32x16 tile while it still leaves >= 160 tiles,
     // its units split over KS wavefronts up to ~2048 wavefronts (1536 for float32 3x3, whose wavefronts of two channel blocks are mostly start: 64 channels at 56x56
-    // 7.6 -> 7.0 us, 128 at 28x28 7.6 -> 7.2, 64 at 56x56 -> 128 at stride 2 7.7 -> 6.8; 48 layers by 1 % on average); else the 16x16 tile with a
+    // 7.8 -> 7.7 us, weights from HBM 7.4, 128 at 28x28 8.0 -> 7.6, 64 at 56x56 -> 128 at stride 2 7.9 -> 6.9; a wavefront's two chains of products keep the error where
+    // twice the wavefronts had it, gemm_accumulate_3x3); else the 16x16 tile with a
     // moderate split (>= 768 wavefronts) and a deeper register ring, because its few workgroups
     // stream the weights from HBM and each CU keeps only so many misses in flight.
     auto split_for = [&](long t, long target) {
