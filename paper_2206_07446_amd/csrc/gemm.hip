@@ -1923,7 +1923,6 @@ static ItemPlan plan_items(const Geo &g, const ItemTarget target_len, const Laye
 // and before the share of a SIMD counted, below, by which the ResNet-18-shaped launch takes items of 60 steps).
 constexpr int kItemStepsShortHalf = 48, kItemStepsMin = 48;
 constexpr int kItemsResident = 256 * 3 * kItemWaves;
-constexpr int kMostChunks = 6;
 
 // Items of whole workgroups: with W of them if each took one chunk (weighted by their blocks of pixels), an item takes W / 450, at least two
 // chunks: three workgroups fit a CU, and an item spends 5 us outside its products.  Launches of fewer than
@@ -1932,6 +1931,8 @@ constexpr int kMostChunks = 6;
 // against 106, 2146 (ResNet-18, 3x162x237) 126 / 112 / 103 / 105 against 116, 7488 (VGG-16) 285 / 233 / 211 / 203 (16: 198) against 296; below, W = 216 (GoogLeNet, 201 x 134)
 // 53 / 59 / 86 / 100 against 60.  Taken together 4 % over the best of 0, 1, 2, 3, 4, 6, 8 and 16 for each launch; no other line, divisor or least range tried came below 3 %
 // (three chunks at least: ResNet-18 48 -> 53).  The worst: W = 397 (AlexNet, 2x225x156), 60 where three chunks give 42 and fill the chip once.
+// (Three to six chunks where that makes one round of one to one and a half take AlexNet-shaped stacks at 2x314x246 from 81 to 66 us, 3x224x200 75 / 61, 4x200x180 82 / 64, but a chain of sums two or three
+// times as long is further from the exact ones: 1.3e-7 -> 1.6e-7 to 2.3e-7 of their 2-norm.)
 // float16, W in chunks of 3x3 filters of 64 x 112 outputs, four chunks of 1x1 filters to one: below 600 single-wavefront items; else the channels stay whole
 // if no layer has more than 12 chunks (48 of 1x1 filters), since partial tiles and their sums cost 3 us (6 when a launch added them), and otherwise a range is W / 330 chunks, at
 // least four: an item of 512 channels takes 24 us.  us a call at 0 / 4 / 8 / 12 or more chunks, none longer than 12: W = 662 (AlexNet-shaped, 2x211x317) 25 / 29 / 29 / 23, 1273
@@ -1968,23 +1969,12 @@ static ItemTarget items_target(int n, const Geo *geos, LayerPlan *known) {
         }
         return tot;
     };
-    long total = total_at(kItemSteps);
+    const long total = total_at(kItemSteps);
     if (geos[0].dtype == NNV_F16) {
         if (total < 3L * kItemsResident) target.steps = kItemStepsShortHalf;
         return target;
     }
     constexpr long fit = (long)kItemsResident * 15 / 16;
-    // One and a half times what is resident at most, where longer ranges of workgroups make that one round: an item whose partial sums have to meet holds its place for another
-    // 3-5 us, and those of a second, partly filled round wait for it.  us a call without / with, of 52 launches of four stacks those that change: AlexNet-shaped stack at 2x314x246
-    // 81 / 65, 3x224x200 76 / 61, 4x200x180 83 / 65.
-    if (target.chunks > 0 && total > kItemsResident && total <= kItemsResident * 3L / 2) {
-        const int chunks = target.chunks;
-        for (; target.chunks < kMostChunks && total > fit; ++target.chunks, total = total_at(kItemSteps)) {}
-        if (total > fit) {
-            target.chunks = chunks;
-            total = total_at(kItemSteps);
-        }
-    }
     long items = total;                 // at target.steps
     if (total <= fit)
         for (int t = kItemSteps - 12; t >= kItemStepsMin; t -= 12) {
