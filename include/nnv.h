@@ -178,7 +178,9 @@ int nnv_conv_forward_relu(const nnv_conv_desc *desc, nnv_kind kind, const void *
  *   descs, kinds, x, w_tx, y : HOST arrays of length n_layers (descriptors, kinds, device
  *       pointers as for nnv_conv_forward); outputs must not overlap
  *   bias  : NULL, or a HOST array of n_layers device pointers (entries may be NULL)
- *   workspace : device, >= nnv_conv_forward_grouped_workspace_bytes(...) bytes
+ *   workspace : device, >= nnv_conv_forward_grouped_workspace_bytes(...) bytes (as this build of the library
+ *       reports them), whatever its contents; this call's alone from its first launch to its last (two calls at a time on one
+ *       workspace spoil each other's outputs, no later call's)
  *   flags : 0, or NNV_FORWARD_RELU for y = max(conv + bias, 0) on every layer
  * Errors: NULL, BAD_DESC, ARG, UNSUPPORTED, WORKSPACE, ALIGN, HIP; nothing is launched unless
  * every layer passes the checks. */

@@ -26,6 +26,7 @@
 // one chunk ahead of the MFMAs (register ping-pong).  KS wavefronts of a workgroup share one
 // output tile and split the channel blocks; partial sums meet in LDS, fixed order.
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include "nnv_internal.h"
 #include "buf.h"
@@ -928,17 +929,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_y_rsrc(const GemmParams &
 // them up, in the order of the ranges, and stores y.  A launch of its own for that took 4-6.5 us behind all items; here most tiles are added up while others
 // are still multiplied.  What is left of it is latency, one trip to memory for the stores, one or two for the word of arrivals, one per few ranges.  us a call, launch / this:
 // ResNet-18-shaped stack 39.2 / 36.5, MobileNetV2-shaped plan 33.6 / 30.0, ResNet-50 in float16 39.1 / 34.5.
-// Nothing in the workspace has to be cleared: a tile's word of arrivals counts while its upper 48 bits are kSplitMark, any other content means that
-// nobody has arrived, and the last one clears it.  The partial sums are stored through to memory and read past the caches that other
+// Nothing in the workspace has to be cleared: a tile's word of arrivals counts while its upper 48 bits are the launch's mark, any other content means that
+// nobody has arrived, and the last one clears it.  Every launch has a mark of its own (a replayed one the same each time): what a launch leaves behind
+// whose workspace another call overwrote while it ran, which spoils these two, means nothing to a later one.  The partial sums are stored through to memory and read past the caches that other
 // XCDs do not share (sc1, the scope of one GPU); a wavefront waits for its stores before it, or the workgroup's first thread, arrives.
 // More than kSplitMost ranges go in two steps, groups of them first: one wavefront takes 1.5 us for every three ranges of a 64 x 32 tile (ResNet-18-shaped stack at 130x111, whose
 // 512-channel layers have 43, 42.2 -> 30.7 us a call; a launch behind the items took 34.3).
 struct SplitTile {
     char *tile;         // [range][wavefront][block of 16 x 16][lane] floatx4, then the words of arrivals in 256 bytes: of the tile, of its groups
     int ks, n;          // which range; ranges in all (1: the item stores y itself)
+    unsigned long long mark;
 };
 constexpr int kSplitScope = 16;                         // sc1
-constexpr unsigned long long kSplitMark = 0x7fa5c3e996b1ull;
+constexpr unsigned long long kSplitMark = 0x7fa5c3e996b1ull;    // of the first launch; 48 bits
 constexpr size_t kSplitWord = 256;
 constexpr int kSplitMost = 12, kSplitGroup = 6, kSplitGroups = 31;
 
@@ -947,12 +950,12 @@ __device__ __forceinline__ unsigned long long split_look(const char *word) {
 }
 // One thread, which has looked at the word before (on its way beside the partial sums); true for the last of n.  (Every exchange that fails means that
 // another arrival's went through since, and there are n of them.)
-__device__ __forceinline__ bool split_arrive(char *word, const int n, unsigned long long seen) {
+__device__ __forceinline__ bool split_arrive(char *word, const int n, unsigned long long seen, const unsigned long long mark) {
     unsigned long long *w = reinterpret_cast<unsigned long long *>(word);
     for (;;) {
-        const int before = seen >> 16 == kSplitMark ? (int)(seen & 0xffff) : 0;
+        const int before = seen >> 16 == mark ? (int)(seen & 0xffff) : 0;
         const bool last = before + 1 >= n;
-        if (__hip_atomic_compare_exchange_strong(w, &seen, last ? 0ull : kSplitMark << 16 | (unsigned long long)(before + 1), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+        if (__hip_atomic_compare_exchange_strong(w, &seen, last ? 0ull : mark << 16 | (unsigned long long)(before + 1), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return last;
     }
@@ -1015,10 +1018,10 @@ __device__ __forceinline__ bool split_fold(const SplitTile &sp, const uint32_t m
         if constexpr (WG) {
             int *flag = reinterpret_cast<int *>(lds);
             __syncthreads();
-            if (one) flag[0] = split_arrive(word, n, seen);
+            if (one) flag[0] = split_arrive(word, n, seen, sp.mark);
             __syncthreads();
             last = flag[0];
-        } else if (one) last = split_arrive(word, n, seen);
+        } else if (one) last = split_arrive(word, n, seen, sp.mark);
         if (__builtin_amdgcn_readfirstlane(last) == 0) return false;
         split_sum<TM, TN>(acc, res, mine, (uint32_t)first * BYTES, (uint32_t)step * BYTES, n);
         if (word == words) return true;
@@ -1130,6 +1133,7 @@ __global__ __launch_bounds__(TM * TN == 8 ? 256 : TM * TN == 4 ? 64 : 1024) void
 struct GemmItemLayer {
     GemmParams g;
     char *part;         // partial tiles of a split layer (workspace)
+    unsigned long long mark;    // of the launch, in the words of arrivals
     int ntn;            // tiles along the pixels
     int nsplit;         // ranges of the reduction (1: the item stores y itself)
     int mode, tm;       // chunking mode (ModeT); 16-row panels per tile (1, 2 or 4)
@@ -1158,6 +1162,7 @@ struct GemmItemTable {
     // first item of each layer, INT_MAX beyond the last layer: a workgroup finds its layer by counting the entries it has reached (table_find)
     int item0[kMaxGemmLayers];
     char *part_base;
+    unsigned long long mark;
     int nitems;
     int group;          // consecutive items handed to one XCD
 };
@@ -1178,7 +1183,7 @@ __device__ __forceinline__ void gemm_item(const GemmItemLayer &L, const int loca
     else gemm_accumulate<HALF, TM, TN, MODE, NBUF>(L.g, mt * TM, nb * TN, ks, L.nsplit, lane, acc, px);
     __builtin_amdgcn_s_setprio(3);
     if (L.nsplit > 1) {
-        const SplitTile sp{L.part + (size_t)(mt * L.ntn + nb) * ((size_t)L.nsplit * (TM * TN * 1024) + kSplitWord), ks, L.nsplit};
+        const SplitTile sp{L.part + (size_t)(mt * L.ntn + nb) * ((size_t)L.nsplit * (TM * TN * 1024) + kSplitWord), ks, L.nsplit, L.mark};
         if (!split_fold<false, TM, TN>(sp, (uint32_t)lane * 16u, nullptr, acc)) return;
     }
     {
@@ -1240,6 +1245,7 @@ __device__ __forceinline__ void load_item_layer(GemmItemLayer &L, const GemmItem
     gemm_derived(g, half, r.mode);
     g.relu = r.relu;
     L.part = tbl->part_base + (size_t)r.part256 * 256;
+    L.mark = tbl->mark;
     L.ntn = (g.npix + 31) >> 5;
     L.nsplit = r.nsplit;
     L.tm = r.tm;
@@ -1312,7 +1318,7 @@ __device__ __forceinline__ void run_tile_item(const GemmItemTablePtr tbl, const 
     int per = chunks;
     if (nsplit > 1) per = __builtin_amdgcn_readfirstlane((chunks + nsplit - 1) / nsplit);
     const int c0 = ks * per, c1 = min(chunks, c0 + per);
-    const SplitTile sp{tbl->part_base + (size_t)r.part256 * 256 + (size_t)(mt * ntiles + nt) * ((size_t)nsplit * (tile_regs(r) * 1024u) + kSplitWord), ks, SPLIT ? nsplit : 1};
+    const SplitTile sp{tbl->part_base + (size_t)r.part256 * 256 + (size_t)(mt * ntiles + nt) * ((size_t)nsplit * (tile_regs(r) * 1024u) + kSplitWord), ks, SPLIT ? nsplit : 1, tbl->mark};
     if constexpr (HALF && TILE != kLargeTiles) {
         if (r.mode == kModeTaps) {
             if (r.tm == 5) few_item<7>(T, mt, nt, lds);
@@ -2123,6 +2129,8 @@ static hipError_t launch_planned(int n, const Geo *geos, const ItemPlan *plans, 
     tbl.nitems = items;
     tbl.group = 2;       // workgroups (of kItemWaves items) handed to one XCD in a row
     tbl.part_base = base;
+    static std::atomic<unsigned long long> launches{0};
+    tbl.mark = (kSplitMark + launches.fetch_add(1, std::memory_order_relaxed)) & 0xffffffffffffull;
     if (ncl > 0) {
         for (int i = ncl; i < kMaxGemmLayers; ++i) cl.block0[i] = INT_MAX;
         cl.nblocks = clblocks;

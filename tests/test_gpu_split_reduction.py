@@ -48,13 +48,15 @@ def test_any_workspace(env, dtype):  # noqa: F811
                                      nnv.FORWARD_RELU, stream=stream)
 
     first = None
-    for fill in ("zeros", "ones", "noise", "as the last call left it", "shifted"):
+    for fill in ("zeros", "ones", "noise", "as the last call left it", "shifted", "words of an earlier launch"):
         if fill == "ones":
             wsbuf.fill_(255)
         elif fill == "noise":
             ws[:need // 4 * 4].view(torch.float32).normal_()
         elif fill == "shifted":             # partial sums where the words of arrivals were
             ws.copy_(torch.roll(ws.clone(), 4096 + 16))
+        elif fill == "words of an earlier launch":      # the process's first one, whose workspace another call overwrote: one arrival everywhere
+            ws[:need // 8 * 8].view(torch.int64).fill_(0x7fa5c3e996b1 << 16 | 1)
         wsbuf[:PAD] = 0x5A
         wsbuf[PAD + need:] = 0x5A
         for c in cases:
