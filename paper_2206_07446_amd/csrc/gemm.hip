@@ -489,9 +489,13 @@ __device__ __forceinline__ void gemm_accumulate_patch(const GemmParams &g, const
             xr[d][c] = buf_load<float>(ok ? xres : zres, xo, ok ? (uint32_t)cb * g.cb_stride + c * plane : 0u);
         }
     };
+    // (lanes read what others of the wavefront wrote: everything before the fence in order before everything after it; no instruction)
     auto put = [&](const int d, const uint32_t buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) lds[buf + c * kPatchChannel + lane] = xr[d][c];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     acc[0][0] = floatx4{0.f, 0.f, 0.f, 0.f};
     floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
