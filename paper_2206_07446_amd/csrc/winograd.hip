@@ -784,6 +784,135 @@ __global__ __launch_bounds__(wino_fused_threads(SET)) void wino_fused_kernel(con
     else wino_fused_block<SET, 1, TN, WIDE>(w, wg - first, lds);
 }
 
+// ---- layers of one step of channels (four of them: the first layer of a network) by themselves.  A workgroup of the kernel above is all start and end there: its wavefronts wait
+// for four that transform, then M goes through LDS once more.  Here a wavefront owns 16 tiles x 16 output channels and every lane transforms the patch of one (tile, channel) pair in
+// registers: lane (tile l%16, channel l/16) then holds, for every frequency, exactly its element
+// of the B operand of the 16x16x4 MFMA.  The alpha^2 accumulators stay in registers and the
+// output transform is applied to them in place (accumulator register j of lane l is output
+// channel 4*(l/16)+j of tile l%16).  The input transform is repeated by every 16-channel block
+// of K, and a wavefront has nobody beside it to wait for its patches: no longer worth it from two steps on (wino_waves).
+// The sums are those of the kernel above, bit for bit.
+template <int SET>
+__global__ __launch_bounds__(256) void wino_wave_kernel(const WinoParams w) {
+    using Wm = WinoMat<SET>;
+    constexpr int A = Wm::A, M = Wm::M, AA = A * A;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // logical order: tile blocks fastest, so neighbouring workgroups share U; the four
+    // wavefronts of a workgroup share the patches (same tiles, four blocks of output channels)
+    const int lwg = xcd_logical_tile(w.gemm_wgs_per_xi);
+    if (lwg < 0) return;
+    const int T16 = (w.T + 15) >> 4;
+    const int kbg = lwg / T16, tb = lwg - kbg * T16;
+    const int kb = kbg * 4 + wave;
+    if (kb >= w.K16) return;
+    const int col = lane & 15, slot = lane >> 4;
+    const int t = tb * 16 + col;
+    const bool live = t < w.T;
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(w.x, w.x_bytes);
+    const __amdgpu_buffer_rsrc_t ures = make_rsrc(w.U, w.u_bytes);
+    const uint32_t plane4 = (uint32_t)(w.H * w.W) * 16u;     // bytes of 4 channel planes
+    // per-lane byte offsets of the patch rows and columns in channel `slot`; a step adds its
+    // channel base as the scalar offset.  Rows and columns in the zero padding (and every row of
+    // a surplus tile) carry 2^30 instead, which puts the sum beyond the end of x (x is smaller
+    // than 2^30 bytes on this route), so those elements read as zero.
+    constexpr uint32_t kOut = 0x40000000u;
+    uint32_t rowoff[A], coloff[A];
+    {
+        const int tt = live ? t : 0;
+        const int per = w.th * w.tw;
+        const int img = tt / per, rem = tt - img * per;
+        const int ti = rem / w.tw, tj = rem - ti * w.tw;
+        const int ih0 = ti * M - w.ph, iw0 = tj * M - w.pw;
+        const int base = (img * w.C + slot) * w.H * w.W;
+#pragma unroll
+        for (int u = 0; u < A; ++u) {
+            const int ih = ih0 + u;
+            rowoff[u] = (live && (unsigned)ih < (unsigned)w.H) ? (uint32_t)(base + ih * w.W) * 4u : kOut;
+        }
+#pragma unroll
+        for (int v = 0; v < A; ++v) {
+            const int iw = iw0 + v;
+            coloff[v] = (unsigned)iw < (unsigned)w.W ? (uint32_t)iw * 4u : kOut;
+        }
+    }
+    const uint32_t a_voff = lane * 4u;
+    const uint32_t a_base = (uint32_t)kb * w.csteps;          // fragment index at frequency 0, step 0
+    const uint32_t a_xi = (uint32_t)w.K16 * w.csteps;         // fragments per frequency
+    floatx4 acc[AA];
+#pragma unroll
+    for (int i = 0; i < AA; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // Everything a step needs is requested one step earlier.  Patches alternate between two
+    // register sets; the U fragment of frequency i is re-requested for the next step right
+    // after the MFMA that consumed it, into the same register.  Loads complete in order, and
+    // the order of issue is patch(s), U(s), patch(s+1), U(s+1), ..., so waiting for one of
+    // them never waits for anything requested later.  The scheduling barriers keep that order.
+    float d[2][A][A], a[AA];
+    const int full = w.C >> 2;                                // steps whose 4 channels all exist
+    const int last = w.csteps - 1;
+    auto load_patch = [&](int buf, int s) __attribute__((always_inline)) {
+        const uint32_t soff = (uint32_t)s * plane4;
+#pragma unroll
+        for (int u = 0; u < A; ++u)
+#pragma unroll
+            for (int v = 0; v < A; ++v) d[buf][u][v] = buf_load<float>(xres, rowoff[u] + coloff[v], soff);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_a = [&](int i, int s) __attribute__((always_inline)) {
+        a[i] = buf_load<float>(ures, a_voff, (a_base + (uint32_t)i * a_xi + s) * 256u);
+    };
+    auto step = [&](int buf, int s) __attribute__((always_inline)) {
+        float tmp[A][A], V[A][A];
+        NNV_MATMUL_LEFT(Wm::BT, A, A, A, d[buf], tmp)
+        NNV_MATMUL_RIGHT_T(Wm::BT, A, A, A, tmp, V)
+        const int sn = min(s + 1, last);
+#pragma unroll
+        for (int i = 0; i < AA; ++i) {
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], V[i / A][i % A], acc[i], 0, 0, 0);
+            load_a(i, sn);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (full > 0) load_patch(0, 0);
+#pragma unroll
+    for (int i = 0; i < AA; ++i) load_a(i, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (full > 0) {
+        int s = 0;
+        for (; s + 2 <= full; s += 2) {
+            load_patch(1, s + 1);
+            step(0, s);
+            load_patch(0, min(s + 2, full - 1));
+            step(1, s + 1);
+        }
+        if (s < full) step(0, s);
+    }
+    if (w.C & 3) {
+        // last step of a channel count that is not a multiple of 4: lanes of missing channels read zero
+        const bool cok = full * 4 + slot < w.C;
+        const uint32_t soff = (uint32_t)full * plane4;
+#pragma unroll
+        for (int u = 0; u < A; ++u)
+#pragma unroll
+            for (int v = 0; v < A; ++v) d[0][u][v] = buf_load<float>(xres, cok ? rowoff[u] + coloff[v] : kOobOffset, soff);
+        __builtin_amdgcn_sched_barrier(0);
+        step(0, full);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = kb * 16 + slot * 4 + j;
+        if (!live || k >= w.K) continue;
+        float m[A][A], tmp[M][A], Y[M][M];
+#pragma unroll
+        for (int u = 0; u < A; ++u)
+#pragma unroll
+            for (int v = 0; v < A; ++v) m[u][v] = acc[u * A + v][j];
+        NNV_MATMUL_LEFT(Wm::AT, M, A, A, m, tmp)
+        NNV_MATMUL_RIGHT_T(Wm::AT, M, A, M, tmp, Y)
+        wino_store_tile<M, false>(w, Y, t, k);
+    }
+}
+
 // ---------------------------------------------------------------- host side
 
 struct WinoPlan {
@@ -855,8 +984,19 @@ static bool wino_no_workspace(const Geo &g, int kind, const WinoPlan &p) {
     return fused_us < three_us;
 }
 
-// Panels per workgroup of the fused kernel.
-static int wino_fused_panels(const WinoPlan &p) { return p.K16 >= 3 ? 4 : p.K16; }
+// Panels per workgroup of the fused kernel, where a launch has workgroups enough.
+static int wino_fused_panels(const WinoPlan &p, const int most = 4) { return p.K16 >= 3 ? most : std::min(p.K16, most); }
+
+// Layers that do better as wavefronts of their own (wino_wave_kernel) than as workgroups, where a launch of workgroups of four panels fills the chip.
+// us a layer, workgroups / wavefronts: F(4x4), 3 channels at 224x224 -> 64 12.7 / 11.3, at 4x224x224 40.8 / 35.2, 4 at 4x224x224 40.6 / 39.5, 8 40.8 / 52.1, 3 -> 32 30.5 / 32.0 (-> 16 25.5 /
+// 29.5); F(2x2), 3 at 112x112 -> 64 7.1 / 6.1, -> 128 9.7 / 7.2, at 224x224 -> 64 12.6 / 11.9, -> 32 8.8 / 10.3, -> 16 6.5 / 5.9, 4x224x224 -> 16 17.5 / 14.5, 8 at 4x56x56 -> 64 7.1 / 7.6,
+// 7 at 8x31x74 -> 38 9.1 / 8.0 (three panels of four), 4 at 4x224x224 -> 96 57.9 / 62.5, at
+// 112x112 21.0 / 20.6.
+static bool wino_waves(int kind, const WinoPlan &p) {
+    if (p.K16 > 8) return false;                // (more repeat the input transform too often)
+    if (kind == NNV_WINO_F4) return p.csteps == 1 && p.K16 >= 3;
+    return p.csteps == 1 ? p.K16 != 2 && (p.K16 < 5 || p.T16 <= 1024) : p.csteps == 2 && p.K16 == 3;
+}
 
 // Panels per tile of a layer's own tile GEMM, and over how many (1 << shift) wavefronts its channel steps are split.
 // Latency-bound at batch 1 (measured on ResNet-18-shaped layers): the largest wavefront tile that still leaves >= 768 wavefronts; then
@@ -1096,20 +1236,36 @@ hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const
     int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
     WinoPlan plans[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) plans[i] = plan_wino(geos[i], kind);
-    auto blocks_of = [&](int i) { return (long)ceil_div(plans[i].T16, tn) * ceil_div(plans[i].K16, wino_fused_panels(plans[i])); };
+    auto blocks_of = [&](int i, int most) { return (long)ceil_div(plans[i].T16, tn) * ceil_div(plans[i].K16, wino_fused_panels(plans[i], most)); };
+    auto all_of = [&](int most) {
+        long all = 0;
+        for (int i = 0; i < n; ++i) all += blocks_of(i, most);
+        return all;
+    };
     // F(2x2) in fewer workgroups than the chip has CUs: one block of tiles each, twice as many and half as many chunks.  us a layer, two blocks / one: 10 channels at 5x73x22 -> 36 10.8 / 7.9,
     // 20 at 4x46x31 -> 126 11.6 / 9.4.
-    long all = 0;
-    for (int i = 0; i < n; ++i) all += blocks_of(i);
-    if (all < 256) tn = 1;
+    if (all_of(4) < 256) tn = 1;
+    // Fewer panels per workgroup, so more of them, while each still has a CU of its own (a workgroup of F(4x4) fills one).
+    // us a layer, four panels / two / one [workgroups]: F(4x4), 7 channels at 3x23x70 -> 122 [42 / 84 / 168] 14.3 / 10.4 / 8.7, 64 at 2x125x77 -> 59 [80 / 160 / 320] 23.0 / 17.2 / 25.1, 12 at
+    // 3x110x31 -> 206 [168 / 294 / 546] 14.2 / 18.2 / 21.1; F(2x2), 13 at 5x106x7 -> 33 [67 / 134 / 201] 6.7 / 5.4 / 4.9, 26 at 3x21x77 -> 153 [249 / 415 / 830] 9.6 / 10.9 / 12.0.
+    int most = 4;
+    while (most > 1 && all_of(most / 2) <= 256) most /= 2;
+    if (n == 1 && most == 4 && wino_waves(kind, plans[0])) {
+        WinoParams w = wino_params(geos[0], plans[0], x[0], U[0], bias ? bias[0] : nullptr, y[0], nullptr);
+        w.gemm_wgs_per_xi = plans[0].T16 * ceil_div(plans[0].K16, 4);
+        const dim3 grid(xcd_grid(w.gemm_wgs_per_xi));
+        if (kind == NNV_WINO_F2) hipLaunchKernelGGL((wino_wave_kernel<0>), grid, dim3(256), 0, st, w);
+        else hipLaunchKernelGGL((wino_wave_kernel<1>), grid, dim3(256), 0, st, w);
+        return hipGetLastError();
+    }
     long blocks = 0;
     for (int o = 0; o < n; ++o) {
         const int i = order[o];
         if (!wino_fused_able(geos[i], kind)) return hipErrorInvalidValue;
         tbl.layer[o] = wino_params(geos[i], plans[i], x[i], U[i], bias ? bias[i] : nullptr, y[i], nullptr);
-        tbl.tm[o] = wino_fused_panels(plans[i]);
+        tbl.tm[o] = wino_fused_panels(plans[i], most);
         tbl.block0[o] = (int)blocks;
-        blocks += blocks_of(i);
+        blocks += blocks_of(i, most);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.block0[i] = INT_MAX;
