@@ -366,29 +366,29 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
         collect(GroupedPlan::DW_RAW_MANY, NNV_DIRECT, kMaxDwLayers, 2,
                 [&](int i) { return kinds[i] == NNV_DIRECT && same_type(i) && supported(geos[i], NNV_DEPTHWISE); },
                 [&](int) { return (size_t)0; });
-        // The workspace holds every Winograd layer's region, also of those that run fused: which ones do depends on all layers of the call, and
-        // a workspace for many layers has to be enough for some of them.
-        for (int kind : {NNV_WINO_F2, NNV_WINO_F4, NNV_WINO_F6}) {
+        // float32 F(2x2) and F(4x4).  The workspace holds the region of every layer that has one, also of those that run fused: which ones do depends on all layers of the
+        // call, and a workspace for many layers has to be enough for some of them.
+        for (int kind : {NNV_WINO_F2, NNV_WINO_F4}) {
+            std::vector<int> of_kind;
+            for (int i = 0; i < n && !half; ++i)
+                if (kinds[i] == kind && same_type(i)) of_kind.push_back(i);
+            if (of_kind.size() < 2) continue;          // (one layer: runs by itself)
             std::vector<char> fused(n, 0);
-            std::vector<int> part;
             size_t off = 0;
-            auto close = [&]() {
-                std::vector<Geo> pg;
-                for (int i : part) pg.push_back(geos[i]);
-                std::vector<char> pf(part.size(), 0);
-                if (part.size() > 1) wino_fused_layers((int)part.size(), pg.data(), kind, pf.data());      // (one layer: runs by itself)
-                for (size_t j = 0; j < part.size(); ++j) fused[part[j]] = pf[j];
-                part.clear(); off = 0;
-            };
-            for (int i = 0; i < n; ++i) {
-                if (kinds[i] != kind || !same_type(i)) continue;
-                if (!wino_many_supported(geos[i], kind)) { fused[i] = !half && kind != NNV_WINO_F6 && ws_bytes(geos[i], kind) == 0; continue; }
-                off += align_up(ws_bytes(geos[i], kind), 256);
+            int regions = 0;
+            for (int i : of_kind) {
+                if (!wino_many_supported(geos[i], kind)) continue;
+                off = (regions++ % kMaxWinoLayers ? off : 0) + align_up(ws_bytes(geos[i], kind), 256);
                 gp.bytes = std::max(gp.bytes, off);
-                part.push_back(i);
-                if ((int)part.size() == kMaxWinoLayers) close();
             }
-            close();
+            for (size_t at = 0; at < of_kind.size(); at += kMaxWinoLayers) {
+                Geo part[kMaxWinoLayers];
+                char yes[kMaxWinoLayers];
+                const size_t m = std::min<size_t>(of_kind.size() - at, kMaxWinoLayers);
+                for (size_t j = 0; j < m; ++j) part[j] = geos[of_kind[at + j]];
+                wino_fused_layers((int)m, part, kind, yes);
+                for (size_t j = 0; j < m; ++j) fused[of_kind[at + j]] = yes[j];
+            }
             collect(GroupedPlan::WINO_FUSED, kind, kMaxWinoLayers, 1, [&](int i) { return fused[i] != 0; }, [&](int) { return (size_t)0; });
         }
         for (int kind : {NNV_WINO_F2, NNV_WINO_F4, NNV_WINO_F6})

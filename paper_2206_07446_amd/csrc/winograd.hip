@@ -582,7 +582,6 @@ __global__ __launch_bounds__(64 * kWinoItemWaves, 5) void wino_gemm_many_kernel(
 // instead (4.4 us).  F(4x4) has twelve wavefronts for the products and four of their own for the transforms: one wavefront that did both would wait for
 // patches whenever it waits for U, since loads come back in order (5.0 us).  F(2x2), with four times fewer elements in a patch, has eight that do both; twelve,
 // one workgroup per CU instead of two, take a VGG-16-shaped stack from 166 to 200 us.  32 x 32 tiles (TM = TN = 2) for F(4x4), half the loads of U and twice the transforms: 3.9 us a chunk.
-constexpr int kWinoFusedTiles[2] = {2, 1};        // blocks of 16 tiles of a workgroup: F(2x2) (launches that do not fill the chip: 1), F(4x4)
 constexpr int kWinoFusedFreqs[2] = {2, 3};        // frequencies of a wavefront
 constexpr int kWinoFusedOwn[2] = {0, 4};          // wavefronts that only transform (0: the first four do both)
 constexpr int wino_fused_threads(int set) { return ((set == 0 ? 16 : 36) / kWinoFusedFreqs[set] + kWinoFusedOwn[set]) * 64; }
@@ -952,19 +951,20 @@ static int wino_tm(const WinoPlan &p, bool half, int most = 4) {
 
 // Which layers run as the fused kernel.  The three launches are bound by V and M, written and read in between, and by U; the fused kernel reads U once per block
 // of tiles, from L2, and has no parallelism along the channels: a layer of many channels on few tiles is one long chain.  Both are estimated,
-// in us, and a launch of several layers takes those of at most so many channel steps that the sum is least, by 5 % (wino_fused_layers).  A layer whose
+// in us, and a launch of several layers takes those of at most so many channel steps that the sum is least, if that is 3 % less than none (wino_fused_layers).  A layer whose
 // channel steps the three launches would split keeps them: added up in one chain, 512 channels are 1.4 to 2 times further from the exact sums.
 //   three = base + (V + M) / in_out + max((V + M + U) / gemm, operations / rate)                                (sums over the layers)
-//   fused = start + max(workgroups / 256 x (chunks x chunk + each), longest (chunks x chunk x lone) + first)
-// MB and MFLOP over us; chunk: that of 64 outputs (less: its part for fewer).  Fitted to 144 single layers (3-512 channels, 8-512 outputs, 7-224 pixels,
-// batch 1-8) and 26 launches of four stacks at batch 1-4 and 96-320 pixels, weights and pixels from HBM.  us a call, three launches (their patches in wide loads) / all
-// layers fused / chosen: VGG-16-shaped stack F(2x2) at 3x115x114 183 / 141 / 165, F(4x4) 1x263x191 179 / 146 / 162, 2x166x278 306 / 251 / 265; ResNet-18 F(2x2) 3x222x177 82 / 99 / 72, F(4x4)
-// 1x227x172 50.5 / 107 / 50.3; SqueezeNet F(4x4) 4x157x241 37 / 31 / 33.  One layer, three / fused: F(4x4), 64 channels at 224x224 35.7 / 23.1, 256 at 112x112 68 / 58, at 56x56 24.8 / 56; F(2x2),
-// 128 at 112x112 44 / 30.  157 other layers and launches of six stacks against the code before both steps: geometric mean 1.16 times as fast, the slowest 0.95.
+//   fused = start + max(ceil(workgroups / 256) x mean of (chunks x chunk + each), longest (chunks x chunk x lone) + first)
+// MB and MFLOP over us; chunk and each: those of 64 outputs (less: their part for fewer).  Patches that are read element by element (padding other than one column) make a chunk
+// `single` times as long, and three launches by `narrow` per MB of V.  Fitted to 716 layers and launches of five stacks with every line drawn (3-512 channels,
+// 8-512 outputs, 7-320 pixels, batch 1-8), which it meets within 8 %; what it chooses is 0.1 to 0.4 % over the best line for each on average, and the slowest 1.05 times none fused.  us a call, three launches / all
+// layers fused / chosen: VGG-16-shaped stack F(2x2) at 3x115x114 172 / 156 / 156, F(4x4) 1x263x191 168 / 161 / 160, 2x166x278 302 / 265 / 264; ResNet-18 F(2x2) 3x222x177 80 / 85 / 73, F(4x4)
+// 1x224x224 51 / 75 / 51; SqueezeNet F(2x2) at 224x224 25.6 / 13.6 / 13.5, F(4x4) 4x157x241 39 / 31 / 31.  One layer, three / fused: F(4x4), 64 channels at 224x224 35.7 / 23.1, 256 at 112x112 68 / 58, at 56x56 24.8 / 56; F(2x2),
+// 128 at 112x112 44 / 30.
 struct WinoRates {
-    double base, in_out, gemm, rate, start, chunk, each, lone, less, first;
+    double base, in_out, gemm, rate, start, chunk, each, lone, less, first, single, narrow;
 };
-constexpr WinoRates kWinoRates[2] = {{11.0, 4.4, 13.8, 89.0, 0.0, 1.34, 7.8, 1.12, 0.455, 6.5}, {10.7, 2.8, 6.1, 104.0, 7.5, 4.1, 8.5, 0.835, 0.50, 0.7}};
+constexpr WinoRates kWinoRates[2] = {{9.15, 4.29, 5.58, 86.3, 2.55, 1.22, 2.94, 1.43, 0.473, 1.74, 1.32, 0.026}, {9.82, 3.23, 5.47, 91.3, 3.18, 2.93, 8.15, 1.27, 0.477, 3.51, 1.81, 0.048}};
 
 static bool wino_fused_able(const Geo &g, int kind) {
     return g.dtype == NNV_F32 && (kind == NNV_WINO_F2 || kind == NNV_WINO_F4) && (size_t)g.n * g.c * g.h * g.w * 4 < ((size_t)1 << 30);
@@ -984,8 +984,27 @@ static bool wino_no_workspace(const Geo &g, int kind, const WinoPlan &p) {
     return fused_us < three_us;
 }
 
-// Panels per workgroup of the fused kernel, where a launch has workgroups enough.
-static int wino_fused_panels(const WinoPlan &p, const int most = 4) { return p.K16 >= 3 ? most : std::min(p.K16, most); }
+// Panels per workgroup of the fused kernel.
+static int wino_fused_panels(const WinoPlan &p, const int most) { return p.K16 >= 3 ? most : std::min(p.K16, most); }
+
+// Blocks of tiles and, at most, panels of its workgroups.
+struct WinoForm { int tn, most; };
+constexpr int kWinoForms = 4;
+constexpr WinoForm kWinoForm[2][kWinoForms] = {{{2, 4}, {1, 4}, {1, 2}, {1, 1}}, {{1, 4}, {1, 4}, {1, 2}, {1, 1}}};
+static long wino_form_blocks(const WinoPlan &p, const WinoForm &f) { return (long)ceil_div(p.T16, f.tn) * ceil_div(p.K16, wino_fused_panels(p, f.most)); }
+
+// Which of them a launch takes; all: its workgroups in each.
+// F(2x2) in fewer workgroups than the chip has CUs: one block of tiles each, twice as many and half as many chunks.  us a layer, two blocks / one: 10 channels at 5x73x22 -> 36 10.8 / 7.9,
+// 20 at 4x46x31 -> 126 11.6 / 9.4.
+// Fewer panels per workgroup, so more of them, while each still has a CU of its own (a workgroup of F(4x4) fills one).
+// us a layer, four panels / two / one [workgroups]: F(4x4), 7 channels at 3x23x70 -> 122 [42 / 84 / 168] 14.3 / 10.4 / 8.7, 64 at 2x125x77 -> 59 [80 / 160 / 320] 23.0 / 17.2 / 25.1, 12 at
+// 3x110x31 -> 206 [168 / 294 / 546] 14.2 / 18.2 / 21.1; F(2x2), 13 at 5x106x7 -> 33 [67 / 134 / 201] 6.7 / 5.4 / 4.9, 26 at 3x21x77 -> 153 [249 / 415 / 830] 9.6 / 10.9 / 12.0.
+static int wino_form(const long (&all)[kWinoForms]) {
+    if (all[0] >= 256) return 0;
+    int f = 1;
+    while (f + 1 < kWinoForms && all[f + 1] <= 256) ++f;
+    return f;
+}
 
 // Layers that do better as wavefronts of their own (wino_wave_kernel) than as workgroups, where a launch of workgroups of four panels fills the chip.
 // us a layer, workgroups / wavefronts: F(4x4), 3 channels at 224x224 -> 64 12.7 / 11.3, at 4x224x224 40.8 / 35.2, 4 at 4x224x224 40.6 / 39.5, 8 40.8 / 52.1, 3 -> 32 30.5 / 32.0 (-> 16 25.5 /
@@ -1054,42 +1073,69 @@ static long wino_many_split(int n, const WinoPlan *plans, int kind, bool half, l
 
 void wino_fused_layers(int n, const Geo *geos, int kind, char *fused) {
     std::fill(fused, fused + n, 0);
-    if (n > kMaxWinoLayers || (kind != NNV_WINO_F2 && kind != NNV_WINO_F4)) return;
+    if (n > kMaxWinoLayers || (kind != NNV_WINO_F2 && kind != NNV_WINO_F4) || geos[0].dtype == NNV_F16) return;
     const WinoRates &r = kWinoRates[kind == NNV_WINO_F2 ? 0 : 1];
-    const int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
-    struct Cost { int steps; double three, work, chain; };
+    const int set = kind == NNV_WINO_F2 ? 0 : 1;
+    struct Cost { int steps; double three; double blocks[kWinoForms], work[kWinoForms], chain[kWinoForms]; };
     Cost cost[kMaxWinoLayers];
-    WinoPlan plans[kMaxWinoLayers];
-    for (int i = 0; i < n; ++i) plans[i] = plan_wino(geos[i], kind);
-    long mfmas[kMaxWinoLayers];
-    int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];
-    if (n > 1) wino_many_split(n, plans, kind, geos[0].dtype == NNV_F16, mfmas, shifts, runs);
-    else shifts[0] = wino_split(plans[0], geos[0].dtype == NNV_F16).shift;
-    std::vector<int> lines{0};
+    WinoPlan plans[kMaxWinoLayers], many[kMaxWinoLayers];
+    bool only[kMaxWinoLayers];          // no other route
+    int m = 0;
     for (int i = 0; i < n; ++i) {
-        const WinoPlan &p = plans[i];
-        const int tm = wino_fused_panels(p);
-        const double aa = (double)p.alpha * p.alpha, vm = (double)(p.v_bytes + p.m_bytes) * 1e-6, u = aa * p.K16 * p.csteps * 256e-6;
-        const double chunks = (double)ceil_div(p.csteps, 4 / tn) * r.chunk * (tm == 4 ? 1.0 : r.less);
-        const double ops = 2.0 * aa * p.csteps * 4 * p.K16 * 16 * p.Tpad * 1e-6;
-        const bool able = wino_fused_able(geos[i], kind);
-        const int steps = able && wino_no_workspace(geos[i], kind, p) ? 0 : able && shifts[i] == 0 ? p.csteps : INT_MAX;
-        cost[i] = Cost{steps, vm / r.in_out + std::max((vm + u) / r.gemm, ops / r.rate),
-                       (double)ceil_div(p.T16, tn) * ceil_div(p.K16, tm) / 256.0 * (chunks + r.each), chunks * r.lone};
-        if (steps != INT_MAX) lines.push_back(steps);
+        plans[i] = plan_wino(geos[i], kind);
+        only[i] = wino_no_workspace(geos[i], kind, plans[i]);
+        if (!only[i]) many[m++] = plans[i];
     }
-    std::sort(lines.begin(), lines.end());
-    lines.erase(std::unique(lines.begin(), lines.end()), lines.end());
-    int best = 0;
-    double best_us = 0;
-    for (int line : lines) {
-        double three = 0, work = 0, chain = 0;
-        for (int i = 0; i < n; ++i) {
-            if (cost[i].steps > line) three += cost[i].three;
-            else { work += cost[i].work; chain = std::max(chain, cost[i].chain); }
+    long mfmas[kMaxWinoLayers];
+    int shifts[kMaxWinoLayers], runs[kMaxWinoLayers];       // of the others, in three launches
+    if (m > 1) wino_many_split(m, many, kind, false, mfmas, shifts, runs);
+    else if (m == 1) shifts[0] = wino_split(many[0], false).shift;
+    int order[kMaxWinoLayers];
+    double three = 0;
+    for (int i = 0, j = 0; i < n; ++i) {
+        const WinoPlan &p = plans[i];
+        const double aa = (double)p.alpha * p.alpha, v = (double)p.v_bytes * 1e-6, vm = v + (double)p.m_bytes * 1e-6, u = aa * p.K16 * p.csteps * 256e-6;
+        const double ops = 2.0 * aa * p.csteps * 4 * p.K16 * 16 * p.Tpad * 1e-6;
+        Cost &c = cost[i];
+        order[i] = i;
+        c.steps = !wino_fused_able(geos[i], kind) ? INT_MAX : only[i] ? 0 : shifts[j] == 0 ? p.csteps : INT_MAX;
+        j += only[i] ? 0 : 1;
+        c.three = vm / r.in_out + (geos[i].pw != 1 ? v * r.narrow : 0.0) + std::max((vm + u) / r.gemm, ops / r.rate);
+        three += c.three;
+        for (int f = 0; f < kWinoForms; ++f) {
+            const WinoForm &form = kWinoForm[set][f];
+            const double part = wino_fused_panels(p, form.most) == 4 ? 1.0 : r.less;
+            const double chunks = ceil_div(p.csteps, 4 / form.tn) * r.chunk * part * (geos[i].pw != 1 ? r.single : 1.0);
+            c.blocks[f] = (double)wino_form_blocks(p, form);
+            c.work[f] = c.blocks[f] * (chunks + r.each * part);
+            c.chain[f] = chunks * r.lone;
         }
-        const double us = (three > 0 ? r.base + three : 0.0) + (work > 0 ? r.start + std::max(work, chain + r.first) : 0.0);
-        if (line == 0 || us < 0.95 * best_us) { best = line; best_us = us; }
+    }
+    std::sort(order, order + n, [&](int a, int b) { return cost[a].steps < cost[b].steps; });
+    // the layers in this order move to the fused launch one after the other
+    int best = 0;
+    double none = 0, best_us = 0, work[kWinoForms] = {}, chain[kWinoForms] = {};
+    long all[kWinoForms] = {};
+    for (int o = 0; o <= n; ++o) {
+        const int next = o < n ? cost[order[o]].steps : INT_MAX;
+        if (next > 0 && (o == 0 || next != cost[order[o - 1]].steps)) {
+            double us = o < n ? r.base + three : 0.0;
+            if (o > 0) {
+                const int f = wino_form(all);
+                us += r.start + std::max((double)((all[f] + 255) / 256) * work[f] / (double)all[f], chain[f] + r.first);
+            }
+            const int line = o > 0 ? cost[order[o - 1]].steps : 0;
+            if (none == 0) none = best_us = us;
+            else if (us < best_us && us < 0.97 * none) { best = line; best_us = us; }
+        }
+        if (o == n || next == INT_MAX) break;
+        const Cost &c = cost[order[o]];
+        three -= c.three;
+        for (int f = 0; f < kWinoForms; ++f) {
+            all[f] += (long)c.blocks[f];
+            work[f] += c.work[f];
+            chain[f] = std::max(chain[f], c.chain[f]);
+        }
     }
     for (int i = 0; i < n; ++i) fused[i] = cost[i].steps <= best;
 }
@@ -1233,24 +1279,16 @@ hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const
     int order[kMaxWinoLayers];
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order, order + n, [&](int a, int b) { return geos[a].c > geos[b].c; });
-    int tn = kWinoFusedTiles[kind == NNV_WINO_F2 ? 0 : 1];
+    const int set = kind == NNV_WINO_F2 ? 0 : 1;
     WinoPlan plans[kMaxWinoLayers];
-    for (int i = 0; i < n; ++i) plans[i] = plan_wino(geos[i], kind);
-    auto blocks_of = [&](int i, int most) { return (long)ceil_div(plans[i].T16, tn) * ceil_div(plans[i].K16, wino_fused_panels(plans[i], most)); };
-    auto all_of = [&](int most) {
-        long all = 0;
-        for (int i = 0; i < n; ++i) all += blocks_of(i, most);
-        return all;
-    };
-    // F(2x2) in fewer workgroups than the chip has CUs: one block of tiles each, twice as many and half as many chunks.  us a layer, two blocks / one: 10 channels at 5x73x22 -> 36 10.8 / 7.9,
-    // 20 at 4x46x31 -> 126 11.6 / 9.4.
-    if (all_of(4) < 256) tn = 1;
-    // Fewer panels per workgroup, so more of them, while each still has a CU of its own (a workgroup of F(4x4) fills one).
-    // us a layer, four panels / two / one [workgroups]: F(4x4), 7 channels at 3x23x70 -> 122 [42 / 84 / 168] 14.3 / 10.4 / 8.7, 64 at 2x125x77 -> 59 [80 / 160 / 320] 23.0 / 17.2 / 25.1, 12 at
-    // 3x110x31 -> 206 [168 / 294 / 546] 14.2 / 18.2 / 21.1; F(2x2), 13 at 5x106x7 -> 33 [67 / 134 / 201] 6.7 / 5.4 / 4.9, 26 at 3x21x77 -> 153 [249 / 415 / 830] 9.6 / 10.9 / 12.0.
-    int most = 4;
-    while (most > 1 && all_of(most / 2) <= 256) most /= 2;
-    if (n == 1 && most == 4 && wino_waves(kind, plans[0])) {
+    long all[kWinoForms] = {};
+    for (int i = 0; i < n; ++i) {
+        plans[i] = plan_wino(geos[i], kind);
+        for (int f = 0; f < kWinoForms; ++f) all[f] += wino_form_blocks(plans[i], kWinoForm[set][f]);
+    }
+    const WinoForm form = kWinoForm[set][wino_form(all)];
+    const int tn = form.tn;
+    if (n == 1 && form.most == 4 && wino_waves(kind, plans[0])) {
         WinoParams w = wino_params(geos[0], plans[0], x[0], U[0], bias ? bias[0] : nullptr, y[0], nullptr);
         w.gemm_wgs_per_xi = plans[0].T16 * ceil_div(plans[0].K16, 4);
         const dim3 grid(xcd_grid(w.gemm_wgs_per_xi));
@@ -1263,9 +1301,9 @@ hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const
         const int i = order[o];
         if (!wino_fused_able(geos[i], kind)) return hipErrorInvalidValue;
         tbl.layer[o] = wino_params(geos[i], plans[i], x[i], U[i], bias ? bias[i] : nullptr, y[i], nullptr);
-        tbl.tm[o] = wino_fused_panels(plans[i], most);
+        tbl.tm[o] = wino_fused_panels(plans[i], form.most);
         tbl.block0[o] = (int)blocks;
-        blocks += blocks_of(i, most);
+        blocks += wino_form_blocks(plans[i], form);
         if (blocks >= (1L << 30)) return hipErrorInvalidValue;
     }
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.block0[i] = INT_MAX;
