@@ -759,7 +759,8 @@ struct WinoFusedTable {
 };
 static_assert(sizeof(WinoFusedTable) <= 4096, "the table is passed by value as the kernel argument");
 typedef const __attribute__((address_space(4))) WinoFusedTable *WinoFusedTablePtr;
-template <int SET, int TN, bool WIDE>
+// WIDE: layers whose patches are read in wide loads (one column of padding): 0 none, 1 all, 2 some
+template <int SET, int TN, int WIDE>
 __global__ __launch_bounds__(wino_fused_threads(SET)) void wino_fused_kernel(const WinoFusedTable tbl_arg) {
     constexpr int A = WinoMat<SET>::A;
     __shared__ __align__(16) float lds[2 * A * A * 256];
@@ -778,9 +779,14 @@ __global__ __launch_bounds__(wino_fused_threads(SET)) void wino_fused_kernel(con
         for (int k = 0; k < (int)(sizeof(WinoParams) / 4); ++k) dst[k] = src[k];
     }
     const int tm = tbl->tm[li];
-    if (tm == 4) wino_fused_block<SET, 4, TN, WIDE>(w, wg - first, lds);
-    else if (tm == 2) wino_fused_block<SET, 2, TN, WIDE>(w, wg - first, lds);
-    else wino_fused_block<SET, 1, TN, WIDE>(w, wg - first, lds);
+    auto block = [&](auto wide) __attribute__((always_inline)) {
+        constexpr bool W = decltype(wide)::value;
+        if (tm == 4) wino_fused_block<SET, 4, TN, W>(w, wg - first, lds);
+        else if (tm == 2) wino_fused_block<SET, 2, TN, W>(w, wg - first, lds);
+        else wino_fused_block<SET, 1, TN, W>(w, wg - first, lds);
+    };
+    if (WIDE == 1 || (WIDE == 2 && w.pw == 1)) block(std::true_type{});
+    if (WIDE == 0 || (WIDE == 2 && w.pw != 1)) block(std::false_type{});
 }
 
 // ---- layers of one step of channels (four of them: the first layer of a network) by themselves.  A workgroup of the kernel above is all start and end there: its wavefronts wait
@@ -1309,11 +1315,14 @@ hipError_t launch_wino_fused(int n, const Geo *geos, int kind, const void *const
     for (int i = n; i < kMaxWinoLayers; ++i) tbl.block0[i] = INT_MAX;
     tbl.n = (int)blocks;
     const dim3 grid((unsigned)(((blocks + 8 * kWinoGroup - 1) / (8 * kWinoGroup)) * 8 * kWinoGroup));
-    const bool wide = std::all_of(geos, geos + n, [](const Geo &g) { return g.pw == 1; });
+    const auto is_wide = [](const Geo &g) { return g.pw == 1; };
+    const bool all_wide = std::all_of(geos, geos + n, is_wide), some_wide = std::any_of(geos, geos + n, is_wide);
 #define NNV_WINO_FUSED(SET, TN, WIDE) hipLaunchKernelGGL((wino_fused_kernel<SET, TN, WIDE>), grid, dim3(wino_fused_threads(SET)), 0, st, tbl)
-    if (kind == NNV_WINO_F4) { if (wide) NNV_WINO_FUSED(1, 1, true); else NNV_WINO_FUSED(1, 1, false); }
-    else if (tn == 2) { if (wide) NNV_WINO_FUSED(0, 2, true); else NNV_WINO_FUSED(0, 2, false); }
-    else { if (wide) NNV_WINO_FUSED(0, 1, true); else NNV_WINO_FUSED(0, 1, false); }
+#define NNV_WINO_FUSED_OF(SET, TN) { if (all_wide) NNV_WINO_FUSED(SET, TN, 1); else if (some_wide) NNV_WINO_FUSED(SET, TN, 2); else NNV_WINO_FUSED(SET, TN, 0); }
+    if (kind == NNV_WINO_F4) NNV_WINO_FUSED_OF(1, 1)
+    else if (tn == 2) NNV_WINO_FUSED_OF(0, 2)
+    else NNV_WINO_FUSED_OF(0, 1)
+#undef NNV_WINO_FUSED_OF
 #undef NNV_WINO_FUSED
     return hipGetLastError();
 }

@@ -75,3 +75,21 @@ def test_few_channels(env, kind):
         ref = torch.nn.functional.conv2d(c.x.double().cpu(), c.raw.double().cpu(), c.bias.double().cpu(), padding=(ph, pw)).flatten()
         assert (y.double().cpu() - ref).abs().max() <= conv_tolerance(kind, False) * ref.abs().max(), c.shape
         assert torch.equal(alone(nnv, torch, c), y), c.shape
+
+
+# layers that read their patches in wide loads (one column of padding) in a launch with layers that read them element by element
+@pytest.mark.parametrize("kind", ["wino_f2", "wino_f4"])
+def test_mixed_paddings(env, kind):
+    nnv, torch = env
+    kind = nnv.KINDS[kind]
+    shapes = [(1, 16, 120, 130, 64, 1, 1), (1, 16, 120, 130, 64, 1, 0), (2, 21, 90, 101, 33, 1, 2), (2, 21, 90, 101, 33, 1, 1), (1, 40, 150, 97, 16, 0, 1), (1, 3, 130, 140, 40, 1, 0), (1, 12, 33, 64, 48, 1, 1)]
+    cases = [Case(nnv, torch, kind, s, 90 + i) for i, s in enumerate(shapes)]
+    mixed = together(nnv, torch, cases)
+    for sort in ([c for c in cases if c.shape[6] == 1], [c for c in cases if c.shape[6] != 1]):
+        for c, y in zip(sort, together(nnv, torch, sort)):
+            assert torch.equal(mixed[cases.index(c)], y), c.shape
+    # ... and what an unpadded layer reads where a padded one reads zeros
+    n, c, h, w, k, ph, _ = shapes[0]
+    carried = Case(nnv, torch, kind, (n, c, h, w + 2, k, ph, 0), 90)
+    carried.x, carried.wt, carried.bias = torch.nn.functional.pad(cases[0].x, (1, 1)).contiguous(), cases[0].wt, cases[0].bias
+    assert torch.equal(together(nnv, torch, [carried] + cases[1:])[0], mixed[0])
