@@ -972,6 +972,9 @@ struct WinoRates {
 };
 constexpr WinoRates kWinoRates[2] = {{9.15, 4.29, 5.58, 86.3, 2.55, 1.22, 2.94, 1.43, 0.473, 1.74, 1.32, 0.026}, {9.82, 3.23, 5.47, 91.3, 3.18, 2.93, 8.15, 1.27, 0.477, 3.51, 1.81, 0.048}};
 
+// (of one kernel or three: launch_wino takes no more blocks of tiles)
+constexpr int kWinoMostT16 = 65535 * 16;
+
 static bool wino_fused_able(const Geo &g, int kind) {
     return g.dtype == NNV_F32 && (kind == NNV_WINO_F2 || kind == NNV_WINO_F4) && (size_t)g.n * g.c * g.h * g.w * 4 < ((size_t)1 << 30);
 }
@@ -1104,7 +1107,7 @@ void wino_fused_layers(int n, const Geo *geos, int kind, char *fused) {
         const double ops = 2.0 * aa * p.csteps * 4 * p.K16 * 16 * p.Tpad * 1e-6;
         Cost &c = cost[i];
         order[i] = i;
-        c.steps = !wino_fused_able(geos[i], kind) ? INT_MAX : only[i] ? 0 : shifts[j] == 0 ? p.csteps : INT_MAX;
+        c.steps = !wino_fused_able(geos[i], kind) || p.T16 > kWinoMostT16 ? INT_MAX : only[i] ? 0 : shifts[j] == 0 ? p.csteps : INT_MAX;
         j += only[i] ? 0 : 1;
         c.three = vm / r.in_out + (geos[i].pw != 1 ? v * r.narrow : 0.0) + std::max((vm + u) / r.gemm, ops / r.rate);
         three += c.three;
@@ -1333,7 +1336,7 @@ hipError_t launch_wino(const Geo &g, int kind, const void *x, const void *U, con
     char fused = 0;
     wino_fused_layers(1, &g, kind, &fused);
     if (fused) return launch_wino_fused(1, &g, kind, &x, &U, &bias, &y, st);
-    if (p.T16 > 65535 * 16 || p.K16 > 65535) return hipErrorInvalidValue;
+    if (p.T16 > kWinoMostT16 || p.K16 > 65535) return hipErrorInvalidValue;
     WinoParams w = wino_params(g, p, x, U, bias, y, ws);
     const int set = wino_set(kind, g.dtype);
     if (set == WS_F2) {
