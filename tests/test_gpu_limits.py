@@ -8,6 +8,7 @@ import pytest
 from nnv_workloads import ConvLayer
 from nnv_testlib import conv_tolerance, KIND_NAMES
 from oracle.direct import conv2d_at
+from test_wino_rule import fused
 
 pytestmark = pytest.mark.gpu
 
@@ -30,13 +31,13 @@ def sample_positions(layer, rng, n_random=1500):
     return pos
 
 
-def run_and_check(nnv, torch, layer, kinds, seed):
+def run_and_check(nnv, torch, layer, kinds, seed, n_random=1500):
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(seed)
     x = rng.random((layer.n, layer.c, layer.h, layer.w), dtype=np.float32) * 2 - 1
     w = (rng.standard_normal((layer.k, layer.c // layer.groups, layer.r, layer.s)) *
          np.sqrt(2.0 / (layer.c // layer.groups * layer.r * layer.s))).astype(np.float32)
-    pos = sample_positions(layer, rng)
+    pos = sample_positions(layer, rng, n_random)
     ref = conv2d_at(x, w, [(0, k, p, q) for k, p, q in pos], layer.stride, layer.pad, layer.groups)
     scale = np.abs(ref).max()
     xd, wd = torch.from_numpy(x).to(dev), torch.from_numpy(w).to(dev)
@@ -93,10 +94,21 @@ def test_fused_winograd_just_below_1_gib(env):
 
 def test_winograd_workspace_just_below_2_gib(env):
     nnv, torch = env
-    # three-kernel F(4x4) (144 output channels: not the fused route): V + M = 2 143 641 600 bytes
+    # V + M = 2 143 641 600 bytes, which F(4x4) does not use on this layer (one kernel) and F(6x6), with 1.7 GB, does
     layer = ConvLayer("ws2g", 16, 1220, 1220, 144, 3, 3, 1, 1)
     desc = nnv.make_desc(layer, nnv.F32)
     assert 2 ** 31 - 2 ** 23 < nnv.nnv_workspace_bytes(desc, nnv.WINO_F4) < 2 ** 31
-    # F(2x2) has four times the tiles and would need more than 2 GiB of V and M; F(6x6) needs 1.7 GB
+    assert fused([layer], nnv.WINO_F4) and not fused([layer], nnv.WINO_F6)
+    # F(2x2) has four times the tiles and would need more than 2 GiB of V and M
     assert nnv.nnv_kind_supported(desc, nnv.WINO_F2) == 0
     run_and_check(nnv, torch, layer, (nnv.WINO_F4, nnv.WINO_F6), seed=94)
+
+
+def test_three_winograd_launches_just_below_2_gib(env):
+    nnv, torch = env
+    # three launches of F(4x4) (the channel steps are split): V + M = 2 142 388 224 bytes, almost all of it V
+    layer = ConvLayer("ws2g_deep", 58100, 64, 64, 16, 3, 3, 1, 1)
+    desc = nnv.make_desc(layer, nnv.F32)
+    assert 2 ** 31 - 2 ** 23 < nnv.nnv_workspace_bytes(desc, nnv.WINO_F4) < 2 ** 31
+    assert not fused([layer], nnv.WINO_F4)
+    run_and_check(nnv, torch, layer, (nnv.WINO_F4,), seed=95, n_random=300)
