@@ -26,7 +26,10 @@ LAYERS = {
 # ranges in groups (more than twelve of them): wavefronts of 4, 2 and 1 panels, the last group a single range or short; workgroups
 LAYERS["f32 groups"] = [Ly(512, 5, 512, w=4), Ly(1024, 4, 40), Ly(700, 3, 16), Ly(400, 6, 130, 5), Ly(1000, 4, 64, 1), Ly(512, 4, 24, 3, 2), Ly(470, 2, 80)]
 LAYERS["f32 groups, workgroups"] = [Ly(1100, 14, 128), Ly(900, 7, 100, n=4), Ly(64, 20, 64), Ly(832, 8, 70)] * 2
-LAYERS["f16 groups"] = [Ly(2048, 3, 16), Ly(2048, 2, 40), Ly(1500, 3, 24, 5), Ly(2000, 3, 20, 1)]
+LAYERS["f16 groups"] = [Ly(3072, 4, 16, w=8), Ly(3000, 8, 32, w=4), Ly(2048, 3, 16), Ly(2048, 2, 40), Ly(1500, 3, 24, 5), Ly(2000, 3, 20, 1)]
+LAYERS["f16 groups, workgroups"] = [Ly(2048, 8, 256, n=2, w=14), Ly(2048, 16, 64, 3, 2, n=2), Ly(2000, 8, 64, w=14), Ly(2048, 7, 100, n=2), Ly(1900, 13, 70, 3, 2)]
+# layers that fill their tiles: (index in the list, tiles, bytes of a tile's range); more than twelve ranges each (test_grouped_ranges.py counts them)
+FULL = {"f32 groups": [(0, 8, 4 * 2048)], "f16 groups": [(0, 1, 2048), (1, 1, 2 * 2048)], "f16 groups, workgroups": [(0, 8, 7 * 4096), (1, 2, 4 * 4096), (2, 1, 7 * 4096)]}
 
 
 @pytest.mark.parametrize("dtype", list(LAYERS))

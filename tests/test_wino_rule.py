@@ -6,14 +6,7 @@ import pytest
 
 import paper_2206_07446_amd as nnv
 from nnv_workloads import stack
-from test_grouped_ranges import at
-
-FIELDS = "n c h w k r s sh sw ph pw groups dtype p q cg kg relu"
-
-
-class Geo(ctypes.Structure):
-    _fields_ = [(f, ctypes.c_int) for f in FIELDS.split()]
-
+from test_grouped_ranges import Geo, at
 
 def fused(layers, kind, dtype=None, pad_w=1):
     lib = ctypes.CDLL(os.path.join(os.path.dirname(nnv.__file__), "libnnv.so"))
