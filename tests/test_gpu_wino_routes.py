@@ -4,6 +4,7 @@ import pytest
 
 from nnv_testlib import conv_tolerance
 from nnv_workloads import ConvLayer
+from test_wino_rule import fused
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +94,35 @@ def test_mixed_paddings(env, kind):
     carried = Case(nnv, torch, kind, (n, c, h, w + 2, k, ph, 0), 90)
     carried.x, carried.wt, carried.bias = torch.nn.functional.pad(cases[0].x, (1, 1)).contiguous(), cases[0].wt, cases[0].bias
     assert torch.equal(together(nnv, torch, [carried] + cases[1:])[0], mixed[0])
+
+
+# (images, channels, height, width, outputs): ragged everything, up to 31 channel steps, which no route splits
+EITHER = [(1, 64, 56, 56, 64), (2, 20, 40, 37, 70), (1, 100, 33, 40, 33), (3, 37, 21, 30, 48), (1, 124, 28, 28, 96), (2, 80, 14, 20, 130), (1, 9, 60, 61, 200), (4, 50, 14, 14, 64),
+          (1, 64, 28, 28, 64), (2, 33, 30, 50, 17), (1, 120, 40, 44, 128), (5, 30, 10, 11, 40)]
+# ... in three launches beside layers of many channels on few tiles, in the fused kernel beside layers of many tiles
+BESIDE = {"three": [(1, 512, 14, 14, 512)] * 8, "fused": [(4, 60, 112, 112, 64), (2, 64, 150, 140, 64), (4, 96, 90, 90, 128)]}
+
+
+@pytest.mark.parametrize("kind", ["wino_f2", "wino_f4"])
+def test_both_routes(env, kind):
+    nnv, torch = env
+    kind = nnv.KINDS[kind]
+    cases = [Case(nnv, torch, kind, s + (1, 1), 120 + i) for i, s in enumerate(EITHER)]
+    got, takes = {}, {}
+    for route, others in BESIDE.items():
+        beside = [Case(nnv, torch, kind, s + (1, 1), 150 + i) for i, s in enumerate(others)]
+        got[route], takes[route] = [], []
+        for at in range(0, len(EITHER), 4):
+            part = EITHER[at:at + 4]
+            layers = [ConvLayer(str(i), c, h, w, k, 3, 3, 1, 1, 1, n) for i, (n, c, h, w, k) in enumerate(others + part)]
+            names = [l.name for l in fused(layers, kind)]
+            takes[route] += [str(len(others) + i) in names for i in range(len(part))]
+            got[route] += together(nnv, torch, beside + cases[at:at + 4])[len(others):]
+    differ = [i for i in range(len(EITHER)) if takes["fused"][i] and not takes["three"][i]]
+    assert len(differ) >= 6
+    for i, c in enumerate(cases):
+        n, _, h, w, k, ph, pw = c.shape
+        ref = torch.nn.functional.conv2d(c.x.double().cpu(), c.raw.double().cpu(), c.bias.double().cpu(), padding=(ph, pw)).flatten()
+        assert (got["three"][i].double().cpu() - ref).abs().max() <= conv_tolerance(kind, False) * ref.abs().max(), c.shape
+        assert torch.equal(got["three"][i], got["fused"][i]), (c.shape, i in differ)
+        assert torch.equal(alone(nnv, torch, c), got["fused"][i]), c.shape
