@@ -1643,9 +1643,11 @@ static GemmPlan plan_im2col(const Geo &g) {
 size_t im2col_workspace_bytes(const Geo &g) { return plan_im2col(g).xt_bytes; }
 
 // Where the pixels of a tile go through LDS (gemm_accumulate_patch): tiles of 16 x 16 whose wavefronts have enough channels to make up for a longer start.  us a layer alone, gathered /
-// through LDS, [channel blocks of a wavefront, channels, maps -> outputs]: [8, 256, 14x14 -> 256] 7.3 / 7.8, [9, 306, 4x26x30 -> 37] 20.2 / 21.5, [16, 512, 7x7 -> 512] 11.9 / 11.5,
-// [16, 1024, 7x7 -> 1024] 20.9 / 19.0, [13, 836, 2x8x9 -> 23] 17.9 / 16.3, [24, 770, 2x16x14 -> 154] 29.2 / 25.2, [14, 462, 2x33x26 -> 25] 13.4 / 11.0.  Tiles of two panels gain
-// nothing (60 outputs of 318 channels at 73x75 27.6 / 30.3), nor does stride 2, whose rows are twice as long (256, 14x14 -> 512 8.4 / 9.6).
+// through LDS, [channel blocks of a wavefront, channels, maps -> outputs], weights and pixels from HBM: [12, 200, 28x28 -> 64] 8.6 / 8.3, [12, 189, 6x21x9 -> 49] 9.8 / 10.3, [15, 248, 2x18x52 -> 26] 11.6 / 10.0,
+// [16, 512, 7x7 -> 512] 14.2 / 12.5, [14, 462, 4x18x13 -> 48] 13.2 / 12.0, [22, 721, 2x9x8 -> 294] 18.5 / 16.4, [30, 973, 2x26x15 -> 81] 40.3 / 31.3; 72 layers, geometric mean 0.90 (0.74-1.05).  Read again and again,
+// out of the caches, gathered pixels are close by and the longer start counts up to 15 blocks of four wavefronts: the same layers 6.6 / 8.3, 9.5 / 10.3, 7.6 / 9.6, 11.6 / 12.3, 12.8 / 11.8, 15.7 / 15.9, 39.3 /
+// 31.0, geometric mean 0.97 (0.74-1.29).  A layer of a network finds its operands displaced by the others' (cold ResNet-18-shaped pass 118 / 113), which is what the line is drawn for.
+// Tiles of two panels gain nothing (60 outputs of 318 channels at 73x75 27.6 / 30.3), nor does stride 2, whose rows are twice as long (256, 14x14 -> 512 8.4 / 9.6).
 constexpr int kPatchMinBlocks = 12;
 static bool patch_pays(const Geo &g, const GemmPlan &pl) {
     if (g.dtype != NNV_F32 || pl.mode != 3 || pl.tm * pl.tn != 1 || g.sh != 1 || g.sw != 1 || g.pw != 1) return false;

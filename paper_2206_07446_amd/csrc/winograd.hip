@@ -10,7 +10,7 @@
 // V and M live in the caller's workspace.  float16 storage keeps U, V and y in half
 // precision; the transforms and the accumulation are float32.
 // float32 F(2x2) / F(4x4) layers with many tiles for their channels run instead as ONE kernel
-// (wino_fused_kernel below) that keeps V in LDS and M in registers.
+// (wino_fused_kernel below) that keeps V in LDS and M in registers, or, with one step of channels, both in registers (wino_wave_kernel).
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -198,8 +198,8 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const WinoParams w) {
 // (i, slot) takes TM consecutive floats, rows TM (i % (16/TM)) .. of panel i / (16/TM), channel slot: element
 // m is its operand of the m-th row block.  One 16-byte load replaces four, and V is stored so that the TN tile
 // blocks of a lane are neighbours too: 2 loads per 8 MFMAs instead of 6 (64 x 32 tile).
-// What bounds a launch now is U, V and M through the fabric: the tile GEMMs of a VGG-16-shaped F(4x4) stack move
-// 497 MB (U is 235) in 110 us, 0.88 of the rate of a plain copy; its pass took 207 us before, 176 now.  64 x 64 tiles
+// What bounds a launch now is U, V and M through the fabric: the tile GEMMs of all layers of a VGG-16-shaped F(4x4) stack move
+// 497 MB (U is 235) in 110 us, 0.88 of the rate of a plain copy; a pass of three launches 207 -> 176 us.  64 x 64 tiles
 // (TN = 4) move less through L1 and took the same time there, 10 % more on a ResNet-18-shaped stack.
 // float16: fragments are 16 bytes per lane to begin with.
 typedef uint32_t uint32x2 __attribute__((ext_vector_type(2)));
