@@ -579,7 +579,8 @@ __global__ __launch_bounds__(64 * kWinoItemWaves, 5) void wino_gemm_many_kernel(
 // products, requested a chunk ahead.  At the end the frequencies meet in LDS, a row block at a time, and a thread transforms and stores one tile.
 // What bounds it is the matrix cores, at three quarters of the rate of a large product while a workgroup per CU is resident: a chunk of F(4x4) (16 channels) takes 3.0 us,
 // 1.9 of them products at 2.4 GHz; 2.7 without the transforms, as long without the loads of U.  Patches in single elements held the vector memory path
-// instead (4.4 us).  F(4x4) has twelve wavefronts for the products and four of their own for the transforms: one wavefront that did both would wait for
+// instead (4.4 us).  Over a whole launch the matrix pipe is busy 54 % of the cycles in F(2x2) (eight layers of a VGG-16-shaped stack, 116 us) and 30 % in F(4x4) (five, of up to 8 chunks,
+// 61 us): the rest is a workgroup's start and end.  F(4x4) has twelve wavefronts for the products and four of their own for the transforms: one wavefront that did both would wait for
 // patches whenever it waits for U, since loads come back in order (5.0 us).  F(2x2), with four times fewer elements in a patch, has eight that do both; twelve,
 // one workgroup per CU instead of two, take a VGG-16-shaped stack from 166 to 200 us.  32 x 32 tiles (TM = TN = 2) for F(4x4), half the loads of U and twice the transforms: 3.9 us a chunk.
 constexpr int kWinoFusedFreqs[2] = {2, 3};        // frequencies of a wavefront
