@@ -398,7 +398,7 @@ GroupedPlan plan_grouped(int n, const Geo *geos, const nnv_kind *kinds) {
     }
     // Depthwise layers ride along with an item launch of their storage type: the items leave half of the memory path idle and end one by one, and a launch
     // less is 4 us.  Up to kMostDepthwise workgroups of them, ten rounds of what the item kernel's registers let the chip hold; more do better in a launch of
-    // their own, seven wavefronts per SIMD instead of three.  us a call, apart / together, [workgroups]: ShuffleNet-shaped [460] 23.5 / 19.8, MobileNetV1 [1970] 38.1 / 29.0,
+    // their own, four wavefronts per SIMD instead of three and a fourth of the code.  us a call, apart / together, [workgroups]: ShuffleNet-shaped [460] 23.5 / 19.8, MobileNetV1 [1970] 38.1 / 29.0,
     // MobileNetV2 [2350] 32.3 / 27.4, float16 28.1 / 20.9, EfficientNet-B0 [2370] 49.9 / 45.0, MobileNetV2 in float16 at batch 2 [4700] 38.0 / 33.4 and 3 [7050] 49.8 / 48.2,
     // EfficientNet-B0 at batch 3 [7120] 105 / 100; beyond the line MobileNetV2 at batch 4 [9400] 98 / 98, float16 69 / 70.6, at 4x320x320 [18600] 176 / 182, float16 125 / 133.
     constexpr long kMostDepthwise = 7680;
